@@ -233,7 +233,7 @@ int wq_append_kv(wq_ctx* ctx, const void* k_new, const void* v_new, int dtype, i
 /* ---- a decode step in one call (Sec. 2.2): append the generated token's keys and values, then attend over the
  * cache that now includes them.  Same arguments and results as wq_append_kv(k_new, v_new, new_dtype) followed by
  * wq_decode_attention(...).  When the matrix-core kernel handles the whole launch (what WQ_DECODE_AUTO picks for
- * hd/group == 2 with a query of the cache's 16-bit type family), k_new, v_new have the cache's own 16-bit type and there
+ * a query of the cache's 16-bit type family), k_new, v_new have the cache's own 16-bit type and there
  * are at most 64 splits, it is ONE kernel launch: the new row is read from k_new / v_new by the workgroup that walks its block, copied into the cache
  * by another, and len16[b] is raised by the sequence's last workgroup to finish; otherwise the two launches are made.
  * A sequence whose 16-bit segment is full is attended without the new token and raises WQ_DEV_SEG16_OVERFLOW.
@@ -263,7 +263,9 @@ int wq_dequantize(wq_ctx* ctx, int B, const wq_packed_kv* src, const wq_packed_k
  * (natural-log sum of exp of the scaled logits).  num_splits 0 = automatic (wq_auto_splits).  max_seq_tokens: host
  * bound on tokens of any one sequence (used by the automatic split and by WQ_DECODE_BY_LENGTH; a wrong value costs speed,
  * not correctness).  algo: WQ_DECODE_AUTO picks the
- * matrix-core kernel when hd/group == 2, else the generic one.  Limits (WQ_ERR_UNSUPPORTED beyond them): Hq a
+ * matrix-core kernel when hd/group == 2, or for other groups when the query is a 16-bit type and the cache is within that
+ * kernel's limits (the softmax weights then keep fp32 accuracy), else the generic one; WQ_DECODE_MFMA takes hd/group == 2 only.
+ * Limits (WQ_ERR_UNSUPPORTED beyond them): Hq a
  * multiple of Hkv with at most 8 query heads per KV head, hd 64 or 128, group 32, 64 or 128, B at most 65535, and for
  * the matrix-core kernel at most 2^27 token slots in the cache (cap[0] + cap[1] + cap[2] + cap16: it cuts the workgroups'
  * shares on a 32-bit cost axis); num_splits above 1024 is WQ_ERR_ARG.

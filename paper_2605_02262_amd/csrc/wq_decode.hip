@@ -7,8 +7,8 @@
 // the result is deterministic for a given split count.
 //
 // k_decode_generic: plain vector-ALU kernel that reads codes field by field from the storage layout.  It
-// handles every supported (hd, group) and is the reference implementation inside the library; the
-// matrix-core body in wq_decode_mfma.h is the fast path for hd/group == 2.
+// handles every supported (hd, group) and query type and is the reference implementation inside the library; the
+// matrix-core body in wq_decode_mfma.h is the fast path (use_matrix_cores below says where it is taken).
 #include <stdlib.h>
 
 #include <type_traits>
@@ -352,11 +352,11 @@ __global__ __launch_bounds__(256) void k_decode_generic(DecodeArgs a)
 }
 
 // Matrix-core kernel: the quantized classes of one (split, KV head, sequence).
-template <int HD>
+template <int HD, int G>
 __global__ __launch_bounds__(64 * WQ_WAVES) void k_decode_mfma(DecodeArgs a)
 {
-    __shared__ __align__(16) unsigned char smem[sizeof(MfmaSmem<HD>)];
-    wq_decode_mfma_body<HD>(a, smem);
+    __shared__ __align__(16) unsigned char smem[sizeof(MfmaSmem<HD, G>)];
+    wq_decode_mfma_body<HD, G>(a, smem);
 }
 
 // out[b,h,:] = sum_s acc_s e^{m_s - M} / sum_s l_s e^{m_s - M},  M = max_s m_s;  lse = M + log(sum).
@@ -433,6 +433,22 @@ size_t wq_decode_ws_bytes(int B, int Hq, int hd, int splits)
     return wq_align256(sizeof(float) * (size_t)B * Hq * (splits + 32) * (hd + 2));
 }
 
+// The matrix-core kernel's work is cut on a 32-bit cost axis (at most 500 per 32-token block).
+static bool fits_cost_axis(const wq_packed_kv* kv)
+{
+    return (int64_t)kv->cap[0] + kv->cap[1] + kv->cap[2] + kv->cap16 <= (int64_t)1 << 27;
+}
+
+// Which kernel walks the quantized classes.  Two groups per head: the matrix-core kernel, with the weights in one f16 value.
+// One and four groups: the matrix-core kernel with the weights in two, which keeps fp32 accuracy, for 16-bit queries (whose
+// mantissa an f16 operand holds); an fp32 query would lose half of its bits there and stays with the vector kernel, as do
+// caches beyond the cost axis.
+static bool use_matrix_cores(int q_dtype, const wq_packed_kv* kv, int balgo)
+{
+    if (balgo != WQ_DECODE_AUTO) return balgo == WQ_DECODE_MFMA;
+    return kv->hd / kv->group == 2 || (q_dtype != WQ_F32 && fits_cost_axis(kv));
+}
+
 // Can wq_launch_decode append k_new, v_new (element type new_dtype) itself with these arguments?  Only the matrix-core
 // kernel that walks every segment and merges its splits does: it needs the new rows in the cache's own 16-bit type
 // and one more counter per sequence in the workspace header.
@@ -440,7 +456,7 @@ bool wq_decode_can_append(int q_dtype, int B, int Hq, const wq_packed_kv* kv, in
 {
     if (algo & (WQ_DECODE_PARTIALS_ONLY | WQ_DECODE_SEPARATE_MERGE)) return false;
     const int balgo = algo & ~WQ_DECODE_FLAGS;
-    const bool use_mfma = (balgo == WQ_DECODE_MFMA) || (balgo == WQ_DECODE_AUTO && kv->hd / kv->group == 2);
+    const bool use_mfma = use_matrix_cores(q_dtype, kv, balgo);
     const bool mfma16 = use_mfma && !(kv->dtype16 == WQ_BF16 && q_dtype != WQ_BF16);
     const int rep = Hq / kv->Hkv;
     return mfma16 && new_dtype == kv->dtype16 && (int64_t)B * kv->Hkv + B <= WQ_MAX_ARRIVE && num_splits <= WQ_MAX_FUSED_SPLITS &&
@@ -463,7 +479,7 @@ int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, con
     a.rep = Hq / kv->Hkv;
     a.splits = num_splits;
     a.sm_scale = sm_scale;
-    a.use_mfma = (algo == WQ_DECODE_MFMA) || (algo == WQ_DECODE_AUTO && kv->hd / kv->group == 2);
+    a.use_mfma = use_matrix_cores(q_dtype, kv, algo);
     // a bf16 cache needs the exact bf16 query for the bf16 instruction; other query types send the 16-bit
     // segment to the generic kernel
     a.mfma16 = a.use_mfma && !(kv->dtype16 == WQ_BF16 && q_dtype != WQ_BF16);
@@ -476,8 +492,7 @@ int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, con
     // header and a wavefront's lanes hold the splits' weights
     a.fused = a.use_mfma && a.mfma16 && !partials_only && !separate_merge && (int64_t)B * kv->Hkv <= WQ_MAX_ARRIVE &&
               a.nparts <= WQ_MAX_FUSED_SPLITS;
-    // the shares of the token axis are cut on a 32-bit cost axis (at most 500 per 32-token block)
-    if (a.use_mfma && (int64_t)kv->cap[0] + kv->cap[1] + kv->cap[2] + kv->cap16 > ((int64_t)1 << 27))
+    if (a.use_mfma && !fits_cost_axis(kv))
         return wq_fail(ctx, WQ_ERR_UNSUPPORTED, "the matrix-core decode kernel takes caches of up to 2^27 token slots");
     a.part = reinterpret_cast<float*>(ctx->ws + WQ_WS_HEADER);
     a.out = out;
@@ -497,25 +512,16 @@ int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, con
     const dim3 grid_m((unsigned)kv->Hkv, (unsigned)B, (unsigned)a.splits), blk_m(64 * WQ_WAVES);
     const int tslot = (int)(ctx->ev_calls % WQ_TIMING_RING);
     if (ctx->timing) (void)hipEventRecord(ctx->ev[2 * tslot], ctx->stream);
-    if (kv->hd == 128) {
-        if (a.use_mfma) {
-            hipLaunchKernelGGL(k_decode_mfma<128>, grid_m, blk_m, 0, ctx->stream, a);
-            if (ctx->timing) (void)hipEventRecord(ctx->ev[2 * tslot + 1], ctx->stream);
-            if (a.splits16 > 0) hipLaunchKernelGGL(k_decode_generic<128>, grid_16, blk, 0, ctx->stream, a);
-        } else {
-            hipLaunchKernelGGL(k_decode_generic<128>, grid_q, blk, 0, ctx->stream, a);
-            if (ctx->timing) (void)hipEventRecord(ctx->ev[2 * tslot + 1], ctx->stream);
-        }
+    const int groups = kv->hd / kv->group;
+    if (a.use_mfma) {
+        void (*const kernel)(DecodeArgs) = kv->hd == 128 ? (groups == 2 ? k_decode_mfma<128, 2> : groups == 1 ? k_decode_mfma<128, 1> : k_decode_mfma<128, 4>)
+                                                         : (groups == 2 ? k_decode_mfma<64, 2> : k_decode_mfma<64, 1>);
+        hipLaunchKernelGGL(kernel, grid_m, blk_m, 0, ctx->stream, a);
     } else {
-        if (a.use_mfma) {
-            hipLaunchKernelGGL(k_decode_mfma<64>, grid_m, blk_m, 0, ctx->stream, a);
-            if (ctx->timing) (void)hipEventRecord(ctx->ev[2 * tslot + 1], ctx->stream);
-            if (a.splits16 > 0) hipLaunchKernelGGL(k_decode_generic<64>, grid_16, blk, 0, ctx->stream, a);
-        } else {
-            hipLaunchKernelGGL(k_decode_generic<64>, grid_q, blk, 0, ctx->stream, a);
-            if (ctx->timing) (void)hipEventRecord(ctx->ev[2 * tslot + 1], ctx->stream);
-        }
+        hipLaunchKernelGGL(kv->hd == 128 ? k_decode_generic<128> : k_decode_generic<64>, grid_q, blk, 0, ctx->stream, a);
     }
+    if (ctx->timing) (void)hipEventRecord(ctx->ev[2 * tslot + 1], ctx->stream);
+    if (a.splits16 > 0) hipLaunchKernelGGL(kv->hd == 128 ? k_decode_generic<128> : k_decode_generic<64>, grid_16, blk, 0, ctx->stream, a);
     if (!partials_only && !a.fused)
         hipLaunchKernelGGL(k_combine, dim3(Hq, B), dim3(128), 0, ctx->stream, a.part, Hq, a.rep, a.nparts, kv->hd, out, lse);
     if (ctx->timing) ctx->ev_calls++;

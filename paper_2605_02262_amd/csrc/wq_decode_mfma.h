@@ -202,7 +202,7 @@ struct WaveState {
 // is being worked on (a 2-bit block is 2.5 KB, an 8-bit block 8.5 KB)
 constexpr int WQ_D2 = 4, WQ_D4 = 3, WQ_D8 = 2;
 constexpr int WQ_TAPER_TICKETS = 16;   // the last blocks of a workgroup's range, two per wavefront, are walked with half the pipeline (measured: 0.45 us per call)
-constexpr int WQ_FIRST_TICKETS = 4;    // blocks every wavefront starts with (the deepest pipeline's fill)
+constexpr int WQ_FIRST_TICKETS = 4;    // blocks every wavefront starts with (the deepest pipeline's fill), in a range that has as many
 constexpr int WQ_WAVES = 8;            // wavefronts per workgroup: one workgroup per compute unit, two wavefronts per SIMD
 constexpr float WQ_MAX_SLACK = 5.0f;   // log2 of the largest softmax weight tolerated before the reference exponent moves
 // The weights meet the value scales in fp16 (P' = p * s_v).  They are formed 2^up too large (for free, in the exponent of
@@ -422,6 +422,7 @@ struct Tickets {
     unsigned* ctr;      // the workgroup's counter (LDS)
     unsigned held, end; // tickets held: [held, end)
     bool spent;         // none left: another one is due
+    bool dealt;         // the fixed first tickets are the whole range: there is nothing to draw
     bool synced;        // this wavefront has passed the workgroup's set-up barrier
     unsigned taper;     // from this ticket on (the workgroup's last WQ_TAPER_TICKETS) a wavefront refills only every other pipeline slot
 };
@@ -457,8 +458,8 @@ struct BlockSrc {
 __device__ __forceinline__ void settle_tickets(Tickets& t, unsigned n)
 {
     if (t.spent) {
-        t.held = ticket_value(draw_tickets(t.ctr, n));
-        t.end = t.held + n;
+        t.held = t.dealt ? 0xFFFFFFFEu : ticket_value(draw_tickets(t.ctr, n));
+        t.end = t.dealt ? 0xFFFFFFFFu : t.held + n;
         t.spent = false;
     }
 }
@@ -1071,7 +1072,6 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
             return;
         }
     }
-    if (tid == 0) sm.next_ticket = (unsigned)(WQ_FIRST_TICKETS * WQ_WAVES);
     // ---- the query operands of all classes, one class per wavefront ----
     stage_q_operands<HD, G>(a, sm, b, kvh, wave, bf16seg);
 
@@ -1079,11 +1079,6 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
     //      fixed share of it (none unless the launch asks for fixed shares: then there is no pool) ----
     Tickets tk;
     tk.ctr = &sm.next_ticket;
-    // the first tickets are fixed (WQ_FIRST_TICKETS consecutive blocks per wavefront), so that the first loads can go
-    // out before the workgroup's set-up barrier; the counter starts behind them
-    tk.held = (unsigned)(wave * WQ_FIRST_TICKETS);
-    tk.end = tk.held + (unsigned)WQ_FIRST_TICKETS;
-    tk.spent = false;
     tk.synced = false;
     tk.taper = 0xFFFFFFFFu;
     BlockSrc src[4];
@@ -1127,6 +1122,17 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
             base += (unsigned)nb[c] * (unsigned)WQ_BLOCK_COST[c];
         }
         if (!a.fixed_shares && t > (unsigned)WQ_TAPER_TICKETS) tk.taper = t - (unsigned)WQ_TAPER_TICKETS;
+        // The first tickets are fixed, so that the first loads can go out before the workgroup's set-up barrier; the counter
+        // starts behind them.  WQ_FIRST_TICKETS consecutive blocks per wavefront, or, in a range of fewer blocks, what
+        // spreads them over all eight: a block's arithmetic is half a microsecond, and with four blocks each the first
+        // wavefronts of a short range walked it one block after the other beside idle ones (5 blocks, heads of 64: 9.0 -> 6.6 us
+        // a call; 13 blocks, heads of 128: 15.8 -> 13.3)
+        const unsigned first = min((unsigned)WQ_FIRST_TICKETS, (t + (unsigned)WQ_WAVES - 1u) / (unsigned)WQ_WAVES);
+        tk.held = (unsigned)wave * first;
+        tk.end = tk.held + first;
+        tk.spent = first == 0u;
+        tk.dealt = !a.fixed_shares && first * (unsigned)WQ_WAVES >= t;
+        if (tid == 0) sm.next_ticket = first * (unsigned)WQ_WAVES;
     }
 
     WQ_STAMP(1);

@@ -26,7 +26,8 @@ struct DecodeArgs {
     int use_mfma;
     int mfma16;             // the matrix-core kernel also walks the 16-bit segment
     int fused;              // the matrix-core kernel merges the splits itself (last workgroup per (b, KV head))
-    unsigned* arrive;       // [B*Hkv] arrival counters, WQ_ARRIVE_STRIDE words apart, zero between launches
+    unsigned* arrive;       // [B*Hkv] pieces of arrive_unit words (WQ_MAX_REP arrival counters each), then [B] append counters, zero between launches
+    int arrive_unit;
     int fixed_shares;       // every wavefront of the matrix-core kernel gets a fixed share of its workgroup's range
     wq_packed_kv kv;
     float* part;            // [B][Hkv][nparts][rep][hd + 2]
@@ -488,6 +489,12 @@ int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, con
     a.kv = *kv;
     a.fixed_shares = fixed_shares;
     a.arrive = reinterpret_cast<unsigned*>(ctx->ws + 256);
+    // A device-scope atomic takes 12-16 ns of the cache line it is for, and a unit's splits times its heads report in within
+    // a microsecond or two: with a unit's counters in one line, the last of 32 splits x 7 heads was counted 3 us after its
+    // partial had landed.  So a unit gets as many lines as the workspace header has room for, up to one per head.
+    a.arrive_unit = WQ_ARRIVE_STRIDE;
+    while (a.arrive_unit < WQ_ARRIVE_STRIDE * WQ_MAX_REP && (2 * (int64_t)(a.arrive_unit / WQ_ARRIVE_STRIDE) * kv->Hkv + 1) * B <= WQ_MAX_ARRIVE)
+        a.arrive_unit *= 2;
     // one launch does it all when the matrix-core kernel walks every segment, the counters fit the workspace
     // header and a wavefront's lanes hold the splits' weights
     a.fused = a.use_mfma && a.mfma16 && !partials_only && !separate_merge && (int64_t)B * kv->Hkv <= WQ_MAX_ARRIVE &&

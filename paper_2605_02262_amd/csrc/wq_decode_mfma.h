@@ -922,14 +922,14 @@ __device__ __forceinline__ void note_tables_read(const DecodeArgs& a, int b, int
     if (a.k_new && threadIdx.x == 0) {
         unsigned one = 1u;
         asm volatile("; the count follows the read of len16 %1" : "+s"(one) : "s"(len16_read));
-        __hip_atomic_fetch_add(a.arrive + (a.B * a.kv.Hkv + b) * WQ_ARRIVE_STRIDE, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(a.arrive + a.B * a.kv.Hkv * a.arrive_unit + b * WQ_ARRIVE_STRIDE, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
 __device__ __forceinline__ void finish_append(const DecodeArgs& a, int b, int kvh, int split, int new_row)
 {
     if (!a.k_new || threadIdx.x != 0 || kvh != a.kv.Hkv - 1 || split != a.splits - 1) return;
-    unsigned* ctr = a.arrive + (a.B * a.kv.Hkv + b) * WQ_ARRIVE_STRIDE;
+    unsigned* ctr = a.arrive + a.B * a.kv.Hkv * a.arrive_unit + b * WQ_ARRIVE_STRIDE;
     const unsigned all = (unsigned)a.kv.Hkv * (unsigned)a.splits;
     const long long t_start = wall_clock64();
     while (__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != all) {
@@ -1242,7 +1242,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
     if (wave < a.rep) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         WQ_STAMP(56);
-        unsigned* const counter = a.arrive + unit * WQ_ARRIVE_STRIDE + wave;
+        unsigned* const counter = a.arrive + unit * a.arrive_unit + wave * (a.arrive_unit / WQ_MAX_REP);
         static_assert(WQ_ARRIVE_STRIDE >= WQ_MAX_REP, "one counter per head inside a unit's piece");
         unsigned old = 0u;
         if (lane == 0) old = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1267,18 +1267,24 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
 #pragma unroll
         for (int c = 0; c < CPL; c++) acc[c] = 0.f;
         const unsigned chan = row + (unsigned)lane * (CPL * 4u);
-#pragma unroll 1
-        for (int k0 = 0; k0 < np; k0 += 16) {      // 16 splits at a time: their loads are in flight together
-            typename FloatN<CPL>::type pre[16];
+        auto gather = [&](auto N, int k0) {        // N splits at a time: their loads are in flight together
+            constexpr int NS = decltype(N)::value;
+            typename FloatN<CPL>::type pre[NS];
 #pragma unroll
-            for (int k = 0; k < 16; k++) pre[k] = ld_part<CPL>(parts, chan + (unsigned)(k0 + k) * pbytes);
+            for (int k = 0; k < NS; k++) pre[k] = ld_part<CPL>(parts, chan + (unsigned)(k0 + k) * pbytes);
             if (k0 == 0) merge_weights_lanes(m_s, l_s, w_s, M, L);
 #pragma unroll
-            for (int k = 0; k < 16; k++) {
+            for (int k = 0; k < NS; k++) {
                 const float wk = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w_s), k0 + k));   // 0 beyond the last split
 #pragma unroll
                 for (int c = 0; c < CPL; c++) acc[c] = fmaf(part_elem<CPL>(pre[k], c), wk, acc[c]);
             }
+        };
+        if (np <= 16) {
+            gather(std::integral_constant<int, 16>{}, 0);
+        } else {                                   // (a second round trip costs more than the loads of splits that are not there)
+#pragma unroll 1
+            for (int k0 = 0; k0 < np; k0 += 32) gather(std::integral_constant<int, 32>{}, k0);
         }
         WQ_STAMP(58);
         const int hq = kvh * a.rep + wave;

@@ -1,4 +1,4 @@
-"""Decode attention where a workgroup has few blocks (needs an MI355X).
+"""Decode attention where a workgroup has few blocks, and where the arrival counters change their spacing (needs an MI355X).
 
 One group per head: the kernel then keeps fp32 accuracy (2^-15 of a vector's largest entry, see test_gpu_decode_groups), so a
 block that is left out, taken twice or merged too early shows."""
@@ -35,3 +35,35 @@ def test_ranges_of_few_blocks(first_class):
             out = W.wq_decode_attention(ctx, q, run.pk, sm, splits, 1400, flags)
             assert H.attention_error(out.cpu().numpy(), o.out) <= TIGHT, (splits, flags)
     assert ctx.device_status() == 0
+
+
+@pytest.mark.parametrize("B", [14, 15, 28, 29, 50, 51, 84, 85, 126, 127])
+def test_arrival_counters_at_every_spacing(B):
+    """Two KV heads: a unit has 8, 4, 2 or 1 cache lines of counters up to 14, 28, 50 and 84 sequences; from 85 on the append
+    counters do not fit the header, from 127 on the merge is a launch of its own.  Up to 64 splits of a few blocks."""
+    from oracle import wq_oracle as O
+    from paper_2605_02262_amd import binding as W
+    from tests import wq_harness as H
+    specs = [synth.SeqSpec(3, 16, 16, 3 + b % 40, (1, 1, 1)) for b in range(B)]
+    w = synth.Workload("counters", synth.BF16, synth.BF16, 16, 2, 64, 64, 64, 1.0, specs, 600 + B, pin_first=0)
+    bt = synth.batch(w, with_embeddings=False)
+    sc = np.random.default_rng(2).standard_normal(int(bt.t.win_off[-1])).astype(np.float32)
+    cap, off16 = H.capacities(w, slack=4)
+    run = H.run_gpu(bt, cap=cap, off16=off16, splits=1, with_scores=False, scores_override=sc)
+    o = H.run_oracle(bt, scores_override=sc, with_scores=False, cap=cap, off16=off16)
+    ctx = W.Context(W.workspace_bytes(B, w.Hq, w.hd, 64))
+    q, sm = H.to_dev(bt.q, w.dtype), 0.125
+    rng = np.random.default_rng(3)
+    for splits in (2, 17, 33, 64):
+        out = W.wq_decode_attention(ctx, q, run.pk, sm, splits, 100)
+        assert H.attention_error(out.cpu().numpy(), o.out) <= TIGHT, splits
+        kn, vn = (synth.round_to(rng.standard_normal((B, 2, 64)).astype(np.float32), w.dtype) for _ in range(2))
+        out = W.wq_decode_append_attention(ctx, q, run.pk, H.to_dev(kn, w.dtype), H.to_dev(vn, w.dtype), sm, splits, 100)
+        for b in range(B):
+            r = int(o.pk.off16[b] + o.pk.len16[b])
+            o.pk.k16[r], o.pk.v16[r] = kn[b], vn[b]
+            o.pk.len16[b] += 1
+        o.out = O.decode_attention(bt.q, o.pk, sm)
+        assert H.attention_error(out.cpu().numpy(), o.out) <= TIGHT, splits
+        assert np.array_equal(run.pk.len16.cpu().numpy(), o.pk.len16)
+    assert ctx.device_status() == 0 and int(ctx.ws[:16384].count_nonzero()) == 0        # every counter is back at zero

@@ -314,7 +314,8 @@ static int check_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, 
     if (B == 0) return WQ_OK;
     if (!q || !out) return wq_fail(ctx, WQ_ERR_ARG, "NULL q or out");
     if (by_length) *longest = max_seq_tokens;
-    if (*num_splits == 0) {
+    const bool automatic = *num_splits == 0;
+    if (automatic) {
         *num_splits = wq_auto_splits(B, kv->Hkv, max_seq_tokens);
         if (by_length) {    // more splits (the caches' capacities stand in for the tokens), if the workspace has room for them
             int more = wq_auto_splits_ragged(B, kv->Hkv, max_seq_tokens, kv->cap[0] + kv->cap[1] + kv->cap[2] + kv->cap16);
@@ -324,6 +325,13 @@ static int check_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, 
     }
     if (ctx->ws_bytes < WQ_WS_HEADER + wq_decode_ws_bytes(B, Hq, kv->hd, *num_splits))
         return wq_fail(ctx, WQ_ERR_WORKSPACE, "workspace too small for %d splits", *num_splits);
+    // where the kernel merges the splits itself: what makes the launch shortest, as far as the workspace has room
+    bool uneven = false;
+    const int picked = automatic ? wq_decode_pick_splits(ctx, q_dtype, B, Hq, kv, max_seq_tokens, algo, &uneven) : 0;
+    if (picked > 0) {
+        *num_splits = picked;
+        *longest = uneven ? -1 : 0;
+    }
     return WQ_OK;
 }
 

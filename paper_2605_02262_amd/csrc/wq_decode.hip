@@ -38,6 +38,8 @@ struct DecodeArgs {
     const uint16_t* v_new;
     uint32_t* status;       // device status word (a full 16-bit segment is reported there)
     float len_scale;        // > 0: a (sequence, KV head) with n tokens uses ceil(n * len_scale) of the launch's splits (at least one)
+    int packed_grid;        // splits by length, workgroups with work numbered without gaps (place_by_length)
+    int slots;              // ... > 0: automatic, at most this many splits of all sequences together
 #ifdef WQ_TIMELINE
     long long* dbg;
 #endif
@@ -353,11 +355,11 @@ __global__ __launch_bounds__(256) void k_decode_generic(DecodeArgs a)
 }
 
 // Matrix-core kernel: the quantized classes of one (split, KV head, sequence).
-template <int HD, int G>
+template <int HD, int G, bool PACKED>
 __global__ __launch_bounds__(64 * WQ_WAVES) void k_decode_mfma(DecodeArgs a)
 {
     __shared__ __align__(16) unsigned char smem[sizeof(MfmaSmem<HD, G>)];
-    wq_decode_mfma_body<HD, G>(a, smem);
+    wq_decode_mfma_body<HD, G, PACKED>(a, smem);
 }
 
 // out[b,h,:] = sum_s acc_s e^{m_s - M} / sum_s l_s e^{m_s - M},  M = max_s m_s;  lse = M + log(sum).
@@ -450,18 +452,71 @@ static bool use_matrix_cores(int q_dtype, const wq_packed_kv* kv, int balgo)
     return kv->hd / kv->group == 2 || (q_dtype != WQ_F32 && fits_cost_axis(kv));
 }
 
+// Does a launch with these arguments merge the splits itself (all but their number looked at)?
+static bool merges_itself(int q_dtype, int B, const wq_packed_kv* kv, int algo)
+{
+    return !(algo & (WQ_DECODE_PARTIALS_ONLY | WQ_DECODE_SEPARATE_MERGE)) && use_matrix_cores(q_dtype, kv, algo & ~WQ_DECODE_FLAGS) &&
+           !(kv->dtype16 == WQ_BF16 && q_dtype != WQ_BF16) && (int64_t)B * kv->Hkv <= WQ_MAX_ARRIVE;
+}
+
+// Splits of an automatic launch that merges them itself (0: this one does not), for sequences of up to max_seq_tokens.  The
+// kernel's registers leave room for one workgroup per compute unit, so the launch runs in rounds of 256 workgroups: what
+// counts is (rounds) x (fixed cost of a workgroup + its blocks).  A round begun for a few workgroups costs as much as a full
+// one (9 sequences x 4 KV heads of 12800 tokens: 7 splits 20.8 us, 8 splits 30.4 us; 5 sequences: 12 splits 15.3, 13 splits
+// 22.9), and several full rounds can beat one with idle compute units (20 x 8 of 12800: 1 split 68.8, 3 splits 63.3).  Up
+// to 16 splits are merged in one round trip, up to 32 in one twice as large, more in two: 1.2 and 3.5 us in the sum.
+// Within that, the finer the better down to a few blocks per workgroup (28/4 heads of 128, 12800 tokens, batch 1: 13
+// splits 13.2 us, 32 splits 11.9; 1600 tokens: 2 splits 11.1, 12 splits 8.3).
+static int splits_for_rounds(int B, const wq_packed_kv* kv, int64_t max_seq_tokens, int most)
+{
+    const int64_t units = (int64_t)B * kv->Hkv, blocks = (max_seq_tokens + 31) / 32;
+    // a block's cost, averaged over the cache's slots; a block of cost 100 takes 0.12 us of a compute unit (0.08 with heads of 64)
+    const double slots = (double)kv->cap[0] + (double)kv->cap[1] + (double)kv->cap[2] + (double)kv->cap16;
+    const double cost = slots > 0 ? ((double)kv->cap[0] * WQ_BLOCK_COST[0] + (double)kv->cap[1] * WQ_BLOCK_COST[1] +
+                                     (double)kv->cap[2] * WQ_BLOCK_COST[2] + (double)kv->cap16 * WQ_BLOCK_COST[3]) / slots : WQ_BLOCK_COST[0];
+    const double block_us = cost * (kv->hd == 128 ? 1.2e-3 : 0.8e-3), fixed_us = kv->hd == 128 ? 8.0 : 6.5;
+    int best = 1;
+    double best_us = 0;
+    for (int s = 1; s <= most && s <= (blocks > 1 ? blocks : 1); s++) {
+        const double us = (double)((units * s + 255) / 256) * (fixed_us + block_us * (double)blocks / s) + (s > 32 ? 3.5 : s > 16 ? 1.2 : 0.0);
+        if (s == 1 || us < best_us) { best_us = us; best = s; }
+    }
+    return best;
+}
+
+// Splits of an automatic call (0: the launch would not merge them itself, the caller decides).  Under WQ_DECODE_BY_LENGTH the
+// kernel finds every sequence's count (place_by_length) and this is the most that one can get; *by_length is cleared where the
+// capacities say that the sequences are about equally long: finding the counts takes 1.1 us of the launch, and up to there
+// even counts cost less (12 sequences filling 0.76 of the longest one's length: 26.0 us against 26.5; 20 filling 0.54: 33.9
+// against 23.6).  A second round trip of the merge pays from about 900 blocks in the longest sequence.
+int wq_decode_pick_splits(const wq_ctx* ctx, int q_dtype, int B, int Hq, const wq_packed_kv* kv, int64_t max_seq_tokens, int algo, bool* by_length)
+{
+    *by_length = (algo & WQ_DECODE_BY_LENGTH) != 0;
+    if (!merges_itself(q_dtype, B, kv, algo) || max_seq_tokens <= 0 || (*by_length && B > 64)) return 0;
+    const size_t per = sizeof(float) * (size_t)B * Hq * (kv->hd + 2);
+    const size_t room = ctx->ws_bytes > WQ_WS_HEADER ? (ctx->ws_bytes - WQ_WS_HEADER) / per : 0;      // partials that the workspace holds
+    const int most = room < (size_t)WQ_MAX_FUSED_SPLITS ? (int)room : WQ_MAX_FUSED_SPLITS;
+    if (most < 1) return 0;
+    const double slots = (double)kv->cap[0] + (double)kv->cap[1] + (double)kv->cap[2] + (double)kv->cap16;
+    if (slots >= 0.75 * (double)B * (double)max_seq_tokens) *by_length = false;
+    if (*by_length) return most > 32 && max_seq_tokens <= 900 * 32 ? 32 : most;
+    return splits_for_rounds(B, kv, max_seq_tokens, most);
+}
+
 // Can wq_launch_decode append k_new, v_new (element type new_dtype) itself with these arguments?  Only the matrix-core
 // kernel that walks every segment and merges its splits does: it needs the new rows in the cache's own 16-bit type
 // and one more counter per sequence in the workspace header.
 bool wq_decode_can_append(int q_dtype, int B, int Hq, const wq_packed_kv* kv, int num_splits, int algo, int new_dtype)
 {
-    if (algo & (WQ_DECODE_PARTIALS_ONLY | WQ_DECODE_SEPARATE_MERGE)) return false;
-    const int balgo = algo & ~WQ_DECODE_FLAGS;
-    const bool use_mfma = use_matrix_cores(q_dtype, kv, balgo);
-    const bool mfma16 = use_mfma && !(kv->dtype16 == WQ_BF16 && q_dtype != WQ_BF16);
-    const int rep = Hq / kv->Hkv;
-    return mfma16 && new_dtype == kv->dtype16 && (int64_t)B * kv->Hkv + B <= WQ_MAX_ARRIVE && num_splits <= WQ_MAX_FUSED_SPLITS &&
-           rep <= WQ_MAX_REP;
+    return merges_itself(q_dtype, B, kv, algo) && new_dtype == kv->dtype16 && (int64_t)B * kv->Hkv + B <= WQ_MAX_ARRIVE &&
+           num_splits <= WQ_MAX_FUSED_SPLITS && Hq / kv->Hkv <= WQ_MAX_REP;
+}
+
+template <bool PACKED>
+static auto mfma_kernel(int hd, int groups) -> void (*)(DecodeArgs)
+{
+    if (hd == 128) return groups == 2 ? k_decode_mfma<128, 2, PACKED> : groups == 1 ? k_decode_mfma<128, 1, PACKED> : k_decode_mfma<128, 4, PACKED>;
+    return groups == 2 ? k_decode_mfma<64, 2, PACKED> : k_decode_mfma<64, 1, PACKED>;
 }
 
 int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, const wq_packed_kv* kv, float sm_scale,
@@ -470,7 +525,7 @@ int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, con
 {
     const bool partials_only = (algo & WQ_DECODE_PARTIALS_ONLY) != 0;
     const bool fixed_shares = (algo & WQ_DECODE_FIXED_SHARES) != 0;
-    const bool separate_merge = (algo & WQ_DECODE_SEPARATE_MERGE) != 0;
+    const bool fused = merges_itself(q_dtype, B, kv, algo);
     algo &= ~WQ_DECODE_FLAGS;
     DecodeArgs a;
     a.q = q;
@@ -497,8 +552,7 @@ int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, con
         a.arrive_unit *= 2;
     // one launch does it all when the matrix-core kernel walks every segment, the counters fit the workspace
     // header and a wavefront's lanes hold the splits' weights
-    a.fused = a.use_mfma && a.mfma16 && !partials_only && !separate_merge && (int64_t)B * kv->Hkv <= WQ_MAX_ARRIVE &&
-              a.nparts <= WQ_MAX_FUSED_SPLITS;
+    a.fused = fused && a.nparts <= WQ_MAX_FUSED_SPLITS;
     if (a.use_mfma && !fits_cost_axis(kv))
         return wq_fail(ctx, WQ_ERR_UNSUPPORTED, "the matrix-core decode kernel takes caches of up to 2^27 token slots");
     a.part = reinterpret_cast<float*>(ctx->ws + WQ_WS_HEADER);
@@ -509,6 +563,11 @@ int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, con
     if (k_new && !a.fused) return wq_fail(ctx, WQ_ERR_UNSUPPORTED, "this decode launch cannot append");
     // splits by length: only where the kernel merges the splits itself (the separate merge kernel reads every partial)
     a.len_scale = (a.fused && longest_tokens > 0) ? (float)a.splits / (float)longest_tokens : 0.f;
+    a.packed_grid = a.fused && longest_tokens != 0 && B <= 64;
+    // Automatic splits by length: 256 workgroups, one per compute unit, if that is at least two per (sequence, KV head), so
+    // that rounding to whole splits leaves few of them with little to do; else 512
+    const int auto_wgs = (int64_t)B * kv->Hkv <= 128 ? 256 : 512;
+    a.slots = a.packed_grid && longest_tokens < 0 ? auto_wgs / kv->Hkv : 0;
 #ifdef WQ_TIMELINE
     a.dbg = getenv("WQ_TIMELINE") ? reinterpret_cast<long long*>(ctx->ws + ctx->ws_bytes - (8 << 20)) : nullptr;
 #endif
@@ -516,13 +575,13 @@ int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, con
     const dim3 blk(256);
     const dim3 grid_q(a.splits, kv->Hkv, B), grid_16(a.splits16 > 0 ? a.splits16 : 1, kv->Hkv, B);
     // the matrix-core kernel maps workgroups (of WQ_WAVES wavefronts) to units itself
-    const dim3 grid_m((unsigned)kv->Hkv, (unsigned)B, (unsigned)a.splits), blk_m(64 * WQ_WAVES);
+    const dim3 blk_m(64 * WQ_WAVES), grid_m = a.packed_grid ? dim3((unsigned)(a.slots > 0 ? a.slots * kv->Hkv : a.splits * kv->Hkv * B))
+                                                            : dim3((unsigned)kv->Hkv, (unsigned)B, (unsigned)a.splits);
     const int tslot = (int)(ctx->ev_calls % WQ_TIMING_RING);
     if (ctx->timing) (void)hipEventRecord(ctx->ev[2 * tslot], ctx->stream);
     const int groups = kv->hd / kv->group;
     if (a.use_mfma) {
-        void (*const kernel)(DecodeArgs) = kv->hd == 128 ? (groups == 2 ? k_decode_mfma<128, 2> : groups == 1 ? k_decode_mfma<128, 1> : k_decode_mfma<128, 4>)
-                                                         : (groups == 2 ? k_decode_mfma<64, 2> : k_decode_mfma<64, 1>);
+        void (*const kernel)(DecodeArgs) = a.packed_grid ? mfma_kernel<true>(kv->hd, groups) : mfma_kernel<false>(kv->hd, groups);
         hipLaunchKernelGGL(kernel, grid_m, blk_m, 0, ctx->stream, a);
     } else {
         hipLaunchKernelGGL(kv->hd == 128 ? k_decode_generic<128> : k_decode_generic<64>, grid_q, blk, 0, ctx->stream, a);

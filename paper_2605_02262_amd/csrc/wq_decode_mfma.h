@@ -263,6 +263,7 @@ struct MfmaSmem {
     float qx[4][1 + SETS][64];                           // ... with the head's power of two and the group's query sum per set
     float ml[WQ_WAVES][WQ_MAX_REP][2];
     unsigned next_ticket;                                // the workgroup's block counter
+    int expect[64], grown[64];                           // the workgroup that ends an append: per sequence, the workgroups that count themselves on it, and the new len16 (-1: unchanged)
 };
 
 
@@ -943,6 +944,121 @@ __device__ __forceinline__ void finish_append(const DecodeArgs& a, int b, int kv
     if (new_row >= 0) a.kv.len16[b] = new_row + 1;
 }
 
+// ---- which part of which sequence a workgroup of a launch by length gets (at most 64 sequences: one per lane) ----
+// The grid is one-dimensional: sequence 0's S_0 * Hkv workgroups, then sequence 1's, ..., then those with nothing to do.
+// Consecutive workgroups go to different XCDs, so every XCD gets the same share of the work whatever the lengths (with the
+// workgroups of a (sequence, KV head) at a fixed distance, as launches for equal lengths have them, the long sequences'
+// workgroups can all fall on the same XCDs; those without work also took compute units from the others).
+// How many splits S_b a sequence gets: in a launch with a given count ceil(tokens * len_scale); in an automatic one
+// ceil(cost / tau) for the smallest cost per workgroup tau that needs no more workgroups than the launch has
+// (slots * Hkv), found by bisection between the mean (no rounding at all) and what is certain to fit.
+// Every wavefront of the launch computes the same from the same tables.
+struct Place {
+    int b, kvh, split, S;     // (b < 0: nothing to do)
+    int len[4], off[4], end16;
+    float v_scale_max;
+};
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int scan_step(int x)          // x plus the value that a data-parallel-primitive move brings (0 where none)
+{
+    return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, true);
+}
+
+template <int HD, int G>
+__device__ __forceinline__ Place place_by_length(const DecodeArgs& a, MfmaSmem<HD, G>& sm, int wg)
+{
+    const int lane = threadIdx.x & 63, l = min(lane, a.B - 1);
+    int len[4], off[4];
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        len[c] = a.kv.cls_len[c][l];
+        off[c] = a.kv.cls_off[c][l];
+    }
+    const int len16 = a.kv.len16[l], end16 = a.kv.off16[l + 1];
+    off[3] = a.kv.off16[l];
+    const float vmax = a.kv.v_scale_max[l];
+    const bool grows = a.k_new && off[3] + len16 < end16 && (int64_t)off[3] + len16 < a.kv.cap16;
+    len[3] = len16;
+    const bool mine = lane < a.B;
+    int S;
+    if (a.slots == 0) {
+        const int tokens = len[0] + len[1] + len[2] + len[3] + (grows ? 1 : 0);
+        S = max(1, min(a.splits, (int)ceilf((float)tokens * a.len_scale)));
+    } else {
+        int blocks = 1;
+#pragma unroll
+        for (int c = 0; c < 4; c++) blocks += ((len[c] + 31) >> 5) * WQ_BLOCK_COST[c];
+        const float cost = mine ? (float)blocks : 0.f, total = wave_sum(cost), most = wave_max(cost);
+        // (a sequence's share is rounded down by 0.002 first: a quotient that should be whole must not become the next whole number)
+        auto splits_of = [&](float tau) { return mine ? max(1, min(a.splits, (int)ceilf(fmaf(cost, __builtin_amdgcn_rcpf(tau), -0.002f)))) : 0; };
+        float lo = total / (float)a.slots;
+        float hi = fmaxf(lo, a.slots > a.B ? fminf(total / (float)(a.slots - a.B), most) : most);
+#pragma unroll 1
+        for (int k = 0; k < 3; k++) {
+            const float mid = 0.5f * (lo + hi);
+            const bool fits = wave_sum((float)splits_of(mid)) <= (float)a.slots;
+            lo = fits ? lo : mid;
+            hi = fits ? mid : hi;
+        }
+        S = splits_of(hi);
+    }
+    const int n = mine ? S * a.kv.Hkv : 0;
+    int upto = scan_step<0x111, 0xF>(n);                 // row_shr:1, 2, 4, 8, then the rows before
+    upto = scan_step<0x112, 0xF>(upto);
+    upto = scan_step<0x114, 0xF>(upto);
+    upto = scan_step<0x118, 0xF>(upto);
+    upto = scan_step<0x142, 0xA>(upto);                  // row_bcast:15 into the odd rows
+    upto = scan_step<0x143, 0xC>(upto);                  // row_bcast:31 into the upper half
+    const int total = __builtin_amdgcn_readlane(upto, 63);
+    if (a.k_new && wg == (int)gridDim.x - 1 && threadIdx.x < 64) {
+        sm.expect[lane] = n + (lane == 0 ? (int)gridDim.x - total : 0);
+        sm.grown[lane] = mine && grows ? len16 + 1 : -1;
+    }
+    Place p;
+    p.b = -1;
+    if (wg >= total) return p;
+    p.b = (int)__popcll(__builtin_amdgcn_ballot_w64(mine && upto <= wg));
+    const int rem = wg - (__builtin_amdgcn_readlane(upto, p.b) - __builtin_amdgcn_readlane(n, p.b));
+    p.split = __builtin_amdgcn_readfirstlane((int)(((float)rem + 0.5f) * __builtin_amdgcn_rcpf((float)a.kv.Hkv)));
+    p.kvh = rem - p.split * a.kv.Hkv;
+    p.S = __builtin_amdgcn_readlane(S, p.b);
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+        p.len[c] = __builtin_amdgcn_readlane(len[c], p.b);
+        p.off[c] = __builtin_amdgcn_readlane(off[c], p.b);
+    }
+    p.end16 = __builtin_amdgcn_readlane(end16, p.b);
+    p.v_scale_max = lane_value(vmax, p.b);
+    return p;
+}
+
+// ... the end of an append in such a launch: the launch's last workgroup in dispatch order (by the same reasoning as in
+// finish_append) waits until every workgroup has counted itself, those with nothing to do on sequence 0's counter
+template <int HD, int G>
+__device__ __forceinline__ void finish_append_by_length(const DecodeArgs& a, MfmaSmem<HD, G>& sm, int wg)
+{
+    if (!a.k_new || threadIdx.x >= 64 || wg != (int)gridDim.x - 1) return;
+    const int lane = threadIdx.x;
+    const bool mine = lane < a.B;
+    const unsigned expect = (unsigned)sm.expect[lane];
+    unsigned* const ctr = a.arrive + a.B * a.kv.Hkv * a.arrive_unit + (mine ? lane : 0) * WQ_ARRIVE_STRIDE;
+    const long long t_start = wall_clock64();
+    while (true) {
+        const bool there = !mine || __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == expect;
+        if (__builtin_amdgcn_ballot_w64(!there) == 0) break;
+        if (wall_clock64() - t_start > WQ_APPEND_WAIT_TICKS) {
+            if (lane == 0) atomicOr(a.status, WQ_DEV_APPEND_TIMEOUT);
+            break;
+        }
+        __builtin_amdgcn_s_sleep(8);
+    }
+    if (mine) {
+        __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (sm.grown[lane] >= 0) a.kv.len16[lane] = sm.grown[lane];
+    }
+}
+
 // Shares are laid out on a cost axis in integers (a 32-token block of a class costs WQ_BLOCK_COST of it): everything
 // here depends only on the sequence's tables and the workgroup's and wavefront's numbers, which are the same for all
 // lanes, so the compiler keeps it in scalar registers and on the scalar unit, where it does not compete with the vector
@@ -1013,15 +1129,16 @@ __device__ __forceinline__ typename FloatN<N>::type ld_part(__amdgpu_buffer_rsrc
 }
 
 
-template <int HD, int G>
+// PACKED: a launch by length whose grid place_by_length maps (an instantiation of its own: in a common one the registers it
+// takes cost every other launch 0.2-0.5 us)
+template <int HD, int G, bool PACKED>
 __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
 {
     MfmaSmem<HD, G>& sm = *reinterpret_cast<MfmaSmem<HD, G>*>(smem_raw);
     // consecutive workgroups go to different (sequence, KV head) units: the units' tables and queries are then
     // read by all XCDs alike, and the workgroups of one unit do not start in a burst on neighbouring compute units
     // (the grid is (KV heads, sequences, splits): workgroups are dispatched with x fastest, and nothing here has to divide)
-    const int kvh = (int)blockIdx.x, b = (int)blockIdx.y, split = (int)blockIdx.z;
-    const int unit = b * a.kv.Hkv + kvh;
+    int kvh = (int)blockIdx.x, b = (int)blockIdx.y, split = (int)blockIdx.z, S = a.splits;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int j = lane >> 4, col = lane & 15, g = col >> 3, h = col & 7;
     constexpr int CT = HD / 16;
@@ -1029,16 +1146,36 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
     WQ_STAMP(0);
 
     // ---- the sequence's tables first (their loads are in flight while the query operands are built) ----
-    int cls_len[4], cls_off[4];
+    int cls_len[4], cls_off[4], end16;
+    float v_scale_max;
+    if constexpr (PACKED) {
+        const Place p = place_by_length<HD, G>(a, sm, (int)blockIdx.x);
+        note_tables_read(a, max(p.b, 0), p.b);
+        if (p.b < 0) {
+            finish_append_by_length<HD, G>(a, sm, (int)blockIdx.x);
+            return;
+        }
+        b = p.b, kvh = p.kvh, split = p.split, S = p.S;
 #pragma unroll
-    for (int c = 0; c < 3; c++) {
-        cls_len[c] = a.kv.cls_len[c][b];
-        cls_off[c] = a.kv.cls_off[c][b];
+        for (int c = 0; c < 4; c++) {
+            cls_len[c] = p.len[c];
+            cls_off[c] = p.off[c];
+        }
+        end16 = p.end16;
+        v_scale_max = p.v_scale_max;
+    } else {
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            cls_len[c] = a.kv.cls_len[c][b];
+            cls_off[c] = a.kv.cls_off[c][b];
+        }
+        cls_len[3] = a.kv.len16[b];
+        cls_off[3] = a.kv.off16[b];
+        end16 = a.kv.off16[b + 1];
+        v_scale_max = a.kv.v_scale_max[b];
+        note_tables_read(a, b, cls_len[3]);
     }
-    cls_len[3] = a.kv.len16[b];
-    cls_off[3] = a.kv.off16[b];
-    const float v_scale_max = a.kv.v_scale_max[b];
-    note_tables_read(a, b, cls_len[3]);
+    const int unit = b * a.kv.Hkv + kvh;
     // a token appended by this launch becomes the last row of the 16-bit segment: read from k_new / v_new by whoever
     // walks its block, copied into the cache by the first split's workgroup, counted in len16 once every workgroup of
     // the sequence has read len16 (finish_append)
@@ -1046,7 +1183,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
     const uint16_t *knew = nullptr, *vnew = nullptr;
     if (a.k_new) {
         const int64_t row = (int64_t)cls_off[3] + cls_len[3];
-        if (row < a.kv.off16[b + 1] && row < a.kv.cap16) {
+        if (row < end16 && row < a.kv.cap16) {
             new_row = cls_len[3];
             cls_len[3] += 1;
             knew = a.k_new + ((int64_t)b * a.kv.Hkv + kvh) * HD;
@@ -1061,10 +1198,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         }
     }
     WQ_WSTAMP(5, wall_clock64() + (long long)((cls_len[0] + cls_len[1] + cls_len[2] + cls_len[3] + cls_off[0] + cls_off[1] + cls_off[2] + cls_off[3]) & 0));   // the tables have arrived
-    // ---- splits of this (sequence, KV head): all of the launch's, or, in a launch for sequences of different lengths,
-    //      as many as the sequence's share of the longest one asks for; the workgroups beyond them have nothing to do ----
-    int S = a.splits;
-    if (a.len_scale > 0.f) {
+    if (!PACKED && a.len_scale > 0.f) {     // (more than 64 sequences: the sequence's share of the launch's splits, the other workgroups have nothing to do)
         const int tokens = cls_len[0] + cls_len[1] + cls_len[2] + cls_len[3];
         S = max(1, min(a.splits, (int)ceilf((float)tokens * a.len_scale)));
         if (split >= S) {
@@ -1295,7 +1429,10 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         if (a.lse && lane == 0) a.lse[(int64_t)b * a.Hq + hq] = L > 0.f ? M + logf(L) : -INFINITY;
     }
     WQ_STAMP(59);
-    finish_append(a, b, kvh, split, new_row);
+    if constexpr (PACKED)
+        finish_append_by_length<HD, G>(a, sm, (int)blockIdx.x);
+    else
+        finish_append(a, b, kvh, split, new_row);
 }
 
 }  // namespace

@@ -67,3 +67,42 @@ def test_arrival_counters_at_every_spacing(B):
         assert H.attention_error(out.cpu().numpy(), o.out) <= TIGHT, splits
         assert np.array_equal(run.pk.len16.cpu().numpy(), o.pk.len16)
     assert ctx.device_status() == 0 and int(ctx.ws[:16384].count_nonzero()) == 0        # every counter is back at zero
+
+
+@pytest.mark.parametrize("B,Hkv", [(1, 2), (2, 1), (7, 3), (33, 4), (42, 3), (64, 2), (65, 2)])
+def test_splits_by_length(B, Hkv):
+    """Lengths from one token to 40 blocks.  Given counts and automatic ones, the latter also with a workspace for the plain
+    count only; appended tokens, among them some that begin a new block.  Up to 64 sequences the kernel numbers the
+    workgroups with work without gaps, beyond them a sequence's surplus workgroups return."""
+    from oracle import wq_oracle as O
+    from paper_2605_02262_amd import binding as W
+    from tests import wq_harness as H
+    rng = np.random.default_rng(B)
+    specs = [synth.SeqSpec(40, 30, 30, 31, (8, 12, 20))]
+    for b in range(1, B):
+        n = int(rng.integers(0, 12)) if b % 5 else 0
+        top = int(rng.integers(0, n + 1))
+        specs.append(synth.SeqSpec(n, 16, 16, [1, 30, 31, 32][b % 4], (top, (n - top) // 2, n - top - (n - top) // 2)))
+    w = synth.Workload("by-length", synth.BF16, synth.BF16, 3 * Hkv, Hkv, 64, 64, 64, 1.0, specs, 700 + B, pin_first=0)
+    bt = synth.batch(w, with_embeddings=False)
+    sc = rng.standard_normal(int(bt.t.win_off[-1])).astype(np.float32)
+    cap, off16 = H.capacities(w, slack=12)
+    run = H.run_gpu(bt, cap=cap, off16=off16, splits=1, with_scores=False, scores_override=sc)
+    o = H.run_oracle(bt, scores_override=sc, with_scores=False, cap=cap, off16=off16)
+    q, sm, longest = H.to_dev(bt.q, w.dtype), 0.125, 1240
+    large = W.Context(W.workspace_bytes(B, w.Hq, 64, 64))
+    plain = W.Context(W.workspace_bytes(B, w.Hq, 64, W.auto_splits(B, Hkv, longest)))
+    for ctx, splits, flags in ((large, 0, 0), (large, 0, 0), (plain, 0, 0), (large, 0, W.DECODE_FIXED_SHARES), (large, 1, 0), (large, 5, 0), (large, 64, 0)):
+        out = W.wq_decode_attention(ctx, q, run.pk, sm, splits, longest, W.DECODE_BY_LENGTH | flags)
+        assert H.attention_error(out.cpu().numpy(), o.out) <= TIGHT, (splits, flags)
+        kn, vn = (synth.round_to(rng.standard_normal((B, Hkv, 64)).astype(np.float32), w.dtype) for _ in range(2))
+        out = W.wq_decode_append_attention(ctx, q, run.pk, H.to_dev(kn, w.dtype), H.to_dev(vn, w.dtype), sm, splits, longest, W.DECODE_BY_LENGTH | flags)
+        for b in range(B):
+            r = int(o.pk.off16[b] + o.pk.len16[b])
+            o.pk.k16[r], o.pk.v16[r] = kn[b], vn[b]
+            o.pk.len16[b] += 1
+        o.out = O.decode_attention(bt.q, o.pk, sm)
+        assert H.attention_error(out.cpu().numpy(), o.out) <= TIGHT, (splits, flags)
+        assert np.array_equal(run.pk.len16.cpu().numpy(), o.pk.len16)
+    for ctx in (large, plain):
+        assert ctx.device_status() == 0 and int(ctx.ws[:16384].count_nonzero()) == 0

@@ -424,10 +424,17 @@ __global__ __launch_bounds__(256) void k_append16(const T* __restrict__ k_new, c
 // dst's 16-bit segment receives, per sequence, the dequantized tokens of src's 2-, 4- and 8-bit classes (in this order,
 // the order of the cache) and then src's 16-bit rows; dst's classes are empty.  Decode attention over dst is then the
 // plain 16-bit attention that a dequantize-to-memory implementation would run.
-//   k_dense_plan   dst tables, capacity check
-//   k_dequantize   one workgroup per (32-token block of a class, KV head): value = fma(code, s, m) in fp32, rounded to
-//                  nearest even into the 16-bit type
-//   k_dense_copy   src's 16-bit rows
+// One launch: a workgroup per (32-token block of a class, KV head), value = fma(code, s, m) in fp32, rounded to nearest even
+// into the 16-bit type; a workgroup per DENSE_ROWS rows of src's 16-bit segment; and one for dst's tables.
+// Bound by the 16-bit rows that it writes, if the vector unit keeps up: a lane instruction per element costs the whole call
+// 3 us at 8 x 12800 tokens, 4 KV heads of 128.  So a thread turns 8 consecutive channels of a token (16 bytes of a row, a
+// row's pieces by consecutive lanes) from codes that lie one per byte (a conversion instruction takes any byte of a
+// register), two values at a time; and the V codes, whose operand order has 8 tokens of one channel together, are
+// transposed as bytes, 8 lanes x 8 tokens at a time, in three exchanges between lanes (11 instructions per 8 codes).
+// Field by field from LDS, in a launch per class, the call took 93 us (275 MB read and written: 2.9 TB/s); this way 59 us (4.7
+// TB/s; a plain copy of 1 GiB runs at 5.0).
+constexpr int DENSE_ROWS = 8;
+
 __device__ __forceinline__ int dense_total(const wq_packed_kv& src, int b)
 {
     return src.cls_len[0][b] + src.cls_len[1][b] + src.cls_len[2][b] + src.len16[b];
@@ -438,7 +445,7 @@ __device__ __forceinline__ bool dense_fits(const wq_packed_kv& src, const wq_pac
     return dst.off16[b] >= 0 && n <= dst.off16[b + 1] - dst.off16[b] && (int64_t)dst.off16[b] + n <= dst.cap16;
 }
 
-__global__ __launch_bounds__(256) void k_dense_plan(int B, wq_packed_kv src, wq_packed_kv dst, uint32_t* __restrict__ status)
+__device__ __forceinline__ void dense_plan(int B, const wq_packed_kv& src, const wq_packed_kv& dst, uint32_t* __restrict__ status)
 {
     for (int b = threadIdx.x; b < B; b += 256) {
         const bool ok = dense_fits(src, dst, b);
@@ -453,120 +460,212 @@ __global__ __launch_bounds__(256) void k_dense_plan(int B, wq_packed_kv src, wq_
         for (int c = 0; c < 3; c++) dst.cls_off[c][b] = 0;
 }
 
-__device__ __forceinline__ uint16_t to_16bit(float x, bool bf16)
+typedef float float2v __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+
+// two values rounded to nearest even into the 16-bit type
+template <bool BF>
+__device__ __forceinline__ uint32_t pair_16bit(float x, float y)
 {
-    if (bf16) {
-        const uint32_t u = __float_as_uint(x);
-        return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);       // nearest even (finite values)
-    }
-    return __half_as_ushort(__float2half_rn(x));
+    const float2v v = {x, y};
+    if constexpr (BF) return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2v));
+    else return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, half2v));
 }
 
-template <int HD, int BITS>
-__global__ __launch_bounds__(256) void k_dequantize(int B, wq_packed_kv src, wq_packed_kv dst)
+__device__ __forceinline__ float byte_of(uint32_t x, int k) { return (float)((x >> (8 * k)) & 0xFFu); }
+
+template <int NB>
+__device__ __forceinline__ void load_bytes(const uint8_t* p, uint32_t* x)      // NB bytes, aligned to NB
+{
+    if constexpr (NB == 2) {
+        x[0] = *reinterpret_cast<const uint16_t*>(p);
+    } else if constexpr (NB == 4) {
+        x[0] = *reinterpret_cast<const uint32_t*>(p);
+    } else if constexpr (NB == 8) {
+        const uint2 t = *reinterpret_cast<const uint2*>(p);
+        x[0] = t.x, x[1] = t.y;
+    } else {
+        const uint4 t = *reinterpret_cast<const uint4*>(p);
+        x[0] = t.x, x[1] = t.y, x[2] = t.z, x[3] = t.w;
+    }
+}
+
+// 8 consecutive fields of BITS bits as numbers
+template <int BITS>
+__device__ __forceinline__ void codes_of(const uint32_t* w, float (&c)[8])
+{
+    if constexpr (BITS == 8) {
+#pragma unroll
+        for (int i = 0; i < 8; i++) c[i] = byte_of(w[i >> 2], i & 3);
+    } else if constexpr (BITS == 4) {
+        const uint32_t even = w[0] & 0x0F0F0F0Fu, odd = (w[0] >> 4) & 0x0F0F0F0Fu;
+#pragma unroll
+        for (int i = 0; i < 8; i++) c[i] = byte_of((i & 1) ? odd : even, i >> 1);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const uint32_t x = (w[0] >> (2 * k)) & 0x0303u;       // fields k and k + 4
+            c[k] = byte_of(x, 0);
+            c[k + 4] = byte_of(x, 1);
+        }
+    }
+}
+
+// 8 values m + s * code of a token -> 16 bytes of its row
+template <bool BF>
+__device__ __forceinline__ uint4 dense_piece(const float (&c)[8], uint32_t word)
+{
+    const float s = __half2float(__ushort_as_half((uint16_t)(word & 0xFFFFu))), m = __half2float(__ushort_as_half((uint16_t)(word >> 16)));
+    uint32_t o[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) o[i] = pair_16bit<BF>(fmaf(c[2 * i], s, m), fmaf(c[2 * i + 1], s, m));
+    return make_uint4(o[0], o[1], o[2], o[3]);
+}
+
+__device__ __forceinline__ uint32_t byte_perm(uint32_t hi, uint32_t lo, uint32_t sel) { return __builtin_amdgcn_perm(hi, lo, sel); }
+
+// The V codes of a lane of the operand order for one channel tile: 8 tokens of one channel, as bytes in d0, d1 in the order
+// v_tau below.  Eight lanes (channels) x 8 tokens are transposed: lane l = mm & 7 is left with token v_tau(l) and the
+// channels 0..7 of the eight, in order.  Each exchange (partners l ^ 7, l ^ 2, l ^ 1) halves the tokens and doubles the
+// channels; byte i of (hi, lo) is then the channel l ^ x with i = index(x), index linear over xor: 1 -> 4, 2 -> 2, 4 -> 7.
+__device__ __forceinline__ uint2 transpose_codes(uint32_t d0, uint32_t d1, int l)
+{
+    const bool b0 = l & 1, b1 = l & 2, b2 = l & 4;
+    const uint32_t a = b2 ? d1 : d0, b = lanes_moved<0x141>(b2 ? d0 : d1);
+    const uint32_t k = byte_perm(b, a, b1 ? 0x07060302u : 0x05040100u), r = lanes_moved<0x4E>(byte_perm(b, a, b1 ? 0x05040100u : 0x07060302u));
+    const uint32_t lo = byte_perm(r, k, b0 ? 0x07050301u : 0x06040200u), hi = lanes_moved<0xB1>(byte_perm(r, k, b0 ? 0x06040200u : 0x07050301u));
+    const uint32_t own = ((b0 ? 4u : 0u) ^ (b1 ? 2u : 0u) ^ (b2 ? 7u : 0u)) * 0x01010101u;
+    return make_uint2(byte_perm(hi, lo, 0x06020400u ^ own), byte_perm(hi, lo, 0x01050307u ^ own));
+}
+template <int BITS>
+__device__ __forceinline__ int v_tau(int l)      // the token (tau) that byte l & 3 of d[l >> 2] belongs to
+{
+    constexpr uint32_t order = BITS == 8 ? 0x76543210u : BITS == 4 ? 0x75316420u : 0x73625140u;
+    return (int)((order >> (4 * l)) & 7u);
+}
+
+template <int HD>
+struct DenseSmem {
+    static constexpr int PITCH = HD + 8;
+    __attribute__((aligned(16))) uint8_t v[32 * PITCH];      // V codes, a byte each, [token][channel]
+};
+
+template <int HD, int BITS, bool BF>
+__device__ __forceinline__ void dequantize_block(DenseSmem<HD>& sm, int blk, int kvh, int B, const wq_packed_kv& src, const wq_packed_kv& dst)
 {
     constexpr int C = cls_index(BITS);
-    constexpr int CPT = HD / 8;                 // channels per thread: 8 threads share one token row
-    constexpr int Q = HD / 4, CT = HD / 16;
-    constexpr int BLK_B = 32 * HD * BITS / 8;   // bytes of a 32-token block of one plane
-    __shared__ __align__(16) uint8_t s_v[BLK_B];
-    const int tid = threadIdx.x, kvh = blockIdx.y, Hkv = src.Hkv, G = HD / src.group;
+    constexpr int Q = HD / 4, CT = HD / 16, CTW = CT / 4;       // CTW: channel tiles that a wavefront transposes
+    constexpr int ITEMS = HD / 64;                              // pieces of 8 channels per thread and plane
+    const int tid = threadIdx.x, Hkv = src.Hkv, G = HD / src.group;
     const int32_t* off = src.cls_off[C];
-    const int64_t tok0 = (int64_t)blockIdx.x * 32;
-    if (tok0 >= off[B]) return;                 // unused capacity
-    const int b = wq_find_seq(off, B, tok0);
-    if (!dense_fits(src, dst, b)) return;
-    const int d0 = (int)(tok0 - off[b]), len = src.cls_len[C][b];
-    int before = 0;                             // tokens of the lower classes come first
-    for (int c = 0; c < C; c++) before += src.cls_len[c][b];
-    const bool bf16 = dst.dtype16 == WQ_BF16;
-
+    const int64_t tok0 = (int64_t)blk * 32;
     const uint8_t* kc = static_cast<const uint8_t*>(src.codes[C]) + ((int64_t)kvh * src.cap[C] + tok0) * HD * BITS / 8;
     const uint8_t* vc = static_cast<const uint8_t*>(src.codes[C]) + (((int64_t)Hkv + kvh) * src.cap[C] + tok0) * HD * BITS / 8;
-    for (int i = tid; i < BLK_B / 16; i += 256) reinterpret_cast<uint4*>(s_v)[i] = reinterpret_cast<const uint4*>(vc)[i];
-    __syncthreads();
+    const uint32_t* km = static_cast<const uint32_t*>(src.meta[C]) + ((int64_t)kvh * src.cap[C] + tok0) * G;
+    const uint32_t* vm = static_cast<const uint32_t*>(src.meta[C]) + (((int64_t)Hkv + kvh) * src.cap[C] + tok0) * G;
+    // every load of the block first: this lane's V codes of the wavefront's channel tiles, its K pieces, the words of both
+    const int lane = tid & 63, wave = tid >> 6, jj = lane >> 4, mm = lane & 15;
+    constexpr int VB = CTW * BITS, KB = BITS;                   // bytes
+    uint32_t vw[(VB + 3) / 4], kw[ITEMS][(KB + 3) / 4], kword[ITEMS], vword[ITEMS];
+    load_bytes<VB>(vc + lane * (CT * BITS) + wave * VB, vw);
+#pragma unroll
+    for (int i = 0; i < ITEMS; i++) {
+        const int item = i * 256 + tid, u = item / (HD / 8), ch = (item % (HD / 8)) * 8, tile = u >> 4, m = u & 15;
+        const int word = (tile * G + ch / src.group) * 16 + m;
+        load_bytes<KB>(kc + tile * (16 * HD * BITS / 8) + ((ch / Q * 16 + m) * Q + ch % Q) * BITS / 8, kw[i]);
+        kword[i] = km[word];
+        vword[i] = vm[word];
+    }
+    const int b = wq_find_seq(off, B, tok0);
+    if (!dense_fits(src, dst, b)) return;                       // (the same for the whole workgroup)
+    const int d0 = (int)(tok0 - off[b]), len = src.cls_len[C][b];
+    int before = 0;                                             // tokens of the lower classes come first
+    for (int c = 0; c < C; c++) before += src.cls_len[c][b];
 
-    const int u = tid >> 3, p = tid & 7;        // token of the block, part of its row
-    if (d0 + u >= len) return;
-    const int64_t row = (int64_t)dst.off16[b] + before + d0 + u;
-    const int tile = u >> 4, m = u & 15;
-    const int gi = (p * CPT) / src.group;       // the thread's channels lie in one group (group >= CPT)
-    uint32_t ko[CPT / 2], vo[CPT / 2];              // pairs of 16-bit values
+    const int l = mm & 7, tau = v_tau<BITS>(l);
+    uint8_t* const vt = sm.v + (16 * (tau >> 2) + 4 * jj + (tau & 3)) * DenseSmem<HD>::PITCH + 8 * (mm >> 3);
 #pragma unroll
-    for (int i = 0; i < CPT / 2; i++) ko[i] = vo[i] = 0u;
-    {   // K: the thread's codes are consecutive fields of its token's row quarter
-        const uint32_t word = static_cast<const uint32_t*>(src.meta[C])[((int64_t)kvh * src.cap[C] + tok0) * G + (tile * G + gi) * 16 + m];
-        const float s = __half2float(__ushort_as_half((uint16_t)(word & 0xFFFFu))), mn = __half2float(__ushort_as_half((uint16_t)(word >> 16)));
-        const int j = (p * CPT) / Q, e0 = (p * CPT) % Q;
-        const uint8_t* in = kc + tile * (16 * HD * BITS / 8) + ((j * 16 + m) * Q + e0) * BITS / 8;
-        constexpr int NB = CPT * BITS / 8;      // bytes of the thread's codes: 2..16, aligned to their size
-        uint32_t pw[(NB + 3) / 4];
-        if constexpr (NB == 2) {
-            pw[0] = *reinterpret_cast<const uint16_t*>(in);
-        } else if constexpr (NB == 4) {
-            pw[0] = *reinterpret_cast<const uint32_t*>(in);
-        } else if constexpr (NB == 8) {
-            const uint2 t = *reinterpret_cast<const uint2*>(in);
-            pw[0] = t.x, pw[1] = t.y;
+    for (int k = 0; k < CTW; k++) {
+        uint32_t c0, c1;
+        if constexpr (BITS == 8) {
+            c0 = vw[2 * k], c1 = vw[2 * k + 1];
+        } else if constexpr (BITS == 4) {
+            c0 = vw[k] & 0x0F0F0F0Fu, c1 = (vw[k] >> 4) & 0x0F0F0F0Fu;
         } else {
-            const uint4 t = *reinterpret_cast<const uint4*>(in);
-            pw[0] = t.x, pw[1] = t.y, pw[2] = t.z, pw[3] = t.w;
+            const uint32_t x = k == 0 ? vw[0] & 0xFFFFu : vw[0] >> 16, y = (x << 14) | x;
+            c0 = y & 0x03030303u, c1 = (y >> 4) & 0x03030303u;
         }
-#pragma unroll
-        for (int i = 0; i < CPT; i++) {
-            const uint32_t code = (pw[(i * BITS) >> 5] >> ((i * BITS) & 31)) & ((1u << BITS) - 1u);
-            ko[i >> 1] |= (uint32_t)to_16bit(fmaf((float)code, s, mn), bf16) << (16 * (i & 1));
-        }
+        *reinterpret_cast<uint2*>(vt + 16 * (wave * CTW + k)) = transpose_codes(c0, c1, l);
     }
-    {   // V: field n = ((jj*16 + mm)*CT + ct)*8 + tau of the block, channel 16 ct + mm
-        const uint32_t word = static_cast<const uint32_t*>(src.meta[C])[(((int64_t)Hkv + kvh) * src.cap[C] + tok0) * G + (tile * G + gi) * 16 + m];
-        const float s = __half2float(__ushort_as_half((uint16_t)(word & 0xFFFFu))), mn = __half2float(__ushort_as_half((uint16_t)(word >> 16)));
-        const int jj = m >> 2, tau = 4 * tile + (u & 3);
+    __syncthreads();
+    const int64_t row0 = (int64_t)dst.off16[b] + before + d0;
 #pragma unroll
-        for (int i = 0; i < CPT; i++) {
-            const int ch = p * CPT + i, ct = ch >> 4, mm = ch & 15;
-            const int bit = (((jj * 16 + mm) * CT + ct) * 8 + tau) * BITS;
-            const uint32_t code = (s_v[bit >> 3] >> (bit & 7)) & ((1u << BITS) - 1u);
-            vo[i >> 1] |= (uint32_t)to_16bit(fmaf((float)code, s, mn), bf16) << (16 * (i & 1));
-        }
-    }
-    uint16_t* k16 = static_cast<uint16_t*>(dst.k16) + (row * Hkv + kvh) * HD + p * CPT;
-    uint16_t* v16 = static_cast<uint16_t*>(dst.v16) + (row * Hkv + kvh) * HD + p * CPT;
+    for (int i = 0; i < ITEMS; i++) {
+        const int item = i * 256 + tid, u = item / (HD / 8), ch = (item % (HD / 8)) * 8;
+        if (d0 + u >= len) continue;
+        const int64_t o = ((row0 + u) * Hkv + kvh) * HD + ch;
+        float c[8];
+        codes_of<BITS>(kw[i], c);
+        *reinterpret_cast<uint4*>(static_cast<uint16_t*>(dst.k16) + o) = dense_piece<BF>(c, kword[i]);
+        const uint2 v = *reinterpret_cast<const uint2*>(sm.v + u * DenseSmem<HD>::PITCH + ch);
 #pragma unroll
-    for (int i = 0; i < CPT; i += 8) {
-        *reinterpret_cast<uint4*>(k16 + i) = make_uint4(ko[i / 2], ko[i / 2 + 1], ko[i / 2 + 2], ko[i / 2 + 3]);
-        *reinterpret_cast<uint4*>(v16 + i) = make_uint4(vo[i / 2], vo[i / 2 + 1], vo[i / 2 + 2], vo[i / 2 + 3]);
+        for (int k = 0; k < 8; k++) c[k] = byte_of(k < 4 ? v.x : v.y, k & 3);
+        *reinterpret_cast<uint4*>(static_cast<uint16_t*>(dst.v16) + o) = dense_piece<BF>(c, vword[i]);
     }
 }
 
-__global__ __launch_bounds__(256) void k_dense_copy(int B, int row_elems, wq_packed_kv src, wq_packed_kv dst)
+__device__ __forceinline__ void dense_copy(int64_t r0, int B, int pieces, const wq_packed_kv& src, const wq_packed_kv& dst)
 {
-    const int64_t r = blockIdx.x;               // a row of src's 16-bit segment
-    const int b = wq_find_seq(src.off16, B, r);
-    if (r < src.off16[0] || r >= src.off16[B]) return;
-    const int i = (int)(r - src.off16[b]);
-    if (i >= src.len16[b] || !dense_fits(src, dst, b)) return;
-    const int64_t d = (int64_t)dst.off16[b] + src.cls_len[0][b] + src.cls_len[1][b] + src.cls_len[2][b] + i;
-    const uint4* ks = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(src.k16) + r * row_elems);
-    const uint4* vs = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(src.v16) + r * row_elems);
-    uint4* kd = reinterpret_cast<uint4*>(static_cast<uint16_t*>(dst.k16) + d * row_elems);
-    uint4* vd = reinterpret_cast<uint4*>(static_cast<uint16_t*>(dst.v16) + d * row_elems);
-    for (int e = threadIdx.x; e < row_elems / 8; e += 256) {
-        kd[e] = ks[e];
-        vd[e] = vs[e];
+    for (int e = threadIdx.x; e < DENSE_ROWS * pieces; e += 256) {
+        const int64_t r = r0 + e / pieces;      // a row of src's 16-bit segment
+        if (r < src.off16[0] || r >= src.off16[B] || r >= src.cap16) continue;
+        const int b = wq_find_seq(src.off16, B, r);
+        const int i = (int)(r - src.off16[b]);
+        if (i >= src.len16[b] || !dense_fits(src, dst, b)) continue;
+        const int64_t d = (int64_t)dst.off16[b] + src.cls_len[0][b] + src.cls_len[1][b] + src.cls_len[2][b] + i;
+        const int64_t from = r * pieces + e % pieces, to = d * pieces + e % pieces;
+        const uint4 k = static_cast<const uint4*>(src.k16)[from], v = static_cast<const uint4*>(src.v16)[from];
+        static_cast<uint4*>(dst.k16)[to] = k;
+        static_cast<uint4*>(dst.v16)[to] = v;
     }
+}
+
+// workgroup 0: the tables; then the 16-bit rows (rows16 workgroups), then the blocks of the classes that are in use, numbered
+// without gaps (the capacities can be far larger: every class then has room for all tokens)
+template <int HD, bool BF>
+__global__ __launch_bounds__(256) void k_dequantize(int B, wq_packed_kv src, wq_packed_kv dst, unsigned rows16, uint32_t* __restrict__ status)
+{
+    __shared__ DenseSmem<HD> sm;
+    if (blockIdx.x == 0) {
+        dense_plan(B, src, dst, status);
+        return;
+    }
+    unsigned w = blockIdx.x - 1;
+    if (w < rows16) {
+        dense_copy((int64_t)w * DENSE_ROWS, B, src.Hkv * HD / 8, src, dst);
+        return;
+    }
+    w -= rows16;
+    const unsigned Hkv = (unsigned)src.Hkv;
+    const unsigned n0 = (unsigned)src.cls_off[0][B] / 32u * Hkv, n1 = (unsigned)src.cls_off[1][B] / 32u * Hkv, n2 = (unsigned)src.cls_off[2][B] / 32u * Hkv;
+    if (w < n0)
+        dequantize_block<HD, 2, BF>(sm, (int)(w / Hkv), (int)(w % Hkv), B, src, dst);
+    else if (w - n0 < n1)
+        dequantize_block<HD, 4, BF>(sm, (int)((w - n0) / Hkv), (int)((w - n0) % Hkv), B, src, dst);
+    else if (w - n0 - n1 < n2)
+        dequantize_block<HD, 8, BF>(sm, (int)((w - n0 - n1) / Hkv), (int)((w - n0 - n1) % Hkv), B, src, dst);
 }
 
 template <int HD>
 int run_dequantize(wq_ctx* ctx, int B, const wq_packed_kv* src, const wq_packed_kv* dst)
 {
-    hipStream_t st = ctx->stream;
-    hipLaunchKernelGGL(k_dense_plan, dim3(1), dim3(256), 0, st, B, *src, *dst, wq_status_ptr(ctx));
-    const dim3 blk(256);
-    if (src->cap[0] > 0) hipLaunchKernelGGL((k_dequantize<HD, 2>), dim3((unsigned)(src->cap[0] / 32), src->Hkv), blk, 0, st, B, *src, *dst);
-    if (src->cap[1] > 0) hipLaunchKernelGGL((k_dequantize<HD, 4>), dim3((unsigned)(src->cap[1] / 32), src->Hkv), blk, 0, st, B, *src, *dst);
-    if (src->cap[2] > 0) hipLaunchKernelGGL((k_dequantize<HD, 8>), dim3((unsigned)(src->cap[2] / 32), src->Hkv), blk, 0, st, B, *src, *dst);
-    if (src->cap16 > 0) hipLaunchKernelGGL(k_dense_copy, dim3((unsigned)src->cap16), blk, 0, st, B, src->Hkv * HD, *src, *dst);
+    const int64_t rows16 = (src->cap16 + DENSE_ROWS - 1) / DENSE_ROWS;
+    const int64_t blocks = (src->cap[0] + src->cap[1] + src->cap[2]) / 32;
+    const int64_t wgs = 1 + rows16 + blocks * src->Hkv;
+    if (wgs > 0x7FFFFFFF) return wq_fail(ctx, WQ_ERR_UNSUPPORTED, "too many blocks for one launch");
+    hipLaunchKernelGGL((dst->dtype16 == WQ_BF16 ? k_dequantize<HD, true> : k_dequantize<HD, false>), dim3((unsigned)wgs), dim3(256), 0, ctx->stream, B,
+                       *src, *dst, (unsigned)rows16, wq_status_ptr(ctx));
     WQ_HIP_CHECK(ctx, hipGetLastError());
     return WQ_OK;
 }

@@ -332,64 +332,99 @@ __device__ __forceinline__ void quantize_block(QuantSmem<HD>& sm, int blk, int k
     }
 }
 
-// row r of all 16-bit rows of the batch
+// rows r0 .. r0 + ROWS16 - 1 of all 16-bit rows of the batch, 8 elements (one store of 16 bytes) per thread at a time.  A
+// workgroup per row, an element per thread, took 150 us where the whole cache stays in 16 bits (8 x 12800 tokens, 4 KV heads
+// of 128, bf16), this way 82.
+constexpr int ROWS16 = 8;
 template <typename T>
-__device__ __forceinline__ void copy16_row(int64_t r, const T* __restrict__ K, const T* __restrict__ V, int B, int row_elems,
-                                           const int32_t* __restrict__ kv_off, const int32_t* __restrict__ win_size,
-                                           const int32_t* __restrict__ win_off, const int32_t* __restrict__ perm,
-                                           const int32_t* __restrict__ seg_windows, const int32_t* __restrict__ pre16,
-                                           const wq_packed_kv& pk)
+__device__ __forceinline__ void copy16_rows(int64_t r0, const T* __restrict__ K, const T* __restrict__ V, int B, int pieces,
+                                            const int32_t* __restrict__ kv_off, const int32_t* __restrict__ win_size,
+                                            const int32_t* __restrict__ win_off, const int32_t* __restrict__ perm,
+                                            const int32_t* __restrict__ seg_windows, const int32_t* __restrict__ pre16,
+                                            const wq_packed_kv& pk)
 {
-    if (r >= pre16[B]) return;
-    const int b = wq_find_seq(pre16, B, r);
-    const int i = (int)(r - pre16[b]);
-    const int S = win_size[b];
-    const int W = win_off[b + 1] - win_off[b];
-    const int n16w = seg_windows[4 * b + 3] * S;
-    int64_t src;
-    if (i < n16w) {
-        int pos0 = seg_windows[4 * b] + seg_windows[4 * b + 1] + seg_windows[4 * b + 2];
-        int rr = i / S, o = i - rr * S;
-        src = (int64_t)kv_off[b] + (int64_t)perm[win_off[b] + pos0 + rr] * S + o;
-    } else {
-        src = (int64_t)kv_off[b] + (int64_t)W * S + (i - n16w);
+    __shared__ int64_t s_src[ROWS16], s_dst[ROWS16];
+    if (r0 >= pre16[B]) return;
+    const int rows = (int)min((int64_t)ROWS16, pre16[B] - r0);
+    if (threadIdx.x < rows) {
+        const int64_t r = r0 + threadIdx.x;
+        const int b = wq_find_seq(pre16, B, r);
+        const int i = (int)(r - pre16[b]);
+        const int S = win_size[b];
+        const int W = win_off[b + 1] - win_off[b];
+        const int n16w = seg_windows[4 * b + 3] * S;
+        int64_t src;
+        if (i < n16w) {
+            int pos0 = seg_windows[4 * b] + seg_windows[4 * b + 1] + seg_windows[4 * b + 2];
+            int rr = i / S, o = i - rr * S;
+            src = (int64_t)kv_off[b] + (int64_t)perm[win_off[b] + pos0 + rr] * S + o;
+        } else {
+            src = (int64_t)kv_off[b] + (int64_t)W * S + (i - n16w);
+        }
+        s_src[threadIdx.x] = src * pieces;
+        s_dst[threadIdx.x] = ((int64_t)pk.off16[b] + i) * pieces;
     }
-    const int64_t dst = (int64_t)pk.off16[b] + i;
-    uint16_t* k16 = static_cast<uint16_t*>(pk.k16) + dst * row_elems;
-    uint16_t* v16 = static_cast<uint16_t*>(pk.v16) + dst * row_elems;
-    for (int e = threadIdx.x; e < row_elems; e += 256) {
-        float kx = wq_ld(K, src * row_elems + e), vx = wq_ld(V, src * row_elems + e);
-        if constexpr (std::is_same_v<T, __hip_bfloat16>) {          // bf16 -> bf16
-            k16[e] = (uint16_t)(__float_as_uint(kx) >> 16);
-            v16[e] = (uint16_t)(__float_as_uint(vx) >> 16);
-        } else {                                                           // fp16 / fp32 -> fp16 (nearest even)
-            k16[e] = __half_as_ushort(__float2half_rn(kx));
-            v16[e] = __half_as_ushort(__float2half_rn(vx));
+    __syncthreads();
+    for (int e = threadIdx.x; e < rows * pieces; e += 256) {
+        const int row = e / pieces, piece = e - row * pieces;
+        const int64_t from = s_src[row] + piece, to = s_dst[row] + piece;
+#pragma unroll
+        for (int plane = 0; plane < 2; plane++) {
+            const T* const src = (plane ? V : K) + from * 8;
+            uint4* const dst = static_cast<uint4*>(plane ? pk.v16 : pk.k16) + to;
+            if constexpr (std::is_same_v<T, float>) {          // fp32 -> fp16 (nearest even)
+                float x[8];
+                wq_ld8(src, x);
+                uint32_t o[4];
+#pragma unroll
+                for (int k = 0; k < 4; k++)
+                    o[k] = (uint32_t)__half_as_ushort(__float2half_rn(x[2 * k])) | (uint32_t)__half_as_ushort(__float2half_rn(x[2 * k + 1])) << 16;
+                *dst = make_uint4(o[0], o[1], o[2], o[3]);
+            } else {
+                *dst = *reinterpret_cast<const uint4*>(src);
+            }
         }
     }
 }
 
-// The whole call after k_plan in one launch: workgroups [0, n0) take the 2-bit blocks, [n0, n1) the 4-bit blocks,
-// [n1, n2) the 8-bit blocks (consecutive workgroups = the KV heads of one token block: together they read whole source
-// rows), the rest one 16-bit row each.
+// The whole call after k_plan in one launch.  The blocks of the classes first (consecutive workgroups = the KV heads of one
+// token block: together they read whole source rows), the 2-bit ones, then 4-bit, then 8-bit; then ROWS16 16-bit rows each.
+// The blocks are numbered by the capacities (n0 workgroups for the 2-bit class, n1 for the 4-bit one) or, with n0 =
+// WQ_BY_USE, without gaps by what k_plan has found to be in use.  The latter where the capacities hold more than all rows
+// together fill: where thresholds decide, every class has room for all tokens, and a call for 16 ragged sequences (198 500
+// tokens, fp16) took 144 us with workgroups for the unused room, 136 without.  Else the former: reading the tables first
+// costs 2.5 of 61 us (8 x 12800 tokens).
+// n: workgroups for the blocks, a bound on their number.
+constexpr unsigned WQ_BY_USE = 0xFFFFFFFFu;
 template <typename T, int HD>
 __global__ __launch_bounds__(256) void k_quantize_all(const T* __restrict__ K, const T* __restrict__ V, int B, int group,
                                                       const int32_t* __restrict__ kv_off, const int32_t* __restrict__ win_size,
                                                       const int32_t* __restrict__ win_off, const int32_t* __restrict__ perm,
                                                       const int32_t* __restrict__ seg_windows, const int32_t* __restrict__ pre16,
-                                                      wq_packed_kv pk, unsigned n0, unsigned n1, unsigned n2, uint32_t* __restrict__ status)
+                                                      wq_packed_kv pk, unsigned n, unsigned n0, unsigned n1, uint32_t* __restrict__ status)
 {
     __shared__ QuantSmem<HD> sm;
-    const unsigned w = blockIdx.x;
+    unsigned w = blockIdx.x;
     const unsigned Hkv = (unsigned)pk.Hkv;
-    if (w < n0)
+    if (w >= n) {
+        copy16_rows<T>((int64_t)(w - n) * ROWS16, K, V, B, pk.Hkv * HD / 8, kv_off, win_size, win_off, perm, seg_windows, pre16, pk);
+        return;
+    }
+    if (n0 == WQ_BY_USE) {
+        n0 = (unsigned)pk.cls_off[0][B] / 32u * Hkv;
+        n1 = (unsigned)pk.cls_off[1][B] / 32u * Hkv;
+    }
+    if (w < n0) {
         quantize_block<T, HD, 2>(sm, (int)(w / Hkv), (int)(w % Hkv), K, V, B, group, kv_off, win_size, win_off, perm, seg_windows, pk, status);
-    else if (w < n1)
-        quantize_block<T, HD, 4>(sm, (int)((w - n0) / Hkv), (int)((w - n0) % Hkv), K, V, B, group, kv_off, win_size, win_off, perm, seg_windows, pk, status);
-    else if (w < n2)
-        quantize_block<T, HD, 8>(sm, (int)((w - n1) / Hkv), (int)((w - n1) % Hkv), K, V, B, group, kv_off, win_size, win_off, perm, seg_windows, pk, status);
-    else
-        copy16_row<T>((int64_t)(w - n2), K, V, B, pk.Hkv * HD, kv_off, win_size, win_off, perm, seg_windows, pre16, pk);
+        return;
+    }
+    w -= n0;
+    if (w < n1) {
+        quantize_block<T, HD, 4>(sm, (int)(w / Hkv), (int)(w % Hkv), K, V, B, group, kv_off, win_size, win_off, perm, seg_windows, pk, status);
+        return;
+    }
+    w -= n1;
+    quantize_block<T, HD, 8>(sm, (int)(w / Hkv), (int)(w % Hkv), K, V, B, group, kv_off, win_size, win_off, perm, seg_windows, pk, status);
 }
 
 // one generated token per sequence -> the end of its 16-bit segment
@@ -680,12 +715,17 @@ int run(wq_ctx* ctx, const void* K_, const void* V_, int B, const int32_t* kv_of
     int32_t* pre16 = reinterpret_cast<int32_t*>(ctx->ws + WQ_WS_HEADER);
     hipLaunchKernelGGL(k_plan, dim3(1), dim3(256), 0, st, B, kv_off, win_size, win_off, seg_windows, *pk, pre16,
                        wq_status_ptr(ctx));
-    const int64_t n0 = pk->cap[0] / 32 * pk->Hkv, n1 = n0 + pk->cap[1] / 32 * pk->Hkv, n2 = n1 + pk->cap[2] / 32 * pk->Hkv;
+    // blocks in use: no more than the capacities hold, nor than the rows fill if every sequence's last block of every class is
+    // a partial one
+    const int64_t held = (pk->cap[0] + pk->cap[1] + pk->cap[2]) / 32, filled = total_rows / 32 + 3 * (int64_t)B;
+    const int64_t n = (held < filled ? held : filled) * pk->Hkv;
+    const unsigned n0 = held <= filled ? (unsigned)(pk->cap[0] / 32 * pk->Hkv) : WQ_BY_USE, n1 = (unsigned)(pk->cap[1] / 32 * pk->Hkv);
     const int64_t rows16 = pk->cap16 > 0 ? (total_rows < pk->cap16 ? total_rows : pk->cap16) : 0;
-    if (n2 + rows16 > 0x7FFFFFFF) return wq_fail(ctx, WQ_ERR_UNSUPPORTED, "too many blocks for one launch");
-    if (n2 + rows16 > 0)
-        hipLaunchKernelGGL((k_quantize_all<T, HD>), dim3((unsigned)(n2 + rows16)), dim3(256), 0, st, K, V, B, pk->group, kv_off, win_size,
-                           win_off, perm, seg_windows, pre16, *pk, (unsigned)n0, (unsigned)n1, (unsigned)n2, wq_status_ptr(ctx));
+    const int64_t wgs16 = (rows16 + ROWS16 - 1) / ROWS16;
+    if (n + wgs16 > 0x7FFFFFFF) return wq_fail(ctx, WQ_ERR_UNSUPPORTED, "too many blocks for one launch");
+    if (n + wgs16 > 0)
+        hipLaunchKernelGGL((k_quantize_all<T, HD>), dim3((unsigned)(n + wgs16)), dim3(256), 0, st, K, V, B, pk->group, kv_off, win_size,
+                           win_off, perm, seg_windows, pre16, *pk, (unsigned)n, n0, n1, wq_status_ptr(ctx));
     if (B > 0) hipLaunchKernelGGL(k_v_scale_max, dim3((unsigned)B * WQ_VS_PARTS), dim3(256), 0, st, B, *pk);
     WQ_HIP_CHECK(ctx, hipGetLastError());
     return WQ_OK;

@@ -428,14 +428,30 @@ struct Tickets {
     unsigned taper;     // from this ticket on (the workgroup's last WQ_TAPER_TICKETS) a wavefront refills only every other pipeline slot
 };
 
+// ---- a launch that appends a token (k_new != NULL) must not change len16[b] while a wavefront of a workgroup of sequence b
+// may still read it (under WQ_DECODE_BY_LENGTH the split count of a sequence depends on its length).  Every workgroup of the
+// sequence, also one that has nothing to do, counts itself on the sequence's counter behind a barrier that all its wavefronts
+// pass with the tables in their registers: the set-up barrier, or one for this purpose where there is no work (an add that
+// returns nothing: nobody waits for it).  Counted as soon as the first wavefront has the tables, a workgroup's other
+// wavefronts could read the raised length where the one that raises it has nothing else to do.
+// The sequence's last workgroup in dispatch order (highest KV head, highest split; every other one of the sequence was
+// dispatched before it and waits for nobody before it counts itself) waits at its very end until the count is complete,
+// clears the counter for the next launch and writes the new length.
+__device__ __forceinline__ void count_tables_read(const DecodeArgs& a, int b)
+{
+    if (a.k_new && threadIdx.x == 0)
+        __hip_atomic_fetch_add(a.arrive + a.B * a.kv.Hkv * a.arrive_unit + b * WQ_ARRIVE_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // The set-up barrier (staged query operands, initial value of the block counter) is taken by every wavefront
 // exactly once: after the first loads of the first class it walks have been issued, or, by a wavefront that has
 // no blocks at all, before the final merge.
-__device__ __forceinline__ void pass_setup_barrier(Tickets& t)
+__device__ __forceinline__ void pass_setup_barrier(const DecodeArgs& a, int b, Tickets& t)
 {
     if (!t.synced) {
         __syncthreads();
         t.synced = true;
+        count_tables_read(a, b);
     }
 }
 
@@ -567,7 +583,7 @@ __device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD
         bi[d] = next_block(src, tk, DEPTH - d);
         if (bi[d] >= 0) load(bi[d], f[d]);
     }
-    pass_setup_barrier(tk);
+    pass_setup_barrier(a, b, tk);
     U4 Bqw[NK];
     float qexp, qsum[SETS];
     fetch_q_operands<HD, G>(sm, C, Bqw, qexp, qsum);
@@ -766,7 +782,7 @@ __device__ __forceinline__ void walk_seg16_mfma(const DecodeArgs& a, MfmaSmem<HD
     const int64_t rstride = (int64_t)kv.Hkv * HD;
     const uint16_t* k16 = static_cast<const uint16_t*>(kv.k16) + (int64_t)kvh * HD;
     const uint16_t* v16 = static_cast<const uint16_t*>(kv.v16) + (int64_t)kvh * HD;
-    pass_setup_barrier(tk);
+    pass_setup_barrier(a, b, tk);
     constexpr bool WIDE = wide_of(G);              // weights to fp32 accuracy: three bf16 terms, or two f16 ones of 2^10 times the weight
     constexpr float UP16 = (WIDE && !BF) ? 10.0f : 0.0f;
     U4 Bq[NK];
@@ -910,22 +926,8 @@ __device__ __forceinline__ void walk_seg16_mfma(const DecodeArgs& a, MfmaSmem<HD
     }
 }
 
-// ---- a launch that appends a token (k_new != NULL) must not change len16[b] while a workgroup of sequence b may still
-// read it (under WQ_DECODE_BY_LENGTH the split count of a sequence depends on its length).  Every workgroup of the
-// sequence, also one that has nothing to do, counts itself on the sequence's counter once the tables are in its registers
-// (an add that returns nothing: nobody waits for it).  The sequence's last workgroup in dispatch order (highest KV head,
-// highest split; every other one of the sequence was dispatched before it and waits for nobody before it counts itself)
-// waits at its very end until the count is complete, clears the counter for the next launch and writes the new length.
+// ---- the end of an append (count_tables_read above has the protocol) ----
 constexpr long long WQ_APPEND_WAIT_TICKS = 400000000ll;   // 4 s of the 100 MHz clock: far beyond any launch; a wait that long gives up
-
-__device__ __forceinline__ void note_tables_read(const DecodeArgs& a, int b, int len16_read)
-{
-    if (a.k_new && threadIdx.x == 0) {
-        unsigned one = 1u;
-        asm volatile("; the count follows the read of len16 %1" : "+s"(one) : "s"(len16_read));
-        __hip_atomic_fetch_add(a.arrive + a.B * a.kv.Hkv * a.arrive_unit + b * WQ_ARRIVE_STRIDE, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
 
 __device__ __forceinline__ void finish_append(const DecodeArgs& a, int b, int kvh, int split, int new_row)
 {
@@ -1150,8 +1152,9 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
     float v_scale_max;
     if constexpr (PACKED) {
         const Place p = place_by_length<HD, G>(a, sm, (int)blockIdx.x);
-        note_tables_read(a, max(p.b, 0), p.b);
         if (p.b < 0) {
+            if (a.k_new) __syncthreads();
+            count_tables_read(a, 0);
             finish_append_by_length<HD, G>(a, sm, (int)blockIdx.x);
             return;
         }
@@ -1173,7 +1176,6 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         cls_off[3] = a.kv.off16[b];
         end16 = a.kv.off16[b + 1];
         v_scale_max = a.kv.v_scale_max[b];
-        note_tables_read(a, b, cls_len[3]);
     }
     const int unit = b * a.kv.Hkv + kvh;
     // a token appended by this launch becomes the last row of the 16-bit segment: read from k_new / v_new by whoever
@@ -1202,6 +1204,8 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         const int tokens = cls_len[0] + cls_len[1] + cls_len[2] + cls_len[3];
         S = max(1, min(a.splits, (int)ceilf((float)tokens * a.len_scale)));
         if (split >= S) {
+            if (a.k_new) __syncthreads();
+            count_tables_read(a, b);
             finish_append(a, b, kvh, split, new_row);
             return;
         }
@@ -1327,7 +1331,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         sm.ml[wave][h][0] = st.m;
         sm.ml[wave][h][1] = l;
     }
-    pass_setup_barrier(tk);
+    pass_setup_barrier(a, b, tk);
     __syncthreads();
     // ---- merge the wavefronts, write the partial (m in natural-log units): wavefront r takes head r, a lane CPL
     //      neighbouring channels, so the eight scales of a head are computed once per lane ----

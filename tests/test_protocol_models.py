@@ -10,7 +10,8 @@ workgroup runs until it ends, and a dispatched workgroup's next step is eventual
    depends on its length).  The protocol that counted only the workgroups that had work is shown to let a late workgroup
    read the raised length; the protocol in the library (every workgroup counts itself once it has read the tables, the
    sequence's last workgroup in dispatch order raises the length when the count is complete) never does, never deadlocks,
-   raises the length exactly once and leaves its counter at zero.
+   raises the length exactly once and leaves its counter at zero.  Its wavefronts read the tables each for itself: counting
+   behind a barrier that all of them have passed is right, counting when the first one has read them is not.
 2. The merge of the splits: a workgroup counts itself on the arrival counter only after its partial is in memory; the one
    that counts last reads all partials.  Counting before the stores have landed (what a workgroup-scope fence alone gives)
    is shown to let the merging workgroup read a stale partial.
@@ -124,6 +125,37 @@ def test_counting_only_the_workgroups_with_work_lets_a_late_one_read_the_raised_
     # with room for every workgroup the same protocol can still go wrong or right, depending on the order
     finals_all, _ = append_model(1, 3, 3, 8, 12, counts_everybody=False)
     assert any(len(set(f[1])) == 1 for f in finals_all)
+
+
+def append_wavefront_model(splits, waves, tokens, longest, behind_barrier):
+    """One sequence and KV head, `splits` resident workgroups of `waves` wavefronts that read the tables each for itself.  A
+    workgroup counts itself when its wavefront 0 has read them or, behind a barrier, when all have; wavefront 0 of the last
+    workgroup then waits for the full count, if it has no work to do first, and raises the length.
+    State: (split count each wavefront saw, 0 = not yet read; workgroups counted; len16)."""
+    init = (tuple([0] * (splits * waves)), tuple([False] * splits), tokens)
+
+    def steps(st):
+        seen, counted, len16 = st
+        for w in range(splits * waves):
+            if seen[w] == 0:
+                yield (seen[:w] + (splits_used(len16, splits, longest),) + seen[w + 1:], counted, len16)
+        for g in range(splits):
+            own = seen[g * waves:(g + 1) * waves]
+            if not counted[g] and (all(own) if behind_barrier else own[0]):
+                yield (seen, counted[:g] + (True,) + counted[g + 1:], len16)
+        if all(counted) and len16 == tokens:
+            yield (seen, counted, len16 + 1)
+
+    return explore(init, steps, None, lambda st: all(st[0]) and st[2] == tokens + 1)
+
+
+@pytest.mark.parametrize("splits,waves,tokens,longest", [(2, 2, 6, 12), (3, 2, 8, 12), (3, 3, 4, 12), (1, 4, 5, 12)])
+def test_a_workgroup_counts_itself_behind_a_barrier_of_all_its_wavefronts(splits, waves, tokens, longest):
+    finals, deadlock = append_wavefront_model(splits, waves, tokens, longest, behind_barrier=True)
+    assert finals and not deadlock
+    assert all(set(seen) == {splits_used(tokens, splits, longest)} for seen, _, _ in finals)
+    early, _ = append_wavefront_model(splits, waves, tokens, longest, behind_barrier=False)
+    assert any(len(set(seen)) > 1 for seen, _, _ in early) == (splits > 1)       # a late wavefront saw the raised length
 
 
 # ---------------------------------------------------------------------------------------------------------------------

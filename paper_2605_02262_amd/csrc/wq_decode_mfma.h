@@ -982,15 +982,16 @@ __device__ __forceinline__ Place place_by_length(const DecodeArgs& a, MfmaSmem<H
     const float vmax = a.kv.v_scale_max[l];
     const bool grows = a.k_new && off[3] + len16 < end16 && (int64_t)off[3] + len16 < a.kv.cap16;
     len[3] = len16;
+    const int len16_after = len16 + (grows ? 1 : 0);     // with the token that this launch appends, as append followed by attention counts
     const bool mine = lane < a.B;
     int S;
     if (a.slots == 0) {
-        const int tokens = len[0] + len[1] + len[2] + len[3] + (grows ? 1 : 0);
+        const int tokens = len[0] + len[1] + len[2] + len16_after;
         S = max(1, min(a.splits, (int)ceilf((float)tokens * a.len_scale)));
     } else {
-        int blocks = 1;
+        int blocks = 1 + ((len16_after + 31) >> 5) * WQ_BLOCK_COST[3];
 #pragma unroll
-        for (int c = 0; c < 4; c++) blocks += ((len[c] + 31) >> 5) * WQ_BLOCK_COST[c];
+        for (int c = 0; c < 3; c++) blocks += ((len[c] + 31) >> 5) * WQ_BLOCK_COST[c];
         const float cost = mine ? (float)blocks : 0.f, total = wave_sum(cost), most = wave_max(cost);
         // (a sequence's share is rounded down by 0.002 first: a quotient that should be whole must not become the next whole number)
         auto splits_of = [&](float tau) { return mine ? max(1, min(a.splits, (int)ceilf(fmaf(cost, __builtin_amdgcn_rcpf(tau), -0.002f)))) : 0; };
@@ -1015,7 +1016,7 @@ __device__ __forceinline__ Place place_by_length(const DecodeArgs& a, MfmaSmem<H
     const int total = __builtin_amdgcn_readlane(upto, 63);
     if (a.k_new && wg == (int)gridDim.x - 1 && threadIdx.x < 64) {
         sm.expect[lane] = n + (lane == 0 ? (int)gridDim.x - total : 0);
-        sm.grown[lane] = mine && grows ? len16 + 1 : -1;
+        sm.grown[lane] = mine && grows ? len16_after : -1;
     }
     Place p;
     p.b = -1;

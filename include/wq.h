@@ -77,7 +77,7 @@ typedef enum { WQ_DECODE_AUTO = 0, WQ_DECODE_GENERIC = 1, WQ_DECODE_MFMA = 2 } w
 /* or-ed into algo: every wavefront of the matrix-core kernel gets a fixed share of the token axis, so that the
  * summation order, and with it every bit of the result, is the same on every run.  Without it the wavefronts of a
  * workgroup take the blocks of the workgroup's share one by one as they get free (faster; results agree to
- * rounding).                                                                                                   */
+ * rounding).  With one or four groups per head the shares are always fixed.                                    */
 #define WQ_DECODE_FIXED_SHARES 0x200
 /* or-ed into algo, for batches whose sequences differ a lot in length: a sequence uses ceil(num_splits * tokens /
  * max_seq_tokens) of the launch's splits (at least one; the workgroups beyond them return at once); with num_splits = 0 the
@@ -205,8 +205,8 @@ typedef struct {
     int32_t* len16;        /* device [B], written by wq_reorder_quantize, bumped by the caller on append    */
     float* v_scale_max;    /* device [wq_v_scale_floats(B, Hkv, cap)]: entry b, written by wq_reorder_quantize (and
                             * set to 0 by wq_dequantize in its destination, where B entries are enough), is the largest
-                            * scale of a value (V) group among sequence b's quantized tokens, 0 if it has none: the
-                            * matrix-core decode kernel places its fp16 weights by it.  The entries behind the first
+                            * scale of a value (V) group among sequence b's quantized tokens, 0 if it has none: with
+                            * hd/group == 2 the matrix-core decode kernel places its fp16 weights by it.  The entries behind the first
                             * B (one per 32-token block and KV head) are wq_reorder_quantize's scratch for finding it */
 } wq_packed_kv;
 
@@ -259,19 +259,20 @@ int wq_dequantize(wq_ctx* ctx, int B, const wq_packed_kv* src, const wq_packed_k
  * out[b,h,:] = sum_t softmax_t(sm_scale * q[b,h].k^_t) v^_t over the 2-, 4-, 8- and 16-bit segments of
  * sequence b, one softmax over all of them, no mask (Sec. 2.1); head h reads KV head h/(Hq/Hkv).
  * Codes are expanded in registers; the token axis is split over num_splits workgroups per (b, KV head)
- * and merged by log-sum-exp in a fixed order (no float atomics).  Which wavefront sums which tokens is fixed
- * only under WQ_DECODE_FIXED_SHARES.
+ * and merged by log-sum-exp in a fixed order (no float atomics).  With hd/group == 2, which wavefront
+ * sums which tokens is fixed only under WQ_DECODE_FIXED_SHARES.
  * q [B,Hq,hd] device, element type q_dtype; out [B,Hq,hd] device fp32; lse [B,Hq] device fp32 or NULL
  * (natural-log sum of exp of the scaled logits).  num_splits 0 = automatic (see wq_auto_splits).  max_seq_tokens: host
  * bound on tokens of any one sequence (used by the automatic split and by WQ_DECODE_BY_LENGTH; a wrong value costs speed,
  * not correctness).  algo: WQ_DECODE_AUTO picks the
  * matrix-core kernel when hd/group == 2, or for other groups when the query is a 16-bit type and the cache is within that
- * kernel's limits (the softmax weights then keep fp32 accuracy), else the generic one; WQ_DECODE_MFMA takes hd/group == 2 only.
+ * kernel's limits (it then computes in fp32 as the generic kernel does: keys and values dequantized by one fused
+ * multiply-add, fp32 queries, weights and sums), else the generic one; WQ_DECODE_MFMA takes hd/group == 2 only.
  * Limits (WQ_ERR_UNSUPPORTED beyond them): Hq a
  * multiple of Hkv with at most 8 query heads per KV head, hd 64 or 128, group 32, 64 or 128, B at most 65535, and for
  * the matrix-core kernel at most 2^27 token slots in the cache (cap[0] + cap[1] + cap[2] + cap16: it cuts the workgroups'
  * shares on a 32-bit cost axis); num_splits above 1024 is WQ_ERR_ARG.
- * Value range: the matrix-core kernel multiplies the softmax weights (at most 32 relative to its running reference) with
+ * Value range: with hd/group == 2 the matrix-core kernel multiplies the softmax weights (at most 32 relative to its running reference) with
  * the scales of the value groups in fp16.  It places that product by the sequence's largest value scale (v_scale_max[b] of
  * the cache, which wq_reorder_quantize writes): the largest product is 2^14..2^15 whatever the values' magnitude, so nothing
  * overflows for any scale that fp16 holds, and a token's weight is lost to fp16's subnormal range only when it is below

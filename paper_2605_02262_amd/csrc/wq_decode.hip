@@ -358,7 +358,7 @@ __global__ __launch_bounds__(256) void k_decode_generic(DecodeArgs a)
 template <int HD, int G, bool PACKED>
 __global__ __launch_bounds__(64 * WQ_WAVES) void k_decode_mfma(DecodeArgs a)
 {
-    __shared__ __align__(16) unsigned char smem[sizeof(MfmaSmem<HD, G>)];
+    __shared__ __align__(16) unsigned char smem[sizeof(DecodeSmem<HD, G>)];
     wq_decode_mfma_body<HD, G, PACKED>(a, smem);
 }
 
@@ -443,9 +443,9 @@ static bool fits_cost_axis(const wq_packed_kv* kv)
 }
 
 // Which kernel walks the quantized classes.  Two groups per head: the matrix-core kernel, with the weights in one f16 value.
-// One and four groups: the matrix-core kernel with the weights in two, which keeps fp32 accuracy, for 16-bit queries (whose
-// mantissa an f16 operand holds); an fp32 query would lose half of its bits there and stays with the vector kernel, as do
-// caches beyond the cost axis.
+// One and four groups: the matrix-core kernel with its fp32 walkers for 16-bit queries (measured, 8 x 12795 tokens, 28 / 4
+// heads of 128, group 32: 917 us a call on the vector kernel); fp32 queries and caches beyond the cost axis stay with the
+// vector kernel.
 static bool use_matrix_cores(int q_dtype, const wq_packed_kv* kv, int balgo)
 {
     if (balgo != WQ_DECODE_AUTO) return balgo == WQ_DECODE_MFMA;
@@ -472,8 +472,9 @@ static int splits_for_rounds(int B, const wq_packed_kv* kv, int64_t max_seq_toke
     const int64_t units = (int64_t)B * kv->Hkv, blocks = (max_seq_tokens + 31) / 32;
     // a block's cost, averaged over the cache's slots; a block of cost 100 takes 0.12 us of a compute unit (0.08 with heads of 64)
     const double slots = (double)kv->cap[0] + (double)kv->cap[1] + (double)kv->cap[2] + (double)kv->cap16;
-    const double cost = slots > 0 ? ((double)kv->cap[0] * WQ_BLOCK_COST[0] + (double)kv->cap[1] * WQ_BLOCK_COST[1] +
-                                     (double)kv->cap[2] * WQ_BLOCK_COST[2] + (double)kv->cap16 * WQ_BLOCK_COST[3]) / slots : WQ_BLOCK_COST[0];
+    const int* const unit = kv->hd / kv->group == 2 ? WQ_BLOCK_COST : WQ_BLOCK_COST_F32;
+    const double cost = slots > 0 ? ((double)kv->cap[0] * unit[0] + (double)kv->cap[1] * unit[1] +
+                                     (double)kv->cap[2] * unit[2] + (double)kv->cap16 * unit[3]) / slots : unit[0];
     const double block_us = cost * (kv->hd == 128 ? 1.2e-3 : 0.8e-3), fixed_us = kv->hd == 128 ? 8.0 : 6.5;
     int best = 1;
     double best_us = 0;

@@ -1,17 +1,8 @@
 // a4, matrix-core path: decode attention over the packed cache (Alg. 2 decode half).
 // (included by wq_decode.hip, after DecodeArgs and load_q)
 //
-// The text below describes two groups per head (hd/group == 2).  The other group counts run on the same walkers:
-//   one group    the two halves of the head are treated as two groups that read the same metadata word
-//   four groups  (hd 128, group 32) two sets of columns: set T holds groups 2T and 2T + 1, with query operands, logits
-//                parts, weights P' and value-minimum sums of its own; a channel tile of the values belongs to one set, so
-//                the value product costs no more instructions, the logit product twice as many
-// There the weights P' meet the codes as a sum of two f16 values (P' = hi + lo, 22 bits, the residual formed exactly by a
-// fused multiply-add) where two groups use one, and the codes are multiplied by 2^15 into f16's normal range first: the
-// matrix cores add up products in fixed point below the largest one, so that a subnormal factor costs the bits of its
-// leading zeros (measured: outputs 1e-4 too small for 2-bit codes, 3e-5 for 4-bit, 3e-6 for 8-bit ones).  The results keep
-// the fp32 accuracy of the vector kernel that these group counts ran on before (measured, 8 x 12795 tokens, 28 / 4 heads of 128, group 32: 917 -> 25.5 us a call;
-// 16 x 6558 tokens, 14 / 2 heads of 64, group 64: 296 -> 12.1).
+// The walkers here and the text below are those of two groups per head (hd/group == 2).  One and four groups have walkers of
+// their own, in fp32 (wq_decode_f32.h); the body at the end of this file cuts and merges the work of both.
 //
 // One wavefront walks 32-token blocks of a class on its own (no workgroup barrier inside the loop):
 //
@@ -90,19 +81,6 @@ __device__ __forceinline__ uint32_t mul_f16lo_to_lo(uint32_t w, float p)
 __device__ __forceinline__ uint32_t mul_f16lo_to_hi(uint32_t acc, uint32_t w, float p)
 {
     asm("v_fma_mixhi_f16 %0, %1, %2, 0 op_sel_hi:[1,0,0]" : "+v"(acc) : "v"(w), "v"(p));
-    return acc;
-}
-// what the rounding of the product left: (f16 in the low half of w) * p - r's low (high) half, rounded to f16, into the low
-// (the high) half of a register
-__device__ __forceinline__ uint32_t rest_of_mul_lo(uint32_t w, float p, uint32_t r)
-{
-    uint32_t d;
-    asm("v_fma_mixlo_f16 %0, %1, %2, -%3 op_sel_hi:[1,0,1]" : "=v"(d) : "v"(w), "v"(p), "v"(r));
-    return d;
-}
-__device__ __forceinline__ uint32_t rest_of_mul_hi(uint32_t acc, uint32_t w, float p, uint32_t r)
-{
-    asm("v_fma_mixhi_f16 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "+v"(acc) : "v"(w), "v"(p), "v"(r));
     return acc;
 }
 
@@ -194,7 +172,7 @@ struct WaveState {
     floatx4 O[HD / 16];   // O^T tiles: row = channel 16ct + 4j + i, column = (g,h)
     float m;              // reference exponent of this column (a recent largest logit), log2 domain, shared by the four lane groups
     float l;              // this lane's share of sum p
-    float accM[2];        // this lane's share of sum p * m_v, per set of columns (the second one with four groups only)
+    float accM;           // this lane's share of sum p * m_v
     float up;             // log2 of the factor that the weights of the quantized classes are formed with (the same in all lanes)
 };
 
@@ -223,44 +201,17 @@ __device__ __forceinline__ float weight_upscale(float s_max)
 __device__ __forceinline__ float pow2_of(float e) { return __uint_as_float((uint32_t)(127 + (int)e) << 23); }   // e an integer in [-126, 127]
 constexpr int VT_PAD = 4;   // row pitch of the transposition buffer: (HD/2+4)*2 bytes, i.e. 4 rows apart = 8 banks (mod 32)
 
-// WIDE: weights and codes to fp32 accuracy (one and four groups)
-constexpr bool wide_of(int G) { return G != 2; }
-constexpr float code_log2(int G) { return wide_of(G) ? 9.0f : 24.0f; }       // a code of 1 is 2^-this in a product
-template <int G>
-__device__ __forceinline__ half8 v_code_operand(half8 x)
-{
-    return wide_of(G) ? x * (_Float16)32768.0f : x;
-}
-// ... and for the keys the slot's shift is undone here as well, so that the query keeps all its bits (a query scaled by
-// 2^-shift loses f16 bits: errors of 3e-5 with an fp16 query and 2-bit codes)
-template <int C, int G>
-__device__ __forceinline__ half8 k_code_operand(half8 x, int r)
-{
-    if constexpr (wide_of(G)) {
-        half8 f;
-#pragma unroll
-        for (int e = 0; e < 8; e++) {
-            int ch, sh;
-            k_slot(C, r, e, ch, sh);
-            f[e] = (_Float16)(float)(1 << (15 - sh));
-        }
-        return x * f;
-    }
-    return x;
-}
-
-template <int HD, int G>
+template <int HD>
 struct MfmaSmem {
-    static constexpr int SETS = G == 4 ? 2 : 1;          // sets of 16 columns (two groups x 8 heads)
     struct {
-        uint32_t meta[WQ_WAVES][2][32 * G];              // per wave: K and V metadata words of the current block
+        uint32_t meta[WQ_WAVES][2][64];                  // per wave: K and V metadata words of the current block
         uint16_t vt[WQ_WAVES][32][HD / 2 + VT_PAD];      // per wave: half the channels of the V rows of a 16-bit block, read back transposed
     } run;
     // per-wave numerators for the merge; rows one bank apart.  A space of its own: a wavefront hands its numerators over
     // as soon as its loops end, while others still use the run-time part
     float O[WQ_WAVES][WQ_MAX_REP][HD + 1];
     U4 bq[4][HD / 32][64];                               // query operands of the four classes (index 3 = 16-bit segment), per lane
-    float qx[4][1 + SETS][64];                           // ... with the head's power of two and the group's query sum per set
+    float qx[4][2][64];                                  // ... with the head's power of two and the group's query sum
     float ml[WQ_WAVES][WQ_MAX_REP][2];
     unsigned next_ticket;                                // the workgroup's block counter
     int expect[64], grown[64];                           // the workgroup that ends an append: per sequence, the workgroups that count themselves on it, and the new len16 (-1: unchanged)
@@ -301,13 +252,10 @@ __device__ __forceinline__ float max_over_rows(float x)
 // largest magnitude is found with two cross-lane exchanges, the query is scaled by a power of two into [-1, 1)
 // and laid out as the B operands of the k-steps: slot e of k-step r takes channel k_slot(c, r, e) of the quarter,
 // times 2^-shift of that slot; lanes whose quarter is not in their column's group hold zeros (block-diagonal B).
-// With four groups a quarter is a group: lane (j, (g,h)) holds its quarter if j is one of the groups g, g + 2 of its column
-// in the two sets; which of the sets takes it is j / 2, and the other set's operand is zero there (walk_class_mfma).  The
-// 16-bit segment knows no groups and keeps the two halves.
 // Returns the head's power of two (1 for the raw-bf16 operands of a bf16 16-bit segment) and the sum of the scaled
-// query over the lane's group, per set.
-template <int HD, int CLS, int G>
-__device__ __forceinline__ void build_q_operands(const DecodeArgs& a, int b, int kvh, bool raw_bf16, U4* Bq, float& qexp, float* qsum)
+// query over the lane's group.
+template <int HD, int CLS>
+__device__ __forceinline__ void build_q_operands(const DecodeArgs& a, int b, int kvh, bool raw_bf16, U4* Bq, float& qexp, float& qsum)
 {
     constexpr int QC = HD / 4, NK = HD / 32;
     const int lane = threadIdx.x & 63;
@@ -346,15 +294,8 @@ __device__ __forceinline__ void build_q_operands(const DecodeArgs& a, int b, int
     const float pair = quarters.even + quarters.odd;                         // both quarters of group j/2
     const RowPair groups = halves_32(pair);
     const float other = (lane & 32) ? groups.even : groups.odd;
-    const bool mine = (G == 4 && CLS != 3) ? (j & 1) == g : (j >> 1) == g;
-    if constexpr (G == 4) {                        // the quarters g and g + 2: even (odd) rows of the lower and the upper half
-        const float q_g = g ? quarters.odd : quarters.even;
-        const RowPair sets = halves_32(q_g);
-        qsum[0] = sets.even;
-        qsum[1] = sets.odd;
-    } else {
-        qsum[0] = (j >> 1) == g ? pair : other;
-    }
+    const bool mine = (j >> 1) == g;
+    qsum = mine ? pair : other;
     qexp = raw_bf16 ? 1.0f : up;
 #pragma unroll
     for (int r = 0; r < NK; r++) {
@@ -366,7 +307,6 @@ __device__ __forceinline__ void build_q_operands(const DecodeArgs& a, int b, int
             for (int t = 0; t < 2; t++) {
                 int ch, sh;
                 k_slot(CLS, r, 2 * e2 + t, ch, sh);
-                if (wide_of(G)) sh = 0;            // (undone on the codes' side)
                 const _Float16 f = (_Float16)(v[ch] * dn * __uint_as_float((uint32_t)(127 - sh) << 23));
                 half[t] = raw_bf16 ? (__float_as_uint(v[ch]) >> 16) : (uint32_t)__builtin_bit_cast(uint16_t, f);
             }
@@ -378,35 +318,32 @@ __device__ __forceinline__ void build_q_operands(const DecodeArgs& a, int b, int
 
 // The wavefronts of a workgroup walk the same classes, so the workgroup builds the operands of all four once, one
 // class per wavefront (the first four), and keeps them in LDS.
-template <int HD, int G>
-__device__ __forceinline__ void stage_q_operands(const DecodeArgs& a, MfmaSmem<HD, G>& sm, int b, int kvh, int wave, bool bf16seg)
+template <int HD>
+__device__ __forceinline__ void stage_q_operands(const DecodeArgs& a, MfmaSmem<HD>& sm, int b, int kvh, int wave, bool bf16seg)
 {
     constexpr int NK = HD / 32;
     const int lane = threadIdx.x & 63;
-    constexpr int SETS = MfmaSmem<HD, G>::SETS;
     U4 Bq[NK];
-    float qexp, qsum[SETS];
+    float qexp, qsum;
     if (wave >= 4) return;
-    if (wave == 0) build_q_operands<HD, 0, G>(a, b, kvh, false, Bq, qexp, qsum);
-    else if (wave == 1) build_q_operands<HD, 1, G>(a, b, kvh, false, Bq, qexp, qsum);
-    else if (wave == 2) build_q_operands<HD, 2, G>(a, b, kvh, false, Bq, qexp, qsum);
-    else build_q_operands<HD, 3, G>(a, b, kvh, bf16seg, Bq, qexp, qsum);
+    if (wave == 0) build_q_operands<HD, 0>(a, b, kvh, false, Bq, qexp, qsum);
+    else if (wave == 1) build_q_operands<HD, 1>(a, b, kvh, false, Bq, qexp, qsum);
+    else if (wave == 2) build_q_operands<HD, 2>(a, b, kvh, false, Bq, qexp, qsum);
+    else build_q_operands<HD, 3>(a, b, kvh, bf16seg, Bq, qexp, qsum);
 #pragma unroll
     for (int r = 0; r < NK; r++) sm.bq[wave][r][lane] = Bq[r];
     sm.qx[wave][0][lane] = qexp;
-#pragma unroll
-    for (int T = 0; T < SETS; T++) sm.qx[wave][1 + T][lane] = qsum[T];
+    sm.qx[wave][1][lane] = qsum;
 }
 
-template <int HD, int G>
-__device__ __forceinline__ void fetch_q_operands(const MfmaSmem<HD, G>& sm, int c, U4* Bq, float& qexp, float* qsum)
+template <int HD>
+__device__ __forceinline__ void fetch_q_operands(const MfmaSmem<HD>& sm, int c, U4* Bq, float& qexp, float& qsum)
 {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int r = 0; r < HD / 32; r++) Bq[r] = sm.bq[c][r][lane];
     qexp = sm.qx[c][0][lane];
-#pragma unroll
-    for (int T = 0; T < MfmaSmem<HD, G>::SETS; T++) qsum[T] = sm.qx[c][1 + T][lane];
+    qsum = sm.qx[c][1][lane];
 }
 
 // ---- shares of the token axis ---------------------------------------------------------------------------------
@@ -501,13 +438,13 @@ __device__ __forceinline__ int next_block(BlockSrc& s, Tickets& t, unsigned fill
     return s.pool_first + (int)(v - s.tk_lo);
 }
 
-template <int HD, int BITS, int G>
+template <int HD, int BITS>
 struct Frag {
     static constexpr int KDW = (HD / 4) * BITS / 32;        // dwords of K codes per lane per 16-token tile
     static constexpr int VDW = (HD / 16) * 8 * BITS / 32;   // dwords of V codes per lane per 32-token block
     uint32_t k[2][KDW];
     uint32_t v[VDW];
-    uint32_t m[G];                                          // the block's metadata words, K plane then V plane, 64 at a time
+    uint32_t km, vm;                                        // one metadata word per lane and plane
 };
 
 template <int N>
@@ -533,17 +470,14 @@ __device__ __forceinline__ void load_dwords(const uint32_t* __restrict__ p, uint
 
 // One class of one (sequence, KV head): this wavefront's share of its 32-token blocks (len tokens from token slot
 // tok_base of the class buffers).
-template <int HD, int BITS, int G, int DEPTH>
-__device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD, G>& sm, int b, int kvh, int len, int tok_base, BlockSrc& src,
+template <int HD, int BITS, int DEPTH>
+__device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD>& sm, int b, int kvh, int len, int tok_base, BlockSrc& src,
                                                 Tickets& tk, float c_log2, WaveState<HD>& st)
 {
     constexpr int C = BITS == 2 ? 0 : (BITS == 4 ? 1 : 2);
     constexpr int NK = HD / 32;                    // k-steps of the logit product per 16-token tile
     constexpr int CT = HD / 16;                    // channel tiles of the value product
-    constexpr int SETS = MfmaSmem<HD, G>::SETS;
-    constexpr bool WIDE = wide_of(G);
-    constexpr int MW = 16 * G;                     // metadata words of a 16-token tile
-    using F = Frag<HD, BITS, G>;
+    using F = Frag<HD, BITS>;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int j = lane >> 4, col = lane & 15, g = col >> 3;
 
@@ -552,27 +486,18 @@ __device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD
     const int64_t cap = kv.cap[C];
     const uint8_t* kbase = static_cast<const uint8_t*>(kv.codes[C]) + ((int64_t)kvh * cap + tok_base) * HD * BITS / 8 + lane * (F::KDW * 4);
     const uint8_t* vbase = static_cast<const uint8_t*>(kv.codes[C]) + (((int64_t)kv.Hkv + kvh) * cap + tok_base) * HD * BITS / 8 + lane * (F::VDW * 4);
-    // (one group: a block has 32 words per plane, the lower half of the wavefront loads K's, the upper half V's)
-    const int mplane = G == 1 ? lane >> 5 : 0, mlane = G == 1 ? lane & 31 : lane;
-    const uint32_t* kmeta = static_cast<const uint32_t*>(kv.meta[C]) + ((int64_t)(mplane * kv.Hkv + kvh) * cap + tok_base) * G + mlane;
-    const uint32_t* vmeta = static_cast<const uint32_t*>(kv.meta[C]) + (((int64_t)kv.Hkv + kvh) * cap + tok_base) * G + mlane;
+    const uint32_t* kmeta = static_cast<const uint32_t*>(kv.meta[C]) + ((int64_t)kvh * cap + tok_base) * 2 + lane;
+    const uint32_t* vmeta = static_cast<const uint32_t*>(kv.meta[C]) + (((int64_t)kv.Hkv + kvh) * cap + tok_base) * 2 + lane;
     uint32_t* smeta = &sm.run.meta[wave][0][0];
-    const int moff = (G == 1 ? 0 : g * 16) + 4 * j;               // (group g, tokens 4j..4j+3) inside a metadata tile
+    const int moff = g * 16 + 4 * j;               // (group g, tokens 4j..4j+3) inside a metadata tile of 32 words
 
     auto load = [&](int blk, F& f) {
         const int64_t o = (int64_t)blk * (32 * HD * BITS / 8);
         load_dwords<F::KDW>(reinterpret_cast<const uint32_t*>(kbase + o), f.k[0]);
         load_dwords<F::KDW>(reinterpret_cast<const uint32_t*>(kbase + o + 16 * HD * BITS / 8), f.k[1]);
         load_dwords<F::VDW>(reinterpret_cast<const uint32_t*>(vbase + o), f.v);
-        if constexpr (G == 1) {
-            f.m[0] = kmeta[(int64_t)blk * 32];
-        } else {
-#pragma unroll
-            for (int k = 0; k < G / 2; k++) {
-                f.m[k] = kmeta[(int64_t)blk * (32 * G) + 64 * k];
-                f.m[G / 2 + k] = vmeta[(int64_t)blk * (32 * G) + 64 * k];
-            }
-        }
+        f.km = kmeta[(int64_t)blk * 64];
+        f.vm = vmeta[(int64_t)blk * 64];
     };
 
     // software pipeline: DEPTH blocks in flight per wavefront; the first loads go out before anything else
@@ -585,30 +510,21 @@ __device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD
     }
     pass_setup_barrier(a, b, tk);
     U4 Bqw[NK];
-    float qexp, qsum[SETS];
-    fetch_q_operands<HD, G>(sm, C, Bqw, qexp, qsum);
-    half8 Bq[SETS][NK];
+    float qexp, qsum;
+    fetch_q_operands<HD>(sm, C, Bqw, qexp, qsum);
+    half8 Bq[NK];
 #pragma unroll
-    for (int T = 0; T < SETS; T++)
-#pragma unroll
-        for (int r = 0; r < NK; r++)
-            Bq[T][r] = (SETS == 1 || (j >> 1) == T) ? __builtin_bit_cast(half8, Bqw[r]) : as_half8(0u, 0u, 0u, 0u);
-    // logits come out of the matrix cores as 2^-24 * sum q' code (2^-9 with WIDE); fold 2^24, the head's power of two and
+    for (int r = 0; r < NK; r++) Bq[r] = __builtin_bit_cast(half8, Bqw[r]);
+    // logits come out of the matrix cores as 2^-24 * sum q' code; fold 2^24, the head's power of two and
     // sm_scale*log2(e) into one constant, and pre-divide the m-term by 2^24 so both terms share it.
-    const float cexp = c_log2 * qexp * pow2_of(code_log2(G));
-    float qs[SETS];
-#pragma unroll
-    for (int T = 0; T < SETS; T++) qs[T] = qsum[T] * pow2_of(-code_log2(G));
+    const float cexp = c_log2 * qexp * 16777216.0f;
+    const float qs = qsum * (1.0f / 16777216.0f);
 
     // added to the logits: zero, except for the tokens past the end of the sequence's last block of the class
     // (the last block this wavefront gets: shares and tickets go up the stream), which get -inf
     float pen[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     // partial sums per slot register v: its weights carry 2^-shift(v) (folded into the exponent), undone after the loop
-    float lv[4] = {0.f, 0.f, 0.f, 0.f}, av[SETS][4], ms[4];
-#pragma unroll
-    for (int T = 0; T < SETS; T++)
-#pragma unroll
-        for (int v = 0; v < 4; v++) av[T][v] = 0.f;
+    float lv[4] = {0.f, 0.f, 0.f, 0.f}, av[4] = {0.f, 0.f, 0.f, 0.f}, ms[4];
 #pragma unroll
     for (int v = 0; v < 4; v++) ms[v] = st.m + v_slot_shift<BITS>(v) - st.up;
 
@@ -624,21 +540,19 @@ __device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD
                 for (int i = 0; i < 4; i++) pen[4 * t + i] = (16 * t + 4 * j + i >= nv) ? -INFINITY : 0.f;
         }
         // ---- scales and minima: one word per lane in, the lane's 4 tokens x 2 tiles x {K,V} out ----
-#pragma unroll
-        for (int k = 0; k < G; k++) smeta[64 * k + lane] = f.m[k];
+        smeta[lane] = f.km;
+        smeta[64 + lane] = f.vm;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        uint32_t kw[SETS][8], vw[SETS][8];
+        uint32_t kw[8], vw[8];
 #pragma unroll
-        for (int T = 0; T < SETS; T++)
-#pragma unroll
-            for (int t = 0; t < 2; t++) {
-                const uint4 a = *reinterpret_cast<const uint4*>(smeta + t * MW + 32 * T + moff);
-                const uint4 c = *reinterpret_cast<const uint4*>(smeta + 32 * G + t * MW + 32 * T + moff);
-                kw[T][4 * t] = a.x, kw[T][4 * t + 1] = a.y, kw[T][4 * t + 2] = a.z, kw[T][4 * t + 3] = a.w;
-                vw[T][4 * t] = c.x, vw[T][4 * t + 1] = c.y, vw[T][4 * t + 2] = c.z, vw[T][4 * t + 3] = c.w;
-            }
+        for (int t = 0; t < 2; t++) {
+            const uint4 a = *reinterpret_cast<const uint4*>(smeta + t * 32 + moff);
+            const uint4 c = *reinterpret_cast<const uint4*>(smeta + 64 + t * 32 + moff);
+            kw[4 * t] = a.x, kw[4 * t + 1] = a.y, kw[4 * t + 2] = a.z, kw[4 * t + 3] = a.w;
+            vw[4 * t] = c.x, vw[4 * t + 1] = c.y, vw[4 * t + 2] = c.z, vw[4 * t + 3] = c.w;
+        }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();   // the next block's words may overwrite the buffer after this point
 
@@ -646,23 +560,12 @@ __device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD
         float x[8];
 #pragma unroll
         for (int t = 0; t < 2; t++) {
-            floatx4 acc[SETS];
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int T = 0; T < SETS; T++) acc[T] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int r = 0; r < NK; r++) {
-                const half8 kop = k_code_operand<C, G>(k_operand<BITS>(f.k[t], r), r);
-#pragma unroll
-                for (int T = 0; T < SETS; T++) acc[T] = mfma(kop, Bq[T][r], acc[T]);
-            }
+            for (int r = 0; r < NK; r++) acc = mfma(k_operand<BITS>(f.k[t], r), Bq[r], acc);
 #pragma unroll
             for (int i = 0; i < 4; i++) {
-                float y = pen[4 * t + i];
-#pragma unroll
-                for (int T = 0; T < SETS; T++) {
-                    const uint32_t w = kw[T][4 * t + i];
-                    y = fmaf(f16lo(w), acc[T][i], fmaf(f16hi(w), qs[T], y));
-                }
+                const float y = fmaf(f16lo(kw[4 * t + i]), acc[i], fmaf(f16hi(kw[4 * t + i]), qs, pen[4 * t + i]));
                 x[4 * t + i] = y + ror8(y);
             }
         }
@@ -675,13 +578,11 @@ __device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD
             const float alpha = (mn == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(st.m - mn);   // 0 on the first block
             st.m = mn;
             st.l *= alpha;
-#pragma unroll
-            for (int T = 0; T < SETS; T++) st.accM[T] *= alpha;
+            st.accM *= alpha;
 #pragma unroll
             for (int v = 0; v < 4; v++) {
                 lv[v] *= alpha;
-#pragma unroll
-                for (int T = 0; T < SETS; T++) av[T][v] *= alpha;
+                av[v] *= alpha;
                 ms[v] = mn + v_slot_shift<BITS>(v) - st.up;
             }
 #pragma unroll
@@ -693,29 +594,16 @@ __device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD
         for (int k = 0; k < 8; k++) {
             p[k] = __builtin_amdgcn_exp2f(fmaf(x[k], cexp, -ms[k & 3]));
             lv[k & 3] += p[k];
-#pragma unroll
-            for (int T = 0; T < SETS; T++) av[T][k & 3] = fmaf(f16hi(vw[T][k]), p[k], av[T][k & 3]);
+            av[k & 3] = fmaf(f16hi(vw[k]), p[k], av[k & 3]);
         }
-        half8 Bp[SETS], Br[SETS];                  // P' and, with WIDE, what its rounding to f16 left
+        uint32_t bp[4];
 #pragma unroll
-        for (int T = 0; T < SETS; T++) {
-            uint32_t bp[4], br[4];
+        for (int v = 0; v < 4; v++)                // slots (2v, 2v+1) = (tile 0, tile 1) token 4j+v
+            bp[v] = mul_f16lo_to_hi(mul_f16lo_to_lo(vw[v], p[v]), vw[4 + v], p[4 + v]);
+        const half8 Bp = as_half8(bp[0], bp[1], bp[2], bp[3]);
+        // ---- values ----
 #pragma unroll
-            for (int v = 0; v < 4; v++) {          // slots (2v, 2v+1) = (tile 0, tile 1) token 4j+v
-                bp[v] = mul_f16lo_to_hi(mul_f16lo_to_lo(vw[T][v], p[v]), vw[T][4 + v], p[4 + v]);
-                br[v] = WIDE ? rest_of_mul_hi(rest_of_mul_lo(vw[T][v], p[v], bp[v]), vw[T][4 + v], p[4 + v], bp[v]) : 0u;
-            }
-            Bp[T] = as_half8(bp[0], bp[1], bp[2], bp[3]);
-            Br[T] = as_half8(br[0], br[1], br[2], br[3]);
-        }
-        // ---- values: a channel tile belongs to a group, hence to a set ----
-#pragma unroll
-        for (int ct = 0; ct < CT; ct++) {
-            const int T = ct / (CT / SETS);
-            const half8 vop = v_code_operand<G>(v_operand<BITS>(f.v, ct));
-            st.O[ct] = mfma(vop, Bp[T], st.O[ct]);
-            if constexpr (WIDE) st.O[ct] = mfma(vop, Br[T], st.O[ct]);
-        }
+        for (int ct = 0; ct < CT; ct++) st.O[ct] = mfma(v_operand<BITS>(f.v, ct), Bp, st.O[ct]);
         const unsigned got = ticket_value(drawn);      // read on every path: nothing is left pending at the loop edge
         if (redraw) {
             tk.held = got;
@@ -744,8 +632,7 @@ __device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD
 #pragma unroll
     for (int v = 0; v < 4; v++) {
         st.l = fmaf(lv[v], down * (1.0f / v_slot_scale<BITS>(v)), st.l);
-#pragma unroll
-        for (int T = 0; T < SETS; T++) st.accM[T] = fmaf(av[T][v], down * (1.0f / v_slot_scale<BITS>(v)), st.accM[T]);
+        st.accM = fmaf(av[v], down * (1.0f / v_slot_scale<BITS>(v)), st.accM);
     }
 }
 
@@ -766,10 +653,10 @@ __device__ __forceinline__ floatx4 mfma16(uint32_t a0, uint32_t a1, uint32_t a2,
 // quarter per lane); V rows go through LDS and are read back one channel x 8 tokens per lane.  bf16 caches use
 // the bf16 instruction with the exact bf16 query and the weights split into two bf16 terms (p = hi + lo);
 // fp16 caches use the f16 instruction.  Accumulators are in true units here (no 2^-24).
-template <int HD, bool BF, int G>
+template <int HD, bool BF>
 // new_row >= 0: row new_row (= len - 1) is not in the cache yet: it is read from knew / vnew, this (sequence, KV head)'s
 // [hd] slices of the token that the launch appends.
-__device__ __forceinline__ void walk_seg16_mfma(const DecodeArgs& a, MfmaSmem<HD, G>& sm, int b, int kvh, int len, int first_row, BlockSrc& src,
+__device__ __forceinline__ void walk_seg16_mfma(const DecodeArgs& a, MfmaSmem<HD>& sm, int b, int kvh, int len, int first_row, BlockSrc& src,
                                                 Tickets& tk, float c_log2, WaveState<HD>& st, int new_row, const uint16_t* knew,
                                                 const uint16_t* vnew)
 {
@@ -783,11 +670,9 @@ __device__ __forceinline__ void walk_seg16_mfma(const DecodeArgs& a, MfmaSmem<HD
     const uint16_t* k16 = static_cast<const uint16_t*>(kv.k16) + (int64_t)kvh * HD;
     const uint16_t* v16 = static_cast<const uint16_t*>(kv.v16) + (int64_t)kvh * HD;
     pass_setup_barrier(a, b, tk);
-    constexpr bool WIDE = wide_of(G);              // weights to fp32 accuracy: three bf16 terms, or two f16 ones of 2^10 times the weight
-    constexpr float UP16 = (WIDE && !BF) ? 10.0f : 0.0f;
     U4 Bq[NK];
-    float qexp, qsum[MfmaSmem<HD, G>::SETS];
-    fetch_q_operands<HD, G>(sm, 3, Bq, qexp, qsum);
+    float qexp, qsum;
+    fetch_q_operands<HD>(sm, 3, Bq, qexp, qsum);
     const float cexp = c_log2 * qexp;
     uint16_t* vt = &sm.run.vt[wave][0][0];
 
@@ -840,45 +725,36 @@ __device__ __forceinline__ void walk_seg16_mfma(const DecodeArgs& a, MfmaSmem<HD
             const float mn = fmaxf(st.m, lm);
             const float alpha = (mn == -INFINITY) ? 1.0f : __builtin_amdgcn_exp2f(st.m - mn);
             st.m = mn;
-            st.l *= alpha;                         // (nothing has been added to st.accM yet: this segment is walked first)
+            st.l *= alpha;
+            st.accM *= alpha;
 #pragma unroll
             for (int ct = 0; ct < CT; ct++) st.O[ct] *= alpha;
         }
         float p[8];
 #pragma unroll
         for (int k = 0; k < 8; k++) {
-            p[k] = __builtin_amdgcn_exp2f(fmaf(x[k], cexp, UP16 != 0.0f ? UP16 - st.m : -st.m));
+            p[k] = __builtin_amdgcn_exp2f(fmaf(x[k], cexp, -st.m));
             st.l += p[k];
         }
         // ---- weights as B operands: slots (2v, 2v+1) = (tile 0 token 4j+v, tile 1 token 4j+v) ----
-        U4 Ph, Pl, Px;
+        U4 Ph, Pl;
         {
-            uint32_t hi[4], lo[4], ex[4];
+            uint32_t hi[4], lo[4];
 #pragma unroll
             for (int v = 0; v < 4; v++) {
                 if constexpr (BF) {
                     const uint32_t u0 = __float_as_uint(p[v]), u1 = __float_as_uint(p[4 + v]);
                     const float r0 = p[v] - __uint_as_float(u0 & 0xFFFF0000u), r1 = p[4 + v] - __uint_as_float(u1 & 0xFFFF0000u);
                     hi[v] = (u0 >> 16) | (u1 & 0xFFFF0000u);
-                    const uint32_t l0 = __float_as_uint(r0), l1 = __float_as_uint(r1);
-                    lo[v] = (l0 >> 16) | (l1 & 0xFFFF0000u);
-                    if constexpr (WIDE) {
-                        const float x0 = r0 - __uint_as_float(l0 & 0xFFFF0000u), x1 = r1 - __uint_as_float(l1 & 0xFFFF0000u);
-                        ex[v] = (__float_as_uint(x0) >> 16) | (__float_as_uint(x1) & 0xFFFF0000u);
-                    }
+                    lo[v] = (__float_as_uint(r0) >> 16) | (__float_as_uint(r1) & 0xFFFF0000u);
                 } else {
                     const _Float16 h0 = (_Float16)p[v], h1 = (_Float16)p[4 + v];
                     hi[v] = (uint32_t)__builtin_bit_cast(uint16_t, h0) | ((uint32_t)__builtin_bit_cast(uint16_t, h1) << 16);
                     lo[v] = 0;
-                    if constexpr (WIDE) {
-                        const _Float16 l0 = (_Float16)(p[v] - (float)h0), l1 = (_Float16)(p[4 + v] - (float)h1);
-                        lo[v] = (uint32_t)__builtin_bit_cast(uint16_t, l0) | ((uint32_t)__builtin_bit_cast(uint16_t, l1) << 16);
-                    }
                 }
             }
             Ph = U4{hi[0], hi[1], hi[2], hi[3]};
             Pl = U4{lo[0], lo[1], lo[2], lo[3]};
-            if constexpr (BF && WIDE) Px = U4{ex[0], ex[1], ex[2], ex[3]};
         }
         // ---- V rows -> LDS -> one channel x 8 tokens per lane, half of the channels at a time ----
 #pragma unroll
@@ -906,8 +782,7 @@ __device__ __forceinline__ void walk_seg16_mfma(const DecodeArgs& a, MfmaSmem<HD
                     a[v] = e0 | (e1 << 16);
                 }
                 st.O[ct] = mfma16<BF>(a[0], a[1], a[2], a[3], Ph, st.O[ct]);
-                if constexpr (BF || WIDE) st.O[ct] = mfma16<BF>(a[0], a[1], a[2], a[3], Pl, st.O[ct]);
-                if constexpr (BF && WIDE) st.O[ct] = mfma16<BF>(a[0], a[1], a[2], a[3], Px, st.O[ct]);
+                if constexpr (BF) st.O[ct] = mfma16<BF>(a[0], a[1], a[2], a[3], Pl, st.O[ct]);
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();          // the buffer is overwritten next
@@ -919,12 +794,13 @@ __device__ __forceinline__ void walk_seg16_mfma(const DecodeArgs& a, MfmaSmem<HD
             tk.spent = false;
         }
     }
-    if constexpr (UP16 != 0.0f) {
-        st.l *= pow2_of(-UP16);
-#pragma unroll
-        for (int ct = 0; ct < CT; ct++) st.O[ct] *= pow2_of(-UP16);
-    }
 }
+
+}  // namespace
+
+#include "wq_decode_f32.h"
+
+namespace {
 
 // ---- the end of an append (count_tables_read above has the protocol) ----
 constexpr long long WQ_APPEND_WAIT_TICKS = 400000000ll;   // 4 s of the 100 MHz clock: far beyond any launch; a wait that long gives up
@@ -967,8 +843,8 @@ __device__ __forceinline__ int scan_step(int x)          // x plus the value tha
     return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, true);
 }
 
-template <int HD, int G>
-__device__ __forceinline__ Place place_by_length(const DecodeArgs& a, MfmaSmem<HD, G>& sm, int wg)
+template <int G, class Smem>
+__device__ __forceinline__ Place place_by_length(const DecodeArgs& a, Smem& sm, int wg)
 {
     const int lane = threadIdx.x & 63, l = min(lane, a.B - 1);
     int len[4], off[4];
@@ -979,7 +855,7 @@ __device__ __forceinline__ Place place_by_length(const DecodeArgs& a, MfmaSmem<H
     }
     const int len16 = a.kv.len16[l], end16 = a.kv.off16[l + 1];
     off[3] = a.kv.off16[l];
-    const float vmax = a.kv.v_scale_max[l];
+    const float vmax = G == 2 ? a.kv.v_scale_max[l] : 0.f;
     const bool grows = a.k_new && off[3] + len16 < end16 && (int64_t)off[3] + len16 < a.kv.cap16;
     len[3] = len16;
     const int len16_after = len16 + (grows ? 1 : 0);     // with the token that this launch appends, as append followed by attention counts
@@ -989,9 +865,9 @@ __device__ __forceinline__ Place place_by_length(const DecodeArgs& a, MfmaSmem<H
         const int tokens = len[0] + len[1] + len[2] + len16_after;
         S = max(1, min(a.splits, (int)ceilf((float)tokens * a.len_scale)));
     } else {
-        int blocks = 1 + ((len16_after + 31) >> 5) * WQ_BLOCK_COST[3];
+        int blocks = 1 + ((len16_after + 31) >> 5) * block_cost<G>(3);
 #pragma unroll
-        for (int c = 0; c < 3; c++) blocks += ((len[c] + 31) >> 5) * WQ_BLOCK_COST[c];
+        for (int c = 0; c < 3; c++) blocks += ((len[c] + 31) >> 5) * block_cost<G>(c);
         const float cost = mine ? (float)blocks : 0.f, total = wave_sum(cost), most = wave_max(cost);
         // (a sequence's share is rounded down by 0.002 first: a quotient that should be whole must not become the next whole number)
         auto splits_of = [&](float tau) { return mine ? max(1, min(a.splits, (int)ceilf(fmaf(cost, __builtin_amdgcn_rcpf(tau), -0.002f)))) : 0; };
@@ -1038,8 +914,8 @@ __device__ __forceinline__ Place place_by_length(const DecodeArgs& a, MfmaSmem<H
 
 // ... the end of an append in such a launch: the launch's last workgroup in dispatch order (by the same reasoning as in
 // finish_append) waits until every workgroup has counted itself, those with nothing to do on sequence 0's counter
-template <int HD, int G>
-__device__ __forceinline__ void finish_append_by_length(const DecodeArgs& a, MfmaSmem<HD, G>& sm, int wg)
+template <class Smem>
+__device__ __forceinline__ void finish_append_by_length(const DecodeArgs& a, Smem& sm, int wg)
 {
     if (!a.k_new || threadIdx.x >= 64 || wg != (int)gridDim.x - 1) return;
     const int lane = threadIdx.x;
@@ -1076,12 +952,13 @@ __device__ __forceinline__ int range_edge(unsigned x, unsigned base, int n)
     return (int)min(e, (unsigned)n);
 }
 
+template <int G>
 __device__ __forceinline__ int range_edge_of(int c, unsigned x, unsigned base, int n)
 {
-    return c == 0 ? range_edge<(unsigned)WQ_BLOCK_COST[0]>(x, base, n)
-         : c == 1 ? range_edge<(unsigned)WQ_BLOCK_COST[1]>(x, base, n)
-         : c == 2 ? range_edge<(unsigned)WQ_BLOCK_COST[2]>(x, base, n)
-                  : range_edge<(unsigned)WQ_BLOCK_COST[3]>(x, base, n);
+    return c == 0 ? range_edge<(unsigned)block_cost<G>(0)>(x, base, n)
+         : c == 1 ? range_edge<(unsigned)block_cost<G>(1)>(x, base, n)
+         : c == 2 ? range_edge<(unsigned)block_cost<G>(2)>(x, base, n)
+                  : range_edge<(unsigned)block_cost<G>(3)>(x, base, n);
 }
 
 // ---- helpers of the two merges --------------------------------------------------------------------------------
@@ -1132,12 +1009,16 @@ __device__ __forceinline__ typename FloatN<N>::type ld_part(__amdgpu_buffer_rsrc
 }
 
 
+template <int HD, int G>
+using DecodeSmem = std::conditional_t<G == 2, MfmaSmem<HD>, F32Smem<HD, G>>;
+
 // PACKED: a launch by length whose grid place_by_length maps (an instantiation of its own: in a common one the registers it
 // takes cost every other launch 0.2-0.5 us)
 template <int HD, int G, bool PACKED>
 __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
 {
-    MfmaSmem<HD, G>& sm = *reinterpret_cast<MfmaSmem<HD, G>*>(smem_raw);
+    constexpr bool F32 = G != 2;
+    DecodeSmem<HD, G>& sm = *reinterpret_cast<DecodeSmem<HD, G>*>(smem_raw);
     // consecutive workgroups go to different (sequence, KV head) units: the units' tables and queries are then
     // read by all XCDs alike, and the workgroups of one unit do not start in a burst on neighbouring compute units
     // (the grid is (KV heads, sequences, splits): workgroups are dispatched with x fastest, and nothing here has to divide)
@@ -1152,11 +1033,11 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
     int cls_len[4], cls_off[4], end16;
     float v_scale_max;
     if constexpr (PACKED) {
-        const Place p = place_by_length<HD, G>(a, sm, (int)blockIdx.x);
+        const Place p = place_by_length<G>(a, sm, (int)blockIdx.x);
         if (p.b < 0) {
             if (a.k_new) __syncthreads();
             count_tables_read(a, 0);
-            finish_append_by_length<HD, G>(a, sm, (int)blockIdx.x);
+            finish_append_by_length(a, sm, (int)blockIdx.x);
             return;
         }
         b = p.b, kvh = p.kvh, split = p.split, S = p.S;
@@ -1176,7 +1057,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         cls_len[3] = a.kv.len16[b];
         cls_off[3] = a.kv.off16[b];
         end16 = a.kv.off16[b + 1];
-        v_scale_max = a.kv.v_scale_max[b];
+        v_scale_max = F32 ? 0.f : a.kv.v_scale_max[b];
     }
     const int unit = b * a.kv.Hkv + kvh;
     // a token appended by this launch becomes the last row of the 16-bit segment: read from k_new / v_new by whoever
@@ -1212,10 +1093,11 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         }
     }
     // ---- the query operands of all classes, one class per wavefront ----
-    stage_q_operands<HD, G>(a, sm, b, kvh, wave, bf16seg);
+    if constexpr (!F32) stage_q_operands<HD>(a, sm, b, kvh, wave, bf16seg);
 
     // ---- the workgroup's range of the stream [16-bit | 8-bit | 4-bit | 2-bit] of (b, kvh), and this wavefront's
-    //      fixed share of it (none unless the launch asks for fixed shares: then there is no pool) ----
+    //      fixed share of it (none unless the launch asks for fixed shares or the walkers are the fp32 ones: then there is no pool) ----
+    const bool fixed_shares = F32 || a.fixed_shares;
     Tickets tk;
     tk.ctr = &sm.next_ticket;
     tk.synced = false;
@@ -1228,7 +1110,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         nb[3] = a.mfma16 ? (cls_len[3] + 31) >> 5 : 0;
         unsigned total = 0u;
 #pragma unroll
-        for (int c = 0; c < 4; c++) total += (unsigned)nb[c] * (unsigned)WQ_BLOCK_COST[c];
+        for (int c = 0; c < 4; c++) total += (unsigned)nb[c] * (unsigned)block_cost<G>(c);
         // cost at which split x starts: floor(total * x / S) up to rounding (one reciprocal, the same bits in every
         // wavefront of the launch); split 0 starts at cost 0, the last one ends behind everything
         const float rS = __builtin_amdgcn_rcpf((float)S);
@@ -1241,14 +1123,14 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         unsigned t = 0;
 #pragma unroll
         for (int c = 3; c >= 0; c--) {
-            const int e0 = range_edge_of(c, G0, base, nb[c]);
-            const int e1 = range_edge_of(c, G1, base, nb[c]);
-            if (a.fixed_shares) {                  // the range is divided among the wavefronts by cost; no pool
+            const int e0 = range_edge_of<G>(c, G0, base, nb[c]);
+            const int e1 = range_edge_of<G>(c, G1, base, nb[c]);
+            if (fixed_shares) {                    // the range is divided among the wavefronts by cost; no pool
                 const unsigned long long span = G1 - G0;
                 const unsigned x0 = G0 + (unsigned)((span * (unsigned)wave) >> 3), x1 = G0 + (unsigned)((span * (unsigned)(wave + 1)) >> 3);
                 static_assert(WQ_WAVES == 8, "the shift above");
-                src[c].cur = wave == 0 ? e0 : range_edge_of(c, x0, base, nb[c]);
-                src[c].end = wave == WQ_WAVES - 1 ? e1 : range_edge_of(c, x1, base, nb[c]);
+                src[c].cur = wave == 0 ? e0 : range_edge_of<G>(c, x0, base, nb[c]);
+                src[c].end = wave == WQ_WAVES - 1 ? e1 : range_edge_of<G>(c, x1, base, nb[c]);
                 src[c].pool_first = e1;
                 src[c].tk_lo = src[c].tk_hi = t;
             } else {                               // the whole range is the pool
@@ -1258,9 +1140,9 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
                 t += (unsigned)(e1 - e0);
                 src[c].tk_hi = t;
             }
-            base += (unsigned)nb[c] * (unsigned)WQ_BLOCK_COST[c];
+            base += (unsigned)nb[c] * (unsigned)block_cost<G>(c);
         }
-        if (!a.fixed_shares && t > (unsigned)WQ_TAPER_TICKETS) tk.taper = t - (unsigned)WQ_TAPER_TICKETS;
+        if (!fixed_shares && t > (unsigned)WQ_TAPER_TICKETS) tk.taper = t - (unsigned)WQ_TAPER_TICKETS;
         // The first tickets are fixed, so that the first loads can go out before the workgroup's set-up barrier; the counter
         // starts behind them.  WQ_FIRST_TICKETS consecutive blocks per wavefront, or, in a range of fewer blocks, what
         // spreads them over all eight: a block's arithmetic is half a microsecond, and with four blocks each the first
@@ -1270,7 +1152,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         tk.held = (unsigned)wave * first;
         tk.end = tk.held + first;
         tk.spent = first == 0u;
-        tk.dealt = !a.fixed_shares && first * (unsigned)WQ_WAVES >= t;
+        tk.dealt = !fixed_shares && first * (unsigned)WQ_WAVES >= t;
         if (tid == 0) sm.next_ticket = first * (unsigned)WQ_WAVES;
     }
 
@@ -1282,55 +1164,71 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
     }
 #endif
 
-    WaveState<HD> st;
+    if constexpr (F32) {
+        F32State<HD> st;
 #pragma unroll
-    for (int ct = 0; ct < CT; ct++) st.O[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
-    st.m = -INFINITY;
-    st.l = 0.f;
-    st.accM[0] = st.accM[1] = 0.f;
-    st.up = weight_upscale(v_scale_max);
-    const float o_unit = pow2_of(code_log2(G) - st.up);   // what an accumulator of the value product counts in units of
-    const float c_log2 = a.sm_scale * 1.4426950408889634f;
-    WQ_WSTAMP(0, wall_clock64());
-    if (has_blocks(src[3], tk, 1u)) {              // (most wavefronts have no block of the 16-bit segment and go straight on)
-        if (bf16seg)
-            walk_seg16_mfma<HD, true, G>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3], tk, c_log2, st, new_row, knew, vnew);
-        else
-            walk_seg16_mfma<HD, false, G>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3], tk, c_log2, st, new_row, knew, vnew);
-        // the quantized classes accumulate 2^(up-24) * (p s_v code) (up-9 with WIDE); bring the 16-bit part to the same unit (exact)
-        const float to_unit = pow2_of(st.up - code_log2(G));
-#pragma unroll
-        for (int ct = 0; ct < CT; ct++) st.O[ct] *= to_unit;
-    }
-    WQ_WSTAMP(1, wall_clock64());
-    walk_class_mfma<HD, 8, G, WQ_D8>(a, sm, b, kvh, cls_len[2], cls_off[2], src[2], tk, c_log2, st);
-    WQ_WSTAMP(2, wall_clock64());
-    walk_class_mfma<HD, 4, G, WQ_D4>(a, sm, b, kvh, cls_len[1], cls_off[1], src[1], tk, c_log2, st);
-    WQ_WSTAMP(3, wall_clock64());
-    walk_class_mfma<HD, 2, G, WQ_D2>(a, sm, b, kvh, cls_len[0], cls_off[0], src[0], tk, c_log2, st);
-    WQ_WSTAMP(4, wall_clock64());
-
-    WQ_STAMP(4);
-#ifdef WQ_TIMELINE
-    if (a.dbg && threadIdx.x == 0) a.dbg[WQ_WG * 64 + 7] += (long long)__builtin_readcyclecounter();
-#endif
-    // ---- reduce the lane groups' shares, hand the wave's numerators to LDS ----
-    constexpr int SETS = MfmaSmem<HD, G>::SETS;
-    const float l = sum_over_rows(st.l);
-    float am[SETS];
-#pragma unroll
-    for (int T = 0; T < SETS; T++) am[T] = sum_over_rows(st.accM[T]);
-#pragma unroll
-    for (int ct = 0; ct < CT; ct++) {
-        const int owner = ct / (CT / (2 * SETS));  // the group (or half, with one group) that channel tile ct belongs to
-        if ((owner & 1) == g) {                    // ... is this column's in set owner / 2
-#pragma unroll
-            for (int i = 0; i < 4; i++) sm.O[wave][h][16 * ct + 4 * j + i] = fmaf(st.O[ct][i], o_unit, am[owner >> 1]);
+        for (int ct = 0; ct < CT; ct++) st.O[ct][0] = st.O[ct][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+        st.m = -INFINITY;
+        st.l = 0.f;
+        load_q_quarter<HD>(a, b, kvh, st.q);
+        if (src[3].cur < src[3].end) {
+            if (bf16seg)
+                walk_seg16_f32<HD, true, G>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3].cur, src[3].end, tk, st, new_row, knew, vnew);
+            else
+                walk_seg16_f32<HD, false, G>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3].cur, src[3].end, tk, st, new_row, knew, vnew);
         }
-    }
-    if (j == 0 && g == 0) {
-        sm.ml[wave][h][0] = st.m;
-        sm.ml[wave][h][1] = l;
+        walk_class_f32<HD, 8, G>(a, sm, b, kvh, cls_len[2], cls_off[2], src[2].cur, src[2].end, tk, st);
+        walk_class_f32<HD, 4, G>(a, sm, b, kvh, cls_len[1], cls_off[1], src[1].cur, src[1].end, tk, st);
+        walk_class_f32<HD, 2, G>(a, sm, b, kvh, cls_len[0], cls_off[0], src[0].cur, src[0].end, tk, st);
+        hand_over_f32<HD, G>(sm, st);
+    } else {
+        const float c_log2 = a.sm_scale * 1.4426950408889634f;
+        WaveState<HD> st;
+#pragma unroll
+        for (int ct = 0; ct < CT; ct++) st.O[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
+        st.m = -INFINITY;
+        st.l = 0.f;
+        st.accM = 0.f;
+        st.up = weight_upscale(v_scale_max);
+        const float o_unit = pow2_of(24.0f - st.up);   // what an accumulator of the value product counts in units of
+        WQ_WSTAMP(0, wall_clock64());
+        if (has_blocks(src[3], tk, 1u)) {              // (most wavefronts have no block of the 16-bit segment and go straight on)
+            if (bf16seg)
+                walk_seg16_mfma<HD, true>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3], tk, c_log2, st, new_row, knew, vnew);
+            else
+                walk_seg16_mfma<HD, false>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3], tk, c_log2, st, new_row, knew, vnew);
+            // the quantized classes accumulate 2^(up-24) * (p s_v code); bring the 16-bit part to the same unit (exact)
+            const float to_unit = pow2_of(st.up - 24.0f);
+#pragma unroll
+            for (int ct = 0; ct < CT; ct++) st.O[ct] *= to_unit;
+        }
+        WQ_WSTAMP(1, wall_clock64());
+        walk_class_mfma<HD, 8, WQ_D8>(a, sm, b, kvh, cls_len[2], cls_off[2], src[2], tk, c_log2, st);
+        WQ_WSTAMP(2, wall_clock64());
+        walk_class_mfma<HD, 4, WQ_D4>(a, sm, b, kvh, cls_len[1], cls_off[1], src[1], tk, c_log2, st);
+        WQ_WSTAMP(3, wall_clock64());
+        walk_class_mfma<HD, 2, WQ_D2>(a, sm, b, kvh, cls_len[0], cls_off[0], src[0], tk, c_log2, st);
+        WQ_WSTAMP(4, wall_clock64());
+
+        WQ_STAMP(4);
+#ifdef WQ_TIMELINE
+        if (a.dbg && threadIdx.x == 0) a.dbg[WQ_WG * 64 + 7] += (long long)__builtin_readcyclecounter();
+#endif
+        // ---- reduce the lane groups' shares, hand the wave's numerators to LDS ----
+        float l = st.l, am = st.accM;
+        l = sum_over_rows(l);
+        am = sum_over_rows(am);
+#pragma unroll
+        for (int ct = 0; ct < CT; ct++) {
+            if ((ct >= CT / 2) == (g == 1)) {          // this column's group owns channel tile ct
+#pragma unroll
+                for (int i = 0; i < 4; i++) sm.O[wave][h][16 * ct + 4 * j + i] = fmaf(st.O[ct][i], o_unit, am);
+            }
+        }
+        if (j == 0 && g == 0) {
+            sm.ml[wave][h][0] = st.m;
+            sm.ml[wave][h][1] = l;
+        }
     }
     pass_setup_barrier(a, b, tk);
     __syncthreads();
@@ -1353,7 +1251,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         for (int c = 0; c < CPL; c++) num[c] = 0.f;
 #pragma unroll
         for (int w = 0; w < WQ_WAVES; w++) {
-            const float sc = (mw[w] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mw[w] - M);
+            const float sc = (mw[w] == -INFINITY) ? 0.f : F32 ? __expf(mw[w] - M) : __builtin_amdgcn_exp2f(mw[w] - M);
 #pragma unroll
             for (int c = 0; c < CPL; c++) num[c] = fmaf(sm.O[w][wave][CPL * lane + c], sc, num[c]);
             L = fmaf(sm.ml[w][wave][1], sc, L);
@@ -1362,7 +1260,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         // is needed to hand the partial to the workgroup that merges the splits
         store_through<CPL>(out + CPL * lane, num);
         if (lane == 0) {
-            const float ml2[2] = {M * 0.6931471805599453f, L};
+            const float ml2[2] = {F32 ? M : M * 0.6931471805599453f, L};       // (the fp32 walkers keep the reference in natural units)
             store_through<2>(out + HD, ml2);
         }
     }
@@ -1435,7 +1333,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
     }
     WQ_STAMP(59);
     if constexpr (PACKED)
-        finish_append_by_length<HD, G>(a, sm, (int)blockIdx.x);
+        finish_append_by_length(a, sm, (int)blockIdx.x);
     else
         finish_append(a, b, kvh, split, new_row);
 }

@@ -327,7 +327,7 @@ static int check_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, 
         return wq_fail(ctx, WQ_ERR_WORKSPACE, "workspace too small for %d splits", *num_splits);
     // where the kernel merges the splits itself: what makes the launch shortest, as far as the workspace has room
     bool uneven = false;
-    const int picked = automatic ? wq_decode_pick_splits(ctx, q_dtype, B, Hq, kv, max_seq_tokens, algo, &uneven) : 0;
+    const int picked = automatic ? wq_decode_pick_splits(ctx, q, q_dtype, B, Hq, kv, max_seq_tokens, algo, &uneven) : 0;
     if (picked > 0) {
         *num_splits = picked;
         *longest = uneven ? -1 : 0;
@@ -348,7 +348,7 @@ int wq_decode_append_attention(wq_ctx* ctx, const void* q, int q_dtype, int B, i
     int64_t longest = 0;
     int rc = check_decode(ctx, q, q_dtype, B, Hq, kv, sm_scale, &num_splits, max_seq_tokens, algo, out, &longest);
     if (rc != WQ_OK || B == 0) return rc;
-    if (wq_decode_can_append(q_dtype, B, Hq, kv, num_splits, algo, new_dtype))
+    if (wq_decode_can_append(q, q_dtype, B, Hq, kv, num_splits, algo, k_new, v_new, new_dtype))
         return wq_launch_decode(ctx, q, q_dtype, B, Hq, kv, sm_scale, num_splits, algo, out, lse, k_new, v_new, longest);
     // other kernels, other element types: two launches
     rc = wq_launch_append(ctx, k_new, v_new, new_dtype, B, kv);

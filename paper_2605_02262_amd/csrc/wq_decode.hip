@@ -11,6 +11,7 @@
 // matrix-core body in wq_decode_mfma.h is the fast path (use_matrix_cores below says where it is taken).
 #include <stdlib.h>
 
+#include <initializer_list>
 #include <type_traits>
 
 #include "wq_internal.h"
@@ -442,20 +443,29 @@ static bool fits_cost_axis(const wq_packed_kv* kv)
     return (int64_t)kv->cap[0] + kv->cap[1] + kv->cap[2] + kv->cap16 <= (int64_t)1 << 27;
 }
 
+static bool aligned_16(std::initializer_list<const void*> pointers)
+{
+    uintptr_t bits = 0;
+    for (const void* p : pointers) bits |= reinterpret_cast<uintptr_t>(p);
+    return bits % 16 == 0;
+}
+
 // Which kernel walks the quantized classes.  Two groups per head: the matrix-core kernel, with the weights in one f16 value.
 // One and four groups: the matrix-core kernel with its fp32 walkers for 16-bit queries (measured, 8 x 12795 tokens, 28 / 4
 // heads of 128, group 32: 917 us a call on the vector kernel); fp32 queries and caches beyond the cost axis stay with the
-// vector kernel.
-static bool use_matrix_cores(int q_dtype, const wq_packed_kv* kv, int balgo)
+// vector kernel, which also takes what does not lie on 16-byte boundaries (a query cut out of a larger tensor): it reads
+// element by element.
+static bool use_matrix_cores(const void* q, int q_dtype, const wq_packed_kv* kv, int balgo)
 {
     if (balgo != WQ_DECODE_AUTO) return balgo == WQ_DECODE_MFMA;
-    return kv->hd / kv->group == 2 || (q_dtype != WQ_F32 && fits_cost_axis(kv));
+    return kv->hd / kv->group == 2 ||
+           (q_dtype != WQ_F32 && fits_cost_axis(kv) && aligned_16({q, kv->k16, kv->v16, kv->codes[0], kv->codes[1], kv->codes[2]}));
 }
 
 // Does a launch with these arguments merge the splits itself (all but their number looked at)?
-static bool merges_itself(int q_dtype, int B, const wq_packed_kv* kv, int algo)
+static bool merges_itself(const void* q, int q_dtype, int B, const wq_packed_kv* kv, int algo)
 {
-    return !(algo & (WQ_DECODE_PARTIALS_ONLY | WQ_DECODE_SEPARATE_MERGE)) && use_matrix_cores(q_dtype, kv, algo & ~WQ_DECODE_FLAGS) &&
+    return !(algo & (WQ_DECODE_PARTIALS_ONLY | WQ_DECODE_SEPARATE_MERGE)) && use_matrix_cores(q, q_dtype, kv, algo & ~WQ_DECODE_FLAGS) &&
            !(kv->dtype16 == WQ_BF16 && q_dtype != WQ_BF16) && (int64_t)B * kv->Hkv <= WQ_MAX_ARRIVE;
 }
 
@@ -490,10 +500,10 @@ static int splits_for_rounds(int B, const wq_packed_kv* kv, int64_t max_seq_toke
 // capacities say that the sequences are about equally long: finding the counts takes 1.1 us of the launch, and up to there
 // even counts cost less (12 sequences filling 0.76 of the longest one's length: 26.0 us against 26.5; 20 filling 0.54: 33.9
 // against 23.6).  A second round trip of the merge pays from about 900 blocks in the longest sequence.
-int wq_decode_pick_splits(const wq_ctx* ctx, int q_dtype, int B, int Hq, const wq_packed_kv* kv, int64_t max_seq_tokens, int algo, bool* by_length)
+int wq_decode_pick_splits(const wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, const wq_packed_kv* kv, int64_t max_seq_tokens, int algo, bool* by_length)
 {
     *by_length = (algo & WQ_DECODE_BY_LENGTH) != 0;
-    if (!merges_itself(q_dtype, B, kv, algo) || max_seq_tokens <= 0 || (*by_length && B > 64)) return 0;
+    if (!merges_itself(q, q_dtype, B, kv, algo) || max_seq_tokens <= 0 || (*by_length && B > 64)) return 0;
     const size_t per = sizeof(float) * (size_t)B * Hq * (kv->hd + 2);
     const size_t room = ctx->ws_bytes > WQ_WS_HEADER ? (ctx->ws_bytes - WQ_WS_HEADER) / per : 0;      // partials that the workspace holds
     const int most = room < (size_t)WQ_MAX_FUSED_SPLITS ? (int)room : WQ_MAX_FUSED_SPLITS;
@@ -505,11 +515,12 @@ int wq_decode_pick_splits(const wq_ctx* ctx, int q_dtype, int B, int Hq, const w
 }
 
 // Can wq_launch_decode append k_new, v_new (element type new_dtype) itself with these arguments?  Only the matrix-core
-// kernel that walks every segment and merges its splits does: it needs the new rows in the cache's own 16-bit type
-// and one more counter per sequence in the workspace header.
-bool wq_decode_can_append(int q_dtype, int B, int Hq, const wq_packed_kv* kv, int num_splits, int algo, int new_dtype)
+// kernel that walks every segment and merges its splits does: it needs the new rows in the cache's own 16-bit type and on
+// 16-byte boundaries, and one more counter per sequence in the workspace header.
+bool wq_decode_can_append(const void* q, int q_dtype, int B, int Hq, const wq_packed_kv* kv, int num_splits, int algo, const void* k_new,
+                          const void* v_new, int new_dtype)
 {
-    return merges_itself(q_dtype, B, kv, algo) && new_dtype == kv->dtype16 && (int64_t)B * kv->Hkv + B <= WQ_MAX_ARRIVE &&
+    return merges_itself(q, q_dtype, B, kv, algo) && new_dtype == kv->dtype16 && aligned_16({k_new, v_new}) && (int64_t)B * kv->Hkv + B <= WQ_MAX_ARRIVE &&
            num_splits <= WQ_MAX_FUSED_SPLITS && Hq / kv->Hkv <= WQ_MAX_REP;
 }
 
@@ -526,7 +537,7 @@ int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, con
 {
     const bool partials_only = (algo & WQ_DECODE_PARTIALS_ONLY) != 0;
     const bool fixed_shares = (algo & WQ_DECODE_FIXED_SHARES) != 0;
-    const bool fused = merges_itself(q_dtype, B, kv, algo);
+    const bool fused = merges_itself(q, q_dtype, B, kv, algo);
     algo &= ~WQ_DECODE_FLAGS;
     DecodeArgs a;
     a.q = q;
@@ -536,7 +547,7 @@ int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, con
     a.rep = Hq / kv->Hkv;
     a.splits = num_splits;
     a.sm_scale = sm_scale;
-    a.use_mfma = use_matrix_cores(q_dtype, kv, algo);
+    a.use_mfma = use_matrix_cores(q, q_dtype, kv, algo);
     // a bf16 cache needs the exact bf16 query for the bf16 instruction; other query types send the 16-bit
     // segment to the generic kernel
     a.mfma16 = a.use_mfma && !(kv->dtype16 == WQ_BF16 && q_dtype != WQ_BF16);

@@ -371,7 +371,8 @@ __device__ __forceinline__ void copy16_rows(int64_t r0, const T* __restrict__ K,
 #pragma unroll
         for (int plane = 0; plane < 2; plane++) {
             const T* const src = (plane ? V : K) + from * 8;
-            uint4* const dst = static_cast<uint4*>(plane ? pk.v16 : pk.k16) + to;
+            uint16_t* const dst = static_cast<uint16_t*>(plane ? pk.v16 : pk.k16) + to * 8;
+            uint4 row;
             if constexpr (std::is_same_v<T, float>) {          // fp32 -> fp16 (nearest even)
                 float x[8];
                 wq_ld8(src, x);
@@ -379,9 +380,16 @@ __device__ __forceinline__ void copy16_rows(int64_t r0, const T* __restrict__ K,
 #pragma unroll
                 for (int k = 0; k < 4; k++)
                     o[k] = (uint32_t)__half_as_ushort(__float2half_rn(x[2 * k])) | (uint32_t)__half_as_ushort(__float2half_rn(x[2 * k + 1])) << 16;
-                *dst = make_uint4(o[0], o[1], o[2], o[3]);
+                row = make_uint4(o[0], o[1], o[2], o[3]);
             } else {
-                *dst = *reinterpret_cast<const uint4*>(src);
+                row = *reinterpret_cast<const uint4*>(src);
+            }
+            if (reinterpret_cast<uintptr_t>(dst) % 16 == 0) {
+                *reinterpret_cast<uint4*>(dst) = row;
+            } else {                                           // (a segment that does not begin on a 16-byte boundary)
+                const uint32_t w[4] = {row.x, row.y, row.z, row.w};
+#pragma unroll
+                for (int k = 0; k < 8; k++) dst[k] = (uint16_t)(w[k >> 1] >> (16 * (k & 1)));
             }
         }
     }

@@ -123,8 +123,8 @@ size_t wq_workspace_bytes(int B, int Hq, int hd, int max_splits, int64_t total_v
  * capacity cap_tokens (rounded up to 32 here), both planes and all KV heads.  0 on unsupported shapes.      */
 size_t wq_packed_bytes(int bits, int64_t cap_tokens, int Hkv, int hd, int group, size_t* meta_bytes);
 /* Host-only, pure.  Split count to size a workspace by for calls with num_splits = 0 when the sequences are about equally long.
- * Where the decode kernel merges the splits itself such a call may use another count, by what the launch costs, as far as
- * the workspace has room (wq_workspace_bytes leaves room for 32 more); elsewhere it uses this one.                     */
+ * Where the decode kernel merges the splits itself such a call may use another count, by what the launch costs, up to this one
+ * and 32 more (wq_workspace_bytes leaves room for them; a larger workspace changes nothing); elsewhere it uses this one.  */
 int wq_auto_splits(int B, int Hkv, int64_t max_seq_tokens);
 /* Host-only, pure.  ... and under WQ_DECODE_BY_LENGTH: total_tokens (all sequences together; the decode calls
  * take the sum of the cache's capacities for it) below 3/4 of B * max_seq_tokens gives more splits, of which a sequence

@@ -500,14 +500,13 @@ static int splits_for_rounds(int B, const wq_packed_kv* kv, int64_t max_seq_toke
 // capacities say that the sequences are about equally long: finding the counts takes 1.1 us of the launch, and up to there
 // even counts cost less (12 sequences filling 0.76 of the longest one's length: 26.0 us against 26.5; 20 filling 0.54: 33.9
 // against 23.6).  A second round trip of the merge pays from about 900 blocks in the longest sequence.
-int wq_decode_pick_splits(const wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, const wq_packed_kv* kv, int64_t max_seq_tokens, int algo, bool* by_length)
+int wq_decode_pick_splits(const void* q, int q_dtype, int B, const wq_packed_kv* kv, int64_t max_seq_tokens, int plain_splits, int algo, bool* by_length)
 {
     *by_length = (algo & WQ_DECODE_BY_LENGTH) != 0;
     if (!merges_itself(q, q_dtype, B, kv, algo) || max_seq_tokens <= 0 || (*by_length && B > 64)) return 0;
-    const size_t per = sizeof(float) * (size_t)B * Hq * (kv->hd + 2);
-    const size_t room = ctx->ws_bytes > WQ_WS_HEADER ? (ctx->ws_bytes - WQ_WS_HEADER) / per : 0;      // partials that the workspace holds
-    const int most = room < (size_t)WQ_MAX_FUSED_SPLITS ? (int)room : WQ_MAX_FUSED_SPLITS;
-    if (most < 1) return 0;
+    // what a workspace for plain_splits has room for (wq_decode_ws_bytes), and no more where there is more: the same call then
+    // cuts its work alike, and gives the same bits, whatever the workspace
+    const int most = plain_splits + 32 < WQ_MAX_FUSED_SPLITS ? plain_splits + 32 : WQ_MAX_FUSED_SPLITS;
     const double slots = (double)kv->cap[0] + (double)kv->cap[1] + (double)kv->cap[2] + (double)kv->cap16;
     if (slots >= 0.75 * (double)B * (double)max_seq_tokens) *by_length = false;
     if (*by_length) return most > 32 && max_seq_tokens <= 900 * 32 ? 32 : most;

@@ -326,11 +326,10 @@ static int check_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, 
     if (ctx->ws_bytes < WQ_WS_HEADER + wq_decode_ws_bytes(B, Hq, kv->hd, *num_splits))
         return wq_fail(ctx, WQ_ERR_WORKSPACE, "workspace too small for %d splits", *num_splits);
     // where the kernel merges the splits itself: what makes the launch shortest, as far as a workspace for this count has room
-    bool uneven = false;
-    const int picked = automatic ? wq_decode_pick_splits(q, q_dtype, B, kv, max_seq_tokens, *num_splits, algo, &uneven) : 0;
+    const int picked = automatic ? wq_decode_pick_splits(q, q_dtype, B, kv, max_seq_tokens, *num_splits, algo) : 0;
     if (picked > 0) {
         *num_splits = picked;
-        *longest = uneven ? -1 : 0;
+        *longest = by_length ? -1 : 0;
     }
     return WQ_OK;
 }

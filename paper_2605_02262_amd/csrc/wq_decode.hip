@@ -495,21 +495,30 @@ static int splits_for_rounds(int B, const wq_packed_kv* kv, int64_t max_seq_toke
     return best;
 }
 
-// Splits of an automatic call (0: the launch would not merge them itself, the caller decides).  Under WQ_DECODE_BY_LENGTH the
-// kernel finds every sequence's count (place_by_length) and this is the most that one can get; *by_length is cleared where the
-// capacities say that the sequences are about equally long: finding the counts takes 1.1 us of the launch, and up to there
-// even counts cost less (12 sequences filling 0.76 of the longest one's length: 26.0 us against 26.5; 20 filling 0.54: 33.9
-// against 23.6).  A second round trip of the merge pays from about 900 blocks in the longest sequence.
-int wq_decode_pick_splits(const void* q, int q_dtype, int B, const wq_packed_kv* kv, int64_t max_seq_tokens, int plain_splits, int algo, bool* by_length)
+// Under WQ_DECODE_BY_LENGTH with a given count: are the workgroups with work numbered by the kernel (place_by_length)?  That
+// takes 0.9 us of the launch (8 even sequences: 17.7 us, numbered 18.6), which uneven ones repay (20 that fill 0.49 of the
+// longest one's length, 8 splits: 37.6 -> 36.1).  Room in the cache for less than 3/4 of B longest sequences proves that they
+// differ; room for more than B of them (and their last blocks' padding) says nothing, the caller's flag is believed.
+static bool packs_by_length(int B, const wq_packed_kv* kv, int64_t max_seq_tokens)
 {
-    *by_length = (algo & WQ_DECODE_BY_LENGTH) != 0;
-    if (!merges_itself(q, q_dtype, B, kv, algo) || max_seq_tokens <= 0 || (*by_length && B > 64)) return 0;
+    const double slots = (double)kv->cap[0] + (double)kv->cap[1] + (double)kv->cap[2] + (double)kv->cap16;
+    return B <= 64 && (slots < 0.75 * (double)B * (double)max_seq_tokens || slots > (double)B * ((double)max_seq_tokens + 128.0));
+}
+
+// Splits of an automatic call (0: the launch would not merge them itself, the caller decides).  Under WQ_DECODE_BY_LENGTH the
+// kernel finds every sequence's count (place_by_length) and this is the most that one can get.  The caller's flag alone
+// decides that: the capacities say what the classes have room for, not what they hold (where thresholds decide, every class
+// has room for all tokens; a cache in use has room to grow).  Even sequences lose 0.9 us by it, uneven ones gain far more (20 that
+// fill 0.49 of the longest one's length: 40.2 us with even counts, 29.5 so; 32 that fill 0.52: 78.6 and 57.4).  A second round
+// trip of the merge pays from about 900 blocks in the longest sequence.
+int wq_decode_pick_splits(const void* q, int q_dtype, int B, const wq_packed_kv* kv, int64_t max_seq_tokens, int plain_splits, int algo)
+{
+    const bool by_length = (algo & WQ_DECODE_BY_LENGTH) != 0;
+    if (!merges_itself(q, q_dtype, B, kv, algo) || max_seq_tokens <= 0 || (by_length && B > 64)) return 0;
     // what a workspace for plain_splits has room for (wq_decode_ws_bytes), and no more where there is more: the same call then
     // cuts its work alike, and gives the same bits, whatever the workspace
     const int most = plain_splits + 32 < WQ_MAX_FUSED_SPLITS ? plain_splits + 32 : WQ_MAX_FUSED_SPLITS;
-    const double slots = (double)kv->cap[0] + (double)kv->cap[1] + (double)kv->cap[2] + (double)kv->cap16;
-    if (slots >= 0.75 * (double)B * (double)max_seq_tokens) *by_length = false;
-    if (*by_length) return most > 32 && max_seq_tokens <= 900 * 32 ? 32 : most;
+    if (by_length) return most > 32 && max_seq_tokens <= 900 * 32 ? 32 : most;
     return splits_for_rounds(B, kv, max_seq_tokens, most);
 }
 
@@ -574,7 +583,7 @@ int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, con
     if (k_new && !a.fused) return wq_fail(ctx, WQ_ERR_UNSUPPORTED, "this decode launch cannot append");
     // splits by length: only where the kernel merges the splits itself (the separate merge kernel reads every partial)
     a.len_scale = (a.fused && longest_tokens > 0) ? (float)a.splits / (float)longest_tokens : 0.f;
-    a.packed_grid = a.fused && longest_tokens != 0 && B <= 64;
+    a.packed_grid = a.fused && (longest_tokens < 0 || (longest_tokens > 0 && packs_by_length(B, kv, longest_tokens)));
     // Automatic splits by length: 256 workgroups, one per compute unit, if that is at least two per (sequence, KV head), so
     // that rounding to whole splits leaves few of them with little to do; else 512
     const int auto_wgs = (int64_t)B * kv->Hkv <= 128 ? 256 : 512;

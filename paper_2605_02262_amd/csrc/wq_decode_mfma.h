@@ -873,8 +873,11 @@ __device__ __forceinline__ Place place_by_length(const DecodeArgs& a, Smem& sm, 
         auto splits_of = [&](float tau) { return mine ? max(1, min(a.splits, (int)ceilf(fmaf(cost, __builtin_amdgcn_rcpf(tau), -0.002f)))) : 0; };
         float lo = total / (float)a.slots;
         float hi = fmaxf(lo, a.slots > a.B ? fminf(total / (float)(a.slots - a.B), most) : most);
+        // (even after all: the whole quotient for everyone, no search, 0.3 us)
+        const bool even = total >= 0.97f * most * (float)a.B;
+        if (even) hi = fmaxf(most * __builtin_amdgcn_rcpf(fmaxf(1.0f, floorf((float)a.slots * __builtin_amdgcn_rcpf((float)a.B) + 0.001f))), lo);
 #pragma unroll 1
-        for (int k = 0; k < 3; k++) {
+        for (int k = even ? 3 : 0; k < 3; k++) {
             const float mid = 0.5f * (lo + hi);
             const bool fits = wave_sum((float)splits_of(mid)) <= (float)a.slots;
             lo = fits ? lo : mid;

@@ -27,3 +27,28 @@ def test_the_workspace_size_does_not_change_the_bits(group):
         got.append(W.wq_decode_attention(ctx, q, cache, 0.088, 0, n, W.DECODE_FIXED_SHARES))
         assert ctx.device_status() == 0
     assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+
+
+@pytest.mark.parametrize("hd,group", [(64, 32), (128, 128)])
+def test_by_length_takes_effect_where_capacities_exceed_contents(hd, group):
+    """Uneven sequences in a cache of just their size, in one whose classes have room for all tokens each and whose 16-bit segment
+    has room to grow, and in one with room for about as many tokens as sequences of the longest length would have: the kernel
+    finds the same counts by length, hence, with fixed shares, the same bits."""
+    from paper_2605_02262_amd import binding as W
+    from tests import wq_harness as H
+    rng = np.random.default_rng(11)
+    specs = [synth.SeqSpec(100, 32, 32, 40, (20, 40, 40))] + [synth.SeqSpec(n, 32, 32, 33, (n // 3, n // 3, n - 2 * (n // 3))) for n in range(2, 40, 3)]
+    w = synth.Workload("roomy", synth.BF16, synth.BF16, 8, 2, hd, group, 64, 1.0, specs, 9700, pin_first=0)
+    bt = synth.batch(w, with_embeddings=False)
+    sc = rng.standard_normal(int(bt.t.win_off[-1])).astype(np.float32)
+    total, longest = int(bt.t.kv_off[-1]), int(np.diff(bt.t.kv_off).max())
+    q, ctx = H.to_dev(bt.q, w.dtype), W.Context(W.workspace_bytes(w.B, w.Hq, hd, 64))
+    tight, off16 = H.capacities(w)
+    got = []
+    spare = w.B * longest - sum(tight) - int(off16[-1])
+    for cap, off in ((tight, off16), ([total] * 3, off16 + 1500 * np.arange(w.B + 1)), (tight, off16 + spare // w.B * np.arange(w.B + 1))):
+        run = H.run_gpu(bt, cap=cap, off16=off.astype(np.int32), splits=1, with_scores=False, scores_override=sc)
+        got.append(W.wq_decode_attention(ctx, q, run.pk, 0.1, 0, longest, W.DECODE_BY_LENGTH | W.DECODE_FIXED_SHARES))
+    even = W.wq_decode_attention(ctx, q, run.pk, 0.1, 0, longest, W.DECODE_FIXED_SHARES)
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2]) and not torch.equal(got[0], even)
+    assert ctx.device_status() == 0

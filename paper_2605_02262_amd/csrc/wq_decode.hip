@@ -513,10 +513,11 @@ static bool packs_by_length(int B, const wq_packed_kv* kv, int64_t max_seq_token
 // trip of the merge pays from about 900 blocks in the longest sequence.
 int wq_decode_pick_splits(const void* q, int q_dtype, int B, const wq_packed_kv* kv, int64_t max_seq_tokens, int plain_splits, int algo)
 {
-    // the same count where the caller has the merge done by a second kernel (which then knows no counts by length): the two
-    // merges give the same bits
-    const bool by_length = (algo & WQ_DECODE_BY_LENGTH) != 0 && !(algo & WQ_DECODE_SEPARATE_MERGE);
-    if (!merges_itself(q, q_dtype, B, kv, algo & ~WQ_DECODE_SEPARATE_MERGE) || max_seq_tokens <= 0 || (by_length && B > 64)) return 0;
+    // the same count where the caller has the merge done by a second kernel or left out (there are no counts by length then):
+    // the two merges give the same bits, and a launch without its merge does the same work
+    constexpr int NO_MERGE = WQ_DECODE_SEPARATE_MERGE | WQ_DECODE_PARTIALS_ONLY;
+    const bool by_length = (algo & WQ_DECODE_BY_LENGTH) != 0 && !(algo & NO_MERGE);
+    if (!merges_itself(q, q_dtype, B, kv, algo & ~NO_MERGE) || max_seq_tokens <= 0 || (by_length && B > 64)) return 0;
     // what a workspace for plain_splits has room for (wq_decode_ws_bytes), and no more where there is more: the same call then
     // cuts its work alike, and gives the same bits, whatever the workspace
     const int most = plain_splits + 32 < WQ_MAX_FUSED_SPLITS ? plain_splits + 32 : WQ_MAX_FUSED_SPLITS;

@@ -56,7 +56,8 @@ def test_by_length_takes_effect_where_capacities_exceed_contents(hd, group):
 
 @pytest.mark.parametrize("B,n,group", [(1, 12800, 64), (9, 4000, 64), (1, 12800, 32), (3, 700, 128)])
 def test_both_merges_take_the_same_count(B, n, group):
-    """The merge inside the kernel and the second kernel's: the same bits under fixed shares, automatic counts included."""
+    """The merge inside the kernel and the second kernel's: the same bits under fixed shares, automatic counts included.  A launch
+    without any merge leaves the same partials."""
     from paper_2605_02262_amd import binding as W
     Hkv, hd = 4, 128
     gen = torch.Generator(device="cuda").manual_seed(6)
@@ -65,8 +66,12 @@ def test_both_merges_take_the_same_count(B, n, group):
     cache.v16.copy_(torch.randn(n * B, Hkv, hd, generator=gen, device="cuda"))
     cache.len16.copy_(n - torch.arange(B, dtype=torch.int32) * 31)
     q = torch.randn(B, 28, hd, generator=gen, device="cuda").to(torch.bfloat16)
-    ctx = W.Context(W.workspace_bytes(B, 28, hd, W.auto_splits(B, Hkv, n)))
+    ctx = W.Context(W.workspace_bytes(B, 28, hd, W.auto_splits(B, Hkv, n)))          # (zero)
     inside = W.wq_decode_attention(ctx, q, cache, 0.088, 0, n, W.DECODE_FIXED_SHARES)
     for flags in (W.DECODE_SEPARATE_MERGE, W.DECODE_SEPARATE_MERGE | W.DECODE_BY_LENGTH):
+        partials = ctx.ws[16384:].clone()
         assert torch.equal(W.wq_decode_attention(ctx, q, cache, 0.088, 0, n, W.DECODE_FIXED_SHARES | flags), inside)
+        ctx.ws[16384:].zero_()
+        W.wq_decode_attention(ctx, q, cache, 0.088, 0, n, W.DECODE_FIXED_SHARES | W.DECODE_PARTIALS_ONLY)
+        assert torch.equal(ctx.ws[16384:], partials)
     assert ctx.device_status() == 0

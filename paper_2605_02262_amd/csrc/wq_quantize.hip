@@ -675,7 +675,8 @@ __device__ __forceinline__ void dense_copy(int64_t r0, int B, int pieces, const 
 }
 
 // workgroup 0: the tables; then the 16-bit rows (rows16 workgroups), then the blocks of the classes that are in use, numbered
-// without gaps (the capacities can be far larger: every class then has room for all tokens)
+// without gaps (the capacities can be far larger: every class then has room for all tokens), but never more of them than the
+// class has room for, whatever its table says
 template <int HD, bool BF>
 __global__ __launch_bounds__(256) void k_dequantize(int B, wq_packed_kv src, wq_packed_kv dst, unsigned rows16, uint32_t* __restrict__ status)
 {
@@ -691,7 +692,8 @@ __global__ __launch_bounds__(256) void k_dequantize(int B, wq_packed_kv src, wq_
     }
     w -= rows16;
     const unsigned Hkv = (unsigned)src.Hkv;
-    const unsigned n0 = (unsigned)src.cls_off[0][B] / 32u * Hkv, n1 = (unsigned)src.cls_off[1][B] / 32u * Hkv, n2 = (unsigned)src.cls_off[2][B] / 32u * Hkv;
+    auto blocks = [&](int c) { return (unsigned)(max((int64_t)0, min((int64_t)src.cls_off[c][B], src.cap[c])) / 32) * Hkv; };
+    const unsigned n0 = blocks(0), n1 = blocks(1), n2 = blocks(2);
     if (w < n0)
         dequantize_block<HD, 2, BF>(sm, (int)(w / Hkv), (int)(w % Hkv), B, src, dst);
     else if (w - n0 < n1)

@@ -39,3 +39,23 @@ def test_every_value_is_rounded_once(hd, g, dtype):
             want = torch.from_numpy(want.astype(np.float32)).to(got.dtype)
             assert torch.equal(got[a:a + n].cpu().view(torch.int16), want.view(torch.int16)), b
             assert bool((got[a + n:int(off[b + 1])] == 7.0).all()), b
+
+
+def test_blocks_stay_within_the_capacities():
+    """A cache whose last offsets say more than the classes have room for: every block is still looked for inside its class, and
+    what lies past a sequence's length is left out, so the result is that of the right offsets."""
+    from paper_2605_02262_amd import binding as W
+    from tests import wq_harness as H
+    bt = _custom(977, 128, 64, 3, 2, synth.BF16, [synth.SeqSpec(40, 16, 16, 9, (10, 14, 16)), synth.SeqSpec(9, 21, 21, 13, (2, 3, 4))], pin=0)
+    run = H.run_gpu(bt)
+    rows = [0] + np.cumsum(np.diff(bt.t.kv_off)).tolist()
+    got = []
+    for beyond in (0, 1 << 20):
+        for c in range(3):
+            run.pk.cls_off[c][-1] = (beyond + run.pk.cap[c]) if beyond else run.pk.cls_off[c][-1]
+        dense = W.PackedKV(bt.w.B, bt.w.Hkv, 128, 64, run.pk.dtype16, [0, 0, 0], rows)
+        W.wq_dequantize(run.ctx, run.pk, dense)
+        got.append(dense)
+    assert run.ctx.device_status() == 0
+    assert got[0].k16.abs().sum() > 0 and torch.equal(got[0].k16, got[1].k16) and torch.equal(got[0].v16, got[1].v16)
+    assert torch.equal(got[0].len16, got[1].len16)

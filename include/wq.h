@@ -82,7 +82,7 @@ typedef enum { WQ_DECODE_AUTO = 0, WQ_DECODE_GENERIC = 1, WQ_DECODE_MFMA = 2 } w
 /* or-ed into algo, for batches whose sequences differ a lot in length: a sequence uses ceil(num_splits * tokens /
  * max_seq_tokens) of the launch's splits (at least one; the workgroups beyond them return at once); with num_splits = 0
  * the kernel gives every sequence (of at most 64) splits in proportion to what its blocks cost, whatever the cache's capacities
- * (about 1 us of the launch, which sequences of equal lengths do not repay).  Needs max_seq_tokens > 0: the length of the longest
+ * (1 to 2 us of the launch, which sequences of equal lengths do not repay).  Needs max_seq_tokens > 0: the length of the longest
  * sequence (a value below it only makes more sequences use all splits).  Has an effect only where the matrix-core kernel merges its splits
  * itself (the launches that can also append); elsewhere every sequence uses all splits.                              */
 #define WQ_DECODE_BY_LENGTH 0x400

@@ -329,7 +329,7 @@ static int check_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, 
     const int picked = automatic ? wq_decode_pick_splits(q, q_dtype, B, kv, max_seq_tokens, *num_splits, algo) : 0;
     if (picked > 0) {
         *num_splits = picked;
-        *longest = by_length ? -1 : 0;      // (the kernel finds the counts, if it merges the splits)
+        *longest = by_length && B > 1 ? -max_seq_tokens : 0;      // (the kernel finds the counts, if it merges the splits)
     }
     return WQ_OK;
 }

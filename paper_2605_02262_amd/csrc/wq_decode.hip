@@ -41,6 +41,7 @@ struct DecodeArgs {
     float len_scale;        // > 0: a (sequence, KV head) with n tokens uses ceil(n * len_scale) of the launch's splits (at least one)
     int packed_grid;        // splits by length, workgroups with work numbered without gaps (place_by_length)
     int slots;              // ... > 0: automatic, at most this many splits of all sequences together
+    int even_splits;        // ... and what a sequence gets where the kernel finds all of them equally long
 #ifdef WQ_TIMELINE
     long long* dbg;
 #endif
@@ -508,15 +509,16 @@ static bool packs_by_length(int B, const wq_packed_kv* kv, int64_t max_seq_token
 // Splits of an automatic call (0: the launch would not merge them itself, the caller decides).  Under WQ_DECODE_BY_LENGTH the
 // kernel finds every sequence's count (place_by_length) and this is the most that one can get.  The caller's flag alone
 // decides that: the capacities say what the classes have room for, not what they hold (where thresholds decide, every class
-// has room for all tokens; a cache in use has room to grow).  Even sequences lose 0.9 us by it, uneven ones gain far more (20 that
-// fill 0.49 of the longest one's length: 40.2 us with even counts, 29.5 so; 32 that fill 0.52: 78.6 and 57.4).  A second round
-// trip of the merge pays from about 900 blocks in the longest sequence.
+// has room for all tokens; a cache in use has room to grow).  Even sequences lose 1 to 2 us by it (8 x 12800: 17.0 us, 18.7
+// with the flag), uneven ones gain far more (20 that fill 0.49 of the longest one's length: 40.2 us with even counts, 29.5 so;
+// 32 that fill 0.52: 78.6 and 57.4); one sequence has nothing to differ from.  A second round trip of the merge pays from
+// about 900 blocks in the longest sequence.
 int wq_decode_pick_splits(const void* q, int q_dtype, int B, const wq_packed_kv* kv, int64_t max_seq_tokens, int plain_splits, int algo)
 {
     // the same count where the caller has the merge done by a second kernel or left out (there are no counts by length then):
     // the two merges give the same bits, and a launch without its merge does the same work
     constexpr int NO_MERGE = WQ_DECODE_SEPARATE_MERGE | WQ_DECODE_PARTIALS_ONLY;
-    const bool by_length = (algo & WQ_DECODE_BY_LENGTH) != 0 && !(algo & NO_MERGE);
+    const bool by_length = (algo & WQ_DECODE_BY_LENGTH) != 0 && !(algo & NO_MERGE) && B > 1;
     if (!merges_itself(q, q_dtype, B, kv, algo & ~NO_MERGE) || max_seq_tokens <= 0 || (by_length && B > 64)) return 0;
     // what a workspace for plain_splits has room for (wq_decode_ws_bytes), and no more where there is more: the same call then
     // cuts its work alike, and gives the same bits, whatever the workspace
@@ -591,6 +593,9 @@ int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, con
     // that rounding to whole splits leaves few of them with little to do; else 512
     const int auto_wgs = (int64_t)B * kv->Hkv <= 128 ? 256 : 512;
     a.slots = a.packed_grid && longest_tokens < 0 ? auto_wgs / kv->Hkv : 0;
+    // (sequences that turn out to be even get the count of a call without the flag: 40 x 3200 tokens, 4 KV heads, are 480
+    // workgroups with the whole quotient 3, 28.8 us, and 160 so, 23.7 us; 22.4 without the flag)
+    a.even_splits = a.slots > 0 ? splits_for_rounds(B, kv, -longest_tokens, a.splits < a.slots / B ? a.splits : a.slots / B) : 0;
 #ifdef WQ_TIMELINE
     a.dbg = getenv("WQ_TIMELINE") ? reinterpret_cast<long long*>(ctx->ws + ctx->ws_bytes - (8 << 20)) : nullptr;
 #endif

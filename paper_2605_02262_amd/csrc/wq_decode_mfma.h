@@ -873,9 +873,7 @@ __device__ __forceinline__ Place place_by_length(const DecodeArgs& a, Smem& sm, 
         auto splits_of = [&](float tau) { return mine ? max(1, min(a.splits, (int)ceilf(fmaf(cost, __builtin_amdgcn_rcpf(tau), -0.002f)))) : 0; };
         float lo = total / (float)a.slots;
         float hi = fmaxf(lo, a.slots > a.B ? fminf(total / (float)(a.slots - a.B), most) : most);
-        // (even after all: the whole quotient for everyone, no search, 0.3 us)
-        const bool even = total >= 0.97f * most * (float)a.B;
-        if (even) hi = fmaxf(most * __builtin_amdgcn_rcpf(fmaxf(1.0f, floorf((float)a.slots * __builtin_amdgcn_rcpf((float)a.B) + 0.001f))), lo);
+        const bool even = total >= 0.97f * most * (float)a.B;      // (no search then, 0.3 us)
 #pragma unroll 1
         for (int k = even ? 3 : 0; k < 3; k++) {
             const float mid = 0.5f * (lo + hi);
@@ -883,7 +881,7 @@ __device__ __forceinline__ Place place_by_length(const DecodeArgs& a, Smem& sm, 
             lo = fits ? lo : mid;
             hi = fits ? mid : hi;
         }
-        S = splits_of(hi);
+        S = !even ? splits_of(hi) : mine ? a.even_splits : 0;
     }
     const int n = mine ? S * a.kv.Hkv : 0;
     int upto = scan_step<0x111, 0xF>(n);                 // row_shr:1, 2, 4, 8, then the rows before

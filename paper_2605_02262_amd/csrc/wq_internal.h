@@ -125,7 +125,7 @@ int wq_launch_append(wq_ctx* ctx, const void* k_new, const void* v_new, int dtyp
 int wq_launch_dequantize(wq_ctx* ctx, int B, const wq_packed_kv* src, const wq_packed_kv* dst);
 int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, const wq_packed_kv* kv, float sm_scale,
                      int num_splits, int algo, float* out, float* lse, const void* k_new = nullptr, const void* v_new = nullptr,
-                     int64_t longest_tokens = 0);      // longest_tokens: 0 the same splits for all sequences, > 0 by length, < 0 by length, found by the kernel
+                     int64_t longest_tokens = 0);      // longest_tokens: 0 the same splits for all sequences, > 0 by length, < 0 by length, found by the kernel (the longest one's length in both)
 int wq_decode_pick_splits(const void* q, int q_dtype, int B, const wq_packed_kv* kv, int64_t max_seq_tokens, int plain_splits, int algo);
 bool wq_decode_can_append(const void* q, int q_dtype, int B, int Hq, const wq_packed_kv* kv, int num_splits, int algo, const void* k_new,
                           const void* v_new, int new_dtype);

@@ -75,3 +75,27 @@ def test_both_merges_take_the_same_count(B, n, group):
         W.wq_decode_attention(ctx, q, cache, 0.088, 0, n, W.DECODE_FIXED_SHARES | W.DECODE_PARTIALS_ONLY)
         assert torch.equal(ctx.ws[16384:], partials)
     assert ctx.device_status() == 0
+
+
+@pytest.mark.parametrize("B,n,Hkv,group", [(1, 1600, 4, 64), (8, 12800, 4, 64), (40, 3200, 4, 64), (40, 3200, 4, 128), (64, 700, 1, 64)])
+def test_even_sequences_get_the_plain_count_by_length_too(B, n, Hkv, group):
+    """The flag for lengths on sequences that are equally long: the count of the call without it, hence the same bits under fixed
+    shares; a step in one call included."""
+    from paper_2605_02262_amd import binding as W
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    cache = W.PackedKV(B, Hkv, 128, group, torch.bfloat16, [0, 0, 0], [(n + 4) * b for b in range(B + 1)])
+    cache.k16.copy_(torch.randn((n + 4) * B, Hkv, 128, generator=gen, device="cuda"))
+    cache.v16.copy_(torch.randn((n + 4) * B, Hkv, 128, generator=gen, device="cuda"))
+    cache.len16.fill_(n)
+    q = torch.randn(B, 7 * Hkv, 128, generator=gen, device="cuda").to(torch.bfloat16)
+    kn = torch.randn(B, Hkv, 128, generator=gen, device="cuda").to(torch.bfloat16)
+    ctx = W.Context(W.workspace_bytes(B, 7 * Hkv, 128, W.auto_splits(B, Hkv, n + 4)))
+    got = []
+    for flags in (W.DECODE_FIXED_SHARES, W.DECODE_FIXED_SHARES | W.DECODE_BY_LENGTH):
+        cache.len16.fill_(n)
+        got.append((W.wq_decode_attention(ctx, q, cache, 0.088, 0, n + 4, flags),
+                    W.wq_decode_append_attention(ctx, q, cache, kn, kn, 0.088, 0, n + 4, flags)))
+        assert cache.len16.tolist() == [n + 1] * B
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    assert ctx.device_status() == 0

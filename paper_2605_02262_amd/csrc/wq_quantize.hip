@@ -7,7 +7,7 @@
 //               perm (the window reorder is fused into the load), finds each group's min/max with
 //               wavefront shuffles, computes codes with the exact fp32 sequence of the format definition,
 //               stages them in LDS and writes the K tile / V block / metadata images with coalesced stores
-//               The remaining workgroups copy one row each of the 16-bit windows, video tail and text -> k16/v16
+//               The remaining workgroups copy eight rows each of the 16-bit windows, video tail and text -> k16/v16
 // HBM-bound: reads 2 x 2 bytes per (K,V) element pair once, writes b/8 + 4/group bytes per element.
 // This file is compiled with floating-point contraction off: the code sequence must round exactly as stated.
 #include <type_traits>
@@ -334,7 +334,7 @@ __device__ __forceinline__ void quantize_block(QuantSmem<HD>& sm, int blk, int k
 
 // rows r0 .. r0 + ROWS16 - 1 of all 16-bit rows of the batch, 8 elements (one store of 16 bytes) per thread at a time.  A
 // workgroup per row, an element per thread, took 150 us where the whole cache stays in 16 bits (8 x 12800 tokens, 4 KV heads
-// of 128, bf16), this way 82.
+// of 128, bf16), this way 84.
 constexpr int ROWS16 = 8;
 template <typename T>
 __device__ __forceinline__ void copy16_rows(int64_t r0, const T* __restrict__ K, const T* __restrict__ V, int B, int pieces,
@@ -365,34 +365,39 @@ __device__ __forceinline__ void copy16_rows(int64_t r0, const T* __restrict__ K,
         s_dst[threadIdx.x] = ((int64_t)pk.off16[b] + i) * pieces;
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < rows * pieces; e += 256) {
-        const int row = e / pieces, piece = e - row * pieces;
-        const int64_t from = s_src[row] + piece, to = s_dst[row] + piece;
+    // (a test of every store's address, in the loop, kept a piece's two loads from being sent together: 83.5 us -> 87.8)
+    auto copy = [&](auto aligned) {
+        for (int e = threadIdx.x; e < rows * pieces; e += 256) {
+            const int row = e / pieces, piece = e - row * pieces;
+            const int64_t from = s_src[row] + piece, to = s_dst[row] + piece;
 #pragma unroll
-        for (int plane = 0; plane < 2; plane++) {
-            const T* const src = (plane ? V : K) + from * 8;
-            uint16_t* const dst = static_cast<uint16_t*>(plane ? pk.v16 : pk.k16) + to * 8;
-            uint4 row;
-            if constexpr (std::is_same_v<T, float>) {          // fp32 -> fp16 (nearest even)
-                float x[8];
-                wq_ld8(src, x);
-                uint32_t o[4];
+            for (int plane = 0; plane < 2; plane++) {
+                const T* const src = (plane ? V : K) + from * 8;
+                uint16_t* const dst = static_cast<uint16_t*>(plane ? pk.v16 : pk.k16) + to * 8;
+                uint4 x;
+                if constexpr (std::is_same_v<T, float>) {      // fp32 -> fp16 (nearest even)
+                    float f[8];
+                    wq_ld8(src, f);
+                    uint32_t o[4];
 #pragma unroll
-                for (int k = 0; k < 4; k++)
-                    o[k] = (uint32_t)__half_as_ushort(__float2half_rn(x[2 * k])) | (uint32_t)__half_as_ushort(__float2half_rn(x[2 * k + 1])) << 16;
-                row = make_uint4(o[0], o[1], o[2], o[3]);
-            } else {
-                row = *reinterpret_cast<const uint4*>(src);
-            }
-            if (reinterpret_cast<uintptr_t>(dst) % 16 == 0) {
-                *reinterpret_cast<uint4*>(dst) = row;
-            } else {                                           // (a segment that does not begin on a 16-byte boundary)
-                const uint32_t w[4] = {row.x, row.y, row.z, row.w};
+                    for (int k = 0; k < 4; k++)
+                        o[k] = (uint32_t)__half_as_ushort(__float2half_rn(f[2 * k])) | (uint32_t)__half_as_ushort(__float2half_rn(f[2 * k + 1])) << 16;
+                    x = make_uint4(o[0], o[1], o[2], o[3]);
+                } else {
+                    x = *reinterpret_cast<const uint4*>(src);
+                }
+                if constexpr (decltype(aligned)::value) {
+                    *reinterpret_cast<uint4*>(dst) = x;
+                } else {
+                    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-                for (int k = 0; k < 8; k++) dst[k] = (uint16_t)(w[k >> 1] >> (16 * (k & 1)));
+                    for (int k = 0; k < 8; k++) dst[k] = (uint16_t)(w[k >> 1] >> (16 * (k & 1)));
+                }
             }
         }
-    }
+    };
+    if ((reinterpret_cast<uintptr_t>(pk.k16) | reinterpret_cast<uintptr_t>(pk.v16)) % 16 == 0) copy(std::true_type{});
+    else copy(std::false_type{});                              // (a segment that does not begin on a 16-byte boundary)
 }
 
 // The whole call after k_plan in one launch.  The blocks of the classes first (consecutive workgroups = the KV heads of one

@@ -686,11 +686,12 @@ template <int HD, bool BF>
 __global__ __launch_bounds__(256) void k_dequantize(int B, wq_packed_kv src, wq_packed_kv dst, unsigned rows16, uint32_t* __restrict__ status)
 {
     __shared__ DenseSmem<HD> sm;
-    if (blockIdx.x == 0) {
+    unsigned w = blockIdx.y * gridDim.x + blockIdx.x;
+    if (w == 0) {
         dense_plan(B, src, dst, status);
         return;
     }
-    unsigned w = blockIdx.x - 1;
+    w -= 1;
     if (w < rows16) {
         dense_copy((int64_t)w * DENSE_ROWS, B, src.Hkv * HD / 8, src, dst);
         return;
@@ -714,8 +715,11 @@ int run_dequantize(wq_ctx* ctx, int B, const wq_packed_kv* src, const wq_packed_
     const int64_t blocks = (src->cap[0] + src->cap[1] + src->cap[2]) / 32;
     const int64_t wgs = 1 + rows16 + blocks * src->Hkv;
     if (wgs > 0x7FFFFFFF) return wq_fail(ctx, WQ_ERR_UNSUPPORTED, "too many blocks for one launch");
-    hipLaunchKernelGGL((dst->dtype16 == WQ_BF16 ? k_dequantize<HD, true> : k_dequantize<HD, false>), dim3((unsigned)wgs), dim3(256), 0, ctx->stream, B,
-                       *src, *dst, (unsigned)rows16, wq_status_ptr(ctx));
+    // (a dimension of a launch ends at 2^32 threads, which class room for 2^29 tokens times KV heads reaches: the second one)
+    constexpr int64_t MAX_X = 1 << 22;
+    const dim3 grid((unsigned)(wgs < MAX_X ? wgs : MAX_X), (unsigned)((wgs + MAX_X - 1) / MAX_X));
+    hipLaunchKernelGGL((dst->dtype16 == WQ_BF16 ? k_dequantize<HD, true> : k_dequantize<HD, false>), grid, dim3(256), 0, ctx->stream, B, *src, *dst,
+                       (unsigned)rows16, wq_status_ptr(ctx));
     WQ_HIP_CHECK(ctx, hipGetLastError());
     return WQ_OK;
 }

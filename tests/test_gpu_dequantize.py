@@ -59,3 +59,26 @@ def test_blocks_stay_within_the_capacities():
     assert run.ctx.device_status() == 0
     assert got[0].k16.abs().sum() > 0 and torch.equal(got[0].k16, got[1].k16) and torch.equal(got[0].v16, got[1].v16)
     assert torch.equal(got[0].len16, got[1].len16)
+
+
+def test_class_room_beyond_a_grid_dimension():
+    """Room for 2^26 tokens of 8 KV heads (21 GB, hardly any of it in use): one workgroup each per block and head is more than
+    one dimension of a launch takes.  The rows are those of the same cache in buffers of its size."""
+    from paper_2605_02262_amd import binding as W
+    from tests import wq_harness as H
+    bt = _custom(983, 64, 64, 8, 1, synth.BF16, [synth.SeqSpec(40, 16, 16, 9, (10, 14, 16)), synth.SeqSpec(9, 21, 21, 13, (2, 3, 4))], pin=0)
+    w = bt.w
+    cap, off16 = H.capacities(w)
+    rows = [0] + np.cumsum(np.diff(bt.t.kv_off)).tolist()
+    sc = np.random.default_rng(5).standard_normal(int(bt.t.win_off[-1])).astype(np.float32)
+    got = []
+    for room in (cap[0], 1 << 26):
+        run = H.run_gpu(bt, cap=[room, cap[1], cap[2]], off16=off16, splits=2, with_scores=False, scores_override=sc)
+        dense = W.PackedKV(w.B, w.Hkv, 64, 64, run.pk.dtype16, [0, 0, 0], rows)
+        W.wq_dequantize(run.ctx, run.pk, dense)
+        assert run.ctx.device_status() == 0
+        got.append(dense)
+        del run
+    assert got[0].len16.cpu().tolist() == np.diff(rows).tolist() and got[0].k16.abs().sum() > 0
+    for name in ("k16", "v16", "len16"):
+        assert torch.equal(getattr(got[0], name), getattr(got[1], name)), name

@@ -417,7 +417,7 @@ __global__ __launch_bounds__(256) void k_quantize_all(const T* __restrict__ K, c
                                                       wq_packed_kv pk, unsigned n, unsigned n0, unsigned n1, uint32_t* __restrict__ status)
 {
     __shared__ QuantSmem<HD> sm;
-    unsigned w = blockIdx.x;
+    unsigned w = blockIdx.y * gridDim.x + blockIdx.x;
     const unsigned Hkv = (unsigned)pk.Hkv;
     if (w >= n) {
         copy16_rows<T>((int64_t)(w - n) * ROWS16, K, V, B, pk.Hkv * HD / 8, kv_off, win_size, win_off, perm, seg_windows, pre16, pk);
@@ -708,6 +708,14 @@ __global__ __launch_bounds__(256) void k_dequantize(int B, wq_packed_kv src, wq_
         dequantize_block<HD, 8, BF>(sm, (int)((w - n0 - n1) / Hkv), (int)((w - n0 - n1) % Hkv), B, src, dst);
 }
 
+// Workgroups numbered row by row.  A dimension of a launch ends at 2^32 threads without an error (2^24 workgroups: one each for
+// the blocks of 2^29 tokens times KV heads), so more than 2^22 of them go into two.
+dim3 grid_of(int64_t wgs)
+{
+    constexpr int64_t MAX_X = 1 << 22;
+    return dim3((unsigned)(wgs < MAX_X ? wgs : MAX_X), (unsigned)((wgs + MAX_X - 1) / MAX_X));
+}
+
 template <int HD>
 int run_dequantize(wq_ctx* ctx, int B, const wq_packed_kv* src, const wq_packed_kv* dst)
 {
@@ -715,11 +723,8 @@ int run_dequantize(wq_ctx* ctx, int B, const wq_packed_kv* src, const wq_packed_
     const int64_t blocks = (src->cap[0] + src->cap[1] + src->cap[2]) / 32;
     const int64_t wgs = 1 + rows16 + blocks * src->Hkv;
     if (wgs > 0x7FFFFFFF) return wq_fail(ctx, WQ_ERR_UNSUPPORTED, "too many blocks for one launch");
-    // (a dimension of a launch ends at 2^32 threads, which class room for 2^29 tokens times KV heads reaches: the second one)
-    constexpr int64_t MAX_X = 1 << 22;
-    const dim3 grid((unsigned)(wgs < MAX_X ? wgs : MAX_X), (unsigned)((wgs + MAX_X - 1) / MAX_X));
-    hipLaunchKernelGGL((dst->dtype16 == WQ_BF16 ? k_dequantize<HD, true> : k_dequantize<HD, false>), grid, dim3(256), 0, ctx->stream, B, *src, *dst,
-                       (unsigned)rows16, wq_status_ptr(ctx));
+    hipLaunchKernelGGL((dst->dtype16 == WQ_BF16 ? k_dequantize<HD, true> : k_dequantize<HD, false>), grid_of(wgs), dim3(256), 0, ctx->stream, B,
+                       *src, *dst, (unsigned)rows16, wq_status_ptr(ctx));
     WQ_HIP_CHECK(ctx, hipGetLastError());
     return WQ_OK;
 }
@@ -743,7 +748,7 @@ int run(wq_ctx* ctx, const void* K_, const void* V_, int B, const int32_t* kv_of
     const int64_t wgs16 = (rows16 + ROWS16 - 1) / ROWS16;
     if (n + wgs16 > 0x7FFFFFFF) return wq_fail(ctx, WQ_ERR_UNSUPPORTED, "too many blocks for one launch");
     if (n + wgs16 > 0)
-        hipLaunchKernelGGL((k_quantize_all<T, HD>), dim3((unsigned)(n + wgs16)), dim3(256), 0, st, K, V, B, pk->group, kv_off, win_size,
+        hipLaunchKernelGGL((k_quantize_all<T, HD>), grid_of(n + wgs16), dim3(256), 0, st, K, V, B, pk->group, kv_off, win_size,
                            win_off, perm, seg_windows, pre16, *pk, (unsigned)n, n0, n1, wq_status_ptr(ctx));
     if (B > 0) hipLaunchKernelGGL(k_v_scale_max, dim3((unsigned)B * WQ_VS_PARTS), dim3(256), 0, st, B, *pk);
     WQ_HIP_CHECK(ctx, hipGetLastError());

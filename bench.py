@@ -266,8 +266,8 @@ def main():
             cap[c] += (n * s.win_size + 31) // 32 * 32
         n16.append((n_top if w.top_bits == 16 else 0) * s.win_size + (s.n_vis - s.n_win * s.win_size) + s.n_text + 64)
     off16 = np.concatenate([[0], np.cumsum(n16)]).astype(np.int32)
-    # sequences of very different lengths (workload 4): splits by length, the library's count for them; nsplit is the count
-    # the decode calls end up with, for the workspace and the report
+    # sequences of very different lengths (workload 4): splits by length; nsplit is the count that the workspace is sized
+    # for (the library's own choice of the splits stays within such a workspace)
     plain = W.auto_splits(B, w.Hkv, max_tok)
     ragged = W.auto_splits_ragged(B, w.Hkv, max_tok, sum(cap) + int(off16[-1]))
     by_length = W.DECODE_BY_LENGTH if (ragged > plain and not args.splits) else 0
@@ -369,7 +369,7 @@ def main():
     if args.decode_only:
         alg_bytes = copies[0].bytes_algorithmic()
         print(json.dumps({"workload": w.name, "mix_8_4": args.mix or "config", "frames_per_sequence": w.seqs[0].frames,
-                          "tokens_per_sequence": max_tok, "splits": nsplit, "bytes": alg_bytes,
+                          "tokens_per_sequence": max_tok, "splits": args.splits or "automatic", "bytes": alg_bytes,
                           "decode_us": {k: round(v, 2) for k, v in dstat.items()},
                           "decode_us_graph_replay": {k: round(v, 2) for k, v in gstat.items()}, "kernel_without_merge_us": {k: round(v, 2) for k, v in kstat.items()},
                           "GBs": round(alg_bytes / dec_us / 1e3, 1), "pct_hbm_peak": round(100 * alg_bytes / dec_us / 1e3 / HBM_PEAK_GBS, 1),
@@ -447,7 +447,7 @@ def main():
         "config": {"workload": w.name, "B": B, "Hq": w.Hq, "Hkv": w.Hkv, "head_dim": w.hd, "group": w.group,
                    "visual_tokens_per_seq": w.seqs[0].n_vis, "text_tokens_per_seq": w.seqs[0].n_text,
                    "window": w.seqs[0].win_size, "bit_mix_windows_8_4_2": list(map(int, w.seqs[0].quota)),
-                   "splits": nsplit, "splits_by_length": bool(by_length), "kv_copies_rotated": N_COPIES, "calls_per_stage_timing": n},
+                   "splits": args.splits or "automatic", "splits_by_length": bool(by_length), "kv_copies_rotated": N_COPIES, "calls_per_stage_timing": n},
         "decode_us_per_step": round(dec_us, 2),
         "decode_us": {k: (round(v, 2) if isinstance(v, float) else v) for k, v in dstat.items()},
         "decode_us_graph_replay": {k: (round(v, 2) if isinstance(v, float) else v) for k, v in gstat.items()},

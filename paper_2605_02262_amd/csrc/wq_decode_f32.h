@@ -21,13 +21,13 @@
 //
 // Between them the four quarters' parts are added up and every lane group gets its own tokens, in registers (tokens_of_group).
 //
-// Bound by instruction issue: a 32-token block takes 4 HD matrix instructions (9.6 cycles each) and about as much again on the
+// Bound by instruction issue: a 32-token block takes 2 HD matrix instructions (9.6 cycles each) and about as much again on the
 // vector unit, and neither overlaps the other to speak of, not even between the two wavefronts of a SIMD.  Codes are therefore
 // converted by the dequantizing instruction itself: masked in place, a code is the f16 subnormal code * 2^(shift - 24), which
 // a mixed-precision fused multiply-add takes as it is; the power of two is put into the scale (keys) or into the minimum and
 // the weight (values), where it changes no rounding.  A workgroup's 32-token block takes 0.49 us with heads of 128, 0.29 with
 // heads of 64 (0.60 and 0.32 in the 16-bit segment); 8 x 12795 tokens, 28 / 4 heads of 128, group 32: 917 us a call on the
-// vector kernel.  A wavefront's blocks are a fixed share of its workgroup's range, so that a split count fixes every bit of
+// vector kernel, 34.0 here.  A wavefront's blocks are a fixed share of its workgroup's range, so that a split count fixes every bit of
 // the result, as it does in the vector kernel.
 #pragma once
 

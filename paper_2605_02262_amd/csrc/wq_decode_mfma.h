@@ -828,8 +828,9 @@ __device__ __forceinline__ void finish_append(const DecodeArgs& a, int b, int kv
 // workgroups of a (sequence, KV head) at a fixed distance, as launches for equal lengths have them, the long sequences'
 // workgroups can all fall on the same XCDs; those without work also took compute units from the others).
 // How many splits S_b a sequence gets: in a launch with a given count ceil(tokens * len_scale); in an automatic one
-// ceil(cost / tau) for the smallest cost per workgroup tau that needs no more workgroups than the launch has
-// (slots * Hkv), found by bisection between the mean (no rounding at all) and what is certain to fit.
+// ceil(cost / tau) for a cost per workgroup tau that needs no more workgroups than the launch has (slots * Hkv): three
+// halvings between the mean (no rounding at all) and what is certain to fit, of which the end that fits is taken (not
+// the smallest such tau, but at most an eighth of the interval above it); or even_splits each where the costs are equal to 3 %.
 // Every wavefront of the launch computes the same from the same tables.
 struct Place {
     int b, kvh, split, S;     // (b < 0: nothing to do)

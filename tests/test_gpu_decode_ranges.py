@@ -1,6 +1,6 @@
 """Decode attention where a workgroup has few blocks, and where the arrival counters change their spacing (needs an MI355X).
 
-One group per head: the kernel then keeps fp32 accuracy (2^-15 of a vector's largest entry, see test_gpu_decode_groups), so a
+One group per head: the kernel then computes in fp32 (2^-15 of a vector's largest entry, see test_gpu_decode_groups), so a
 block that is left out, taken twice or merged too early shows."""
 import numpy as np
 import pytest

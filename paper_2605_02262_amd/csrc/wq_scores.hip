@@ -180,28 +180,32 @@ __global__ __launch_bounds__(256) void k_window_mean(const float* __restrict__ t
 
 // ---- pairwise path on the matrix cores --------------------------------------------------------------------------
 // The similarity equation taken literally: C = E_v E_t^T (every window token against every text token), then
-// c_k = 1/(N |w_k|) sum_j C[k,j] / |t_j|.  A tile is 128 (112, 96) visual rows of one sequence; its text tokens are
-// walked in passes of up to 512 columns, so that the visual rows are read from memory once when the sequence has at
-// most 512 text tokens.  One workgroup of eight wavefronts per compute unit takes a contiguous share of the launch's
-// tiles.  Over D it goes in steps of 128 elements (two 128-byte lines per row):
-//   visual rows   memory -> LDS directly (buffer loads with the LDS bit, two steps ahead, three buffers, one barrier per
-//                 step) -> A operands of all wavefronts, read two product groups ahead of their use;
-//   text rows     each wavefront owns 64 columns of the pass, so its B operands are private to it.  An operand is
-//                 16 rows x 16 bytes per lane group: read from the row-major text that is 64 scattered pieces per
-//                 load, which the memory pipeline takes one lane at a time.  k_pack_text therefore rewrites the text
-//                 once (a few MB) into operand order, [tile of 16 rows][32 elements of D][lane][8 elements], so that
-//                 a wavefront's operand is one contiguous KB; it goes from there (L2) straight into registers, a
-//                 whole step ahead.
-// A wavefront multiplies a [16 RT] x 64 tile per step with v_mfma_f32_16x16x32 bf16/f16 (RT = 8 row tiles: 128
-// accumulator registers, two wavefronts per SIMD).  Sequences with at most 256 (128) text tokens use passes of 256
-// (128) columns and split the rows between wavefronts instead, RT = 4 (2).  At the end of a pass the products are
-// multiplied by 1/|t_j| and summed over the columns, so C never leaves the registers.  |w_k|^2 comes from the A
-// operands of one row tile per wavefront during the first pass.  Reductions have a fixed order: results are
-// deterministic.
-// With operands that change from product to product the matrix cores of this GPU sustain about three quarters of
-// their nominal rate (wq_probe_mfma measures it: the clock drops under the load); this kernel keeps them busy three
-// quarters of its cycles.  Variants measured and dropped because they were not faster: steps of 64 elements; text
-// operands sent for one by one, three quarters of a step ahead; the 32x32x16 form of the instruction.
+// c_k = 1/(N |w_k|) sum_j C[k,j] / |t_j|.  A tile is up to 256 visual rows of one sequence (128 where it has more than 256
+// text tokens); its text tokens are walked in passes of up to 256 (512) columns, so that the visual rows are read from memory
+// once when the sequence has at most 512 text tokens.  One workgroup of eight wavefronts per compute unit takes a contiguous
+// share of the launch's rows.  Over D it goes in steps of KS elements (64, or 128 with 128-row tiles: 32 KB of rows each):
+//   visual rows   memory -> LDS directly (buffer loads with the LDS bit, two or three steps ahead, three or four buffers, one
+//                 barrier per step) -> A operands of all wavefronts, read two product groups ahead of their use;
+//   text rows     each wavefront owns 16 CT columns of the pass (CT = 4, or 2 with up to 256 columns), so its B operands are
+//                 private to it.  An operand is 16 rows x 16 bytes per lane group: read from the row-major text that is 64
+//                 scattered pieces per load, which the memory pipeline takes one lane at a time.  k_pack_text therefore
+//                 rewrites the text once (a few MB) into operand order, [tile of 16 rows][32 elements of D][lane][8 elements],
+//                 so that a wavefront's operand is one contiguous KB; it goes from there (L2) straight into registers, 64 of
+//                 them whatever CT, 16 / CT instructions deep ahead.
+// A wavefront multiplies a [16 RT] x [16 CT] tile per step with v_mfma_f32_16x16x32 bf16/f16 (up to 128 accumulator registers,
+// two wavefronts per SIMD).  At the end of a pass the products are multiplied by 1/|t_j| and summed over the columns, so C
+// never leaves the registers.  |w_k|^2 comes from the A operands of one or two row tiles per wavefront during the first pass.
+// Reductions have a fixed order: results are deterministic.
+// What bounds it: above 256 columns the matrix cores, which sustain about three quarters of their nominal rate with operands
+// that change from product to product (wq_probe_mfma measures it: the clock drops under the load) and are kept busy three
+// quarters of the kernel's cycles.  Up to 256 columns what passes the compute unit's memory pipeline: a wavefront's loads
+// complete in order, so the text operands wait for the rows sent for before them, and have to be sent for about as far ahead.
+// 8 x 12544 rows of 3584 bf16, us per call (a read of the rows alone: 117), tiles of 128 rows x 64 columns of a wavefront ->
+// tiles of up to 256 rows x 32: 256 text tokens 264 -> 192, 128: 230 -> 159, 20: 219 -> 128; 32 x 3136 rows of 4096, 256 text
+// tokens: 430 -> 234; one sequence of 19600 rows, 200 text tokens: 63 -> 57.  (64 columns and two row groups of 128 rows: 206 at
+// 256 text tokens; every text operand is then loaded twice, and only half as far ahead.)
+// Variants measured and dropped because they were not faster: text operands sent for one by one, three quarters of a step
+// ahead; the 32x32x16 form of the instruction; each XCD or each workgroup beginning elsewhere in D.
 typedef float floatx4s __attribute__((ext_vector_type(4)));
 typedef _Float16 half8s __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8s __attribute__((ext_vector_type(8)));
@@ -238,29 +242,26 @@ __device__ __forceinline__ float sumsq8(const uint4& u)
 }
 
 constexpr int PA_THREADS = 512, PA_WAVES = 8;
-constexpr int PA_ROWS = 128;             // visual rows per workgroup
-constexpr int PA_KS = 128;               // elements of D per step (two 128-byte lines per row)
-constexpr int PA_Q = PA_KS / 32;         // quarters of a step: one matrix instruction deep each
-constexpr int PA_PITCH = PA_KS + 16;     // LDS row pitch in elements (288 bytes: rows start 32 bytes apart in the banks; measured free of bank conflicts, a pitch of 272 bytes is not)
-constexpr int PA_WCOLS = 64;             // text columns per wavefront and pass
-constexpr int PA_CT = PA_WCOLS / 16;     // column tiles per wavefront
-constexpr int PA_PCS = PA_PITCH / 8;     // 16-byte pieces per LDS row, the padding included
-constexpr int PA_DMA = (PA_ROWS * PA_PCS + 64 * PA_WAVES - 1) / (64 * PA_WAVES);   // loads to LDS per wavefront and step (64 pieces each)
+constexpr int PA_BUF = 16384;            // elements of one LDS buffer: 128 rows of 128 elements, or 256 rows of 64
+constexpr int PA_DMA = PA_BUF / 8 / (64 * PA_WAVES);   // loads to LDS per wavefront and step (64 16-byte pieces each)
 constexpr int PA_ROW_POLICY = 2;         // cache policy of the visual rows' loads: non-temporal (read once; measured 1 % fewer cycles)
-constexpr int PA_BUF = PA_WAVES * PA_DMA * 64 * 8;                                 // elements of one LDS buffer
 
 // Tiles of 16 text rows in operand order.  Sequence b's tiles start at tile txt_off[b] / 16 + b: room for
 // ceil(N_b / 16) tiles each, whatever the lengths.  Rows past N_b are zero.
 __device__ __forceinline__ int pair_tile_base(const int32_t* txt_off, int b) { return (txt_off[b] >> 4) + b; }
 
-__global__ __launch_bounds__(256) void k_pack_text(const uint16_t* __restrict__ txt, int D, int B, const int32_t* __restrict__ txt_off,
-                                                   int64_t total_tiles, uint4* __restrict__ packed)
+// A workgroup takes a tile: its wavefronts the chunks of 32 elements in turn, PT_FLIGHT of them in flight, and 1/|t_j| of its rows
+// on the way (0 for a zero row).  Bound by the latency of its loads.  (Chunk by chunk over four times the wavefronts, behind
+// a kernel of its own for the norms: 14 us of a call for 8 x 256 rows of 3584 between them, this one 8.)
+constexpr int PT_THREADS = 1024, PT_FLIGHT = 4;
+template <bool BF>
+__global__ __launch_bounds__(PT_THREADS) void k_pack_text(const uint16_t* __restrict__ txt, int D, int B, const int32_t* __restrict__ txt_off,
+                                                          uint4* __restrict__ packed, float* __restrict__ inv_norm)
 {
-    const int chunks = D / 32;
-    const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);      // (tile, chunk of 32 elements)
-    if (item >= total_tiles * chunks) return;
-    const int64_t tile = item / chunks;
-    const int c = (int)(item - tile * chunks), lane = threadIdx.x & 63, lm = lane & 15, lj = lane >> 4;
+    constexpr int WAVES = PT_THREADS / 64;
+    __shared__ float s_sum[WAVES][16];
+    const int chunks = D / 32, tile = (int)blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lm = lane & 15, lj = lane >> 4;
     // the sequence that owns this tile: the last b with pair_tile_base(b) <= tile
     int lo = 0, hi = B - 1;
     while (lo < hi) {
@@ -268,22 +269,61 @@ __global__ __launch_bounds__(256) void k_pack_text(const uint16_t* __restrict__ 
         if (pair_tile_base(txt_off, mid) <= tile) lo = mid; else hi = mid - 1;
     }
     const int n0 = txt_off[lo], N = txt_off[lo + 1] - n0;
-    const int row = (int)(tile - pair_tile_base(txt_off, lo)) * 16 + lm;
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (row < N) v = *reinterpret_cast<const uint4*>(txt + ((int64_t)n0 + row) * D + c * 32 + lj * 8);
-    packed[item * 64 + lane] = v;
+    const int row = (tile - pair_tile_base(txt_off, lo)) * 16 + lm;
+    const uint16_t* const src = txt + ((int64_t)n0 + row) * D + lj * 8;
+    uint4* const dst = packed + (int64_t)tile * chunks * 64 + lane;
+    float ss = 0.f;
+    for (int c0 = wave; c0 < chunks; c0 += WAVES * PT_FLIGHT) {
+        uint4 v[PT_FLIGHT];
+#pragma unroll
+        for (int k = 0; k < PT_FLIGHT; k++) {
+            const int c = c0 + k * WAVES;
+            v[k] = (row < N && c < chunks) ? *reinterpret_cast<const uint4*>(src + c * 32) : make_uint4(0u, 0u, 0u, 0u);
+        }
+#pragma unroll
+        for (int k = 0; k < PT_FLIGHT; k++) {
+            const int c = c0 + k * WAVES;
+            if (c < chunks) dst[c * 64] = v[k];
+            const uint32_t w[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const float x = BF ? wq_bf16_bits_to_float(w[e] & 0xFFFFu) : wq_f16_bits_to_float(w[e] & 0xFFFFu);
+                const float y = BF ? wq_bf16_bits_to_float(w[e] >> 16) : wq_f16_bits_to_float(w[e] >> 16);
+                ss = fmaf(y, y, fmaf(x, x, ss));
+            }
+        }
+    }
+    ss += __shfl_xor(ss, 16, 64);
+    ss += __shfl_xor(ss, 32, 64);
+    if (lane < 16) s_sum[wave][lane] = ss;
+    __syncthreads();
+    if (threadIdx.x < 16 && row < N) {
+        float t = 0.f;
+#pragma unroll
+        for (int w = 0; w < WAVES; w++) t += s_sum[w][lane];
+        inv_norm[n0 + row] = t > 0.f ? 1.0f / sqrtf(t) : 0.f;
+    }
 }
 
-// The three buffers of visual rows are separate arrays on purpose: the compiler then knows that a read of one cannot
+// The buffers of visual rows are separate arrays on purpose: the compiler then knows that a read of one cannot
 // see a load in flight to another, and makes a wavefront wait for exactly the loads it reads behind.
 __shared__ __attribute__((aligned(16))) uint16_t pair_a0[PA_BUF];
 __shared__ __attribute__((aligned(16))) uint16_t pair_a1[PA_BUF];
 __shared__ __attribute__((aligned(16))) uint16_t pair_a2[PA_BUF];
+__shared__ __attribute__((aligned(16))) uint16_t pair_a3[PA_BUF];
 template <int P>
 __device__ __forceinline__ uint16_t* pair_buf()
 {
-    static_assert(P >= 0 && P < 3, "three buffers");
-    return P == 0 ? pair_a0 : (P == 1 ? pair_a1 : pair_a2);
+    static_assert(P >= 0 && P < 4, "four buffers");
+    return P == 0 ? pair_a0 : (P == 1 ? pair_a1 : (P == 2 ? pair_a2 : pair_a3));
+}
+// Where 16-byte piece c of row r lies in its row of a buffer.  A wavefront's 16-byte reads go to LDS sixteen lanes at a time,
+// eight of one lane group (rows 0-3, 12-15 or 4-11 of a tile) and eight of the next (the other rows, the next piece): so
+// placed, the sixteen touch every bank once, without padding (with rows 288 bytes apart a sixth of the loads filled it).
+template <int KS>
+__device__ __forceinline__ int pair_place(int r, int c)
+{
+    return KS == 128 ? c ^ (r & 15) : c ^ ((r >> 1) & 7);
 }
 
 // x of the lane that a data-parallel-primitive control pairs this lane with (rows of 16 lanes)
@@ -315,8 +355,8 @@ __device__ __forceinline__ void pair_halve(float (&v)[32], bool upper)
 constexpr int PA_WCAP = 1024;            // text columns whose 1/|t_j| stay in LDS for a whole run
 struct PairSmem {
     float W[PA_WCAP];                    // 1/|t_j| (0 past the end): of all passes if they fit, else of the current one
-    float R[PA_WAVES][PA_ROWS];          // row sums, one array per column block
-    float N2[PA_ROWS];                   // |w_k|^2
+    float R[2048];                       // row sums, one array per column block
+    float N2[256];                       // |w_k|^2
 };
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
@@ -324,55 +364,55 @@ template <int P> struct PairBuf { static constexpr int value = P; };
 struct PairUnit { int tile, pass; };     // a row tile of the sequence x a pass of columns
 struct PairCursor { PairUnit u; int s; }; // a step of a unit
 
-// A run: `ntiles` consecutive row tiles of one sequence, from tile `tile0`, each walked in ceil(N / PASS) passes of PASS
-// text columns; a (tile, pass) is a unit of D / 128 steps.  All units of a run form one pipeline: visual rows are sent
-// for two steps ahead and text operands one step ahead, across the ends of units, so the matrix cores do not wait for
+// A run: rows [row0, row_end) of one sequence in `ntiles` tiles of `rows` rows (a multiple of 16; the last tile may have
+// fewer), each walked in ceil(N / PASS) passes of PASS
+// text columns; a (tile, pass) is a unit of D / KS steps.  All units of a run form one pipeline: visual rows are sent
+// for AL steps ahead and text operands BL steps ahead, across the ends of units, so the matrix cores do not wait for
 // memory at the start of a tile, and what a unit leaves behind (scaling by 1/|t_j|, the sum over its columns, at a
 // tile's end the scores) happens while those loads are in flight.
-// The eight wavefronts are NCB column blocks of 64 text columns x 8 / NCB row groups of RT row tiles of 16:
-// (RT, NCB) = (8, 8): 128 rows x a 512-column pass; (4, 4): two row halves x 256 columns; (2, 2): four row quarters
-// x 128 columns; (7, 8) and (6, 8): 112 and 96 rows x 512 columns, for launches whose number of 128-row tiles
-// would leave most of the chip idle in the last round.  A wavefront whose column block's number is below RT also
-// sums |w_k|^2 of the row tile of that number in its row group (read from LDS once more, a quarter at a time).
-template <bool BF, int RT, int NCB>
+// The eight wavefronts are NCB column blocks of 16 CT text columns x RG = 8 / NCB row groups of RT row tiles of 16.
+// A wavefront whose column block's number is c also
+// sums |w_k|^2 of the row tiles c, c + NCB of its row group (read from LDS once more, a quarter at a time).
+template <bool BF, int RT, int CT, int NCB, int KS>
 __device__ __forceinline__ void pair_run(PairSmem& sm, const uint16_t* __restrict__ va, const char* __restrict__ tbb,
-                                         const float* __restrict__ inv_tn, int D, int M, int N, int tile0, int ntiles, int rows,
+                                         const float* __restrict__ inv_tn, int D, int N, int row0, int row_end, int ntiles, int rows,
                                          float* __restrict__ out)
 {
-    constexpr int PASS = NCB * PA_WCOLS;                  // columns per pass
-    constexpr int DMA = (RT * (PA_WAVES / NCB) * 16 * PA_PCS + 64 * PA_WAVES - 1) / (64 * PA_WAVES);   // loads to LDS per wavefront and step
-    static_assert(DMA <= PA_DMA, "LDS buffers too small");
+    constexpr int WCOLS = CT * 16, PASS = NCB * WCOLS;    // columns per wavefront, per pass
+    constexpr int RG = PA_WAVES / NCB, OWN = (RT + NCB - 1) / NCB, CAP = RT * RG * 16;   // row groups, |w_k|^2 tiles per wavefront, most rows of a tile
+    constexpr int AHEAD = 16 / CT;                        // quarters (32 elements of D, one matrix instruction deep) that text operands are sent for ahead: 64 registers
+    constexpr int Q = KS / 32, NB = AHEAD == Q ? 3 : 4, AL = NB - 1, BL = AHEAD / Q;     // quarters per step, buffers, lead of rows and text in steps
+    constexpr int PCS = KS / 8, DMA = (CAP * PCS + 64 * PA_WAVES - 1) / (64 * PA_WAVES); // 16-byte pieces of a row, loads to LDS per wavefront and step
+    static_assert(DMA <= PA_DMA && NCB * CAP <= 2048 && CAP <= 256 && CAP * KS <= PA_BUF, "LDS arrays too small");
+    static_assert(NB % BL == 0 || BL == 1, "a step's text registers are fixed by its buffer");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lj = lane >> 4, lm = lane & 15;
     const int cb = wave % NCB, rb = (wave / NCB) * RT;
-    const int steps = D / PA_KS, ntile = (N + 15) >> 4, npass = (N + PASS - 1) / PASS;
+    const int steps = D / KS, ntile = (N + 15) >> 4, npass = (N + PASS - 1) / PASS;
 
     // visual rows: memory -> LDS without passing registers.  A load instruction fills 64 consecutive 16-byte pieces
-    // of the buffer, one per lane; piece p is column p % PA_PCS of row p / PA_PCS.  The descriptor covers the tile's
-    // rows only: rows past the sequence's end lie outside it and read as zero, as do the padding columns and the
-    // rows past the tile, whose offsets are out of any range.
+    // of the buffer, one per lane; the lane fetches the piece that belongs there.  The descriptor covers the tile's
+    // rows only: rows past its end lie outside it and read as zero.
     auto rows_of = [&](PairUnit u) {
-        const int row0 = u.tile * rows;
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(va + (int64_t)row0 * D), 0, min(rows, M - row0) * D * 2,
-                                                 0x00020000);
+        const int r0 = row0 + u.tile * rows;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(va + (int64_t)r0 * D), 0, min(rows, row_end - r0) * D * 2, 0x00020000);
     };
-    int voff[DMA];
-#pragma unroll
-    for (int t = 0; t < DMA; t++) {
-        const int p = (wave + PA_WAVES * t) * 64 + lane, r = p / PA_PCS, c = p - r * PA_PCS;
-        voff[t] = (c < PA_KS / 8 && r < rows) ? (r * D + c * 8) * 2 : (int)0x80000000;
-    }
-    auto send_rows = [&](auto P, __amdgpu_buffer_rsrc_t tile_rows, int byte0) {     // 256 bytes of every row, from byte0 -> buffer P
+    constexpr int RSTEP = 64 * PA_WAVES / PCS;            // rows from one load of a wavefront to its next (a multiple of 16: the same places)
+    static_assert(RSTEP % 16 == 0, "pair_place repeats");
+    const int pr = (wave * 64 + lane) / PCS, voff = (pr * D + pair_place<KS>(pr, lane % PCS) * 8) * 2;
+    auto send_rows = [&](auto P, __amdgpu_buffer_rsrc_t tile_rows, int byte0) {     // 2 KS bytes of every row, from byte0 -> buffer P
         uint16_t* const dst = pair_buf<decltype(P)::value>();
+        int v = voff;
+        asm volatile("" : "+v"(v));                       // (the other loads' offsets: computed here, not kept)
 #pragma unroll
         for (int t = 0; t < DMA; t++)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(tile_rows, (lds_ptr_t)(dst + (wave + PA_WAVES * t) * 512), 16, voff[t], byte0, 0,
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(tile_rows, (lds_ptr_t)(dst + (wave + PA_WAVES * t) * 512), 16, v + t * (RSTEP * D * 2), byte0, 0,
                                                      PA_ROW_POLICY);
     };
-    // byte offset of this lane's operand piece in a row tile's first quarter: of the wavefront's first tile (the
-    // tiles follow each other by 16 rows), and of the tile whose |w_k|^2 it sums
-    constexpr int TILE_BYTES = 16 * PA_PITCH * 2;
-    const int ro = ((rb * 16 + lm) * PA_PITCH + lj * 8) * 2, ro_own = ro + (cb < RT ? cb : 0) * TILE_BYTES;
+    // byte offset of this lane's operand piece: of the wavefront's first tile (the tiles follow each other by 16 rows),
+    // first quarter; a quarter further its place changes by an exclusive or (pair_place)
+    constexpr int TILE_BYTES = 16 * KS * 2;
+    const int ro = (rb * 16 + lm) * KS * 2 + pair_place<KS>(lm, lj) * 16;
     // A read from the buffer that this wavefront has sent loads for: the compiler puts the wait for those loads in
     // front of it (loads land in the order sent), whatever else it has moved around them.
     auto peek = [&](auto P) {
@@ -382,19 +422,19 @@ __device__ __forceinline__ void pair_run(PairSmem& sm, const uint16_t* __restric
     auto use = [&](uint32_t x) { asm volatile("" ::"v"(x)); };
     // the wavefront's column tiles of a pass in the packed text (tiles past the end re-read the last one: their
     // weights are zero); a lane's 16 bytes of operand c of a tile sit at 1024 c + 16 lane
-    auto text_of = [&](PairUnit u, const char* (&t)[PA_CT]) {
+    auto text_of = [&](PairUnit u, const char* (&t)[CT]) {
 #pragma unroll
-        for (int k = 0; k < PA_CT; k++)
-            t[k] = tbb + (int64_t)min((u.pass * PASS + cb * PA_WCOLS) / 16 + k, ntile - 1) * (D / 32) * 1024;
+        for (int k = 0; k < CT; k++)
+            t[k] = tbb + (int64_t)min((u.pass * PASS + cb * WCOLS) / 16 + k, ntile - 1) * (D / 32) * 1024;
     };
-    auto load_b = [&](const char* const (&t)[PA_CT], int c, uint4 (&gb)[PA_CT]) {      // elements 32 c .. 32 c + 31 of D
+    auto load_b = [&](const char* const (&t)[CT], int c, uint4 (&gb)[CT]) {      // elements 32 c .. 32 c + 31 of D
         const uint32_t off = (uint32_t)(c * 1024) + (uint32_t)lane * 16u;
 #pragma unroll
-        for (int k = 0; k < PA_CT; k++) gb[k] = *reinterpret_cast<const uint4*>(t[k] + off);
+        for (int k = 0; k < CT; k++) gb[k] = *reinterpret_cast<const uint4*>(t[k] + off);
     };
     auto after = [&](PairUnit u) {                        // the unit after u; the run's last unit is followed by itself
         if (++u.pass == npass) { u.pass = 0; ++u.tile; }
-        if (u.tile == tile0 + ntiles) { u.tile = tile0 + ntiles - 1; u.pass = npass - 1; }
+        if (u.tile == ntiles) { u.tile = ntiles - 1; u.pass = npass - 1; }
         return u;
     };
     // 1/|t_j| in LDS: all passes' at once if they fit, else pass by pass (the slow way: behind a barrier at a unit's end)
@@ -403,8 +443,8 @@ __device__ __forceinline__ void pair_run(PairSmem& sm, const uint16_t* __restric
         for (int k = threadIdx.x; k < n; k += PA_THREADS) sm.W[k] = col0 + k < N ? inv_tn[col0 + k] : 0.f;
     };
 
-    // Three cursors walk the run's steps: (uc, s) the step whose products are being summed; cb_, one step ahead, the
-    // step whose text operands are sent for (tc: its unit's text); ca, two steps ahead, the step whose visual rows are
+    // Three cursors walk the run's steps: (uc, s) the step whose products are being summed; cb_, BL steps ahead, the
+    // step whose text operands are sent for (tc: its unit's text); ca, AL steps ahead, the step whose visual rows are
     // sent for (dc: its tile's rows).  Past the run's end they stay in its last unit.
     auto advance = [&](PairCursor& c) {                   // true when it has entered another unit
         if (++c.s < steps) return false;
@@ -412,36 +452,48 @@ __device__ __forceinline__ void pair_run(PairSmem& sm, const uint16_t* __restric
         c.u = after(c.u);
         return true;
     };
-    PairUnit uc{tile0, 0};
+    PairUnit uc{0, 0};
     PairCursor cb_{uc, 0}, ca{uc, 0};
     __amdgpu_buffer_rsrc_t dc = rows_of(uc);
-    const char* tc[PA_CT];
+    const char* tc[CT];
     text_of(uc, tc);
-    floatx4s acc[RT][PA_CT];
+    floatx4s acc[RT][CT];
 #pragma unroll
     for (int i = 0; i < RT; i++)
 #pragma unroll
-        for (int k = 0; k < PA_CT; k++) acc[i][k] = floatx4s{0.f, 0.f, 0.f, 0.f};
-    float nsq = 0.f;
+        for (int k = 0; k < CT; k++) acc[i][k] = floatx4s{0.f, 0.f, 0.f, 0.f};
+    float nsq[OWN];
+#pragma unroll
+    for (int o = 0; o < OWN; o++) nsq[o] = 0.f;
     int s = 0;
 
     __syncthreads();                                      // whoever used the buffers before is done with them
     stage_weights(0, w_all ? npass * PASS : PASS);
     __syncthreads();
-    // gq[q]: B operands of quarter q of a step, sent for a whole step ahead (replaced one by one during the following
-    // quarter, three quarters ahead, they cost 8 % more cycles: the text does not always come from the nearest cache)
-    uint4 gq[PA_Q][PA_CT];
-    send_rows(PairBuf<0>{}, dc, 0);
-    if (advance(ca)) dc = rows_of(ca.u);
-    send_rows(PairBuf<1>{}, dc, ca.s * (PA_KS * 2));
-    if (advance(ca)) dc = rows_of(ca.u);
+    // gq: B operands of AHEAD quarters
+    uint4 gq[AHEAD][CT];
+    // the first loads in the order of the steps: otherwise the waits of the loop's first steps are those of the way into it
+    auto load_step = [&](auto slot) {                     // the text operands of the step at cb_
 #pragma unroll
-    for (int q = 0; q < PA_Q; q++) load_b(tc, q, gq[q]);
-    if (advance(cb_)) text_of(cb_.u, tc);
+        for (int q = 0; q < Q; q++) load_b(tc, Q * cb_.s + q, gq[decltype(slot)::value * Q + q]);
+        if (advance(cb_)) text_of(cb_.u, tc);
+    };
+    auto before = [&](auto V) {                           // what step V - LEAD would send for
+        constexpr int LEAD = AL > BL ? AL : BL, r = decltype(V)::value - LEAD + AL, t = decltype(V)::value - LEAD + BL;
+        if constexpr (r >= 0 && r < AL) {
+            send_rows(PairBuf<(r < NB ? r : 0)>{}, dc, ca.s * (KS * 2));
+            if (advance(ca)) dc = rows_of(ca.u);
+        }
+        if constexpr (t >= 0 && t < BL) load_step(PairBuf<t>{});
+    };
+    before(PairBuf<0>{});
+    before(PairBuf<1>{});
+    before(PairBuf<2>{});
+    before(PairBuf<3>{});
     use(peek(PairBuf<0>{}));
 
     // What a unit leaves behind.  The lane holds, of its i-th row tile, rows 4 lj + e at column lm of column tile k.
-    // Scale by 1/|t_j| and sum over the wavefront's 64 columns: over k in the lane, over lm across the 16 lanes of a
+    // Scale by 1/|t_j| and sum over the wavefront's columns: over k in the lane, over lm across the 16 lanes of a
     // row in four stages of pairwise exchanges, each of which halves the number of values a lane carries (the
     // partners are lm ^ 8, lm ^ 7, lm ^ 2, lm ^ 1; the stages split on bits 3, 2, 1, 0 of lm).
     // (Both work from a copy of the thread's number that the compiler cannot trace: what they derive from it is then
@@ -450,69 +502,75 @@ __device__ __forceinline__ void pair_run(PairSmem& sm, const uint16_t* __restric
         int t = tid;
         asm volatile("" : "+v"(t));
         const int lm = t & 15, lj = (t >> 4) & 3;
-        float wk[PA_CT];
+        float wk[CT];
 #pragma unroll
-        for (int k = 0; k < PA_CT; k++) wk[k] = sm.W[(w_all ? uc.pass * PASS : 0) + cb * PA_WCOLS + k * 16 + lm];
-        float v[32];
+        for (int k = 0; k < CT; k++) wk[k] = sm.W[(w_all ? uc.pass * PASS : 0) + cb * WCOLS + k * 16 + lm];
 #pragma unroll
-        for (int i = 0; i < RT; i++)
+        for (int i0 = 0; i0 < RT; i0 += 8) {              // eight row tiles at a time
+            constexpr int MOST = RT < 8 ? RT : 8;
+            float v[32];
 #pragma unroll
-            for (int e = 0; e < 4; e++) {
-                float x = 0.f;
+            for (int i = 0; i < MOST; i++)
 #pragma unroll
-                for (int k = 0; k < PA_CT; k++) x = fmaf(acc[i][k][e], wk[k], x);
-                v[i * 4 + e] = x;
-            }
+                for (int e = 0; e < 4; e++) {
+                    float x = 0.f;
 #pragma unroll
-        for (int i = 0; i < RT; i++)
+                    for (int k = 0; k < CT; k++) x = i0 + i < RT ? fmaf(acc[i0 + i < RT ? i0 + i : 0][k][e], wk[k], x) : 0.f;
+                    v[i * 4 + e] = x;
+                }
+            constexpr int NV = MOST > 4 ? 32 : MOST > 2 ? 16 : MOST * 4;      // a power of two
 #pragma unroll
-            for (int k = 0; k < PA_CT; k++) acc[i][k] = floatx4s{0.f, 0.f, 0.f, 0.f};
-        constexpr int NV = RT > 4 ? 32 : RT * 4;            // a power of two
+            for (int j = MOST * 4; j < NV; j++) v[j] = 0.f;
+            pair_halve<0x128, NV>(v, (lm & 8) != 0);                    // row_ror:8
+            pair_halve<0x141, NV / 2>(v, (lm & 4) != 0);                // row_half_mirror
+            pair_halve<0x4E, (NV >= 4 ? NV / 4 : 1)>(v, (lm & 2) != 0); // quad_perm [2,3,0,1]
+            pair_halve<0xB1, (NV >= 8 ? NV / 8 : 1)>(v, (lm & 1) != 0); // quad_perm [1,0,3,2]
+            // what is left: values j0 .. j0 + KEEP - 1 of the NV (j = 4 i + e), j0 made of the bits of lm that split a
+            // stage; a stage that did not split left the sum in both lanes, the lower one writes
+            constexpr int KEEP = NV >= 16 ? NV / 16 : 1;
+            int j0 = 0;
+            bool writer = true;
+            if constexpr (NV >= 2) j0 += (lm & 8) ? NV / 2 : 0;
+            if constexpr (NV >= 4) j0 += (lm & 4) ? NV / 4 : 0;
+            if constexpr (NV >= 8) j0 += (lm & 2) ? NV / 8 : 0; else writer = writer && !(lm & 2);
+            if constexpr (NV >= 16) j0 += (lm & 1) ? NV / 16 : 0; else writer = writer && !(lm & 1);
+            if (writer) {
 #pragma unroll
-        for (int j = RT * 4; j < NV; j++) v[j] = 0.f;
-        pair_halve<0x128, NV>(v, (lm & 8) != 0);                    // row_ror:8
-        pair_halve<0x141, NV / 2>(v, (lm & 4) != 0);                // row_half_mirror
-        pair_halve<0x4E, (NV >= 4 ? NV / 4 : 1)>(v, (lm & 2) != 0); // quad_perm [2,3,0,1]
-        pair_halve<0xB1, (NV >= 8 ? NV / 8 : 1)>(v, (lm & 1) != 0); // quad_perm [1,0,3,2]
-        // what is left: values j0 .. j0 + KEEP - 1 of the NV (j = 4 i + e), j0 made of the bits of lm that split a
-        // stage; a stage that did not split left the sum in both lanes, the lower one writes
-        constexpr int KEEP = NV >= 16 ? NV / 16 : 1;
-        int j0 = 0;
-        bool writer = true;
-        if constexpr (NV >= 2) j0 += (lm & 8) ? NV / 2 : 0;
-        if constexpr (NV >= 4) j0 += (lm & 4) ? NV / 4 : 0;
-        if constexpr (NV >= 8) j0 += (lm & 2) ? NV / 8 : 0; else writer = writer && !(lm & 2);
-        if constexpr (NV >= 16) j0 += (lm & 1) ? NV / 16 : 0; else writer = writer && !(lm & 1);
-        if (writer) {
-#pragma unroll
-            for (int r = 0; r < KEEP; r++) {
-                const int j = j0 + r, tile = rb + (j >> 2);
-                if ((j >> 2) < RT) sm.R[cb][tile * 16 + 4 * lj + (j & 3)] += v[r];    // one writer per (column block, row)
+                for (int r = 0; r < KEEP; r++) {
+                    const int j = j0 + r, i = i0 + (j >> 2);
+                    if (i < RT) sm.R[cb * CAP + (rb + i) * 16 + 4 * lj + (j & 3)] += v[r];    // one writer per (column block, row)
+                }
             }
         }
+#pragma unroll
+        for (int i = 0; i < RT; i++)
+#pragma unroll
+            for (int k = 0; k < CT; k++) acc[i][k] = floatx4s{0.f, 0.f, 0.f, 0.f};
     };
-    // A tile's last unit is done: its scores.  |w_k|^2: a wavefront summed row tile number `wave` (in every tiling the
-    // first tile it walks; with seven or six tiles the last wavefronts summed nothing and write zeros to rows that do
-    // not exist); its lane (lm, lj) holds the sum over the pieces lj, lj + 4, ... of row lm.
+    // A tile's last unit is done: its scores.  |w_k|^2: lane (lm, lj) of a wavefront holds, for each of its own row tiles,
+    // the sum over the pieces lj, lj + 4, ... of row lm.
     auto tile_done = [&](int tile) {
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
         const int lane = tid & 63;
-        nsq += __shfl_xor(nsq, 16, 64);
-        nsq += __shfl_xor(nsq, 32, 64);
-        if (lane < 16) sm.N2[wave * 16 + lane] = nsq;
-        nsq = 0.f;
+#pragma unroll
+        for (int o = 0; o < OWN; o++) {
+            nsq[o] += __shfl_xor(nsq[o], 16, 64);
+            nsq[o] += __shfl_xor(nsq[o], 32, 64);
+            if (lane < 16 && cb + NCB * o < RT) sm.N2[(rb + cb + NCB * o) * 16 + lane] = nsq[o];
+            nsq[o] = 0.f;
+        }
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // (no fence: loads for the next unit are in flight)
-        const int row = tile * rows + tid;
-        if (tid < PA_ROWS) {
+        const int row = row0 + tile * rows + tid;
+        if (tid < CAP) {
             float r = 0.f;
 #pragma unroll
-            for (int c = 0; c < PA_WAVES; c++) {
-                r += sm.R[c][tid];
-                sm.R[c][tid] = 0.f;                       // for the next tile; the barriers of its steps come before its sums
+            for (int c = 0; c < NCB; c++) {
+                r += sm.R[c * CAP + tid];
+                sm.R[c * CAP + tid] = 0.f;                // for the next tile; the barriers of its steps come before its sums
             }
             const float nn = sm.N2[tid];
-            if (tid < rows && row < M) out[row] = nn > 0.f ? r / (sqrtf(nn) * (float)N) : 0.f;
+            if (tid < rows && row < row_end) out[row] = nn > 0.f ? r / (sqrtf(nn) * (float)N) : 0.f;
         }
     };
 
@@ -520,33 +578,44 @@ __device__ __forceinline__ void pair_run(PairSmem& sm, const uint16_t* __restric
     // branches: it stays one block, which keeps the wait counts of the loads in flight exact.
     auto step = [&](auto P) {
         using Cur = decltype(P);
-        using Nxt = PairBuf<(Cur::value + 1) % 3>;
-        using Far = PairBuf<(Cur::value + 2) % 3>;
+        using Nxt = PairBuf<(Cur::value + 1) % NB>;
+        using Far = PairBuf<(Cur::value + AL) % NB>;
+        constexpr int G0 = (Cur::value % BL) * Q;         // the step's first quarter in gq
         // every wavefront's rows of this step have landed (each waited for its own before it came here), and all are
-        // done reading the buffer of the step before, which takes the rows two steps ahead.  No fence: a fence would
+        // done reading the buffer of the step before, which takes the rows AL steps ahead.  No fence: a fence would
         // wait for the B operands in flight.
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        send_rows(Far{}, dc, ca.s * (PA_KS * 2));
-        const float count = (uc.pass == 0 && cb < RT) ? 1.f : 0.f;   // |w_k|^2 is summed during the first pass, by the tile's owner (a factor, not a branch)
+        send_rows(Far{}, dc, ca.s * (KS * 2));
+        const float count = uc.pass == 0 ? 1.f : 0.f;     // |w_k|^2 is summed during the first pass (a factor, not a branch)
         const char* const sa = reinterpret_cast<const char*>(pair_buf<Cur::value>());
-        // PA_Q RT groups of PA_CT products: row tile i, quarter q; the A operand is read from LDS two groups
+        int r1 = ro;
+        asm volatile("" : "+v"(r1));                      // (the quarters' and buffers' addresses: computed here, not kept)
+        auto place = [&](int q) { return r1 ^ (q * 64); };
+        // Q RT groups of CT products: row tile i, quarter q; the A operand is read from LDS two groups
         // ahead.  A quarter's B operands are replaced as soon as their last product has issued.
-        auto read_a = [&](int g) { return *reinterpret_cast<const uint4*>(sa + ro + (g % RT) * TILE_BYTES + (g / RT) * 64); };
-        uint4 f[3], own;
+        auto read_a = [&](int g) { return *reinterpret_cast<const uint4*>(sa + place(g / RT) + (g % RT) * TILE_BYTES); };
+        uint4 f[3], own[OWN];
         uint32_t landed = 0u;
         f[0] = read_a(0);
         f[1] = read_a(1);
 #pragma unroll
-        for (int g = 0; g < PA_Q * RT; g++) {
+        for (int g = 0; g < Q * RT; g++) {
             const int i = g % RT, q = g / RT;
-            if (g + 2 < PA_Q * RT) f[(g + 2) % 3] = read_a(g + 2);
-            if (i == 0) own = *reinterpret_cast<const uint4*>(sa + ro_own + q * 64);
-            if (g == PA_Q * RT - 2) landed = peek(Nxt{});             // waits for the next step's rows, as late as it can
-            if (i == RT - 1) nsq = fmaf(sumsq8<BF>(own), count, nsq);
+            if (g + 2 < Q * RT) f[(g + 2) % 3] = read_a(g + 2);
+            if (i == 0) {
 #pragma unroll
-            for (int k = 0; k < PA_CT; k++) acc[i][k] = mfma_s<BF>(f[g % 3], gq[q][k], acc[i][k]);
-            if (i == RT - 1) load_b(tc, PA_Q * cb_.s + q, gq[q]);
+                for (int o = 0; o < OWN; o++)             // (a wavefront without such a tile reads its first one: nothing is made of it)
+                    own[o] = *reinterpret_cast<const uint4*>(sa + place(q) + (cb + NCB * o < RT ? cb + NCB * o : 0) * TILE_BYTES);
+            }
+            if (g == Q * RT - 2) landed = peek(Nxt{});                // waits for the next step's rows, as late as it can
+            if (i == RT - 1) {
+#pragma unroll
+                for (int o = 0; o < OWN; o++) nsq[o] = fmaf(sumsq8<BF>(own[o]), count, nsq[o]);
+            }
+#pragma unroll
+            for (int k = 0; k < CT; k++) acc[i][k] = mfma_s<BF>(f[g % 3], gq[G0 + q][k], acc[i][k]);
+            if (i == RT - 1) load_b(tc, Q * cb_.s + q, gq[G0 + q]);
             __builtin_amdgcn_sched_barrier(0);            // issue order as written: one LDS read, then the group's products
         }
         use(landed);
@@ -568,63 +637,88 @@ __device__ __forceinline__ void pair_run(PairSmem& sm, const uint16_t* __restric
     };
     const int total = ntiles * npass * steps;
     int gs = 0;
-    for (; gs + 2 < total; gs += 3) {
+    for (; gs + NB <= total; gs += NB) {
         step(PairBuf<0>{});
         step(PairBuf<1>{});
         step(PairBuf<2>{});
+        if constexpr (NB == 4) step(PairBuf<3>{});
     }
     if (gs < total) step(PairBuf<0>{});
     if (gs + 1 < total) step(PairBuf<1>{});
+    if constexpr (NB == 4) {
+        if (gs + 2 < total) step(PairBuf<2>{});
+        use(peek(PairBuf<3>{}));
+    }
     use(peek(PairBuf<0>{}));                              // nothing of this run is in flight to LDS any more
     use(peek(PairBuf<1>{}));
     use(peek(PairBuf<2>{}));
 }
 
-// The launch's row tiles (`rows` = 128, 112 or 96 visual rows) are numbered sequence after sequence; a workgroup takes
-// a contiguous share of them and walks it as runs of tiles of one sequence.
+// What 16 rows of a sequence with N text tokens cost: reading them, up to 256 columns (the products take no longer), or the
+// products of 512 columns and more.  (Not above 32: the rows that a card's memory holds then fit 32 bits.)
+__device__ __forceinline__ uint32_t pair_cost(int N)
+{
+    return N <= 256 ? 1u : min(32u, 2u * ((uint32_t)(N + 511) / 512u));
+}
+
+// The launch's rows, sixteen at a time, are laid out sequence after sequence on an axis of their cost; a workgroup takes an
+// equal share of it and walks it as runs of rows of one sequence, a run in tiles of equal height (as few as there can be).
+// Forms: what is left of 256 columns without text halves the column blocks and doubles the row groups.  Up to 8 sixteens of
+// rows steps of 128 elements (half the barriers, and only half the LDS buffers' rows are there).  The heights above are those
+// at which a workgroup's share of a batch falls into two or three tiles; products of rows that a tile does not have are the
+// price of a height that is not listed.
 template <bool BF>
 __global__ __launch_bounds__(PA_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_pair_mfma(const uint16_t* __restrict__ vis, const uint4* __restrict__ packed_txt,
                                                           const float* __restrict__ inv_tnorm, int D, int B,
                                                           const int32_t* __restrict__ vis_off, const int32_t* __restrict__ txt_off,
-                                                          int rows, float* __restrict__ tok_score)
+                                                          float* __restrict__ tok_score)
 {
     __shared__ PairSmem sm;
     const int tid = threadIdx.x;
-    uint32_t T = 0;
-    for (int b = 0; b < B; b++) T += (uint32_t)(vis_off[b + 1] - vis_off[b] + rows - 1) / (uint32_t)rows;
-    int g = (int)((uint64_t)T * blockIdx.x / gridDim.x);
-    const int end = (int)((uint64_t)T * (blockIdx.x + 1) / gridDim.x);
-    if (g >= end) return;
-    for (int k = tid; k < PA_WAVES * PA_ROWS; k += PA_THREADS) sm.R[k / PA_ROWS][k % PA_ROWS] = 0.f;     // (a run starts with a barrier)
-    int b = 0, first = 0;                                 // first: number of sequence b's first tile
-    while (g < end) {
-        int Tb = (vis_off[b + 1] - vis_off[b] + rows - 1) / rows;
-        while (g >= first + Tb) {
-            first += Tb;
-            ++b;
-            Tb = (vis_off[b + 1] - vis_off[b] + rows - 1) / rows;
-        }
-        const int n = min(end, first + Tb) - g, tile0 = g - first;
-        const int m0 = vis_off[b], M = vis_off[b + 1] - m0;
+    auto tiles_of = [&](int b) { return (uint32_t)(vis_off[b + 1] - vis_off[b] + 15) >> 4; };
+    uint32_t total = 0;
+    for (int b = 0; b < B; b++) total += tiles_of(b) * pair_cost(txt_off[b + 1] - txt_off[b]);
+    // neighbouring shares on one XCD (workgroups go to the eight in turn): each then reads one or two sequences' text through its L2
+    const uint32_t wg = gridDim.x % 8 == 0 ? blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8 : blockIdx.x;
+    const uint32_t lo = (uint32_t)((uint64_t)total * wg / gridDim.x), hi = (uint32_t)((uint64_t)total * (wg + 1) / gridDim.x);
+    for (int k = tid; k < 2048; k += PA_THREADS) sm.R[k] = 0.f;     // (a run starts with a barrier)
+    uint32_t at = 0;                                      // cost of the sequences before b
+    for (int b = 0; b < B && at < hi; b++) {
         const int n0 = txt_off[b], N = txt_off[b + 1] - n0;
+        const uint32_t T = tiles_of(b), cost = pair_cost(N), begin = at;
+        at += T * cost;
+        if (at <= lo) continue;
+        auto edge = [&](uint32_t x) { return x <= begin ? 0 : (int)min(T, (x - begin + cost - 1) / cost); };
+        const int t0 = edge(lo), t1 = edge(hi);
+        if (t0 >= t1) continue;
+        const int m0 = vis_off[b], M = vis_off[b + 1] - m0, row0 = t0 * 16, row_end = min(M, t1 * 16);
         const uint16_t* va = vis + (int64_t)m0 * D;
         const char* tb = reinterpret_cast<const char*>(packed_txt) + (int64_t)pair_tile_base(txt_off, b) * (D / 32) * 1024;
         float* out = tok_score + m0;
+        const int most = N > 256 ? 8 : 16, n = (t1 - t0 + most - 1) / most, h = (t1 - t0 + n - 1) / n, rows = h * 16;     // tiles, their height
+#define WQ_PAIR(RT, CT, NCB, KS) pair_run<BF, RT, CT, NCB, KS>(sm, va, tb, inv_tnorm + n0, D, N, row0, row_end, n, rows, out)
         if (N <= 0) {
-            for (int r = tile0 * rows + tid; r < min(M, (tile0 + n) * rows); r += PA_THREADS) out[r] = 0.f;
-        } else if (N > 4 * PA_WCOLS) {
-            if (rows == 128)
-                pair_run<BF, 8, 8>(sm, va, tb, inv_tnorm + n0, D, M, N, tile0, n, rows, out);
-            else if (rows == 112)
-                pair_run<BF, 7, 8>(sm, va, tb, inv_tnorm + n0, D, M, N, tile0, n, rows, out);
-            else
-                pair_run<BF, 6, 8>(sm, va, tb, inv_tnorm + n0, D, M, N, tile0, n, rows, out);
-        } else if (N > 2 * PA_WCOLS) {                    // (fewer rows than 128: the last row tiles are empty)
-            pair_run<BF, 4, 4>(sm, va, tb, inv_tnorm + n0, D, M, N, tile0, n, rows, out);
+            for (int r = row0 + tid; r < row_end; r += PA_THREADS) out[r] = 0.f;
+        } else if (N > 256) {
+            if (h == 8) WQ_PAIR(8, 4, 8, 128);
+            else if (h == 7) WQ_PAIR(7, 4, 8, 128);
+            else WQ_PAIR(6, 4, 8, 128);
+        } else if (N > 128) {
+            if (h > 14) WQ_PAIR(16, 2, 8, 64);
+            else if (h > 13) WQ_PAIR(14, 2, 8, 64);
+            else if (h > 12) WQ_PAIR(13, 2, 8, 64);
+            else if (h > 10) WQ_PAIR(12, 2, 8, 64);
+            else if (h > 8) WQ_PAIR(10, 2, 8, 64);
+            else if (h > 4) WQ_PAIR(8, 2, 8, 128);
+            else WQ_PAIR(4, 2, 8, 128);
+        } else if (N > 64) {
+            WQ_PAIR(8, 2, 4, 64);
+        } else if (N > 32) {
+            WQ_PAIR(4, 2, 2, 64);
         } else {
-            pair_run<BF, 2, 2>(sm, va, tb, inv_tnorm + n0, D, M, N, tile0, n, rows, out);
+            WQ_PAIR(2, 2, 1, 64);
         }
-        g += n;
+#undef WQ_PAIR
     }
 }
 
@@ -690,19 +784,9 @@ int wq_launch_scores(wq_ctx* ctx, const void* vis, const void* txt, int dtype, i
         hipStream_t st = ctx->stream;
         const uint16_t* v16 = static_cast<const uint16_t*>(vis);
         const uint16_t* t16 = static_cast<const uint16_t*>(txt);
-        if (total_txt > 0) {
-            if (dtype == WQ_BF16)
-                hipLaunchKernelGGL((k_text_norm<__hip_bfloat16, true>), dim3((unsigned)((total_txt + 3) / 4)), dim3(256), 0, st,
-                                   static_cast<const __hip_bfloat16*>(txt), D, total_txt, inv_norm);
-            else
-                hipLaunchKernelGGL((k_text_norm<__half, true>), dim3((unsigned)((total_txt + 3) / 4)), dim3(256), 0, st,
-                                   static_cast<const __half*>(txt), D, total_txt, inv_norm);
-        }
         if (total_vis > 0) {
-            const int64_t items = tiles * (D / 32);
-            hipLaunchKernelGGL(k_pack_text, dim3((unsigned)((items + 3) / 4)), dim3(256), 0, st, t16, D, B, txt_off, tiles, packed);
-            // rows per workgroup: a workgroup occupies a compute unit, so the launch runs in rounds of as many
-            // workgroups as the chip has compute units; take the size whose rounds cover the fewest rows in all
+            hipLaunchKernelGGL((dtype == WQ_BF16 ? k_pack_text<true> : k_pack_text<false>), dim3((unsigned)tiles), dim3(PT_THREADS), 0, st, t16, D, B,
+                               txt_off, packed, inv_norm);
             static int cus = 0;
             if (cus <= 0) {
                 int dev = 0;
@@ -710,19 +794,13 @@ int wq_launch_scores(wq_ctx* ctx, const void* vis, const void* txt, int dtype, i
                     hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
                     cus = 256;
             }
-            int rows = PA_ROWS;
-            int64_t best = 0;
-            for (int r = PA_ROWS; r >= 96; r -= 16) {
-                const int64_t wgs = (total_vis + r - 1) / r, cost = ((wgs + cus - 1) / cus) * r;
-                if (r == PA_ROWS || cost < best) { best = cost; rows = r; }
-            }
-            // one workgroup per compute unit, or fewer if there are fewer tiles (a sequence has at most one partial tile)
-            const int64_t tiles_most = (total_vis + rows - 1) / rows + B;
+            // one workgroup per compute unit, or fewer if there are fewer tiles of 16 rows (a sequence has at most one partial one)
+            const int64_t tiles_most = (total_vis + 15) / 16 + B;
             const dim3 grid((unsigned)(tiles_most < cus ? tiles_most : cus));
             if (dtype == WQ_BF16)
-                hipLaunchKernelGGL(k_pair_mfma<true>, grid, dim3(PA_THREADS), 0, st, v16, packed, inv_norm, D, B, vis_off, txt_off, rows, tok_score);
+                hipLaunchKernelGGL(k_pair_mfma<true>, grid, dim3(PA_THREADS), 0, st, v16, packed, inv_norm, D, B, vis_off, txt_off, tok_score);
             else
-                hipLaunchKernelGGL(k_pair_mfma<false>, grid, dim3(PA_THREADS), 0, st, v16, packed, inv_norm, D, B, vis_off, txt_off, rows, tok_score);
+                hipLaunchKernelGGL(k_pair_mfma<false>, grid, dim3(PA_THREADS), 0, st, v16, packed, inv_norm, D, B, vis_off, txt_off, tok_score);
         }
         hipLaunchKernelGGL(k_window_mean, dim3((unsigned)((total_win + 3) / 4)), dim3(256), 0, st, tok_score, B, vis_off, txt_off,
                            win_size, win_off, total_win, scores);

@@ -1,0 +1,40 @@
+"""The pairwise scoring kernel's forms (text columns x height of a workgroup's row tiles), each at its edges."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _exact(vis, txt, n_vis, n_txt, window):
+    """Mean cosine per window in float64 (by linearity: against the mean unit text vector)."""
+    out, v0, t0 = [], 0, 0
+    for m, n in zip(n_vis, n_txt):
+        v, t = vis[v0:v0 + m].double(), txt[t0:t0 + n].double()
+        unit = (t / t.norm(dim=1, keepdim=True)).mean(0) if n else torch.zeros(vis.shape[1], dtype=torch.float64, device=vis.device)
+        c = (v @ unit) / v.norm(dim=1)
+        out.append(c[:m // window * window].view(-1, window).mean(1))
+        v0, t0 = v0 + m, t0 + n
+    return torch.cat(out)
+
+
+@pytest.mark.parametrize("dtype,dim", [(torch.bfloat16, 128), (torch.float16, 384)])
+@pytest.mark.parametrize("text", [1, 32, 33, 64, 65, 128, 129, 256, 257])
+def test_pairwise_every_form(text, dtype, dim):
+    """One sequence beside a short one of another text length; `per` sixteens of rows for each of the 256 workgroups reach every
+    tile height (1 to 16 and one more, which takes two tiles), the odd rows at the end a partial tile of 16.  dim 128: fewer
+    steps than the loads are sent ahead; 384: three times as many.  float64 reference; fp32 sums of a few hundred terms."""
+    from paper_2605_02262_amd import binding as W
+    gen = torch.Generator(device="cuda").manual_seed(text)
+    window = 16
+    for per in ([1, 4, 5, 8, 9, 10, 12, 13, 14, 16, 17] if 128 < text <= 256 else [1, 6, 7, 8, 16, 17]):
+        n_vis, n_txt = [per * 4096 - 5, 37], [text, 300]
+        vis = torch.randn(sum(n_vis), dim, generator=gen, device="cuda").add_(0.05).to(dtype)
+        txt = torch.randn(sum(n_txt), dim, generator=gen, device="cuda").add_(0.05).to(dtype)
+        table = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")  # noqa: E731
+        n_win = [m // window for m in n_vis]
+        ctx = W.Context(W.workspace_bytes(2, 0, 0, 0, sum(n_vis), sum(n_txt), dim))
+        got = W.wq_window_scores(ctx, vis, txt, table([0, n_vis[0], sum(n_vis)]), table([0, n_txt[0], sum(n_txt)]), table([window, window]),
+                                 table([0, n_win[0], sum(n_win)]), sum(n_vis), sum(n_txt), sum(n_win), algo=W.SCORE_PAIRWISE_MFMA)
+        want = _exact(vis, txt, n_vis, n_txt, window)
+        worst = ((got.double() - want).abs() - 1e-4 * want.abs()).max().item()
+        assert worst <= 1e-7, (per, worst)

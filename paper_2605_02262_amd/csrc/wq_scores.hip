@@ -7,6 +7,7 @@
 //   k_text_mean   thread per channel            -> tbar[b][d] = 1/N sum_j t_j[d]/|t_j|
 //   k_token_score one wavefront per visual row  -> c_k = (w_k . tbar) / |w_k|    (0 for a zero row)
 //   k_window_mean one wavefront per window      -> score = 1/S sum_k c_k, fixed order
+//   k_scores_small  all of it for a short text and few rows, a workgroup per window
 // All accumulation is fp32 and every reduction has a fixed order (no atomics): results are deterministic.
 #include "wq_internal.h"
 
@@ -20,10 +21,24 @@ constexpr int WAVE = 64;
 constexpr int WQ_TS_ROWS = 2;
 #define WQ_TS_UNROLL 2
 
+// Sum over the wavefront, in every lane: lane ^ 32, ^ 16, ^ 8, ^ 4, ^ 2, ^ 1 in turn, by moves between registers (exchanging
+// through LDS takes six round trips).  Once lanes that differ in the bits above are equal, a rotation by 8, 4, 2, 1 inside a
+// row of 16 lanes brings the value of lane ^ 8, ^ 4, ^ 2, ^ 1.
+template <int CTRL>
+__device__ __forceinline__ float lanes_moved(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
+}
 __device__ __forceinline__ float wave_sum(float v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    v += lanes_moved<0x128>(v);
+    v += lanes_moved<0x124>(v);
+    v += lanes_moved<0x122>(v);
+    v += lanes_moved<0x121>(v);
     return v;
 }
 
@@ -177,6 +192,109 @@ __global__ __launch_bounds__(256) void k_window_mean(const float* __restrict__ t
     if (lane == 0) scores[w] = (S > 0 && txt_off[b + 1] > txt_off[b]) ? acc / (float)S : 0.f;
 }
 
+// A call of a few windows in one launch: a workgroup per window finds the norms and the mean of its sequence's text for itself
+// (in LDS), then its rows' scores and their mean, in the order of the four kernels above, so that the bits are theirs.
+// Launches and round trips to memory are all that such a call costs, so the text is read once, into LDS, and a wavefront's
+// first row is on its way meanwhile: 8 windows of 16 rows, 16 text tokens, 896 floats: four launches, 16 us; this one 6.
+// The limits: the text fits LDS (every workgroup reads it), and a workgroup's rows take no longer than a launch.
+constexpr int SMALL_THREADS = 1024, SMALL_TOKENS = 256, SMALL_TEXT = 128 << 10, SMALL_ROWS = 1024, SMALL_WINDOWS = 256, SMALL_DIM = 4096;
+constexpr int64_t SMALL_BYTES = 1 << 20;
+template <typename T>
+__global__ __launch_bounds__(SMALL_THREADS) void k_scores_small(const T* __restrict__ vis, const T* __restrict__ txt, int D, int B,
+                                                                const int32_t* __restrict__ vis_off, const int32_t* __restrict__ txt_off,
+                                                                const int32_t* __restrict__ win_size, const int32_t* __restrict__ win_off,
+                                                                float* __restrict__ scores)
+{
+    __shared__ float s_inv[SMALL_TOKENS], s_tok[SMALL_ROWS];
+    __shared__ __align__(16) float s_tbar[SMALL_DIM];
+    __shared__ __align__(16) T s_txt[SMALL_TEXT / sizeof(T)];
+    constexpr int WAVES = SMALL_THREADS / WAVE;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, w = (int)blockIdx.x;
+    const int b = wq_find_seq(win_off, B, w);
+    const int n0 = txt_off[b], N = txt_off[b + 1] - n0, S = win_size[b];
+    const int64_t r0 = (int64_t)vis_off[b] + (int64_t)(w - win_off[b]) * S;
+    constexpr int FIRST = 2;                              // pieces per lane of the first row that are sent for at once
+    float first[FIRST][8];
+#pragma unroll
+    for (int i = 0; i < FIRST; i++)
+        if (wave < S && lane * 8 + i * WAVE * 8 < D) wq_ld8(vis + (r0 + wave) * D + lane * 8 + i * WAVE * 8, first[i]);
+    for (int j = wave; j < N; j += WAVES) {               // (k_text_norm)
+        const T* p = txt + (int64_t)(n0 + j) * D;
+        float ss = 0.f;
+        for (int d = lane * 8; d < D; d += WAVE * 8) {
+            constexpr int W = sizeof(T) / 2;              // 16-byte words of 8 elements
+            uint4 u[W];
+#pragma unroll
+            for (int i = 0; i < W; i++) u[i] = reinterpret_cast<const uint4*>(p + d)[i];
+#pragma unroll
+            for (int i = 0; i < W; i++) reinterpret_cast<uint4*>(s_txt + j * D + d)[i] = u[i];
+            float x[8];
+            wq_ld8(reinterpret_cast<const T*>(u), x);
+#pragma unroll
+            for (int k = 0; k < 8; k++) ss = fmaf(x[k], x[k], ss);
+        }
+        ss = wave_sum(ss);
+        if (lane == 0) s_inv[j] = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
+    }
+    __syncthreads();
+    for (int d = tid; d < D; d += SMALL_THREADS) {        // (k_text_mean: 32 slices of the tokens, then their sums)
+        float s = 0.f;
+#pragma unroll 1
+        for (int t0 = 0; t0 < min(N, 32); t0 += 8) {
+            float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int j = t0; j < N; j += 32) {
+                float x[8], v[8];
+#pragma unroll
+                for (int k = 0; k < 8; k++) {
+                    const int i = min(j + k, N - 1);
+                    x[k] = wq_ld(s_txt, i * D + d);
+                    v[k] = s_inv[i];
+                }
+#pragma unroll
+                for (int k = 0; k < 8; k++) acc[k] = j + k < N ? fmaf(x[k], v[k], acc[k]) : acc[k];
+            }
+#pragma unroll
+            for (int k = 0; k < 8; k++) s += acc[k];
+        }
+        s_tbar[d] = N > 0 ? s / (float)N : 0.f;
+    }
+    __syncthreads();
+    for (int r = wave; r < S; r += WAVES) {               // (k_token_score)
+        const T* p = vis + (r0 + r) * D;
+        float ss = 0.f, dt = 0.f;
+        auto piece = [&](const float (&x)[8], int d) {
+            float t[8];
+            wq_ld8(s_tbar + d, t);
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                ss = fmaf(x[k], x[k], ss);
+                dt = fmaf(x[k], t[k], dt);
+            }
+        };
+        int d = lane * 8;
+        if (r == wave) {
+#pragma unroll
+            for (int i = 0; i < FIRST; i++, d += WAVE * 8)
+                if (d < D) piece(first[i], d);
+        }
+        for (; d < D; d += WAVE * 8) {
+            float x[8];
+            wq_ld8(p + d, x);
+            piece(x, d);
+        }
+        ss = wave_sum(ss);
+        dt = wave_sum(dt);
+        if (lane == 0) s_tok[r] = ss > 0.f ? dt / sqrtf(ss) : 0.f;
+    }
+    __syncthreads();
+    if (wave == 0) {                                      // (k_window_mean)
+        float acc = 0.f;
+        for (int k = lane; k < S; k += WAVE) acc += s_tok[k];
+        acc = wave_sum(acc);
+        if (lane == 0) scores[w] = (S > 0 && N > 0) ? acc / (float)S : 0.f;
+    }
+}
 
 // ---- pairwise path on the matrix cores --------------------------------------------------------------------------
 // The similarity equation taken literally: C = E_v E_t^T (every window token against every text token), then
@@ -736,6 +854,13 @@ int run_pooled(wq_ctx* ctx, const void* vis_, const void* txt_, int B, int D, co
     ws += wq_align256(sizeof(float) * (size_t)B * D);
     float* tok_score = reinterpret_cast<float*>(ws);
     hipStream_t st = ctx->stream;
+    if (VEC && total_txt <= SMALL_TOKENS && total_txt * D * (int64_t)sizeof(T) <= SMALL_TEXT && total_vis <= SMALL_ROWS && total_win <= SMALL_WINDOWS && total_vis <= 64 * total_win && D <= SMALL_DIM &&
+        total_vis * D * (int64_t)sizeof(T) <= SMALL_BYTES) {
+        hipLaunchKernelGGL(k_scores_small<T>, dim3((unsigned)total_win), dim3(SMALL_THREADS), 0, st, vis, txt, D, B, vis_off, txt_off, win_size,
+                           win_off, scores);
+        WQ_HIP_CHECK(ctx, hipGetLastError());
+        return WQ_OK;
+    }
     if (total_txt > 0)
         hipLaunchKernelGGL((k_text_norm<T, VEC>), dim3((unsigned)((total_txt + 3) / 4)), dim3(256), 0, st, txt, D, total_txt, inv_norm);
     hipLaunchKernelGGL((k_text_mean<T, VEC>), dim3(VEC ? (D + 63) / 64 : (D + 255) / 256, B), dim3(256), 0, st, txt, inv_norm, D, txt_off, tbar);

@@ -2,6 +2,7 @@
 //
 //   k_plan      one workgroup: per-class padded offsets / lengths of every sequence, 16-bit row counts,
 //               capacity checks (device status word)
+//   k_quantize_small  the whole call in one launch, for a few hundred workgroups
 //   k_quantize_all  one launch for the three classes and the 16-bit rows.  A class workgroup takes one
 //               (32-token destination block, KV head): gathers the source rows through
 //               perm (the window reorder is fused into the load), finds each group's min/max with
@@ -20,49 +21,62 @@ namespace {
 
 __device__ __forceinline__ int pad32(int n) { return (n + 31) & ~31; }
 
+// Class c's place for every sequence: off[B + 1], len[B]; n_of(b): its tokens.  True where something did not fit.
+template <typename Tokens>
+__device__ __forceinline__ bool plan_class(int B, int64_t cap, Tokens n_of, int32_t* off, int32_t* len)
+{
+    int64_t run = 0;
+    bool over = false;
+    off[0] = 0;
+    for (int b = 0; b < B; b++) {
+        int n = n_of(b);
+        int64_t nxt = run + pad32(n);
+        if (nxt > cap) {                // does not fit: drop the sequence's share of this class
+            over = true;
+            n = 0;
+            nxt = run;
+        }
+        len[b] = n;
+        run = nxt;
+        off[b + 1] = (int32_t)run;
+    }
+    return over;
+}
+// ... and of the 16-bit rows: len[B], and their running count pre[B + 1]; begins(b): where sequence b's begin
+template <typename Tokens, typename Begins>
+__device__ __forceinline__ bool plan_rows(int B, int64_t cap16, Tokens n_of, Begins begins, int32_t* pre, int32_t* len)
+{
+    int64_t run = 0;
+    bool over = false;
+    pre[0] = 0;
+    for (int b = 0; b < B; b++) {
+        int n = n_of(b);
+        const int at = begins(b), room = begins(b + 1) - at;
+        if (n > room || (int64_t)at + n > cap16 || at < 0) {
+            over = true;
+            n = 0;
+        }
+        len[b] = n;
+        run += n;
+        pre[b + 1] = (int32_t)run;
+    }
+    return over;
+}
+
 __global__ __launch_bounds__(256) void k_plan(int B, const int32_t* __restrict__ kv_off, const int32_t* __restrict__ win_size,
                                               const int32_t* __restrict__ win_off, const int32_t* __restrict__ seg_windows,
                                               wq_packed_kv pk, int32_t* __restrict__ pre16, uint32_t* __restrict__ status)
 {
     const int tid = threadIdx.x;
     if (tid < 3) {
-        const int c = tid;
-        int32_t* off = pk.cls_off[c];
-        int32_t* len = pk.cls_len[c];
-        int64_t run = 0;
-        bool over = false;
-        off[0] = 0;
-        for (int b = 0; b < B; b++) {
-            int n = seg_windows[4 * b + c] * win_size[b];
-            int64_t nxt = run + pad32(n);
-            if (nxt > pk.cap[c]) {          // does not fit: drop the sequence's share of this class
-                over = true;
-                n = 0;
-                nxt = run;
-            }
-            len[b] = n;
-            run = nxt;
-            off[b + 1] = (int32_t)run;
-        }
-        if (over) atomicOr(status, WQ_DEV_CLASS_OVERFLOW);
+        if (plan_class(B, pk.cap[tid], [&](int b) { return seg_windows[4 * b + tid] * win_size[b]; }, pk.cls_off[tid], pk.cls_len[tid]))
+            atomicOr(status, WQ_DEV_CLASS_OVERFLOW);
     } else if (tid == 3) {
-        int64_t run = 0;
-        bool over = false;
-        pre16[0] = 0;
-        for (int b = 0; b < B; b++) {
-            int W = win_off[b + 1] - win_off[b];
-            int rows = kv_off[b + 1] - kv_off[b];
-            int n = seg_windows[4 * b + 3] * win_size[b] + (rows - W * win_size[b]);
-            int room = pk.off16[b + 1] - pk.off16[b];
-            if (n > room || (int64_t)pk.off16[b] + n > pk.cap16 || pk.off16[b] < 0) {
-                over = true;
-                n = 0;
-            }
-            pk.len16[b] = n;
-            run += n;
-            pre16[b + 1] = (int32_t)run;
-        }
-        if (over) atomicOr(status, WQ_DEV_SEG16_OVERFLOW);
+        auto rows = [&](int b) {
+            const int W = win_off[b + 1] - win_off[b];
+            return seg_windows[4 * b + 3] * win_size[b] + (kv_off[b + 1] - kv_off[b] - W * win_size[b]);
+        };
+        if (plan_rows(B, pk.cap16, rows, [&](int b) { return pk.off16[b]; }, pre16, pk.len16)) atomicOr(status, WQ_DEV_SEG16_OVERFLOW);
     } else if (tid >= 64) {
         for (int b = tid - 64; b < B; b += 192) pk.v_scale_max[b] = 0.f;      // k_v_scale_max raises it
     }
@@ -169,28 +183,29 @@ __device__ __forceinline__ void pack16(const uint32_t (&x)[4], uint32_t (&y)[4])
     }
 }
 
-// one (32-token destination block `blk` of class BITS, KV head `kvh`)
-template <typename T, int HD, int BITS>
-__device__ __forceinline__ void quantize_block(QuantSmem<HD>& sm, int blk, int kvh, const T* __restrict__ K, const T* __restrict__ V,
+// one (32-token destination block `blk` of class BITS, KV head `kvh`); off, lens: the class's tables (cls_off, cls_len).
+// SMALL: in a launch of few workgroups, where latency counts: the values are sent for with the keys, and the block's largest
+// value scale goes through to memory, for another workgroup of the launch
+template <typename T, int HD, int BITS, bool SMALL = false>
+__device__ __forceinline__ void quantize_block(QuantSmem<HD>& sm, int blk, int kvh, const int32_t* off, const int32_t* lens,
+                                               const T* __restrict__ K, const T* __restrict__ V,
                                                int B, int group, const int32_t* __restrict__ kv_off,
                                                const int32_t* __restrict__ win_size, const int32_t* __restrict__ win_off,
                                                const int32_t* __restrict__ perm, const int32_t* __restrict__ seg_windows,
-                                               const wq_packed_kv& pk, uint32_t* __restrict__ status)
+                                               const wq_packed_kv& pk)
 {
     constexpr int C = cls_index(BITS);
     constexpr int QMAX = (1 << BITS) - 1;
     constexpr int CPT = HD / 8;                 // channels per thread: 8 threads share one token row
-    constexpr int PER_DW = 32 / BITS;           // codes per output dword
     auto& s_meta = sm.meta;
     const int tid = threadIdx.x;
     const int Hkv = pk.Hkv;
     const int G = HD / group;
-    const int32_t* off = pk.cls_off[C];
     const int64_t tok0 = (int64_t)blk * 32;
     if (tok0 >= off[B]) return;                 // unused capacity
     const int b = wq_find_seq(off, B, tok0);
     const int d0 = (int)(tok0 - off[b]);        // first destination token of the block inside the segment
-    const int len = pk.cls_len[C][b];
+    const int len = lens[b];
     const int S = win_size[b];
     int pos0 = 0;                               // windows of lower classes come first in perm
     for (int c = 0; c < C; c++) pos0 += seg_windows[4 * b + c];
@@ -206,15 +221,25 @@ __device__ __forceinline__ void quantize_block(QuantSmem<HD>& sm, int blk, int k
         src = (int64_t)kv_off[b] + (int64_t)win * S + o;
     }
     const int tpg = group / CPT;                // threads per group (2, 4 or 8; 16 when group=128, hd=64 is excluded)
+    const int64_t base = (src * Hkv + kvh) * HD + p * CPT;
+    float later[CPT];
+    if (SMALL && valid) {
+#pragma unroll
+        for (int i = 0; i < CPT; i += 8) wq_ld8(V + base + i, later + i);
+    }
 #pragma unroll
     for (int plane = 0; plane < 2; plane++) {
         const T* X = plane == 0 ? K : V;
         float x[CPT];
         float lo = INFINITY, hi = -INFINITY;
         if (valid) {
-            const int64_t base = (src * Hkv + kvh) * HD + p * CPT;
+            if (SMALL && plane == 1) {
 #pragma unroll
-            for (int i = 0; i < CPT; i += 8) wq_ld8(X + base + i, x + i);     // 16-byte pieces (rows are 16-byte aligned)
+                for (int i = 0; i < CPT; i++) x[i] = later[i];
+            } else {
+#pragma unroll
+                for (int i = 0; i < CPT; i += 8) wq_ld8(X + base + i, x + i);     // 16-byte pieces (rows are 16-byte aligned)
+            }
 #pragma unroll
             for (int i = 0; i < CPT; i++) {
                 lo = fminf(lo, x[i]);
@@ -299,7 +324,11 @@ __device__ __forceinline__ void quantize_block(QuantSmem<HD>& sm, int blk, int k
         uint32_t top = 0;
         for (int i = tid; i < 32 * G; i += 64) top = max(top, s_meta[1][i >> 5][i & 31] & 0xFFFFu);
         top = lanes_max_u16(top);
-        if (tid == 0) pk.v_scale_max[v_scale_slot(pk, B, C, blk, kvh)] = wq_f16_bits_to_float(top);
+        if (tid == 0) {
+            float* const slot = pk.v_scale_max + v_scale_slot(pk, B, C, blk, kvh);
+            if constexpr (SMALL) __hip_atomic_store(slot, wq_f16_bits_to_float(top), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else *slot = wq_f16_bits_to_float(top);
+        }
     }
 
     // ---- V plane: block of 32 tokens, field n = ((jj*16 + mm)*(HD/16) + ct)*8 + tau: LDS holds the codes in this
@@ -340,7 +369,7 @@ template <typename T>
 __device__ __forceinline__ void copy16_rows(int64_t r0, const T* __restrict__ K, const T* __restrict__ V, int B, int pieces,
                                             const int32_t* __restrict__ kv_off, const int32_t* __restrict__ win_size,
                                             const int32_t* __restrict__ win_off, const int32_t* __restrict__ perm,
-                                            const int32_t* __restrict__ seg_windows, const int32_t* __restrict__ pre16,
+                                            const int32_t* __restrict__ seg_windows, const int32_t* pre16,
                                             const wq_packed_kv& pk)
 {
     __shared__ int64_t s_src[ROWS16], s_dst[ROWS16];
@@ -428,16 +457,96 @@ __global__ __launch_bounds__(256) void k_quantize_all(const T* __restrict__ K, c
         n1 = (unsigned)pk.cls_off[1][B] / 32u * Hkv;
     }
     if (w < n0) {
-        quantize_block<T, HD, 2>(sm, (int)(w / Hkv), (int)(w % Hkv), K, V, B, group, kv_off, win_size, win_off, perm, seg_windows, pk, status);
+        quantize_block<T, HD, 2>(sm, (int)(w / Hkv), (int)(w % Hkv), pk.cls_off[0], pk.cls_len[0], K, V, B, group, kv_off, win_size, win_off, perm, seg_windows, pk);
         return;
     }
     w -= n0;
     if (w < n1) {
-        quantize_block<T, HD, 4>(sm, (int)(w / Hkv), (int)(w % Hkv), K, V, B, group, kv_off, win_size, win_off, perm, seg_windows, pk, status);
+        quantize_block<T, HD, 4>(sm, (int)(w / Hkv), (int)(w % Hkv), pk.cls_off[1], pk.cls_len[1], K, V, B, group, kv_off, win_size, win_off, perm, seg_windows, pk);
         return;
     }
     w -= n1;
-    quantize_block<T, HD, 8>(sm, (int)(w / Hkv), (int)(w % Hkv), K, V, B, group, kv_off, win_size, win_off, perm, seg_windows, pk, status);
+    quantize_block<T, HD, 8>(sm, (int)(w / Hkv), (int)(w % Hkv), pk.cls_off[2], pk.cls_len[2], K, V, B, group, kv_off, win_size, win_off, perm, seg_windows, pk);
+}
+
+// The whole call in one launch, where it is a few hundred workgroups and launches are most of what it costs (8 windows of 16
+// tokens, 2 KV heads of 64: three launches, 13 us; this one 6): every workgroup works the plan out for itself, in LDS (two
+// round trips to memory and a loop over the sequences), the first one writes it out, and the last one to finish collects the
+// sequences' largest value scales.  Workgroups report in on one counter of the workspace header (12-16 ns each, as
+// device-scope atomics on one address take), which is zero between launches: hence no more of them than compute units.
+// n: workgroups for the blocks (numbered by use), a bound on their number; the rest take ROWS16 16-bit rows each.
+constexpr int SMALL_SEQS = 16, SMALL_WGS = 256;
+template <typename T, int HD>
+__global__ __launch_bounds__(256) void k_quantize_small(const T* __restrict__ K, const T* __restrict__ V, int B, int group,
+                                                        const int32_t* __restrict__ kv_off, const int32_t* __restrict__ win_size,
+                                                        const int32_t* __restrict__ win_off, const int32_t* __restrict__ perm,
+                                                        const int32_t* __restrict__ seg_windows, wq_packed_kv pk, unsigned n,
+                                                        uint32_t* __restrict__ status, unsigned* __restrict__ arrive)
+{
+    __shared__ QuantSmem<HD> sm;
+    // the tables' own values, and the plan
+    __shared__ int32_t s_kv[SMALL_SEQS + 1], s_win[SMALL_SEQS + 1], s_size[SMALL_SEQS], s_seg[4 * SMALL_SEQS], s_begin[SMALL_SEQS + 1];
+    __shared__ int32_t s_off[3][SMALL_SEQS + 1], s_len[4][SMALL_SEQS], s_pre16[SMALL_SEQS + 1];
+    __shared__ unsigned s_top[SMALL_SEQS], s_last;
+    const int tid = threadIdx.x;
+    if (tid <= B) {
+        s_kv[tid] = kv_off[tid];
+        s_win[tid] = win_off[tid];
+    }
+    if (tid < B) s_size[tid] = win_size[tid];
+    if (tid < 4 * B) s_seg[tid] = seg_windows[tid];
+    if (tid <= B) s_begin[tid] = pk.off16[tid];
+    if (tid < SMALL_SEQS) s_top[tid] = 0u;
+    __syncthreads();
+    if (tid < 3) {
+        if (plan_class(B, pk.cap[tid], [&](int b) { return s_seg[4 * b + tid] * s_size[b]; }, s_off[tid], s_len[tid]) && blockIdx.x == 0)
+            atomicOr(status, WQ_DEV_CLASS_OVERFLOW);
+    } else if (tid == 3) {
+        auto rows = [&](int b) { return s_seg[4 * b + 3] * s_size[b] + (s_kv[b + 1] - s_kv[b] - (s_win[b + 1] - s_win[b]) * s_size[b]); };
+        if (plan_rows(B, pk.cap16, rows, [&](int b) { return s_begin[b]; }, s_pre16, s_len[3]) && blockIdx.x == 0)
+            atomicOr(status, WQ_DEV_SEG16_OVERFLOW);
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && tid <= B) {
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            pk.cls_off[c][tid] = s_off[c][tid];
+            if (tid < B) pk.cls_len[c][tid] = s_len[c][tid];
+        }
+        if (tid < B) pk.len16[tid] = s_len[3][tid];
+    }
+    const unsigned Hkv = (unsigned)pk.Hkv, n0 = (unsigned)s_off[0][B] / 32u * Hkv, n1 = (unsigned)s_off[1][B] / 32u * Hkv;
+    unsigned w = blockIdx.x;
+    if (w >= n) {
+        copy16_rows<T>((int64_t)(w - n) * ROWS16, K, V, B, pk.Hkv * HD / 8, s_kv, s_size, s_win, perm, s_seg, s_pre16, pk);
+    } else if (w < n0) {
+        quantize_block<T, HD, 2, true>(sm, (int)(w / Hkv), (int)(w % Hkv), s_off[0], s_len[0], K, V, B, group, s_kv, s_size, s_win, perm, s_seg, pk);
+    } else if ((w -= n0) < n1) {
+        quantize_block<T, HD, 4, true>(sm, (int)(w / Hkv), (int)(w % Hkv), s_off[1], s_len[1], K, V, B, group, s_kv, s_size, s_win, perm, s_seg, pk);
+    } else {
+        w -= n1;
+        quantize_block<T, HD, 8, true>(sm, (int)(w / Hkv), (int)(w % Hkv), s_off[2], s_len[2], K, V, B, group, s_kv, s_size, s_win, perm, s_seg, pk);
+    }
+    // The thread that has stored the block's value scale (device scope: past the XCD's L2) waits for the store to be
+    // acknowledged before it counts the workgroup, so whoever finds itself last reads scales that have arrived.
+    if (tid == 0) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        s_last = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1u ? 1u : 0u;
+    }
+    __syncthreads();
+    if (s_last == 0u) return;
+    if (tid == 0) __hip_atomic_store(arrive, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // for the next launch
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        const int slots = s_off[c][B] / 32 * (int)Hkv;
+        const float* const src = pk.v_scale_max + v_scale_slot(pk, B, c, 0, 0);
+        for (int i = tid; i < slots; i += 256) {
+            const float top = fmaxf(__hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), 0.f);
+            atomicMax(&s_top[wq_find_seq(s_off[c], B, (int64_t)(i / (int)Hkv) * 32)], __float_as_uint(top));
+        }
+    }
+    __syncthreads();
+    if (tid < B) pk.v_scale_max[tid] = __uint_as_float(s_top[tid]);
 }
 
 // one generated token per sequence -> the end of its 16-bit segment
@@ -736,9 +845,6 @@ int run(wq_ctx* ctx, const void* K_, const void* V_, int B, const int32_t* kv_of
     const T* K = static_cast<const T*>(K_);
     const T* V = static_cast<const T*>(V_);
     hipStream_t st = ctx->stream;
-    int32_t* pre16 = reinterpret_cast<int32_t*>(ctx->ws + WQ_WS_HEADER);
-    hipLaunchKernelGGL(k_plan, dim3(1), dim3(256), 0, st, B, kv_off, win_size, win_off, seg_windows, *pk, pre16,
-                       wq_status_ptr(ctx));
     // blocks in use: no more than the capacities hold, nor than the rows fill if every sequence's last block of every class is
     // a partial one
     const int64_t held = (pk->cap[0] + pk->cap[1] + pk->cap[2]) / 32, filled = total_rows / 32 + 3 * (int64_t)B;
@@ -747,6 +853,15 @@ int run(wq_ctx* ctx, const void* K_, const void* V_, int B, const int32_t* kv_of
     const int64_t rows16 = pk->cap16 > 0 ? (total_rows < pk->cap16 ? total_rows : pk->cap16) : 0;
     const int64_t wgs16 = (rows16 + ROWS16 - 1) / ROWS16;
     if (n + wgs16 > 0x7FFFFFFF) return wq_fail(ctx, WQ_ERR_UNSUPPORTED, "too many blocks for one launch");
+    if (B <= SMALL_SEQS && n + wgs16 <= SMALL_WGS) {
+        hipLaunchKernelGGL((k_quantize_small<T, HD>), dim3((unsigned)(n + wgs16 > 0 ? n + wgs16 : 1)), dim3(256), 0, st, K, V, B, pk->group, kv_off,
+                           win_size, win_off, perm, seg_windows, *pk, (unsigned)n, wq_status_ptr(ctx), wq_small_arrive_ptr(ctx));
+        WQ_HIP_CHECK(ctx, hipGetLastError());
+        return WQ_OK;
+    }
+    int32_t* pre16 = reinterpret_cast<int32_t*>(ctx->ws + WQ_WS_HEADER);
+    hipLaunchKernelGGL(k_plan, dim3(1), dim3(256), 0, st, B, kv_off, win_size, win_off, seg_windows, *pk, pre16,
+                       wq_status_ptr(ctx));
     if (n + wgs16 > 0)
         hipLaunchKernelGGL((k_quantize_all<T, HD>), grid_of(n + wgs16), dim3(256), 0, st, K, V, B, pk->group, kv_off, win_size,
                            win_off, perm, seg_windows, pre16, *pk, (unsigned)n, n0, n1, wq_status_ptr(ctx));

@@ -39,3 +39,45 @@ def test_scores_of_a_small_call(dim, dtype):
                                           _table(_offsets(n)), sum(r), sum(t), sum(n)))
         assert torch.equal(got[0], got[1]), (window, texts)
         assert torch.isfinite(got[0]).all() and (max(texts) == 0 or got[0].abs().max() > 0)
+
+
+@pytest.mark.parametrize("dtype,hd,group", [(torch.bfloat16, 128, 64), (torch.float16, 64, 64), (torch.float32, 128, 32)])
+@pytest.mark.parametrize("short", [False, True], ids=["fits", "overflows"])
+def test_quantizing_a_small_call(dtype, hd, group, short):
+    """16 sequences (one launch) and the same with an empty 17th (three): every class empty somewhere, partial blocks, 16-bit
+    windows, tails, and capacities that some sequences do not fit.  A context is used twice: its counter is zero again."""
+    from paper_2605_02262_amd import binding as W
+    gen = torch.Generator(device="cuda").manual_seed(hd + group)
+    heads, win = 2, [5, 16, 32, 33, 1, 7, 16, 3, 40, 2, 31, 16, 9, 4, 8, 6]
+    seg = [[(b + c) % 3 if b != 5 else 0 for c in range(4)] for b in range(16)]
+    n_win = [sum(s) for s in seg]
+    rows = [n * w + b % 4 for b, (n, w) in enumerate(zip(n_win, win))]
+    K = torch.randn(sum(rows), heads, hd, generator=gen, device="cuda").to(dtype)
+    V = torch.randn(sum(rows), heads, hd, generator=gen, device="cuda").to(dtype)
+    perm = torch.cat([torch.randperm(n, generator=gen, device="cuda") for n in n_win]).to(torch.int32)
+    pad = lambda n: (n + 31) // 32 * 32  # noqa: E731
+    cap = [sum(pad(s[c] * w) for s, w in zip(seg, win)) for c in range(3)]
+    n16 = [s[3] * w + r - n * w for s, w, r, n in zip(seg, win, rows, n_win)]
+    if short:
+        cap = [c - 32 for c in cap]
+        n16[2] -= 1
+    dt16 = torch.bfloat16 if dtype == torch.bfloat16 else torch.float16
+    runs = []
+    for extra in (0, 1, 0):
+        B = 16 + extra
+        ctx = runs[0][1] if len(runs) == 2 else W.Context(W.workspace_bytes(B))
+        pk = W.PackedKV(B, heads, hd, group, dt16, cap, _offsets(n16 + [0] * extra), fill=0)
+        W.wq_reorder_quantize(ctx, K, V, _table(_offsets(rows + [0] * extra)), _table(win + [1] * extra), _table(_offsets(n_win + [0] * extra)),
+                              perm, _table(seg + [[0] * 4] * extra), sum(rows), pk)
+        status = ctx.device_status()
+        assert status == (W.DEV_CLASS_OVERFLOW | W.DEV_SEG16_OVERFLOW if short else 0)
+        runs.append((pk, ctx))
+    a = runs[0][0]
+    for b, _ in runs[1:]:
+        for x, y in zip(a.codes + a.meta + [a.k16, a.v16], b.codes + b.meta + [b.k16, b.v16]):
+            assert torch.equal(x, y)
+        assert torch.equal(a.v_scale_max[:16], b.v_scale_max[:16])
+        for x, y in zip(a.cls_off + a.cls_len + [a.len16], b.cls_off + b.cls_len + [b.len16]):
+            n = min(x.numel(), y.numel())
+            assert torch.equal(x[:n], y[:n])
+    assert (a.v_scale_max[:16] > 0).sum() >= 10

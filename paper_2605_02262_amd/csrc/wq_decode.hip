@@ -483,7 +483,7 @@ static int splits_for_rounds(int B, const wq_packed_kv* kv, int64_t max_seq_toke
     const int64_t units = (int64_t)B * kv->Hkv, blocks = (max_seq_tokens + 31) / 32;
     // a block's cost, averaged over the cache's slots; a block of cost 100 takes 0.12 us of a compute unit (0.08 with heads of 64)
     const double slots = (double)kv->cap[0] + (double)kv->cap[1] + (double)kv->cap[2] + (double)kv->cap16;
-    const int* const unit = kv->hd / kv->group == 2 ? WQ_BLOCK_COST : WQ_BLOCK_COST_F32;
+    const int* const unit = kv->hd / kv->group != 2 ? WQ_BLOCK_COST_F32 : kv->hd == 64 ? WQ_BLOCK_COST_64 : WQ_BLOCK_COST;
     const double cost = slots > 0 ? ((double)kv->cap[0] * unit[0] + (double)kv->cap[1] * unit[1] +
                                      (double)kv->cap[2] * unit[2] + (double)kv->cap16 * unit[3]) / slots : unit[0];
     const double block_us = cost * (kv->hd == 128 ? 1.2e-3 : 0.8e-3), fixed_us = kv->hd == 128 ? 8.0 : 6.5;

@@ -36,10 +36,10 @@ namespace {
 // cost of a 32-token block of the 2-, 4-, 8- and 16-bit class, in the unit of WQ_BLOCK_COST (the classes do the same matrix
 // instructions here)
 constexpr int WQ_BLOCK_COST_F32[4] = {400, 400, 420, 500};
-template <int G>
+template <int HD, int G>
 constexpr int block_cost(int c)
 {
-    return G == 2 ? WQ_BLOCK_COST[c] : WQ_BLOCK_COST_F32[c];
+    return G != 2 ? WQ_BLOCK_COST_F32[c] : HD == 64 ? WQ_BLOCK_COST_64[c] : WQ_BLOCK_COST[c];
 }
 
 template <int HD, int G>

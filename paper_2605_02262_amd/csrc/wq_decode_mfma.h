@@ -844,7 +844,7 @@ __device__ __forceinline__ int scan_step(int x)          // x plus the value tha
     return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, true);
 }
 
-template <int G, class Smem>
+template <int HD, int G, class Smem>
 __device__ __forceinline__ Place place_by_length(const DecodeArgs& a, Smem& sm, int wg)
 {
     const int lane = threadIdx.x & 63, l = min(lane, a.B - 1);
@@ -866,9 +866,9 @@ __device__ __forceinline__ Place place_by_length(const DecodeArgs& a, Smem& sm, 
         const int tokens = len[0] + len[1] + len[2] + len16_after;
         S = max(1, min(a.splits, (int)ceilf((float)tokens * a.len_scale)));
     } else {
-        int blocks = 1 + ((len16_after + 31) >> 5) * block_cost<G>(3);
+        int blocks = 1 + ((len16_after + 31) >> 5) * block_cost<HD, G>(3);
 #pragma unroll
-        for (int c = 0; c < 3; c++) blocks += ((len[c] + 31) >> 5) * block_cost<G>(c);
+        for (int c = 0; c < 3; c++) blocks += ((len[c] + 31) >> 5) * block_cost<HD, G>(c);
         const float cost = mine ? (float)blocks : 0.f, total = wave_sum(cost), most = wave_max(cost);
         // (a sequence's share is rounded down by 0.002 first: a quotient that should be whole must not become the next whole number)
         auto splits_of = [&](float tau) { return mine ? max(1, min(a.splits, (int)ceilf(fmaf(cost, __builtin_amdgcn_rcpf(tau), -0.002f)))) : 0; };
@@ -954,13 +954,13 @@ __device__ __forceinline__ int range_edge(unsigned x, unsigned base, int n)
     return (int)min(e, (unsigned)n);
 }
 
-template <int G>
+template <int HD, int G>
 __device__ __forceinline__ int range_edge_of(int c, unsigned x, unsigned base, int n)
 {
-    return c == 0 ? range_edge<(unsigned)block_cost<G>(0)>(x, base, n)
-         : c == 1 ? range_edge<(unsigned)block_cost<G>(1)>(x, base, n)
-         : c == 2 ? range_edge<(unsigned)block_cost<G>(2)>(x, base, n)
-                  : range_edge<(unsigned)block_cost<G>(3)>(x, base, n);
+    return c == 0 ? range_edge<(unsigned)block_cost<HD, G>(0)>(x, base, n)
+         : c == 1 ? range_edge<(unsigned)block_cost<HD, G>(1)>(x, base, n)
+         : c == 2 ? range_edge<(unsigned)block_cost<HD, G>(2)>(x, base, n)
+                  : range_edge<(unsigned)block_cost<HD, G>(3)>(x, base, n);
 }
 
 // ---- helpers of the two merges --------------------------------------------------------------------------------
@@ -1035,7 +1035,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
     int cls_len[4], cls_off[4], end16;
     float v_scale_max;
     if constexpr (PACKED) {
-        const Place p = place_by_length<G>(a, sm, (int)blockIdx.x);
+        const Place p = place_by_length<HD, G>(a, sm, (int)blockIdx.x);
         if (p.b < 0) {
             if (a.k_new) __syncthreads();
             count_tables_read(a, 0);
@@ -1112,7 +1112,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         nb[3] = a.mfma16 ? (cls_len[3] + 31) >> 5 : 0;
         unsigned total = 0u;
 #pragma unroll
-        for (int c = 0; c < 4; c++) total += (unsigned)nb[c] * (unsigned)block_cost<G>(c);
+        for (int c = 0; c < 4; c++) total += (unsigned)nb[c] * (unsigned)block_cost<HD, G>(c);
         // cost at which split x starts: floor(total * x / S) up to rounding (one reciprocal, the same bits in every
         // wavefront of the launch); split 0 starts at cost 0, the last one ends behind everything
         const float rS = __builtin_amdgcn_rcpf((float)S);
@@ -1125,14 +1125,14 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         unsigned t = 0;
 #pragma unroll
         for (int c = 3; c >= 0; c--) {
-            const int e0 = range_edge_of<G>(c, G0, base, nb[c]);
-            const int e1 = range_edge_of<G>(c, G1, base, nb[c]);
+            const int e0 = range_edge_of<HD, G>(c, G0, base, nb[c]);
+            const int e1 = range_edge_of<HD, G>(c, G1, base, nb[c]);
             if (fixed_shares) {                    // the range is divided among the wavefronts by cost; no pool
                 const unsigned long long span = G1 - G0;
                 const unsigned x0 = G0 + (unsigned)((span * (unsigned)wave) >> 3), x1 = G0 + (unsigned)((span * (unsigned)(wave + 1)) >> 3);
                 static_assert(WQ_WAVES == 8, "the shift above");
-                src[c].cur = wave == 0 ? e0 : range_edge_of<G>(c, x0, base, nb[c]);
-                src[c].end = wave == WQ_WAVES - 1 ? e1 : range_edge_of<G>(c, x1, base, nb[c]);
+                src[c].cur = wave == 0 ? e0 : range_edge_of<HD, G>(c, x0, base, nb[c]);
+                src[c].end = wave == WQ_WAVES - 1 ? e1 : range_edge_of<HD, G>(c, x1, base, nb[c]);
                 src[c].pool_first = e1;
                 src[c].tk_lo = src[c].tk_hi = t;
             } else {                               // the whole range is the pool
@@ -1142,7 +1142,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
                 t += (unsigned)(e1 - e0);
                 src[c].tk_hi = t;
             }
-            base += (unsigned)nb[c] * (unsigned)block_cost<G>(c);
+            base += (unsigned)nb[c] * (unsigned)block_cost<HD, G>(c);
         }
         if (!fixed_shares && t > (unsigned)WQ_TAPER_TICKETS) tk.taper = t - (unsigned)WQ_TAPER_TICKETS;
         // The first tickets are fixed, so that the first loads can go out before the workgroup's set-up barrier; the counter

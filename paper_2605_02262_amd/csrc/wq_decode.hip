@@ -452,8 +452,8 @@ static bool aligned_16(std::initializer_list<const void*> pointers)
 }
 
 // Which kernel walks the quantized classes.  Two groups per head: the matrix-core kernel, with the weights in one f16 value.
-// One and four groups: the matrix-core kernel with its fp32 walkers for 16-bit queries (measured, 8 x 12795 tokens, 28 / 4
-// heads of 128, group 32: 917 us a call on the vector kernel); fp32 queries and caches beyond the cost axis stay with the
+// One and four groups: the matrix-core kernel with its walkers of fp32 accuracy for 16-bit queries (measured, 8 x 12795 tokens,
+// 28 / 4 heads of 128, group 32: 917 us a call on the vector kernel, 21.0 on them); fp32 queries and caches beyond the cost axis stay with the
 // vector kernel, which also takes what does not lie on 16-byte boundaries (a query cut out of a larger tensor): it reads
 // element by element.
 static bool use_matrix_cores(const void* q, int q_dtype, const wq_packed_kv* kv, int balgo)

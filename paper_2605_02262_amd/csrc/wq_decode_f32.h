@@ -1,52 +1,73 @@
-// a4, matrix-core path in fp32: the walkers of caches with one or four groups per head.
+// a4, matrix-core path of fp32 accuracy: the walkers of caches with one or four groups per head.
 // (included by wq_decode_mfma.h, whose body cuts the work and merges it)
 //
-// These group counts keep the arithmetic of the vector kernel (k_decode_generic): a key or value is dequantized by one fp32
-// fused multiply-add, fma(scale, code, minimum); queries, logits, weights and sums are fp32.  Nothing is rounded to 16 bits,
-// so that neither the spread of a query nor that of the value scales costs accuracy, and v_scale_max is not read.  (Two f16
-// values per weight, placed by the sequence's largest value scale, lost 2.5e-4 of a group whose scale is 2^-12 of that.)
+// Nothing that reaches a sum here is less accurate than an fp32 number: queries, codes, scales and minima are exact, weights and
+// sums are fp32.  v_scale_max is not read.
 //
-// The instruction is v_mfma_f32_4x4x1_16b_f32: sixteen 4 x 4 products D += a b^T of one contraction step each, D's elements
-// the fused multiply-adds that the vector unit computes (bit for bit, subnormals included).  Of its 64 A values each meets 4
-// columns; with the broadcast of one A block to two neighbouring blocks (cbsz = 1, abid = 0 or 1) it meets the 8 query heads
-// of a KV head, and no part of the instruction is idle (in 16 x 16 tiles half the columns would be): 115 TFLOP/s measured,
-// against 146 / 2.  The storage layout (wq.h) is the A operand as it stands:
+// The quantized classes go through v_mfma_f32_16x16x32_f16 with operands that f16 holds exactly, in the layout of the walkers
+// for two groups (the storage layout is the A operand; columns (g, h) = one group or half of the head x query head):
 //
-//   logits   lane (j, m), j = l / 16, m = l % 16, holds the codes of quarter j of token m of a 16-token tile: row m % 4 of
+//   logits   A = code - c, an integer (shifted(); c: code_of_zero), B = the query times a
+//            power of two.  One product per group of the head (four groups: two sets of two groups' columns), so that scale
+//            and minimum come in after the contraction:  s sum(q (code - c)) + (m + c s) sum(q).
+//   values   A = code - c, likewise per token and group, B = weight * scale of the token's group, an fp32 number w in two f16 values: hi = w rounded,
+//            lo = what is left, 2^12 times as large and in accumulators of its own (24 bits between them).  A power of two
+//            per group (SplitState::place) keeps w in f16's range; it moves when a scale is larger than those seen so far.
+//            The other part of the values, weight * (m + c s), is a sum per lane.
+//
+// Codes minus a constant, and not the codes themselves, because with them the two parts of a logit or value, which are far larger
+// than their sum, would be rounded at their own size.  The instruction's sums are as good as fp32 additions one by one, or
+// better (a third of their error over 2048 products).  Errors against 64 bits over batches of the benchmark's distributions, relative 2-norm:
+// 1.6e-7 to 4.8e-7, 0.54 to 1.2 times (on average 0.8) those of fp32 products (2.0e-7 to 4.6e-7).
+//
+// Bound by instruction issue: a 32-token block of a head of 128 takes about 370 vector instructions (four groups; 300 with one) of
+// four cycles and 32 products of 16; 136 of them unpack codes, 70 split the weights.  Measured, us per call, products in fp32
+// on v_mfma_f32_4x4x1 (256 of them, 9.6 cycles each, and a dequantizing instruction per number) -> this: 8 x 12795 tokens, 28 / 4
+// heads of 128, group 32: 31.7 -> 21.0, group 128: 31.8 -> 19.2; 4 x 50676, group 32: 53 -> 32; 16 x 6545 tokens, 14 / 2 heads of 64,
+// group 64: 14.5 -> 10.6.  (917 us on the vector kernel, the first of these.)
+//
+// The 16-bit segment keeps fp32 products, on v_mfma_f32_4x4x1_16b_f32: sixteen 4 x 4 products D += a b^T of one contraction
+// step each, D's elements the fused multiply-adds that the vector unit computes (bit for bit, subnormals included).  Of its
+// 64 A values each meets 4 columns; with the broadcast of one A block to two neighbouring blocks (cbsz = 1, abid = 0 or 1) it
+// meets the 8 query heads of a KV head.
+//
+//   logits   lane (j, m), j = l / 16, m = l % 16, holds quarter j of token m of a 16-token tile: row m % 4 of
 //            A block 4j + m / 4.  A step is one channel of every quarter.  B: lane l holds that channel of query l % 8.
 //            abid a leaves in D, lane (j, m), element i: token 8 (m / 8) + 4 a + i, query l % 8, the part of quarter j.
 //   values   lane (j, m) holds channel 16 ct + m of the tokens 4j .. 4j + 3 of both tiles.  A step is one token of every
 //            lane group j.  B: that token's weight for query l % 8.  abid a leaves channel 16 ct + 8 (m / 8) + 4 a + i of
 //            query l % 8, the part of lane group j's tokens.
 //
-// Between them the four quarters' parts are added up and every lane group gets its own tokens, in registers (tokens_of_group).
+// Between them the four quarters' parts are added up and every lane group gets its own tokens, in registers (tokens_of_group);
+// at the end of the segment the channels likewise (carry_on).
 //
-// Bound by instruction issue: a 32-token block takes 2 HD matrix instructions (9.6 cycles each) and about as much again on the
-// vector unit, and neither overlaps the other to speak of, not even between the two wavefronts of a SIMD.  Codes are therefore
-// converted by the dequantizing instruction itself: masked in place, a code is the f16 subnormal code * 2^(shift - 24), which
-// a mixed-precision fused multiply-add takes as it is; the power of two is put into the scale (keys) or into the minimum and
-// the weight (values), where it changes no rounding.  A workgroup's 32-token block takes 0.49 us with heads of 128, 0.29 with
-// heads of 64 (0.60 and 0.32 in the 16-bit segment); 8 x 12795 tokens, 28 / 4 heads of 128, group 32: 917 us a call on the
-// vector kernel, 34.0 here.  A wavefront's blocks are a fixed share of its workgroup's range, so that a split count fixes every bit of
-// the result, as it does in the vector kernel.
+// A wavefront's blocks are a fixed share of its workgroup's range, so that a split count fixes every bit of the result, as it
+// does in the vector kernel.
 #pragma once
 
 namespace {
 
-// cost of a 32-token block of the 2-, 4-, 8- and 16-bit class, in the unit of WQ_BLOCK_COST (the classes do the same matrix
-// instructions here)
-constexpr int WQ_BLOCK_COST_F32[4] = {400, 400, 420, 500};
+// cost of a 32-token block of the 2-, 4-, 8- and 16-bit class, in the unit of WQ_BLOCK_COST
+#ifndef WQ_COSTS_F32
+#define WQ_COSTS_F32 130, 140, 170, 400
+#endif
+constexpr int WQ_BLOCK_COST_F32[4] = {WQ_COSTS_F32};
 template <int HD, int G>
 constexpr int block_cost(int c)
 {
     return G != 2 ? WQ_BLOCK_COST_F32[c] : HD == 64 ? WQ_BLOCK_COST_64[c] : WQ_BLOCK_COST[c];
 }
 
+typedef float floatx2v __attribute__((ext_vector_type(2)));
+
 template <int HD, int G>
 struct F32Smem {
     static constexpr int PITCH = HD + 4;                 // 4 rows apart = 8 banks
-    uint32_t meta[WQ_WAVES][32 * G];                     // per wave: V metadata words of the current block
+    float meta[WQ_WAVES][4][32 * G];                     // per wave: scales and offsets of the current block's K groups, then of its V groups
+    uint32_t vzero[WQ_WAVES][16 * G];                    // ... and what is taken off V's codes (f16, tile 0's token and tile 1's)
     __attribute__((aligned(16))) uint16_t vt[WQ_WAVES][32][PITCH];     // per wave: V rows of a 16-bit block, read back one channel per lane
+    U4 bq[3][HD / 32][64];                               // query operands of the quantized classes, per lane
+    float qx[3][64];                                     // ... their power of two, the sums of set 0's and set 1's group
     // what the body uses (MfmaSmem has the same)
     float O[WQ_WAVES][WQ_MAX_REP][HD + 1];
     float ml[WQ_WAVES][WQ_MAX_REP][2];
@@ -113,12 +134,11 @@ struct TileAcc {
     floatx4 v[2][2];        // [chain][a]
 };
 
-// From the products of a tile (see above) to x[i] = the whole logit of token 4j + i, query l % 8, for lane (j, m)
-__device__ __forceinline__ void tokens_of_group(const TileAcc& t, float* x)
+// From products as the instruction leaves them (a = 0 and 1) to x[i] = the whole sum of row 4j + i, query l % 8, for lane (j, m)
+__device__ __forceinline__ void rows_of_group(const floatx4& acc0, const floatx4& acc1, float* x)
 {
-    const floatx4 acc0 = t.v[0][0] + t.v[1][0], acc1 = t.v[0][1] + t.v[1][1];
     const int lane = threadIdx.x & 63;
-    const bool own = ((lane >> 3) & 1) == (lane >> 5);   // lane (j, m) has the tokens 8 (m / 8) + ..., needs 8 (j / 2) + ...
+    const bool own = ((lane >> 3) & 1) == (lane >> 5);   // lane (j, m) has the rows 8 (m / 8) + ..., needs 8 (j / 2) + ...
 #pragma unroll
     for (int i = 0; i < 4; i++) {
         // rows 2k and 2k + 1 of 16 lanes: the even one keeps a = 0, the odd one a = 1
@@ -128,17 +148,18 @@ __device__ __forceinline__ void tokens_of_group(const TileAcc& t, float* x)
         x[i] = own ? v : o;
     }
 }
+__device__ __forceinline__ void tokens_of_group(const TileAcc& t, float* x) { rows_of_group(t.v[0][0] + t.v[1][0], t.v[0][1] + t.v[1][1], x); }
 
 // Weights of a block's 8 tokens per lane from their logits (-inf: not there).  A logit of -inf leaves its token out, also
 // where all have been -inf so far.
+constexpr float F32_SLACK = 3.5f;                  // weights stay below e^3.5 = 2^5.05; the reference moves when a logit is farther up
 template <int HD>
 __device__ __forceinline__ void softmax_weights(F32State<HD>& st, float* x, float sm_scale, float* p)
 {
-    constexpr float SLACK = 3.5f;                  // weights stay below e^SLACK; the reference moves when a logit is farther up
 #pragma unroll
     for (int k = 0; k < 8; k++) x[k] *= sm_scale;
     float lm = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
-    if (__builtin_amdgcn_ballot_w64(lm > st.m + SLACK) != 0) {
+    if (__builtin_amdgcn_ballot_w64(lm > st.m + F32_SLACK) != 0) {
         lm = max_over_rows(lm);
         const float mn = fmaxf(st.m, lm);
         const float alpha = (mn == -INFINITY) ? 1.0f : __expf(st.m - mn);      // 0 on the first block
@@ -158,32 +179,151 @@ __device__ __forceinline__ void softmax_weights(F32State<HD>& st, float* x, floa
     }
 }
 
+// ---- the quantized classes ----------------------------------------------------------------------------------------
+template <int HD, int G>
+struct SplitState {
+    static constexpr int SETS = G == 4 ? 2 : 1;
+    floatx4 O[HD / 16];     // sums of weight * scale * place[set] * (code - c) * 2^-9: row = channel 16 ct + 4 j + i, column = (g, h)
+    floatx4 P[HD / 16];     // ... of what the first f16 value left of the weights, 2^12 times as large
+    float m;                // reference of head h (a recent largest logit), the same in all lanes of the head
+    float l;                // sum of the weights of lane group j's tokens
+    float accM[SETS];       // ... of the weights times the offsets of the groups that the lane's column is for
+    float place[SETS];      // power of two that brings these groups' weights times scales to at most 2^15
+    uint32_t ref;           // the largest scale (its f16 bits) of group j that the places leave room for; 0: none seen
+    float own;              // group j's place
+};
+
+// The query operands of class CLS, built by one wavefront: lane (j, col) has quarter j of head h = col % 8, times the power of
+// two that brings the head's largest entry into [2^14, 2^15): whatever a 16-bit query holds is exact in f16 then, down to
+// 2^-28 of its largest entry.  sums[s]: of the scaled query over group 2 s + g (four groups), or over the head (one group).
+template <int HD, int CLS, int G>
+__device__ __forceinline__ void build_q_split(const DecodeArgs& a, int b, int kvh, U4* Bq, float& unit, float (&sums)[2])
+{
+    constexpr int QC = HD / 4, NK = HD / 32;
+    const int lane = threadIdx.x & 63, g = (lane >> 3) & 1;
+    float v[QC];
+    load_q_quarter<HD>(a, b, kvh, v);
+    float mx = 0.f;
+#pragma unroll
+    for (int k = 0; k < QC; k++) mx = fmaxf(mx, fabsf(v[k]));
+    mx = max_over_rows(mx);
+    const int eb = (int)((__float_as_uint(mx) >> 23) & 0xFFu), up = min(141 - eb, 126);      // (mx in [2^(eb - 127), 2^(eb - 126)))
+    const float scale = __uint_as_float((uint32_t)(127 + up) << 23);
+    unit = __uint_as_float((uint32_t)(127 - up) << 23);
+    float s = 0.f;
+#pragma unroll
+    for (int k = 0; k < QC; k++) {
+        v[k] *= scale;
+        s += v[k];
+    }
+    const RowPair pair = rows_16(s);                     // the quarters 2 (j / 2) and 2 (j / 2) + 1
+    if constexpr (G == 4) {
+        const RowPair sets = halves_32(g ? pair.odd : pair.even);
+        sums[0] = sets.even;
+        sums[1] = sets.odd;
+    } else {
+        const RowPair halves = halves_32(pair.even + pair.odd);
+        sums[0] = halves.even + halves.odd;
+        sums[1] = 0.f;
+    }
+#pragma unroll
+    for (int r = 0; r < NK; r++) {
+        uint32_t w[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            int ch0, ch1, sh;
+            k_slot(CLS, r, 2 * e, ch0, sh);
+            k_slot(CLS, r, 2 * e + 1, ch1, sh);
+            const half2v pair_e = {(_Float16)v[ch0], (_Float16)v[ch1]};
+            w[e] = __builtin_bit_cast(uint32_t, pair_e);
+        }
+        Bq[r] = U4{w[0], w[1], w[2], w[3]};
+    }
+}
+
+template <int HD, int G>
+__device__ __forceinline__ void stage_q_split(const DecodeArgs& a, F32Smem<HD, G>& sm, int b, int kvh, int wave)
+{
+    const int lane = threadIdx.x & 63;
+    U4 Bq[HD / 32];
+    float unit, sums[2];
+    if (wave >= 3) return;
+    if (wave == 0) build_q_split<HD, 0, G>(a, b, kvh, Bq, unit, sums);
+    else if (wave == 1) build_q_split<HD, 1, G>(a, b, kvh, Bq, unit, sums);
+    else build_q_split<HD, 2, G>(a, b, kvh, Bq, unit, sums);
+#pragma unroll
+    for (int r = 0; r < HD / 32; r++) sm.bq[wave][r][lane] = Bq[r];
+    if (wave == 0) {
+        sm.qx[0][lane] = unit;
+        sm.qx[1][lane] = sums[0];
+        sm.qx[2][lane] = sums[1];
+    }
+}
+
+// What is contracted is code - c, c the code nearest to the number zero, so that sums over many codes stay as small as those
+// over the dequantized numbers themselves (with the middle of the codes, a group that one entry stretches, or one of equal
+// entries, whose scale is 1, would be rounded at the size of the middle); the group's minimum goes up by c * scale.
+template <int BITS>
+__device__ __forceinline__ float code_of_zero(float s, float m)
+{
+    return __builtin_amdgcn_fmed3f(rintf(-m * __builtin_amdgcn_rcpf(fmaxf(s, 0x1p-25f))), 0.f, (float)((1 << BITS) - 1));     // (padding has scale 0)
+}
+// A raw operand (k_operand, v_operand: f16 subnormals code * 2^(shift - 24)) as (code - c) * 2^-9, c512 = -c * 2^-9 per slot: one
+// fused multiply-add of two f16 at a time, exact
+__device__ __forceinline__ half8 shifted(half8 raw, const half2v (&c512)[4], int sh0, int sh1, int sh2, int sh3)
+{
+    const int sh[4] = {sh0, sh1, sh2, sh3};
+    const U4 u = __builtin_bit_cast(U4, raw);
+    uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int v = 0; v < 4; v++) {
+        const _Float16 p = (_Float16)pow2_of((float)(15 - sh[v]));
+        w[v] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(half2v, w[v]), half2v{p, p}, c512[v]));
+    }
+    return as_half8(w[0], w[1], w[2], w[3]);
+}
+
+// Two numbers divided by 2^12, in f16; and what that leaves of them, in f16 (one instruction each: products and sums in fp32,
+// rounded once)
+__device__ __forceinline__ uint32_t scaled_f16(float x, float y)
+{
+    uint32_t r;
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(r) : "v"(x), "s"(1.0f / 4096.0f));
+    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(r) : "v"(y), "s"(1.0f / 4096.0f));
+    return r;
+}
+__device__ __forceinline__ uint32_t rest_f16(float x, float y, uint32_t h)
+{
+    uint32_t r;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "s"(-4096.0f), "v"(x));
+    asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(r) : "v"(h), "s"(-4096.0f), "v"(y));
+    return r;
+}
+
 template <int HD, int BITS, int G>
-struct F32Frag {
+struct SplitFrag {
     static constexpr int KDW = (HD / 4) * BITS / 32;        // dwords of K codes per lane per 16-token tile
     static constexpr int VDW = (HD / 16) * 8 * BITS / 32;   // dwords of V codes per lane per 32-token block
-    static constexpr int VM = G == 4 ? 2 : 1;               // V metadata words per lane per block
-    uint32_t k[2][KDW], v[VDW], km[2], vm[VM];
+    uint32_t k[2][KDW], v[VDW], km[2], vm[2];               // km, vm: metadata of token l % 16 of each tile, group j
 };
 
 // this wavefront's blocks [blk, end) of one class of one (sequence, KV head): len tokens from token slot tok_base
-template <int HD, int BITS, int G>
-__device__ __forceinline__ void walk_class_f32(const DecodeArgs& a, F32Smem<HD, G>& sm, int b, int kvh, int len, int tok_base, int blk, int end,
-                                               Tickets& tk, F32State<HD>& st)
+template <int HD, int BITS, int G, int DEPTH>
+__device__ __forceinline__ void walk_class_split(const DecodeArgs& a, F32Smem<HD, G>& sm, int b, int kvh, int len, int tok_base, int blk, int end,
+                                                 Tickets& tk, SplitState<HD, G>& st)
 {
     static_assert(G == 1 || (G == 4 && HD == 128), "a quarter of the head lies in one group");
-    constexpr int C = BITS == 2 ? 0 : (BITS == 4 ? 1 : 2), CT = HD / 16, DEPTH = 2;
-    using F = F32Frag<HD, BITS, G>;
+    constexpr int C = BITS == 2 ? 0 : (BITS == 4 ? 1 : 2), CT = HD / 16, NK = HD / 32, SETS = SplitState<HD, G>::SETS;
+    using F = SplitFrag<HD, BITS, G>;
     if (blk >= end) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane >> 4;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane >> 4, g = (lane >> 3) & 1;
     const wq_packed_kv& kv = a.kv;
     const int64_t cap = kv.cap[C];
     const uint8_t* kbase = static_cast<const uint8_t*>(kv.codes[C]) + ((int64_t)kvh * cap + tok_base) * HD * BITS / 8 + lane * (F::KDW * 4);
     const uint8_t* vbase = static_cast<const uint8_t*>(kv.codes[C]) + (((int64_t)kv.Hkv + kvh) * cap + tok_base) * HD * BITS / 8 + lane * (F::VDW * 4);
-    // the word of a K tile's token m and quarter j's group: the lane's own with four groups
     const uint32_t* kmeta = static_cast<const uint32_t*>(kv.meta[C]) + ((int64_t)kvh * cap + tok_base) * G + (G == 4 ? lane : lane & 15);
-    const uint32_t* vmeta = static_cast<const uint32_t*>(kv.meta[C]) + (((int64_t)kv.Hkv + kvh) * cap + tok_base) * G + (G == 4 ? lane : lane & 31);
-    uint32_t* const words = sm.meta[wave];
+    const uint32_t* vmeta = static_cast<const uint32_t*>(kv.meta[C]) + (((int64_t)kv.Hkv + kvh) * cap + tok_base) * G + (G == 4 ? lane : lane & 15);
+    float* const words = sm.meta[wave][0];
 
     auto load = [&](int n, F& f) {
         const int64_t o = (int64_t)n * (32 * HD * BITS / 8);
@@ -191,95 +331,199 @@ __device__ __forceinline__ void walk_class_f32(const DecodeArgs& a, F32Smem<HD, 
         load_dwords<F::KDW>(reinterpret_cast<const uint32_t*>(kbase + o + 16 * HD * BITS / 8), f.k[1]);
         load_dwords<F::VDW>(reinterpret_cast<const uint32_t*>(vbase + o), f.v);
 #pragma unroll
-        for (int t = 0; t < 2; t++) f.km[t] = kmeta[(int64_t)n * (32 * G) + t * (16 * G)];
-#pragma unroll
-        for (int k = 0; k < F::VM; k++) f.vm[k] = vmeta[(int64_t)n * (32 * G) + 64 * k];
+        for (int t = 0; t < 2; t++) {
+            f.km[t] = kmeta[(int64_t)n * (32 * G) + t * (16 * G)];
+            f.vm[t] = vmeta[(int64_t)n * (32 * G) + t * (16 * G)];
+        }
     };
-    auto compute = [&](int n, const F& f) {
-        // ---- value words: one or two per lane in, per group the lane group's 4 tokens x 2 tiles out ----
-        if (G == 4 || lane < 32) {
+    F f[DEPTH];
 #pragma unroll
-            for (int k = 0; k < F::VM; k++) words[64 * k + lane] = f.vm[k];
+    for (int d = 0; d < DEPTH; d++)
+        if (blk + d < end) load(blk + d, f[d]);
+    pass_setup_barrier(a, b, tk);
+    // B operands: column (g, h) of set s takes the channels of group 2 s + g (four groups), or of half g of the head
+    half8 Bq[SETS][NK];
+#pragma unroll
+    for (int r = 0; r < NK; r++) {
+        const U4 q = sm.bq[C][r][lane];
+#pragma unroll
+        for (int s = 0; s < SETS; s++) {
+            const bool mine = G == 4 ? j == 2 * s + g : (j >> 1) == g;
+            Bq[s][r] = as_half8(mine ? q.x : 0u, mine ? q.y : 0u, mine ? q.z : 0u, mine ? q.w : 0u);
+        }
+    }
+    const float cexp = a.sm_scale * sm.qx[0][lane] * 512.0f;
+    float qs[SETS];
+#pragma unroll
+    for (int s = 0; s < SETS; s++) qs[s] = sm.qx[1 + s][lane] * (1.0f / 512.0f);
+
+    auto compute = [&](int n, const F& f) {
+        // ---- a scale beyond what the places leave room for moves them, twice as far (rarely: the first block does) ----
+        uint32_t top = max(f.vm[0] & 0xFFFFu, f.vm[1] & 0xFFFFu);
+        if (__builtin_amdgcn_ballot_w64(top > st.ref) != 0) {
+            auto moved = [](uint32_t x, auto ctrl) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, 0xF, 0xF, false); };
+            top = max(top, moved(top, std::integral_constant<int, 0x128>{}));
+            top = max(top, moved(top, std::integral_constant<int, 0x124>{}));
+            top = max(top, moved(top, std::integral_constant<int, 0x122>{}));
+            top = max(top, moved(top, std::integral_constant<int, 0x121>{}));
+            if (top > st.ref) st.ref = min(top + (1u << 10), 0x7BFFu);
+            // weights are below 2^5.1, scales up to ref, which is below 2^(e - 14): their products below 2^15.1
+            const int e = (int)(st.ref >> 10);
+            st.own = st.ref == 0u ? 1.0f : pow2_of((float)(24 - e));
+#pragma unroll
+            for (int s = 0; s < SETS; s++) {
+                float to = st.own;
+                if constexpr (G == 4) {
+                    const float even = lane_value(st.own, 32 * s), odd = lane_value(st.own, 32 * s + 16);
+                    to = g ? odd : even;
+                }
+                const float by = to * (1.0f / st.place[s]);        // (powers of two)
+                st.place[s] = to;
+#pragma unroll
+                for (int ct = s * (CT / SETS); ct < (s + 1) * (CT / SETS); ct++) {
+                    st.O[ct] *= by;
+                    st.P[ct] *= by;
+                }
+            }
+        }
+        // ---- scales and offsets: a lane's words in, the ones of its tokens and column out, V's scales times 2^12 of their place ----
+        half2v kzero[2], vzero;
+        float koff[2], voff[2];
+#pragma unroll
+        for (int t = 0; t < 2; t++) {
+            const float kc = code_of_zero<BITS>(f16lo(f.km[t]), f16hi(f.km[t])), vc = code_of_zero<BITS>(f16lo(f.vm[t]), f16hi(f.vm[t]));
+            kzero[t] = half2v{(_Float16)(kc * (-1.0f / 512.0f)), (_Float16)(kc * (-1.0f / 512.0f))};
+            vzero[t] = (_Float16)(vc * (-1.0f / 512.0f));
+            koff[t] = fmaf(f16lo(f.km[t]), kc, f16hi(f.km[t]));
+            voff[t] = fmaf(f16lo(f.vm[t]), vc, f16hi(f.vm[t]));
+        }
+        if (G == 4 || lane < 16) {
+#pragma unroll
+            for (int t = 0; t < 2; t++) {
+                float* const at = words + 16 * G * t + lane;
+                at[0] = f16lo(f.km[t]);
+                at[32 * G] = koff[t];
+                at[64 * G] = fmaf(f16lo(f.vm[t]), st.own * 4096.0f, 0.f);
+                at[96 * G] = voff[t];
+            }
+            sm.vzero[wave][lane] = __builtin_bit_cast(uint32_t, vzero);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // ---- logits ----
-        float x[8], p[8];
+        auto words_of = [&](int kind, int s, float (&w)[8]) {      // tokens 4 j + i of both tiles, the group of set s
 #pragma unroll
-        for (int t = 0; t < 2; t++) {
-            const float s = f16lo(f.km[t]) * 16777216.0f, mn = f16hi(f.km[t]);
-            TileAcc acc = {};
+            for (int t = 0; t < 2; t++) {
+                const float4 u = *reinterpret_cast<const float4*>(words + kind * (32 * G) + (t * G + (G == 4 ? 2 * s + g : 0)) * 16 + 4 * j);
+                w[4 * t] = u.x, w[4 * t + 1] = u.y, w[4 * t + 2] = u.z, w[4 * t + 3] = u.w;
+            }
+        };
+        // ---- logits of the two 16-token tiles ----
+        float x[8], p[8], ks[SETS][8], kc[SETS][8];
 #pragma unroll
-            for (int r = 0; r < HD / 64; r++) {
-                const half8 codes[2] = {k_operand<BITS>(f.k[t], r), k_operand<BITS>(f.k[t], r + HD / 64)};
+        for (int s = 0; s < SETS; s++) {
+            words_of(0, s, ks[s]);
+            words_of(1, s, kc[s]);
+        }
+        floatx4 acc[2][SETS];                      // (two or four chains of products at a time)
 #pragma unroll
-                for (int e0 = 0; e0 < 8; e0 += 4) {
-                    float kh[2][4], q[2][4];
+        for (int t = 0; t < 2; t++)
 #pragma unroll
-                    for (int c = 0; c < 2; c++)
+            for (int s = 0; s < SETS; s++) acc[t][s] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                        for (int e = 0; e < 4; e++) {
-                            int ch, sh;
-                            k_slot(C, r + c * (HD / 64), e0 + e, ch, sh);
-                            kh[c][e] = fmaf(s * pow2_of(-(float)sh), (float)codes[c][e0 + e], mn);
-                            q[c][e] = st.q[ch];
-                        }
-                    mfma_f32_4(kh[0], q[0], acc.v[0], kh[1], q[1], acc.v[1]);
+        for (int r = 0; r < NK; r++) {
+            int ch, sh[4];
+#pragma unroll
+            for (int v = 0; v < 4; v++) k_slot(C, r, 2 * v, ch, sh[v]);
+#pragma unroll
+            for (int t = 0; t < 2; t++) {
+                const half2v kc4[4] = {kzero[t], kzero[t], kzero[t], kzero[t]};
+                const half8 codes = shifted(k_operand<BITS>(f.k[t], r), kc4, sh[0], sh[1], sh[2], sh[3]);
+#pragma unroll
+                for (int s = 0; s < SETS; s++) acc[t][s] = mfma(codes, Bq[s][r], acc[t][s]);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 2; t++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const int k = 4 * t + i;
+                if constexpr (G == 4) {
+                    const float y = fmaf(ks[1][k], acc[t][1][i], fmaf(kc[1][k], qs[1], fmaf(ks[0][k], acc[t][0][i], kc[0][k] * qs[0])));
+                    x[k] = y + ror8(y);
+                } else {                           // (both halves of the head are of one group: their products first)
+                    x[k] = fmaf(ks[0][k], acc[t][0][i] + ror8(acc[t][0][i]), kc[0][k] * qs[0]);
                 }
             }
-            tokens_of_group(acc, x + 4 * t);
-        }
         const int nv = len - n * 32;               // (the class's last block of the sequence can be a partial one)
         if (nv < 32) {
 #pragma unroll
             for (int k = 0; k < 8; k++)
                 if (16 * (k >> 2) + 4 * j + (k & 3) >= nv) x[k] = -INFINITY;
         }
-        softmax_weights<HD>(st, x, a.sm_scale, p);
-        // ---- values: a token's codes carry 2^(shift - 24), its minimum is given the same factor, its weight the inverse ----
-        float pu[8], unit[8];
+        // ---- weights, as softmax_weights ----
+        float lm = max3(max3(x[0], x[1], x[2]), max3(x[3], x[4], x[5]), max3(x[6], x[7], x[7])) * cexp;      // (cexp > 0)
+        if (__builtin_amdgcn_ballot_w64(lm > st.m + F32_SLACK) != 0) {
+            lm = max_over_rows(lm);
+            const float mn = fmaxf(st.m, lm);
+            const float alpha = (mn == -INFINITY) ? 1.0f : __expf(st.m - mn);      // 0 on the first block
+            st.m = mn;
+            st.l *= alpha;
 #pragma unroll
-        for (int tau = 0; tau < 8; tau++) {
-            unit[tau] = pow2_of(v_slot_shift<BITS>(tau & 3) - 24.0f);
-            pu[tau] = p[tau] * pow2_of(24.0f - v_slot_shift<BITS>(tau & 3));
+            for (int s = 0; s < SETS; s++) st.accM[s] *= alpha;
+#pragma unroll
+            for (int ct = 0; ct < CT; ct++) {
+                st.O[ct] *= alpha;
+                st.P[ct] *= alpha;
+            }
         }
+        const float ref = st.m == -INFINITY ? 0.f : st.m;
 #pragma unroll
-        for (int g = 0; g < G; g++) {
-            uint32_t w[8];
+        for (int k = 0; k < 8; k++) {
+            p[k] = __expf(fmaf(x[k], cexp, -ref));
+            st.l += p[k];
+        }
+        // ---- the weights times the scales in two f16 values each, the second 2^12 times what is left; slots (2v, 2v+1) =
+        //      (tile 0, tile 1) token 4j+v ----
+        half8 hi[SETS], lo[SETS];
 #pragma unroll
-            for (int t = 0; t < 2; t++) {
-                const uint4 u = *reinterpret_cast<const uint4*>(words + (t * G + g) * 16 + 4 * j);
-                w[4 * t] = u.x, w[4 * t + 1] = u.y, w[4 * t + 2] = u.z, w[4 * t + 3] = u.w;
+        for (int s = 0; s < SETS; s++) {
+            float vs[8], vc[8];
+            words_of(2, s, vs);
+            words_of(3, s, vc);
+            uint32_t h[4], l[4];
+#pragma unroll
+            for (int v = 0; v < 4; v++) {
+                const float w0 = p[v] * vs[v], w1 = p[4 + v] * vs[4 + v];
+                h[v] = scaled_f16(w0, w1);
+                l[v] = rest_f16(w0, w1, h[v]);
             }
-            float mn[8];
+            hi[s] = as_half8(h[0], h[1], h[2], h[3]);
+            lo[s] = as_half8(l[0], l[1], l[2], l[3]);
 #pragma unroll
-            for (int tau = 0; tau < 8; tau++) mn[tau] = fmaf(f16hi(w[tau]), unit[tau], 0.f);       // (one mixed-precision instruction)
+            for (int k = 0; k < 8; k++) st.accM[s] = fmaf(p[k], vc[k], st.accM[s]);
+        }
+        half2v vc4[G][4];
 #pragma unroll
-            for (int ct = g * (CT / G); ct < (g + 1) * (CT / G); ct += 2) {
-                const half8 codes[2] = {v_operand<BITS>(f.v, ct), v_operand<BITS>(f.v, ct + 1)};
+        for (int k = 0; k < G; k++) {
+            const uint4 u = *reinterpret_cast<const uint4*>(sm.vzero[wave] + 16 * k + 4 * j);
+            const uint32_t w[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
-                for (int e0 = 0; e0 < 8; e0 += 4) {
-                    float vh[2][4], pw[4];
-#pragma unroll
-                    for (int e = 0; e < 4; e++) {
-                        const int tau = 4 * (e & 1) + ((e0 + e) >> 1);
-                        vh[0][e] = fmaf(f16lo(w[tau]), (float)codes[0][e0 + e], mn[tau]);
-                        vh[1][e] = fmaf(f16lo(w[tau]), (float)codes[1][e0 + e], mn[tau]);
-                        pw[e] = pu[tau];
-                    }
-                    mfma_f32_4(vh[0], pw, st.O[ct], vh[1], pw, st.O[ct + 1]);
-                }
-            }
+            for (int v = 0; v < 4; v++) vc4[k][v] = __builtin_bit_cast(half2v, w[v]);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();           // the next block's words may overwrite the buffer after this point
+        // ---- values ----
+#pragma unroll
+        for (int ct = 0; ct < CT; ct++) {
+            constexpr int PER = CT / SETS;
+            const half8 codes = shifted(v_operand<BITS>(f.v, ct), vc4[ct / (CT / G)], (int)v_slot_shift<BITS>(0), (int)v_slot_shift<BITS>(1),
+                                               (int)v_slot_shift<BITS>(2), (int)v_slot_shift<BITS>(3));
+            st.P[ct] = mfma(codes, lo[ct / PER], st.P[ct]);
+            st.O[ct] = mfma(codes, hi[ct / PER], st.O[ct]);
+        }
     };
 
-    F f[DEPTH];                                    // one block is loaded while the other is worked on
-    load(blk, f[0]);
-    if (blk + 1 < end) load(blk + 1, f[1]);
-    pass_setup_barrier(a, b, tk);
     while (true) {
 #pragma unroll
         for (int d = 0; d < DEPTH; d++) {
@@ -290,7 +534,7 @@ __device__ __forceinline__ void walk_class_f32(const DecodeArgs& a, F32Smem<HD, 
     }
 }
 
-// ... and of the 16-bit segment: rows are plain [token][Hkv][hd], so the K side is the A operand straight from memory (a
+// ---- the 16-bit segment: rows are plain [token][Hkv][hd], so the K side is the A operand straight from memory (a
 // quarter of a token's row per lane); V rows go through LDS and are read back one channel per lane.  Rows past the end stand
 // in as zeros.  new_row >= 0: row new_row (= len - 1) is not in the cache yet, it is read from knew / vnew.
 template <int HD, bool BF, int G>
@@ -375,21 +619,42 @@ __device__ __forceinline__ void walk_seg16_f32(const DecodeArgs& a, F32Smem<HD, 
     }
 }
 
-// The lane groups' parts added up, the wavefront's numerators, reference exponent and weight sum to LDS for the merge
+// What walk_seg16_f32 leaves, as the walkers of the quantized classes carry it on: the lane groups' parts added up, and every
+// lane its own channels (tokens_of_group does the same to a tile's logits)
 template <int HD, int G>
-__device__ __forceinline__ void hand_over_f32(F32Smem<HD, G>& sm, const F32State<HD>& st)
+__device__ __forceinline__ void carry_on(const F32State<HD>& from, SplitState<HD, G>& st)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane >> 4, m = lane & 15, h = lane & 7;
+    st.m = from.m;
+    st.l = from.l;
+#pragma unroll
+    for (int ct = 0; ct < HD / 16; ct++) {
+        float x[4];
+        rows_of_group(from.O[ct][0], from.O[ct][1], x);
+        st.O[ct] = floatx4{x[0], x[1], x[2], x[3]} * (1.0f / 512.0f) * ((G == 4 && ct >= HD / 32) ? st.place[SplitState<HD, G>::SETS - 1] : st.place[0]);
+    }
+}
+
+// The wavefront's numerators, reference and weight sum to LDS for the merge
+template <int HD, int G>
+__device__ __forceinline__ void hand_over_split(F32Smem<HD, G>& sm, const SplitState<HD, G>& st)
+{
+    constexpr int CT = HD / 16, SETS = SplitState<HD, G>::SETS;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = lane >> 4, g = (lane >> 3) & 1, h = lane & 7;
     const float l = sum_over_rows(st.l);
+    float am[SETS], unit[SETS];
 #pragma unroll
-    for (int ct = 0; ct < HD / 16; ct++)
+    for (int s = 0; s < SETS; s++) {
+        am[s] = sum_over_rows(st.accM[s]);
+        unit[s] = 512.0f / st.place[s];
+    }
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-            // even rows of 16 lanes keep a = 0, odd ones a = 1
-            const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(st.O[ct][0][i]), __float_as_uint(st.O[ct][1][i]), false, false);
-            const RowPair s = halves_32(__uint_as_float(r[0]) + __uint_as_float(r[1]));
-            if (j < 2) sm.O[wave][h][16 * ct + 8 * (m >> 3) + 4 * j + i] = s.even + s.odd;
+    for (int ct = 0; ct < CT; ct++) {
+        const int s = ct / (CT / SETS);
+        if (g == (G == 4 ? ct / (CT / 4) % 2 : 0)) {       // this column's group owns channel tile ct
+#pragma unroll
+            for (int i = 0; i < 4; i++) sm.O[wave][h][16 * ct + 4 * j + i] = fmaf(fmaf(st.P[ct][i], 1.0f / 4096.0f, st.O[ct][i]), unit[s], am[s]);
         }
+    }
     if (lane < 8) {
         sm.ml[wave][h][0] = st.m;
         sm.ml[wave][h][1] = l;

@@ -2,7 +2,7 @@
 // (included by wq_decode.hip, after DecodeArgs and load_q)
 //
 // The walkers here and the text below are those of two groups per head (hd/group == 2).  One and four groups have walkers of
-// their own, in fp32 (wq_decode_f32.h); the body at the end of this file cuts and merges the work of both.
+// their own, of fp32 accuracy (wq_decode_f32.h); the body at the end of this file cuts and merges the work of both.
 //
 // One wavefront walks 32-token blocks of a class on its own (no workgroup barrier inside the loop):
 //
@@ -1095,10 +1095,11 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         }
     }
     // ---- the query operands of all classes, one class per wavefront ----
-    if constexpr (!F32) stage_q_operands<HD>(a, sm, b, kvh, wave, bf16seg);
+    if constexpr (F32) stage_q_split<HD, G>(a, sm, b, kvh, wave);
+    else stage_q_operands<HD>(a, sm, b, kvh, wave, bf16seg);
 
     // ---- the workgroup's range of the stream [16-bit | 8-bit | 4-bit | 2-bit] of (b, kvh), and this wavefront's
-    //      fixed share of it (none unless the launch asks for fixed shares or the walkers are the fp32 ones: then there is no pool) ----
+    //      fixed share of it (none unless the launch asks for fixed shares or the walkers are those of one and four groups: then there is no pool) ----
     const bool fixed_shares = F32 || a.fixed_shares;
     Tickets tk;
     tk.ctr = &sm.next_ticket;
@@ -1167,22 +1168,35 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
 #endif
 
     if constexpr (F32) {
-        F32State<HD> st;
+        SplitState<HD, G> st;
 #pragma unroll
-        for (int ct = 0; ct < CT; ct++) st.O[ct][0] = st.O[ct][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int ct = 0; ct < CT; ct++) st.O[ct] = st.P[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
         st.m = -INFINITY;
         st.l = 0.f;
-        load_q_quarter<HD>(a, b, kvh, st.q);
-        if (src[3].cur < src[3].end) {
-            if (bf16seg)
-                walk_seg16_f32<HD, true, G>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3].cur, src[3].end, tk, st, new_row, knew, vnew);
-            else
-                walk_seg16_f32<HD, false, G>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3].cur, src[3].end, tk, st, new_row, knew, vnew);
+        st.ref = 0u;
+        st.own = 1.0f;
+#pragma unroll
+        for (int s = 0; s < SplitState<HD, G>::SETS; s++) {
+            st.accM[s] = 0.f;
+            st.place[s] = 1.0f;
         }
-        walk_class_f32<HD, 8, G>(a, sm, b, kvh, cls_len[2], cls_off[2], src[2].cur, src[2].end, tk, st);
-        walk_class_f32<HD, 4, G>(a, sm, b, kvh, cls_len[1], cls_off[1], src[1].cur, src[1].end, tk, st);
-        walk_class_f32<HD, 2, G>(a, sm, b, kvh, cls_len[0], cls_off[0], src[0].cur, src[0].end, tk, st);
-        hand_over_f32<HD, G>(sm, st);
+        if (src[3].cur < src[3].end) {
+            F32State<HD> st16;
+#pragma unroll
+            for (int ct = 0; ct < CT; ct++) st16.O[ct][0] = st16.O[ct][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+            st16.m = -INFINITY;
+            st16.l = 0.f;
+            load_q_quarter<HD>(a, b, kvh, st16.q);
+            if (bf16seg)
+                walk_seg16_f32<HD, true, G>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3].cur, src[3].end, tk, st16, new_row, knew, vnew);
+            else
+                walk_seg16_f32<HD, false, G>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3].cur, src[3].end, tk, st16, new_row, knew, vnew);
+            carry_on<HD, G>(st16, st);
+        }
+        walk_class_split<HD, 8, G, G == 4 ? 1 : 2>(a, sm, b, kvh, cls_len[2], cls_off[2], src[2].cur, src[2].end, tk, st);
+        walk_class_split<HD, 4, G, 2>(a, sm, b, kvh, cls_len[1], cls_off[1], src[1].cur, src[1].end, tk, st);
+        walk_class_split<HD, 2, G, 2>(a, sm, b, kvh, cls_len[0], cls_off[0], src[0].cur, src[0].end, tk, st);
+        hand_over_split<HD, G>(sm, st);
     } else {
         const float c_log2 = a.sm_scale * 1.4426950408889634f;
         WaveState<HD> st;
@@ -1262,7 +1276,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         // is needed to hand the partial to the workgroup that merges the splits
         store_through<CPL>(out + CPL * lane, num);
         if (lane == 0) {
-            const float ml2[2] = {F32 ? M : M * 0.6931471805599453f, L};       // (the fp32 walkers keep the reference in natural units)
+            const float ml2[2] = {F32 ? M : M * 0.6931471805599453f, L};       // (the walkers of one and four groups keep the reference in natural units)
             store_through<2>(out + HD, ml2);
         }
     }

@@ -85,13 +85,14 @@ def lib() -> C.CDLL:
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
-    if t is None:
-        return None
-    return t.data_ptr() if t.numel() > 0 else None
+    return None if t is None else t.data_ptr()      # (of an empty tensor: 0, a view's too)
+
+
+_DTYPE_ID = {torch.float32: F32, torch.bfloat16: BF16, torch.float16: F16}
 
 
 def _dtype_id(t: torch.Tensor) -> int:
-    return {torch.float32: F32, torch.bfloat16: BF16, torch.float16: F16}[t.dtype]
+    return _DTYPE_ID[t.dtype]
 
 
 def workspace_bytes(B=0, Hq=0, hd=0, max_splits=0, total_vis=0, total_txt=0, D=0) -> int:

@@ -779,8 +779,47 @@ __device__ __forceinline__ uint32_t pair_cost(int N)
     return N <= 256 ? 1u : min(32u, 2u * ((uint32_t)(N + 511) / 512u));
 }
 
+// Whole numbers of workgroups per sequence, so that none has the end of one sequence and the beginning of the next: a run
+// costs about PAIR_SLACK sixteens of rows however short it is (5 x 4704 rows of 3584, 64 text tokens, 5.7 sixteens a
+// workgroup: 95 us a call with equal shares of all rows, 62 so; 7 x 12544 at most, 200 tokens: 138 and 122).  The smallest share
+// from an equal one on that needs no more workgroups than there are, if one below PAIR_SLACK more does; a larger one costs more than the
+// runs it saves (50 short sequences: 67 us with up to 6, 79 with 3).  With more than 256 text tokens, whose products bind a
+// tile, a sequence gets no more workgroups than give them PAIR_LEAST sixteens, the smallest form's height: each reads all the text (4 x 3920 rows of
+// 3584, 300 tokens: 77 us, so 73).  b: this workgroup's sequence, -1 if it has nothing to do.
+constexpr uint32_t PAIR_SLACK = 6, PAIR_LEAST = 6;
+struct PairWhole { bool fits; int b, part, parts; };
+__device__ __forceinline__ PairWhole pair_whole(int B, const int32_t* vis_off, const int32_t* txt_off, uint32_t total)
+{
+    PairWhole p{false, -1, 0, 1};
+    if (B > 64) return p;                                 // (a lane per sequence)
+    const int lane = threadIdx.x & 63, l = min(lane, B - 1);
+    const int N = txt_off[l + 1] - txt_off[l];
+    const uint32_t T = lane < B ? (uint32_t)(vis_off[l + 1] - vis_off[l] + 15) >> 4 : 0u, cost = T * pair_cost(N), most = N > 256 ? (T + PAIR_LEAST - 1) / PAIR_LEAST : T;
+    const uint32_t equal = (total + gridDim.x - 1) / gridDim.x;
+    int n = 0, used = 0;
+#pragma unroll 1
+    for (uint32_t share = max(equal, 1u); share < equal + PAIR_SLACK && !p.fits; share++) {
+        n = (int)min(most, (cost + share - 1) / share);            // (at most gridDim.x + B of them together: exact as floats)
+        used = __builtin_amdgcn_readfirstlane((int)wave_sum((float)n));
+        p.fits = used <= (int)gridDim.x;
+    }
+    // (as many of the used ones on every XCD)
+    const int xcd = (int)blockIdx.x % 8, wg = gridDim.x % 8 == 0 ? xcd * used / 8 + (int)blockIdx.x / 8 : (int)blockIdx.x;
+    if (gridDim.x % 8 == 0 && wg >= (xcd + 1) * used / 8) return p;
+    int upto = 0;
+    for (int b = 0; p.fits && b < B; b++) {
+        const int m = __builtin_amdgcn_readlane(n, b);
+        if (wg < upto + m) {
+            p.b = b, p.part = wg - upto, p.parts = m;
+            break;
+        }
+        upto += m;
+    }
+    return p;
+}
+
 // The launch's rows, sixteen at a time, are laid out sequence after sequence on an axis of their cost; a workgroup takes an
-// equal share of it and walks it as runs of rows of one sequence, a run in tiles of equal height (as few as there can be).
+// equal share of it, or of a sequence (pair_whole), and walks it as runs of rows of one sequence, a run in tiles of equal height (as few as there can be).
 // Forms: what is left of 256 columns without text halves the column blocks and doubles the row groups.  Up to 8 sixteens of
 // rows steps of 128 elements (half the barriers, and only half the LDS buffers' rows are there).  The heights above are those
 // at which a workgroup's share of a batch falls into two or three tiles; products of rows that a tile does not have are the
@@ -800,14 +839,18 @@ __global__ __launch_bounds__(PA_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     const uint32_t wg = gridDim.x % 8 == 0 ? blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8 : blockIdx.x;
     const uint32_t lo = (uint32_t)((uint64_t)total * wg / gridDim.x), hi = (uint32_t)((uint64_t)total * (wg + 1) / gridDim.x);
     for (int k = tid; k < 2048; k += PA_THREADS) sm.R[k] = 0.f;     // (a run starts with a barrier)
+    const PairWhole whole = pair_whole(B, vis_off, txt_off, total);
+    if (whole.fits && whole.b < 0) return;
     uint32_t at = 0;                                      // cost of the sequences before b
-    for (int b = 0; b < B && at < hi; b++) {
+    const int last = whole.fits ? whole.b : B - 1;
+    for (int b = whole.fits ? whole.b : 0; b <= last && (whole.fits || at < hi); b++) {
         const int n0 = txt_off[b], N = txt_off[b + 1] - n0;
         const uint32_t T = tiles_of(b), cost = pair_cost(N), begin = at;
         at += T * cost;
-        if (at <= lo) continue;
+        if (at <= lo && !whole.fits) continue;
         auto edge = [&](uint32_t x) { return x <= begin ? 0 : (int)min(T, (x - begin + cost - 1) / cost); };
-        const int t0 = edge(lo), t1 = edge(hi);
+        const int t0 = whole.fits ? (int)((uint64_t)T * whole.part / whole.parts) : edge(lo);
+        const int t1 = whole.fits ? (int)((uint64_t)T * (whole.part + 1) / whole.parts) : edge(hi);
         if (t0 >= t1) continue;
         const int m0 = vis_off[b], M = vis_off[b + 1] - m0, row0 = t0 * 16, row_end = min(M, t1 * 16);
         const uint16_t* va = vis + (int64_t)m0 * D;

@@ -38,3 +38,27 @@ def test_pairwise_every_form(text, dtype, dim):
         want = _exact(vis, txt, n_vis, n_txt, window)
         worst = ((got.double() - want).abs() - 1e-4 * want.abs()).max().item()
         assert worst <= 1e-7, (per, worst)
+
+
+@pytest.mark.parametrize("n_vis,n_txt", [
+    ([4704] * 5, [64] * 5),                                   # 5.7 sixteens of rows a workgroup
+    ([3920, 700, 16, 2000], [300, 600, 20, 257]),             # few wide tiles: many workgroups without work
+    ([0, 37, 0, 5000, 15], [5, 0, 30, 256, 257]),             # sequences without rows or without text
+    ([16] * 64, [3] * 64),                                    # a lane per sequence, fewer workgroups than the chip has
+    ([48] * 65, [40] * 65),                                   # one sequence too many for that
+    ([90000, 1000, 1000, 33000], [10, 200, 10, 10]),          # large shares: equal ones that cross sequences
+])
+def test_pairwise_whole_workgroups(n_vis, n_txt):
+    """Whole numbers of workgroups per sequence where they fit, else equal shares of all rows: every row scored once."""
+    from paper_2605_02262_amd import binding as W
+    dim, window = 128, 16
+    gen = torch.Generator(device="cuda").manual_seed(len(n_vis))
+    vis = torch.randn(sum(n_vis), dim, generator=gen, device="cuda").add_(0.05).bfloat16()
+    txt = torch.randn(sum(n_txt), dim, generator=gen, device="cuda").add_(0.05).bfloat16()
+    starts = lambda v: torch.tensor([0, *torch.tensor(v).cumsum(0).tolist()], dtype=torch.int32, device="cuda")  # noqa: E731
+    n_win = [m // window for m in n_vis]
+    ctx = W.Context(W.workspace_bytes(len(n_vis), 0, 0, 0, sum(n_vis), sum(n_txt), dim))
+    got = W.wq_window_scores(ctx, vis, txt, starts(n_vis), starts(n_txt), torch.full((len(n_vis),), window, dtype=torch.int32, device="cuda"),
+                             starts(n_win), sum(n_vis), sum(n_txt), sum(n_win), algo=W.SCORE_PAIRWISE_MFMA)
+    want = _exact(vis, txt, n_vis, n_txt, window)
+    assert ((got.double() - want).abs() - 1e-4 * want.abs()).max().item() <= 1e-7

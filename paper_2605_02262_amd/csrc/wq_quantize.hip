@@ -42,6 +42,8 @@ __device__ __forceinline__ bool plan_class(int B, int64_t cap, Tokens n_of, int3
     }
     return over;
 }
+// n 16-bit rows between `at` and the next sequence's first one
+__device__ __forceinline__ bool rows_fit(int at, int next, int n, int64_t cap16) { return n <= next - at && (int64_t)at + n <= cap16 && at >= 0; }
 // ... and of the 16-bit rows: len[B], and their running count pre[B + 1]; begins(b): where sequence b's begin
 template <typename Tokens, typename Begins>
 __device__ __forceinline__ bool plan_rows(int B, int64_t cap16, Tokens n_of, Begins begins, int32_t* pre, int32_t* len)
@@ -51,8 +53,7 @@ __device__ __forceinline__ bool plan_rows(int B, int64_t cap16, Tokens n_of, Beg
     pre[0] = 0;
     for (int b = 0; b < B; b++) {
         int n = n_of(b);
-        const int at = begins(b), room = begins(b + 1) - at;
-        if (n > room || (int64_t)at + n > cap16 || at < 0) {
+        if (!rows_fit(begins(b), begins(b + 1), n, cap16)) {
             over = true;
             n = 0;
         }
@@ -63,33 +64,80 @@ __device__ __forceinline__ bool plan_rows(int B, int64_t cap16, Tokens n_of, Beg
     return over;
 }
 
+// Sum over the lanes up to and including this one
+__device__ __forceinline__ int64_t lanes_upto(int64_t x)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int o = 1; o < 64; o *= 2) {
+        const int64_t y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    return x;
+}
+
+// A wavefront per class and one for the 16-bit rows, a lane per sequence, 64 sequences at a time: bound by the round trip to the
+// tables (one sequence after the other it took 5.7 us for 8 sequences and 8.7 for 16).  Only where a class does not hold
+// everything does what a sequence gets depend on the ones before it: then plan_class does the class over.
 __global__ __launch_bounds__(256) void k_plan(int B, const int32_t* __restrict__ kv_off, const int32_t* __restrict__ win_size,
                                               const int32_t* __restrict__ win_off, const int32_t* __restrict__ seg_windows,
                                               wq_packed_kv pk, int32_t* __restrict__ pre16, uint32_t* __restrict__ status)
 {
-    const int tid = threadIdx.x;
-    if (tid < 3) {
-        if (plan_class(B, pk.cap[tid], [&](int b) { return seg_windows[4 * b + tid] * win_size[b]; }, pk.cls_off[tid], pk.cls_len[tid]))
-            atomicOr(status, WQ_DEV_CLASS_OVERFLOW);
-    } else if (tid == 3) {
-        auto rows = [&](int b) {
-            const int W = win_off[b + 1] - win_off[b];
-            return seg_windows[4 * b + 3] * win_size[b] + (kv_off[b + 1] - kv_off[b] - W * win_size[b]);
-        };
-        if (plan_rows(B, pk.cap16, rows, [&](int b) { return pk.off16[b]; }, pre16, pk.len16)) atomicOr(status, WQ_DEV_SEG16_OVERFLOW);
-    } else if (tid >= 64) {
-        for (int b = tid - 64; b < B; b += 192) pk.v_scale_max[b] = 0.f;      // k_v_scale_max raises it
+    const int tid = threadIdx.x, lane = tid & 63, c = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int b = tid; b < B; b += 256) pk.v_scale_max[b] = 0.f;               // k_v_scale_max raises it
+    int64_t run = 0;                                      // of the sequences before the 64
+    bool over = false;
+    if (c < 3) {
+        int32_t *off = pk.cls_off[c], *len = pk.cls_len[c];
+        const int64_t cap = pk.cap[c];
+        auto tokens = [&](int b) { return seg_windows[4 * b + c] * win_size[b]; };
+        if (lane == 0) off[0] = 0;
+        for (int b0 = 0; b0 < B; b0 += 64) {
+            const int b = b0 + lane, n = b < B ? tokens(b) : 0;
+            const int64_t upto = run + lanes_upto(pad32(n));
+            over = over || upto > cap;
+            if (b < B) {
+                len[b] = n;
+                off[b + 1] = (int32_t)upto;
+            }
+            run = __shfl(upto, 63, 64);
+        }
+        if (__builtin_amdgcn_ballot_w64(over) != 0) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");                // (what is written above is written over)
+            if (lane == 0 && plan_class(B, cap, tokens, off, len)) atomicOr(status, WQ_DEV_CLASS_OVERFLOW);
+        }
+    } else {
+        if (lane == 0) pre16[0] = 0;
+        for (int b0 = 0; b0 < B; b0 += 64) {
+            const int b = b0 + lane;
+            int n = 0;
+            if (b < B) {
+                const int size = win_size[b];
+                n = seg_windows[4 * b + 3] * size + (kv_off[b + 1] - kv_off[b] - (win_off[b + 1] - win_off[b]) * size);
+                if (!rows_fit(pk.off16[b], pk.off16[b + 1], n, pk.cap16)) {
+                    over = true;
+                    n = 0;
+                }
+            }
+            const int64_t upto = run + lanes_upto(n);
+            if (b < B) {
+                pk.len16[b] = n;
+                pre16[b + 1] = (int32_t)upto;
+            }
+            run = __shfl(upto, 63, 64);
+        }
+        if (over) atomicOr(status, WQ_DEV_SEG16_OVERFLOW);
     }
 }
 
-// maximum of a small unsigned value over the 64 lanes of a wavefront: four rotations inside the rows of 16 lanes (one
+// maximum of an unsigned value over the 64 lanes of a wavefront: four rotations inside the rows of 16 lanes (one
 // data-parallel-primitive instruction each, no LDS), then the four rows' results as scalars
 template <int CTRL>
 __device__ __forceinline__ uint32_t lanes_moved(uint32_t x)
 {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false);
 }
-__device__ __forceinline__ uint32_t lanes_max_u16(uint32_t x)
+__device__ __forceinline__ uint32_t lanes_max(uint32_t x)
 {
     x = max(x, lanes_moved<0x128>(x));             // row_ror:8, 4, 2, 1
     x = max(x, lanes_moved<0x124>(x));
@@ -115,28 +163,33 @@ __device__ __forceinline__ int64_t v_scale_slot(const wq_packed_kv& pk, int B, i
 constexpr int WQ_VS_PARTS = 16;
 __global__ __launch_bounds__(256) void k_v_scale_max(int B, wq_packed_kv pk)
 {
-    __shared__ float red[256];
+    __shared__ uint32_t s_top[4];
     const int b = blockIdx.x / WQ_VS_PARTS, part = blockIdx.x % WQ_VS_PARTS, tid = threadIdx.x;
-    float mx = 0.f;
+    const float* src[3];
+    int64_t count[3], longest = 0;
+#pragma unroll
     for (int c = 0; c < 3; c++) {
         const int64_t t0 = pk.cls_off[c][b] / 32, t1 = pk.cls_off[c][b + 1] / 32;
-        const int64_t first = v_scale_slot(pk, B, c, t0, 0), n = (t1 - t0) * pk.Hkv;
-        const int64_t per = (n + WQ_VS_PARTS - 1) / WQ_VS_PARTS, lo = part * per, hi = min(n, lo + per);
-        const float* src = pk.v_scale_max + first;
-        int64_t i = lo + tid;
-        for (; i + 768 < hi; i += 1024) {          // four loads in flight
-            const float a0 = src[i], a1 = src[i + 256], a2 = src[i + 512], a3 = src[i + 768];
-            mx = fmaxf(fmaxf(mx, a0), fmaxf(fmaxf(a1, a2), a3));
-        }
-        for (; i < hi; i += 256) mx = fmaxf(mx, src[i]);
+        const int64_t n = (t1 - t0) * pk.Hkv, per = (n + WQ_VS_PARTS - 1) / WQ_VS_PARTS, lo = part * per;
+        src[c] = pk.v_scale_max + v_scale_slot(pk, B, c, t0, 0) + lo;
+        count[c] = min(n, lo + per) - lo;
+        longest = max(longest, count[c]);
     }
-    red[tid] = mx;
+    float mx = 0.f;
+#pragma unroll 2
+    for (int64_t i = tid; i < longest; i += 256) { // (the three classes' loads in flight together)
+        float x[3];
+#pragma unroll
+        for (int c = 0; c < 3; c++) x[c] = i < count[c] ? src[c][i] : 0.f;
+        mx = fmaxf(fmaxf(mx, x[0]), fmaxf(x[1], x[2]));
+    }
+    const uint32_t top = lanes_max(__float_as_uint(mx));
+    if ((tid & 63) == 0) s_top[tid >> 6] = top;
     __syncthreads();
-    for (int o = 128; o >= 1; o >>= 1) {
-        if (tid < o) red[tid] = fmaxf(red[tid], red[tid + o]);
-        __syncthreads();
+    if (tid == 0) {
+        const uint32_t most = max(max(s_top[0], s_top[1]), max(s_top[2], s_top[3]));
+        if (most != 0u) atomicMax(reinterpret_cast<unsigned*>(pk.v_scale_max + b), most);
     }
-    if (tid == 0 && red[0] > 0.f) atomicMax(reinterpret_cast<unsigned*>(pk.v_scale_max + b), __float_as_uint(red[0]));
 }
 
 // bits -> class index
@@ -323,7 +376,7 @@ __device__ __forceinline__ void quantize_block(QuantSmem<HD>& sm, int blk, int k
     if (tid < 64) {
         uint32_t top = 0;
         for (int i = tid; i < 32 * G; i += 64) top = max(top, s_meta[1][i >> 5][i & 31] & 0xFFFFu);
-        top = lanes_max_u16(top);
+        top = lanes_max(top);
         if (tid == 0) {
             float* const slot = pk.v_scale_max + v_scale_slot(pk, B, C, blk, kvh);
             if constexpr (SMALL) __hip_atomic_store(slot, wq_f16_bits_to_float(top), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -81,3 +81,53 @@ def test_quantizing_a_small_call(dtype, hd, group, short):
             n = min(x.numel(), y.numel())
             assert torch.equal(x[:n], y[:n])
     assert (a.v_scale_max[:16] > 0).sum() >= 10
+
+
+@pytest.mark.parametrize("B", [17, 63, 64, 65, 150])
+@pytest.mark.parametrize("short", ["fits", "classes", "rows"])
+def test_plan_of_many_sequences(B, short):
+    """The tables of a larger call, 64 sequences at a time, against one sequence after the other; with capacities that a sequence in
+    the middle and the last ones do not fit (smaller ones behind them still do); the largest value scales against the metadata."""
+    from paper_2605_02262_amd import binding as W
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    heads, hd, group = 2, 64, 32
+    win = [(7 * b) % 40 + 1 for b in range(B)]
+    seg = [[(b + c) % 3 for c in range(4)] for b in range(B)]
+    seg[B // 2] = [9, 9, 9, 0]
+    n_win = [sum(s) for s in seg]
+    rows = [n * w + b % 4 for b, (n, w) in enumerate(zip(n_win, win))]
+    pad = lambda n: (n + 31) // 32 * 32  # noqa: E731
+    cap = [sum(pad(s[c] * w) for s, w in zip(seg, win)) for c in range(3)]
+    n16 = [s[3] * w + r - n * w for s, w, r, n in zip(seg, win, rows, n_win)]
+    room = list(n16)
+    if short == "classes":
+        cap = [max(32, c - pad(9 * win[B // 2]) - 64) for c in cap]
+    if short == "rows":
+        room[3] -= 1
+        room[-1] = max(0, room[-1] - 1)
+    K, V = (torch.randn(sum(rows), heads, hd, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    perm = torch.cat([torch.randperm(n, generator=gen, device="cuda") for n in n_win]).to(torch.int32)
+    ctx = W.Context(W.workspace_bytes(B))
+    pk = W.PackedKV(B, heads, hd, group, torch.bfloat16, cap, _offsets(room), fill=0)
+    W.wq_reorder_quantize(ctx, K, V, _table(_offsets(rows)), _table(win), _table(_offsets(n_win)), perm, _table(seg), sum(rows), pk)
+    want, top = 0, [0.0] * B
+    for c in range(3):
+        off, lens = [0], []
+        for s, w in zip(seg, win):
+            n = s[c] * w
+            if off[-1] + pad(n) > cap[c]:
+                n, want = 0, want | W.DEV_CLASS_OVERFLOW
+            lens.append(n)
+            off.append(off[-1] + pad(n))
+        assert pk.cls_off[c].tolist() == off and pk.cls_len[c].tolist() == lens, c
+        words = pk.meta[c].view(torch.int32).view(2, heads, cap[c] * (hd // group))[1]
+        scales = (words & 0xFFFF).to(torch.int16).view(torch.float16).float()
+        for b in range(B):
+            part = scales[:, off[b] * (hd // group):off[b + 1] * (hd // group)]
+            top[b] = max(top[b], float(part.max()) if part.numel() else 0.0)
+    fits = [r >= n for r, n in zip(room, n16)]
+    if not all(fits):
+        want |= W.DEV_SEG16_OVERFLOW
+    assert pk.len16.tolist() == [n if ok else 0 for n, ok in zip(n16, fits)]
+    assert pk.v_scale_max[:B].tolist() == top
+    assert ctx.device_status() == want

@@ -98,7 +98,10 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void k_vote(const uint8_t* __restri
 }
 
 // Widths and class order of a sequence in one workgroup: for sequences of a few hundred windows, where the second
-// launch of the other way costs more than the counting that it spreads over the chip.
+// launch of the other way costs more than the counting that it spreads over the chip.  Counting is a chain of LDS reads, so
+// the sixteen wavefronts share it: as many as there are chunks of 64 windows take all windows over one part of the keys (4 sequences
+// of 64, 128, 256 and 320 windows, a thread per window over all keys: 4.7, 6.6, 10.3, 12.3 us; so 3.7, 4.2, 6.3, 8.3).
+constexpr int ASSIGN_ONE_LAUNCH = 320;   // windows per sequence up to which k_assign is taken
 __global__ __launch_bounds__(ASSIGN_THREADS) void k_assign(const float* __restrict__ scores, const int32_t* __restrict__ win_off, int mode,
                                                            const int32_t* __restrict__ quota, const float* __restrict__ thresholds,
                                                            int top_bits, int pin_first, uint8_t* __restrict__ bits,
@@ -107,15 +110,15 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void k_assign(const float* __restri
 {
     // keys and widths are read four at a time in the counting loops; both arrays are padded to a multiple of four
     // (keys with -inf, which no key is smaller than and which never counts as an earlier equal; widths with 0)
-    __shared__ __align__(16) float s_key[WQ_MAX_WINDOWS + 4];
-    __shared__ __align__(16) uint8_t s_bits[WQ_MAX_WINDOWS + 4];
-    __shared__ int s_cnt[4];
-    __shared__ int s_chunk[ASSIGN_CHUNKS][4];
+    __shared__ __align__(16) float s_key[ASSIGN_ONE_LAUNCH + 4];
+    __shared__ __align__(16) uint8_t s_bits[ASSIGN_ONE_LAUNCH + 4];
+    __shared__ int s_rank[ASSIGN_ONE_LAUNCH + 4], s_cnt[4];
+    __shared__ int s_chunk[ASSIGN_ONE_LAUNCH / 64][4];
     const int b = blockIdx.x;
     const int w0 = win_off[b];
     int W = win_off[b + 1] - w0;
     const int tid = threadIdx.x;
-    if (W > max_windows) {                        // more windows than the caller's bound (itself at most WQ_MAX_WINDOWS): reported,
+    if (W > max_windows) {                        // more windows than the caller's bound (here at most ASSIGN_ONE_LAUNCH): reported,
         if (tid == 0) atomicOr(status, WQ_DEV_TOO_MANY_WINDOWS);      // and only the windows inside the bound are assigned
         W = max_windows;
     }
@@ -124,7 +127,13 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void k_assign(const float* __restri
     for (int i = tid; i < W4; i += ASSIGN_THREADS) {
         float s = i < W ? scores[w0 + i] : -INFINITY;
         s_key[i] = (s != s) ? -INFINITY : s;
+        s_rank[i] = 0;
         if (i >= W) s_bits[i] = 0;
+    }
+    int n_top = 0, n4 = 0;
+    if (mode != WQ_MODE_THRESHOLD) {
+        n_top = quota[3 * b];
+        n4 = quota[3 * b + 1];
     }
     __syncthreads();
 
@@ -137,7 +146,6 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void k_assign(const float* __restri
             s_bits[i] = (uint8_t)bt;
         }
     } else {
-        int n_top = quota[3 * b], n4 = quota[3 * b + 1];
         int first = 0;
         if (pin_first && W > 0) {
             first = 1;
@@ -148,22 +156,31 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void k_assign(const float* __restri
         n_top = min(max(n_top, 0), n);
         n4 = min(max(n4, 0), n - n_top);
         const float4* key4 = reinterpret_cast<const float4*>(s_key);
+        const int chunks = max(1, (W + 63) >> 6), parts = ASSIGN_THREADS / 64 / chunks, wave = tid >> 6, part = wave / chunks;
+        const int mine = (wave % chunks) * 64 + (tid & 63);
+        if (part < parts && mine < W) {
+            const int per = (W4 / 4 + parts - 1) / parts * 4, j0 = part * per, j1 = min(W4, j0 + per);
+            const float si = s_key[mine];
+            int r = 0;
+#pragma unroll 4
+            for (int j = j0; j < j1; j += 4) {
+                const float4 k = key4[j >> 2];
+                r += (k.x > si || (k.x == si && j < mine)) ? 1 : 0;
+                r += (k.y > si || (k.y == si && j + 1 < mine)) ? 1 : 0;
+                r += (k.z > si || (k.z == si && j + 2 < mine)) ? 1 : 0;
+                r += (k.w > si || (k.w == si && j + 3 < mine)) ? 1 : 0;
+            }
+            if (r != 0) atomicAdd(&s_rank[mine], r);
+        }
+        __syncthreads();
         for (int i = tid; i < W; i += ASSIGN_THREADS) {
             int bt;
             if (i < first) {
                 bt = top_bits;
             } else {
-                const float si = s_key[i];
-                int r = 0;
-                for (int j = 0; j < W4; j += 4) {
-                    const float4 k = key4[j >> 2];
-                    r += (k.x > si || (k.x == si && j < i)) ? 1 : 0;
-                    r += (k.y > si || (k.y == si && j + 1 < i)) ? 1 : 0;
-                    r += (k.z > si || (k.z == si && j + 2 < i)) ? 1 : 0;
-                    r += (k.w > si || (k.w == si && j + 3 < i)) ? 1 : 0;
-                }
+                int r = s_rank[i];
                 if (first) {            // the pinned window is not part of the ranking
-                    const float s0 = s_key[0];
+                    const float s0 = s_key[0], si = s_key[i];
                     r -= (s0 > si || s0 == si) ? 1 : 0;
                 }
                 bt = r < n_top ? top_bits : (r < n_top + n4 ? 4 : 2);
@@ -179,7 +196,6 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void k_assign(const float* __restri
 // quarter of the sequence's keys, how many windows rank before each of the 64 (several workgroups per sequence: a
 // sequence of W windows costs W^2 comparisons, which one compute unit alone takes 10 us and more to do from 500 windows on).
 constexpr int RANK_THREADS = 256;
-constexpr int ASSIGN_ONE_LAUNCH = 320;   // windows per sequence up to which k_assign is taken
 __global__ __launch_bounds__(RANK_THREADS) void k_rank(const float* __restrict__ scores, const int32_t* __restrict__ win_off, int mode,
                                                        const int32_t* __restrict__ quota, const float* __restrict__ thresholds,
                                                        int top_bits, int pin_first, uint8_t* __restrict__ bits, int max_windows)
@@ -325,8 +341,8 @@ int wq_launch_assign(wq_ctx* ctx, const float* scores, int B, const int32_t* win
                      const int32_t* quota, const float* thresholds, int top_bits, int pin_first, uint8_t* bits,
                      int32_t* perm, int32_t* seg_windows)
 {
-    // measured on MI355X: one workgroup per sequence takes 7.9 us + 43 ns per thousand pairs of windows (10.7 us at 256
-    // windows, 24.1 at 612), the two launches 13 us whatever the count
+    // measured on MI355X: one workgroup per sequence takes 6.3 us at 256 windows and 8.3 at 320, with the square of the windows
+    // from there on; the two launches 13 us whatever the count
     if (max_windows <= ASSIGN_ONE_LAUNCH) {
         hipLaunchKernelGGL(k_assign, dim3(B), dim3(ASSIGN_THREADS), 0, ctx->stream, scores, win_off, mode, quota, thresholds, top_bits,
                            pin_first, bits, perm, seg_windows, max_windows, wq_status_ptr(ctx));

@@ -131,3 +131,11 @@ def test_plan_of_many_sequences(B, short):
     assert pk.len16.tolist() == [n if ok else 0 for n, ok in zip(n16, fits)]
     assert pk.v_scale_max[:B].tolist() == top
     assert ctx.device_status() == want
+
+
+@pytest.mark.parametrize("sizes", [(1, 2, 3), (63, 64, 65), (16,), (128, 129, 0), (191, 193), (256, 257), (319,)])
+def test_widths_counted_by_parts(sizes):
+    """Sequences of up to 320 windows, one to five chunks of 64 that 16, 8, 5, 4 and 3 parts of the keys are counted for: bit for
+    bit against the oracle, ties, NaN and infinities among the scores."""
+    from tests.test_gpu_parity import test_assign_bits_few_and_many_windows as check
+    check(sizes)

@@ -287,17 +287,15 @@ __device__ __forceinline__ half8 shifted(half8 raw, const half2v (&c512)[4], int
 // rounded once)
 __device__ __forceinline__ uint32_t scaled_f16(float x, float y)
 {
-    uint32_t r;
-    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(r) : "v"(x), "s"(1.0f / 4096.0f));
-    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(r) : "v"(y), "s"(1.0f / 4096.0f));
-    return r;
+    const half2v r = {(_Float16)fmaf(x, 1.0f / 4096.0f, 0.f), (_Float16)fmaf(y, 1.0f / 4096.0f, 0.f)};
+    uint32_t u = __builtin_bit_cast(uint32_t, r);
+    asm("" : "+v"(u));                             // (the second one is read where it lies, not computed again into a low half)
+    return u;
 }
 __device__ __forceinline__ uint32_t rest_f16(float x, float y, uint32_t h)
 {
-    uint32_t r;
-    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "s"(-4096.0f), "v"(x));
-    asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(r) : "v"(h), "s"(-4096.0f), "v"(y));
-    return r;
+    const half2v r = {(_Float16)fmaf(f16lo(h), -4096.0f, x), (_Float16)fmaf(f16hi(h), -4096.0f, y)};
+    return __builtin_bit_cast(uint32_t, r);
 }
 
 template <int HD, int BITS, int G>

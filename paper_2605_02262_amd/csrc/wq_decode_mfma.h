@@ -63,25 +63,15 @@ __device__ __forceinline__ floatx4 mfma(half8 a, half8 b, floatx4 c)
 __device__ __forceinline__ float f16lo(uint32_t w) { return wq_f16_bits_to_float(w & 0xFFFFu); }
 __device__ __forceinline__ float f16hi(uint32_t w) { return wq_f16_bits_to_float(w >> 16); }
 
-// largest of three without the quieting moves that fmaxf brings along (inputs here are never signalling NaNs)
-__device__ __forceinline__ float max3(float a, float b, float c)
-{
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
+// largest of three (inputs here are never signalling NaNs: results of additions)
+__device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
-// (f16 in the low half of w) * p, rounded to f16, into the low / the high half of a register
-__device__ __forceinline__ uint32_t mul_f16lo_to_lo(uint32_t w, float p)
+// (f16 in the low half of u) * p and (f16 in the low half of w) * q, each rounded to f16 (a mixed-precision fused multiply-add
+// per product; left to the compiler, which keeps the distance that the matrix cores need behind a vector instruction)
+__device__ __forceinline__ uint32_t mul_f16lo(uint32_t u, float p, uint32_t w, float q)
 {
-    uint32_t r;
-    asm("v_fma_mixlo_f16 %0, %1, %2, 0 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(w), "v"(p));
-    return r;
-}
-__device__ __forceinline__ uint32_t mul_f16lo_to_hi(uint32_t acc, uint32_t w, float p)
-{
-    asm("v_fma_mixhi_f16 %0, %1, %2, 0 op_sel_hi:[1,0,0]" : "+v"(acc) : "v"(w), "v"(p));
-    return acc;
+    const half2v r = {(_Float16)fmaf(f16lo(u), p, 0.f), (_Float16)fmaf(f16lo(w), q, 0.f)};
+    return __builtin_bit_cast(uint32_t, r);
 }
 
 // rotate by 8 lanes inside each row of 16 lanes: lane (g,h) <-> lane (1-g,h)
@@ -599,7 +589,7 @@ __device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD
         uint32_t bp[4];
 #pragma unroll
         for (int v = 0; v < 4; v++)                // slots (2v, 2v+1) = (tile 0, tile 1) token 4j+v
-            bp[v] = mul_f16lo_to_hi(mul_f16lo_to_lo(vw[v], p[v]), vw[4 + v], p[4 + v]);
+            bp[v] = mul_f16lo(vw[v], p[v], vw[4 + v], p[4 + v]);
         const half8 Bp = as_half8(bp[0], bp[1], bp[2], bp[3]);
         // ---- values ----
 #pragma unroll

@@ -189,7 +189,7 @@ struct SplitState {
     float l;                // sum of the weights of lane group j's tokens
     float accM[SETS];       // ... of the weights times the offsets of the groups that the lane's column is for
     float place[SETS];      // power of two that brings these groups' weights times scales to at most 2^15
-    uint32_t ref;           // the largest scale (its f16 bits) of group j that the places leave room for; 0: none seen
+    uint32_t ref;           // the largest magnitude of a scale (its f16 bits) of group j that the places leave room for; 0: none seen
     float own;              // group j's place
 };
 
@@ -356,8 +356,9 @@ __device__ __forceinline__ void walk_class_split(const DecodeArgs& a, F32Smem<HD
     for (int s = 0; s < SETS; s++) qs[s] = sm.qx[1 + s][lane] * (1.0f / 512.0f);
 
     auto compute = [&](int n, const F& f) {
-        // ---- a scale beyond what the places leave room for moves them, twice as far (rarely: the first block does) ----
-        uint32_t top = max(f.vm[0] & 0xFFFFu, f.vm[1] & 0xFFFFu);
+        // ---- a scale beyond what the places leave room for moves them, twice as far (rarely: the first block does).  Magnitudes:
+        //      a group of nearly equal fp32 values can have a negative scale ----
+        uint32_t top = max(f.vm[0] & 0x7FFFu, f.vm[1] & 0x7FFFu);
         if (__builtin_amdgcn_ballot_w64(top > st.ref) != 0) {
             auto moved = [](uint32_t x, auto ctrl) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, 0xF, 0xF, false); };
             top = max(top, moved(top, std::integral_constant<int, 0x128>{}));

@@ -350,7 +350,8 @@ __device__ __forceinline__ void walk_class_split(const DecodeArgs& a, F32Smem<HD
             Bq[s][r] = as_half8(mine ? q.x : 0u, mine ? q.y : 0u, mine ? q.z : 0u, mine ? q.w : 0u);
         }
     }
-    const float cexp = a.sm_scale * sm.qx[0][lane] * 512.0f;
+    // (a finite positive number whatever the softmax scale: -inf and 0 are among the logits that it multiplies)
+    const float cexp = __builtin_amdgcn_fmed3f(a.sm_scale * sm.qx[0][lane] * 512.0f, 0x1p-126f, 0x1.fffffep127f);
     float qs[SETS];
 #pragma unroll
     for (int s = 0; s < SETS; s++) qs[s] = sm.qx[1 + s][lane] * (1.0f / 512.0f);

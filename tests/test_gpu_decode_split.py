@@ -53,3 +53,30 @@ def test_places_and_offsets(hd, g, shape):
         rms = {a: np.linalg.norm(x - o.out) for a, x in got.items()}
         assert rms[W.DECODE_AUTO] <= 2 * rms[W.DECODE_GENERIC], splits
     assert run.ctx.device_status() == 0
+
+
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.F16])
+@pytest.mark.parametrize("hd,g", SHAPES)
+def test_softmax_scales_of_any_size(hd, g, dtype):
+    """Softmax scales from fp32's smallest to its largest number, with queries of zeros and of the type's smallest and largest magnitudes:
+    the power of two that brings a query into f16, times the softmax scale, can lie outside fp32's range.  Logits that are zero, or
+    nothing beside one, weigh all tokens alike, those past a class's end (every class here has a partial block) not at all.  2^-18: fp32
+    sums of 300 terms that cancel to a tenth."""
+    from oracle import wq_oracle as O
+    from paper_2605_02262_amd import binding as W
+    from tests import wq_harness as H
+    specs = [synth.SeqSpec(9, 33, 33, 5, (3, 3, 3)), synth.SeqSpec(3, 17, 17, 40, (1, 1, 1))]
+    w = synth.Workload("scale", dtype, dtype, 14, 2, hd, g, 64, 0.5, specs, 100 + hd + g, pin_first=0)
+    sc = np.random.default_rng(1).standard_normal(18).astype(np.float32)
+    small, large = (2.0 ** -126, 2.0 ** 120) if dtype == synth.BF16 else (2.0 ** -24, 2.0 ** 14)
+    for sm, q_to, k_to in ((2.0 ** -126, 0.0, 1.0), (2.0 ** -60, 0.0, 1.0), (2.0 ** -60, small, 1.0), (2.0 ** 100, 0.0, 1.0), (2.0 ** 126, large, 0.0)):
+        bt = synth.batch(w, with_embeddings=False)
+        bt.q = np.sign(bt.q) * np.float32(q_to)
+        bt.K *= np.float32(k_to)
+        run = H.run_gpu(bt, splits=4, with_scores=False, scores_override=sc)
+        want = O.decode_attention(np.zeros_like(bt.q), H.run_oracle(bt, scores_override=sc, with_scores=False).pk, 1.0)      # (equal logits)
+        q = H.to_dev(bt.q, dtype)
+        for algo in (W.DECODE_AUTO, W.DECODE_GENERIC):
+            got = W.wq_decode_attention(run.ctx, q, run.pk, sm, 4, 400, algo).cpu().numpy()
+            assert np.isfinite(got).all(), (sm, q_to, algo)
+            assert _group_errors(got, want, g).max() <= 2.0 ** -18, (sm, q_to, algo)

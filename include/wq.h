@@ -206,7 +206,7 @@ typedef struct {
     int32_t* len16;        /* device [B], written by wq_reorder_quantize, bumped by the caller on append    */
     float* v_scale_max;    /* device [wq_v_scale_floats(B, Hkv, cap)]: entry b, written by wq_reorder_quantize (and
                             * set to 0 by wq_dequantize in its destination, where B entries are enough), is the largest
-                            * scale of a value (V) group among sequence b's quantized tokens, 0 if it has none: with
+                            * magnitude of the scale of a value (V) group among sequence b's quantized tokens, 0 if it has none: with
                             * hd/group == 2 the matrix-core decode kernel places its fp16 weights by it.  The entries behind the first
                             * B (one per 32-token block and KV head) are wq_reorder_quantize's scratch for finding it */
 } wq_packed_kv;

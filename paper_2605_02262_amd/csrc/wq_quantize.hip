@@ -371,11 +371,11 @@ __device__ __forceinline__ void quantize_block(QuantSmem<HD>& sm, int blk, int k
     __syncthreads();
 
     // ---- the block's largest value scale (the decode kernel places its fp16 weights by the sequence's largest one): the
-    //      scales are the low halves of the V metadata words, zero for tokens past the end; positive f16 values order like
-    //      their bit patterns.  One plain store per workgroup into the table's scratch part; k_v_scale_max collects them ----
+    //      scales are the low halves of the V metadata words, zero for tokens past the end; their magnitudes (a group of
+    //      nearly equal fp32 values can have a negative scale) order like their bit patterns.  One plain store per workgroup into the table's scratch part; k_v_scale_max collects them ----
     if (tid < 64) {
         uint32_t top = 0;
-        for (int i = tid; i < 32 * G; i += 64) top = max(top, s_meta[1][i >> 5][i & 31] & 0xFFFFu);
+        for (int i = tid; i < 32 * G; i += 64) top = max(top, s_meta[1][i >> 5][i & 31] & 0x7FFFu);
         top = lanes_max(top);
         if (tid == 0) {
             float* const slot = pk.v_scale_max + v_scale_slot(pk, B, C, blk, kvh);

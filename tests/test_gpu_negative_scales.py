@@ -12,7 +12,7 @@ assert float(np.float16(0.3)) > 0.3
 
 
 def _batch(hd, g, frames=40):
-    specs = [synth.SeqSpec(frames, 64, 64, 21, (frames // 4, 15, frames - frames // 4 - 15)), synth.SeqSpec(7, 64, 64, 3, (0, 0, 7)), synth.SeqSpec(3, 33, 33, 40, (1, 1, 1))]
+    specs = [synth.SeqSpec(frames, 64, 64, 21, (frames // 4, frames // 4, frames - 2 * (frames // 4))), synth.SeqSpec(7, 64, 64, 3, (0, 0, 7)), synth.SeqSpec(3, 33, 33, 40, (1, 1, 1))]
     w = synth.Workload("negative", synth.F32, synth.F16, 14, 2, hd, g, 64, 0.5, specs, 700 + hd + g, pin_first=0)
     return synth.batch(w, with_embeddings=False)
 
@@ -49,4 +49,24 @@ def test_places_of_one_and_four_groups(hd, g, low):
         assert _group_errors(got[W.DECODE_AUTO], o.out, g).max() <= max(4 * vector, 2.0 ** -20), splits
         rms = {a: np.linalg.norm(x - o.out) for a, x in got.items()}
         assert rms[W.DECODE_AUTO] <= 2 * rms[W.DECODE_GENERIC], splits
+    assert run.ctx.device_status() == 0
+
+
+@pytest.mark.parametrize("frames", [20, 200], ids=["one launch", "three launches"])
+@pytest.mark.parametrize("hd,g", [(128, 64), (64, 32)])
+def test_largest_value_scale_of_two_groups(hd, g, frames):
+    """A token of 0.3 in the first group of every 16th token of ordinary values, the rest of the values 2^-14 of them: a block is in the
+    table by its largest scale whatever their signs, and the f16 weights are placed by that one.  (With a negative scale the largest
+    bit pattern of its block, such blocks were left out and their weights overflowed.)"""
+    from tests import wq_harness as H
+    bt = _batch(hd, g, frames)
+    n = bt.V.shape[0] // 2
+    bt.V[n:] = synth.round_to(bt.V[n:] * np.float32(2.0 ** -14), synth.F16)        # (rows that stay 16-bit are compared bit for bit)
+    bt.V[:n:16, :, :g] = np.float32(0.3)
+    sc = np.random.default_rng(7).standard_normal(int(bt.t.win_off[-1])).astype(np.float32)
+    run = H.run_gpu(bt, splits=16, with_scores=False, scores_override=sc)
+    o = H.run_oracle(bt, scores_override=sc, with_scores=False)
+    _negative(o, 0.01)
+    H.assert_packed_equal(run, o)
+    assert H.attention_error(run.out.cpu().numpy(), o.out) <= H.ATTN_TOL
     assert run.ctx.device_status() == 0

@@ -158,7 +158,7 @@ def assert_packed_equal(g: GpuRun, o: OracleRun):
             t0, t1 = int(o.pk.cls_off[c][bb]) // 16, int(o.pk.cls_off[c][bb + 1]) // 16
             if t1 > t0:
                 sc = (v_meta[:, t0:t1] & 0xFFFF).astype(np.uint16).view(np.float16).astype(np.float32)
-                largest_v_scale[bb] = max(largest_v_scale[bb], float(sc.max()))
+                largest_v_scale[bb] = max(largest_v_scale[bb], float(np.abs(sc).max()))
     assert np.array_equal(g.pk.len16.cpu().numpy(), o.pk.len16), "len16"
     assert np.array_equal(g.pk.v_scale_max[:B].cpu().numpy(), largest_v_scale), "largest value scale per sequence"
     k16 = g.pk.k16.float().cpu().numpy()

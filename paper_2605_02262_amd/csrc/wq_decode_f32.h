@@ -47,18 +47,16 @@
 
 namespace {
 
-// cost of a 32-token block of the 2-, 4-, 8- and 16-bit class, in the unit of WQ_BLOCK_COST
-#ifndef WQ_COSTS_F32
-#define WQ_COSTS_F32 130, 140, 170, 400
-#endif
-constexpr int WQ_BLOCK_COST_F32[4] = {WQ_COSTS_F32};
+// Cost of a 32-token block of the 2-, 4-, 8- and 16-bit class, in the unit of WQ_BLOCK_COST: the quantized classes differ by their
+// unpacking and little else.  us per call with these, with those of two groups (100, 130, 230, 500), with 140 for all quantized ones,
+// with 250 for the 16-bit class: 8 x 12795 tokens, group 32: 21.0, 24.8, 22.7, 22.4; group 128: 19.1, 22.6, 20.5, 21.3; 4 x 50676,
+// group 32: 32.1, 36.3, 33.5, 32.6; 20 ragged ones of up to 15931: 37.5, 46.6, 38.4, 37.6; 16 x 6545, heads of 64: 10.5, 11.6, 10.5, 10.5
+constexpr int WQ_BLOCK_COST_F32[4] = {130, 140, 170, 400};
 template <int HD, int G>
 constexpr int block_cost(int c)
 {
     return G != 2 ? WQ_BLOCK_COST_F32[c] : HD == 64 ? WQ_BLOCK_COST_64[c] : WQ_BLOCK_COST[c];
 }
-
-typedef float floatx2v __attribute__((ext_vector_type(2)));
 
 template <int HD, int G>
 struct F32Smem {

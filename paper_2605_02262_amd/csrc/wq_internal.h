@@ -34,10 +34,7 @@ constexpr int WQ_BLOCK_COST[4] = {100, 130, 230, 500};
 // ... with heads of 64: half the bytes, but nearly the same instructions, which then bound every class alike.  With the costs of
 // heads of 128: 8 x 12800 tokens, 8 KV heads, a step of 12 layers 312 us, with these 272; 4 x 50676: 61.2 us a call -> 53.8;
 // 2 x 39400, 2 KV heads: 24.4 -> 22.0; 1 x 6400: 8.2 -> 7.7
-#ifndef WQ_COSTS_64
-#define WQ_COSTS_64 100, 106, 125, 250
-#endif
-constexpr int WQ_BLOCK_COST_64[4] = {WQ_COSTS_64};
+constexpr int WQ_BLOCK_COST_64[4] = {100, 106, 125, 250};
 constexpr int WQ_MAX_WINDOWS = 8192;   // windows per sequence handled by the ranking kernel
 
 inline int wq_fail(wq_ctx* ctx, int code, const char* fmt, ...)

@@ -496,7 +496,7 @@ __global__ __launch_bounds__(256) void k_quantize_all(const T* __restrict__ K, c
                                                       const int32_t* __restrict__ kv_off, const int32_t* __restrict__ win_size,
                                                       const int32_t* __restrict__ win_off, const int32_t* __restrict__ perm,
                                                       const int32_t* __restrict__ seg_windows, const int32_t* __restrict__ pre16,
-                                                      wq_packed_kv pk, unsigned n, unsigned n0, unsigned n1, uint32_t* __restrict__ status)
+                                                      wq_packed_kv pk, unsigned n, unsigned n0, unsigned n1)
 {
     __shared__ QuantSmem<HD> sm;
     unsigned w = blockIdx.y * gridDim.x + blockIdx.x;
@@ -917,7 +917,7 @@ int run(wq_ctx* ctx, const void* K_, const void* V_, int B, const int32_t* kv_of
                        wq_status_ptr(ctx));
     if (n + wgs16 > 0)
         hipLaunchKernelGGL((k_quantize_all<T, HD>), grid_of(n + wgs16), dim3(256), 0, st, K, V, B, pk->group, kv_off, win_size,
-                           win_off, perm, seg_windows, pre16, *pk, (unsigned)n, n0, n1, wq_status_ptr(ctx));
+                           win_off, perm, seg_windows, pre16, *pk, (unsigned)n, n0, n1);
     if (B > 0) hipLaunchKernelGGL(k_v_scale_max, dim3((unsigned)B * WQ_VS_PARTS), dim3(256), 0, st, B, *pk);
     WQ_HIP_CHECK(ctx, hipGetLastError());
     return WQ_OK;

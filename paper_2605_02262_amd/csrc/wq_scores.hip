@@ -21,14 +21,15 @@ constexpr int WAVE = 64;
 constexpr int WQ_TS_ROWS = 2;
 #define WQ_TS_UNROLL 2
 
-// Sum over the wavefront, in every lane: lane ^ 32, ^ 16, ^ 8, ^ 4, ^ 2, ^ 1 in turn, by moves between registers (exchanging
-// through LDS takes six round trips).  Once lanes that differ in the bits above are equal, a rotation by 8, 4, 2, 1 inside a
-// row of 16 lanes brings the value of lane ^ 8, ^ 4, ^ 2, ^ 1.
+// x of the lane that a data-parallel-primitive control pairs this lane with (rows of 16 lanes)
 template <int CTRL>
 __device__ __forceinline__ float lanes_moved(float x)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
 }
+// Sum over the wavefront, in every lane: lane ^ 32, ^ 16, ^ 8, ^ 4, ^ 2, ^ 1 in turn, by moves between registers (exchanging
+// through LDS takes six round trips).  Once lanes that differ in the bits above are equal, a rotation by 8, 4, 2, 1 inside a
+// row of 16 lanes brings the value of lane ^ 8, ^ 4, ^ 2, ^ 1.
 __device__ __forceinline__ float wave_sum(float v)
 {
     const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -444,13 +445,6 @@ __device__ __forceinline__ int pair_place(int r, int c)
     return KS == 128 ? c ^ (r & 15) : c ^ ((r >> 1) & 7);
 }
 
-// x of the lane that a data-parallel-primitive control pairs this lane with (rows of 16 lanes)
-template <int CTRL>
-__device__ __forceinline__ float pair_lane(float x)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
-}
-
 // One stage of a sum over the 16 lanes of a row, for NV values per lane at once: the lane and its partner (which
 // differ in `upper`) split the values between them, each adding the other's half of the pair's sums to its own, so
 // the lane is left with NV / 2 values, v[0 .. NV/2): the lower half of the indices if !upper, else the upper half.
@@ -463,10 +457,10 @@ __device__ __forceinline__ void pair_halve(float (&v)[32], bool upper)
         for (int j = 0; j < NV / 2; j++) {
             const float give = upper ? v[j] : v[j + NV / 2];
             const float keep = upper ? v[j + NV / 2] : v[j];
-            v[j] = keep + pair_lane<CTRL>(give);
+            v[j] = keep + lanes_moved<CTRL>(give);
         }
     } else {
-        v[0] += pair_lane<CTRL>(v[0]);
+        v[0] += lanes_moved<CTRL>(v[0]);
     }
 }
 

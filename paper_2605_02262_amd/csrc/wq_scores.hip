@@ -815,9 +815,11 @@ __device__ __forceinline__ PairWhole pair_whole(int B, const int32_t* vis_off, c
 // The launch's rows, sixteen at a time, are laid out sequence after sequence on an axis of their cost; a workgroup takes an
 // equal share of it, or of a sequence (pair_whole), and walks it as runs of rows of one sequence, a run in tiles of equal height (as few as there can be).
 // Forms: what is left of 256 columns without text halves the column blocks and doubles the row groups.  Up to 8 sixteens of
-// rows steps of 128 elements (half the barriers, and only half the LDS buffers' rows are there).  The heights above are those
-// at which a workgroup's share of a batch falls into two or three tiles; products of rows that a tile does not have are the
-// price of a height that is not listed.
+// rows steps of 128 elements (half the barriers, and only half the LDS buffers' rows are there).  Every height that more than 8
+// sixteens in tiles of at most 16 can come to has a form of its own (with those of even height and 13 only, shares of 18, 22 and 30 sixteens, tiles of
+// 9, 11 and 15, took 148, 170 and 214 us a call instead of 145, 164 and 208: 8 sequences, 200 text tokens, D 3584).  Lower
+// shares go to the next of 4 and 8 (6, 7 and 8 with more than 256 text tokens): the same sequences in shares of 1 to 8 sixteens
+// take 47, 48, 51, 55, 64, 69, 74 and 79 us.
 template <bool BF>
 __global__ __launch_bounds__(PA_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_pair_mfma(const uint16_t* __restrict__ vis, const uint4* __restrict__ packed_txt,
                                                           const float* __restrict__ inv_tnorm, int D, int B,
@@ -859,11 +861,14 @@ __global__ __launch_bounds__(PA_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
             else if (h == 7) WQ_PAIR(7, 4, 8, 128);
             else WQ_PAIR(6, 4, 8, 128);
         } else if (N > 128) {
-            if (h > 14) WQ_PAIR(16, 2, 8, 64);
-            else if (h > 13) WQ_PAIR(14, 2, 8, 64);
-            else if (h > 12) WQ_PAIR(13, 2, 8, 64);
-            else if (h > 10) WQ_PAIR(12, 2, 8, 64);
-            else if (h > 8) WQ_PAIR(10, 2, 8, 64);
+            if (h == 16) WQ_PAIR(16, 2, 8, 64);
+            else if (h == 15) WQ_PAIR(15, 2, 8, 64);
+            else if (h == 14) WQ_PAIR(14, 2, 8, 64);
+            else if (h == 13) WQ_PAIR(13, 2, 8, 64);
+            else if (h == 12) WQ_PAIR(12, 2, 8, 64);
+            else if (h == 11) WQ_PAIR(11, 2, 8, 64);
+            else if (h == 10) WQ_PAIR(10, 2, 8, 64);
+            else if (h == 9) WQ_PAIR(9, 2, 8, 64);
             else if (h > 4) WQ_PAIR(8, 2, 8, 128);
             else WQ_PAIR(4, 2, 8, 128);
         } else if (N > 64) {

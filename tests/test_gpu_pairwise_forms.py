@@ -26,7 +26,7 @@ def test_pairwise_every_form(text, dtype, dim):
     from paper_2605_02262_amd import binding as W
     gen = torch.Generator(device="cuda").manual_seed(text)
     window = 16
-    for per in ([1, 4, 5, 8, 9, 10, 12, 13, 14, 16, 17] if 128 < text <= 256 else [1, 6, 7, 8, 16, 17]):
+    for per in ([1, 4, 5, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17] if 128 < text <= 256 else [1, 6, 7, 8, 16, 17]):
         n_vis, n_txt = [per * 4096 - 5, 37], [text, 300]
         vis = torch.randn(sum(n_vis), dim, generator=gen, device="cuda").add_(0.05).to(dtype)
         txt = torch.randn(sum(n_txt), dim, generator=gen, device="cuda").add_(0.05).to(dtype)

@@ -194,7 +194,7 @@ __global__ __launch_bounds__(ASSIGN_THREADS) void k_assign(const float* __restri
 
 // Widths by rank or threshold.  A workgroup takes 64 windows of a sequence; its four wavefronts count, each over a
 // quarter of the sequence's keys, how many windows rank before each of the 64 (several workgroups per sequence: a
-// sequence of W windows costs W^2 comparisons, which one compute unit alone takes 10 us and more to do from 500 windows on).
+// sequence of W windows costs W^2 comparisons, which takes one compute unit alone 10 us from 380 windows on).
 constexpr int RANK_THREADS = 256;
 __global__ __launch_bounds__(RANK_THREADS) void k_rank(const float* __restrict__ scores, const int32_t* __restrict__ win_off, int mode,
                                                        const int32_t* __restrict__ quota, const float* __restrict__ thresholds,
@@ -341,8 +341,9 @@ int wq_launch_assign(wq_ctx* ctx, const float* scores, int B, const int32_t* win
                      const int32_t* quota, const float* thresholds, int top_bits, int pin_first, uint8_t* bits,
                      int32_t* perm, int32_t* seg_windows)
 {
-    // measured on MI355X: one workgroup per sequence takes 6.3 us at 256 windows and 8.3 at 320, with the square of the windows
-    // from there on; the two launches 13 us whatever the count
+    // measured on MI355X, 1 to 32 sequences: one workgroup per sequence takes 6.2 us at 256 windows, 8.1 at 320, 10.3 at 384, 14.6 at
+    // 512; the two launches 6.5, 7.3, 7.8 and 8.8 where the stream has work queued, 11 whatever the count where a call waits for
+    // its launches to be submitted.  The line lies between the two crossings (about 270 and 400 windows)
     if (max_windows <= ASSIGN_ONE_LAUNCH) {
         hipLaunchKernelGGL(k_assign, dim3(B), dim3(ASSIGN_THREADS), 0, ctx->stream, scores, win_off, mode, quota, thresholds, top_bits,
                            pin_first, bits, perm, seg_windows, max_windows, wq_status_ptr(ctx));

@@ -21,11 +21,12 @@ def _exact(vis, txt, n_vis, n_txt, window):
 @pytest.mark.parametrize("text", [1, 32, 33, 64, 65, 128, 129, 256, 257])
 def test_pairwise_every_form(text, dtype, dim):
     """One sequence beside a short one of another text length; `per` sixteens of rows for each of the 256 workgroups reach every
-    tile height (1 to 16 and one more, which takes two tiles), the odd rows at the end a partial tile of 16.  dim 128: fewer
-    steps than the loads are sent ahead; 384: three times as many.  float64 reference; fp32 sums of a few hundred terms."""
+    tile height (1 to 16 and one more, which takes two tiles), the odd rows at the end a partial tile of 16.  Windows of one row, so
+    that every row's score is looked at.  dim 128: fewer steps than the loads are sent ahead; 384: three times as many.  float64
+    reference; fp32 sums of a few hundred terms."""
     from paper_2605_02262_amd import binding as W
     gen = torch.Generator(device="cuda").manual_seed(text)
-    window = 16
+    window = 1
     for per in ([1, 4, 5, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17] if 128 < text <= 256 else [1, 6, 7, 8, 16, 17]):
         n_vis, n_txt = [per * 4096 - 5, 37], [text, 300]
         vis = torch.randn(sum(n_vis), dim, generator=gen, device="cuda").add_(0.05).to(dtype)
@@ -49,9 +50,9 @@ def test_pairwise_every_form(text, dtype, dim):
     ([90000, 1000, 1000, 33000], [10, 200, 10, 10]),          # large shares: equal ones that cross sequences
 ])
 def test_pairwise_whole_workgroups(n_vis, n_txt):
-    """Whole numbers of workgroups per sequence where they fit, else equal shares of all rows: every row scored once."""
+    """Whole numbers of workgroups per sequence where they fit, else equal shares of all rows: every row scored once (windows of one row)."""
     from paper_2605_02262_amd import binding as W
-    dim, window = 128, 16
+    dim, window = 128, 1
     gen = torch.Generator(device="cuda").manual_seed(len(n_vis))
     vis = torch.randn(sum(n_vis), dim, generator=gen, device="cuda").add_(0.05).bfloat16()
     txt = torch.randn(sum(n_txt), dim, generator=gen, device="cuda").add_(0.05).bfloat16()

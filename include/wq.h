@@ -267,8 +267,10 @@ int wq_dequantize(wq_ctx* ctx, int B, const wq_packed_kv* src, const wq_packed_k
  * bound on tokens of any one sequence (used by the automatic split and by WQ_DECODE_BY_LENGTH; a wrong value costs speed,
  * not correctness).  algo: WQ_DECODE_AUTO picks the
  * matrix-core kernel when hd/group == 2, or for other groups when the query is a 16-bit type and the cache is within that
- * kernel's limits (it then computes in fp32 as the generic kernel does: keys and values dequantized by one fused
- * multiply-add, fp32 queries, weights and sums), else the generic one; WQ_DECODE_MFMA takes hd/group == 2 only.
+ * kernel's limits (its errors are then those of fp32 arithmetic: codes, scales and minima are exact, sums fp32; a query
+ * entry is exact down to 2^-28 of its head's largest one and off by at most 2^-39 of that one below; a softmax weight times a value
+ * scale keeps 23 bits down to 2^-29 of the largest such product that its group leaves room for), else the generic one, which
+ * dequantizes with one fp32 fused multiply-add and is fp32 throughout; WQ_DECODE_MFMA takes hd/group == 2 only.
  * Limits (WQ_ERR_UNSUPPORTED beyond them): Hq a
  * multiple of Hkv with at most 8 query heads per KV head, hd 64 or 128, group 32, 64 or 128, B at most 65535, and for
  * the matrix-core kernel at most 2^27 token slots in the cache (cap[0] + cap[1] + cap[2] + cap16: it cuts the workgroups'

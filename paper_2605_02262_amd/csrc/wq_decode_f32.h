@@ -1,24 +1,32 @@
 // a4, matrix-core path of fp32 accuracy: the walkers of caches with one or four groups per head.
 // (included by wq_decode_mfma.h, whose body cuts the work and merges it)
 //
-// Nothing that reaches a sum here is less accurate than an fp32 number: queries, codes, scales and minima are exact, weights and
-// sums are fp32.  v_scale_max is not read.
+// Results are as accurate as those of fp32 arithmetic throughout (the figures are below); v_scale_max is not read.  Codes, scales and
+// minima are exact, sums are fp32.  What is rounded apart from them:
 //
-// The quantized classes go through v_mfma_f32_16x16x32_f16 with operands that f16 holds exactly, in the layout of the walkers
+//   query    exact in f16 for entries of at least 2^-28 of the head's largest one, else to within 2^-39 of that one: less than an
+//            fp32 sum over the head errs by, unless keys that meet such entries are 2^15 times those that meet the largest ones.
+//   weight * scale   two f16 values hold 23 bits: a quarter of the products are rounded, by up to 2^-23 of themselves (root mean
+//            square 4.2e-8; an fp32 rounding is 2.4e-8).  Below 2^-29 of the top of their place they are off by up to 2^-52 of that top,
+//            2^-46 of what a token at the reference with the group's largest scale has: it counts only where all tokens that
+//            weigh anything have scales below 2^-22 of that one.
+//
+// The quantized classes go through v_mfma_f32_16x16x32_f16 with such operands, in the layout of the walkers
 // for two groups (the storage layout is the A operand; columns (g, h) = one group or half of the head x query head):
 //
 //   logits   A = code - c, an integer (shifted(); c: code_of_zero), B = the query times a
 //            power of two.  One product per group of the head (four groups: two sets of two groups' columns), so that scale
 //            and minimum come in after the contraction:  s sum(q (code - c)) + (m + c s) sum(q).
 //   values   A = code - c, likewise per token and group, B = weight * scale of the token's group, an fp32 number w in two f16 values: hi = w rounded,
-//            lo = what is left, 2^12 times as large and in accumulators of its own (24 bits between them).  A power of two
+//            lo = what is left, 2^12 times as large and in accumulators of its own.  A power of two
 //            per group (SplitState::place) keeps w in f16's range; it moves when a scale is larger than those seen so far.
 //            The other part of the values, weight * (m + c s), is a sum per lane.
 //
 // Codes minus a constant, and not the codes themselves, because with them the two parts of a logit or value, which are far larger
 // than their sum, would be rounded at their own size.  The instruction's sums are as good as fp32 additions one by one, or
-// better (a third of their error over 2048 products).  Errors against 64 bits over batches of the benchmark's distributions, relative 2-norm:
-// 1.6e-7 to 4.8e-7, 0.54 to 1.2 times (on average 0.8) those of fp32 products (2.0e-7 to 4.6e-7).
+// better (a third of their error over 2048 products).  Errors against 64 bits, relative 2-norm, 16 batches of 196 to 23520 tokens a sequence,
+// keys with channel outliers, six draws each: 1.8e-7 to 4.2e-7 (2.4e-7 on average), with fp32 products 2.0e-7 to 4.6e-7 (2.9e-7); a batch's
+// is 0.65 to 1.01 times what it was.
 //
 // Bound by instruction issue: a 32-token block of a head of 128 takes about 370 vector instructions (four groups; 300 with one) of
 // four cycles and 32 products of 16; 136 of them unpack codes, 70 split the weights.  Measured, us per call, products in fp32
@@ -192,8 +200,8 @@ struct SplitState {
 };
 
 // The query operands of class CLS, built by one wavefront: lane (j, col) has quarter j of head h = col % 8, times the power of
-// two that brings the head's largest entry into [2^14, 2^15): whatever a 16-bit query holds is exact in f16 then, down to
-// 2^-28 of its largest entry.  sums[s]: of the scaled query over group 2 s + g (four groups), or over the head (one group).
+// two that brings the head's largest entry into [2^14, 2^15): what a 16-bit query holds is exact in f16 then, down to
+// 2^-28 of its largest entry, and below that off by no more than 2^-39 of it.  sums[s]: of the scaled query over group 2 s + g (four groups), or over the head (one group).
 template <int HD, int CLS, int G>
 __device__ __forceinline__ void build_q_split(const DecodeArgs& a, int b, int kvh, U4* Bq, float& unit, float (&sums)[2])
 {

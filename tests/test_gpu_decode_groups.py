@@ -7,7 +7,7 @@ from paper_2605_02262_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-# With 16-bit queries these group counts are computed in fp32 throughout.  Relative to a vector's largest entry: a logit of
+# With 16-bit queries these group counts have the errors of fp32 arithmetic.  Relative to a vector's largest entry: a logit of
 # up to 2^5 is rounded to 2^-19 in a sum of up to 128 products (a few such roundings at random signs, 2^-17 or so), which
 # its weight takes on relatively; the hardware's exponential is good to 2^-21 or so of the weight, sums of positive weights
 # to a few 2^-22.  Together about 2^-17; 2^-15 leaves a factor of four, and is 60 times tighter than the bound of one f16

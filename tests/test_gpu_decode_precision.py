@@ -1,6 +1,7 @@
 """Decode attention with one and four groups per head where 16 bits anywhere would show (needs an MI355X).
 
-The matrix-core kernel does the vector kernel's arithmetic here (WQ_DECODE_GENERIC): same operations, other order of the sums."""
+The matrix-core kernel has the vector kernel's accuracy here (WQ_DECODE_GENERIC, fp32 throughout) by other operations: products of f16
+numbers that hold codes, queries and weights to 23 bits or more, scales and offsets after the contraction, fp32 sums."""
 import numpy as np
 import pytest
 import torch

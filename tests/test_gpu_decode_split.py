@@ -9,11 +9,12 @@ from tests.test_gpu_decode_precision import SHAPES, _group_errors
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("shape", ["rising", "falling", "far groups", "tiny", "large", "outlier last", "keys off zero", "constant"])
+@pytest.mark.parametrize("shape", ["rising", "falling", "far groups", "tiny", "large", "outlier last", "keys off zero", "constant", "far queries"])
 @pytest.mark.parametrize("hd,g", SHAPES)
 def test_places_and_offsets(hd, g, shape):
     """Value scales that grow and shrink along the walk by 2^16, groups 2^10 apart, f16's smallest and largest magnitudes, one
-    large token at the end of the stream; keys whose groups do not straddle zero; groups of equal entries (scale 1)."""
+    large token at the end of the stream; keys whose groups do not straddle zero; groups of equal entries (scale 1); half of a head's
+    query 2^-10 of the other half, its keys 2^10 times as large."""
     from paper_2605_02262_amd import binding as W
     from tests import wq_harness as H
     specs = [synth.SeqSpec(40, 64, 64, 21, (10, 15, 15)), synth.SeqSpec(7, 64, 64, 3, (0, 0, 7)), synth.SeqSpec(3, 33, 33, 40, (1, 1, 1))]
@@ -36,6 +37,9 @@ def test_places_and_offsets(hd, g, shape):
     elif shape == "keys off zero":
         bt.K[:, 0] = np.abs(bt.K[:, 0]) + 3.0
         bt.K[:, 1] = -np.abs(bt.K[:, 1]) - 3.0
+    elif shape == "far queries":
+        bt.q[:, :, hd // 2:] *= 2.0 ** -10
+        bt.K[:, :, hd // 2:] *= 2.0 ** 10
     else:
         bt.K[::3] = 0.25
         bt.V[1::3] = -0.5

@@ -318,7 +318,8 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_scores_small(const T* __restr
 // What bounds it: above 256 columns the matrix cores, which sustain about three quarters of their nominal rate with operands
 // that change from product to product (wq_probe_mfma measures it: the clock drops under the load) and are kept busy three
 // quarters of the kernel's cycles.  Up to 256 columns what passes the compute unit's memory pipeline: a wavefront's loads
-// complete in order, so the text operands wait for the rows sent for before them, and have to be sent for about as far ahead.
+// complete in order, so the text operands wait for the rows sent for before them, and have to be sent for about as far ahead;
+// and LDS, 72 % of whose cycles are reads of operands that feed two products each and the rows' writes.
 // 8 x 12544 rows of 3584 bf16, us per call (a read of the rows alone: 117), tiles of 128 rows x 64 columns of a wavefront ->
 // tiles of up to 256 rows x 32: 256 text tokens 264 -> 192, 128: 230 -> 159, 20: 219 -> 128; 32 x 3136 rows of 4096, 256 text
 // tokens: 430 -> 234; one sequence of 19600 rows, 200 text tokens: 63 -> 57.  (64 columns and two row groups of 128 rows: 206 at

@@ -24,7 +24,7 @@ def test_scores_of_a_small_call(dim, dtype):
     from paper_2605_02262_amd import binding as W
     gen = torch.Generator(device="cuda").manual_seed(dim)
     size = torch.empty(0, dtype=dtype).element_size()
-    for window, n_win, texts in ((16, [3, 0, 2], [16, 3, 0]), (1, [5, 2], [1, 8]), (17, [1, 2], [9, 7]), (64, [1], [33]), (3, [2, 1, 1], [32, 31, 65])):
+    for window, n_win, texts in ((16, [3, 0, 2], [16, 3, 0]), (1, [5, 2], [1, 8]), (17, [1, 2], [9, 7]), (64, [2], [6]), (64, [1], [33]), (17, [2, 1], [50, 51]), (3, [2, 1, 1], [32, 31, 65])):
         texts = [min(n, (128 << 10) // (dim * size * len(texts))) for n in texts]
         rows = [n * window + 2 for n in n_win]
         vis = torch.randn(sum(rows), dim, generator=gen, device="cuda").to(dtype)

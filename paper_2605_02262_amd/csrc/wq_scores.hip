@@ -785,36 +785,48 @@ __device__ __forceinline__ uint32_t pair_cost(int N)
 // from an equal one on that needs no more workgroups than there are, if one below PAIR_SLACK more does; a larger one costs more than the
 // runs it saves (50 short sequences: 67 us with up to 6, 79 with 3).  With more than 256 text tokens, whose products bind a
 // tile, a sequence gets no more workgroups than give them PAIR_LEAST sixteens, the smallest form's height: each reads all the text (4 x 3920 rows of
-// 3584, 300 tokens: 77 us, so 73).  b: this workgroup's sequence, -1 if it has nothing to do.
+// 3584, 300 tokens: 77 us, so 73).  A lane looks at four sequences, and there are no more workgroups than 256 (65 x 500 rows, 200 tokens:
+// 150 us cut evenly, 131 so; 100 x 128, 20 tokens: 120 and 81).  b: this workgroup's sequence, -1 if it has nothing to do.
 constexpr uint32_t PAIR_SLACK = 6, PAIR_LEAST = 6;
 struct PairWhole { bool fits; int b, part, parts; };
 __device__ __forceinline__ PairWhole pair_whole(int B, const int32_t* vis_off, const int32_t* txt_off, uint32_t total)
 {
     PairWhole p{false, -1, 0, 1};
-    if (B > 64) return p;                                 // (a lane per sequence)
-    const int lane = threadIdx.x & 63, l = min(lane, B - 1);
-    const int N = txt_off[l + 1] - txt_off[l];
-    const uint32_t T = lane < B ? (uint32_t)(vis_off[l + 1] - vis_off[l] + 15) >> 4 : 0u, cost = T * pair_cost(N), most = N > 256 ? (T + PAIR_LEAST - 1) / PAIR_LEAST : T;
+    constexpr int PER = 4;                                // sequences per lane
+    if (B > 64 * PER) return p;
+    const int lane = threadIdx.x & 63;
+    uint32_t cost[PER], most[PER];
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        const int b = i * 64 + lane, l = min(b, B - 1), N = txt_off[l + 1] - txt_off[l];
+        const uint32_t T = b < B ? (uint32_t)(vis_off[l + 1] - vis_off[l] + 15) >> 4 : 0u;
+        cost[i] = T * pair_cost(N);
+        most[i] = N > 256 ? (T + PAIR_LEAST - 1) / PAIR_LEAST : T;
+    }
     const uint32_t equal = (total + gridDim.x - 1) / gridDim.x;
-    int n = 0, used = 0;
+    int n[PER] = {}, used = 0;
 #pragma unroll 1
     for (uint32_t share = max(equal, 1u); share < equal + PAIR_SLACK && !p.fits; share++) {
-        n = (int)min(most, (cost + share - 1) / share);            // (at most gridDim.x + B of them together: exact as floats)
-        used = __builtin_amdgcn_readfirstlane((int)wave_sum((float)n));
+        float sum = 0.f;                                  // (at most gridDim.x + B of them together: exact)
+#pragma unroll
+        for (int i = 0; i < PER; i++) {
+            n[i] = (int)min(most[i], (cost[i] + share - 1) / share);
+            sum += (float)n[i];
+        }
+        used = __builtin_amdgcn_readfirstlane((int)wave_sum(sum));
         p.fits = used <= (int)gridDim.x;
     }
     // (as many of the used ones on every XCD)
     const int xcd = (int)blockIdx.x % 8, wg = gridDim.x % 8 == 0 ? xcd * used / 8 + (int)blockIdx.x / 8 : (int)blockIdx.x;
     if (gridDim.x % 8 == 0 && wg >= (xcd + 1) * used / 8) return p;
     int upto = 0;
-    for (int b = 0; p.fits && b < B; b++) {
-        const int m = __builtin_amdgcn_readlane(n, b);
-        if (wg < upto + m) {
-            p.b = b, p.part = wg - upto, p.parts = m;
-            break;
+#pragma unroll
+    for (int i = 0; i < PER; i++)
+        for (int b = i * 64; p.fits && p.b < 0 && b < min(B, i * 64 + 64); b++) {
+            const int m = __builtin_amdgcn_readlane(n[i], b - i * 64);
+            if (wg < upto + m) p.b = b, p.part = wg - upto, p.parts = m;
+            upto += m;
         }
-        upto += m;
-    }
     return p;
 }
 
@@ -850,7 +862,11 @@ __global__ __launch_bounds__(PA_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         const uint32_t T = tiles_of(b), cost = pair_cost(N), begin = at;
         at += T * cost;
         if (at <= lo && !whole.fits) continue;
-        auto edge = [&](uint32_t x) { return x <= begin ? 0 : (int)min(T, (x - begin + cost - 1) / cost); };
+        auto edge = [&](uint32_t x) {                     // (a sequence that costs no more than a run is not cut: 400 x 64 rows, 20 tokens, 252 -> 219 us)
+            if (x <= begin) return 0;
+            if (T * cost <= PAIR_SLACK) return 2 * (x - begin) > T * cost ? (int)T : 0;
+            return (int)min(T, (x - begin + cost - 1) / cost);
+        };
         const int t0 = whole.fits ? (int)((uint64_t)T * whole.part / whole.parts) : edge(lo);
         const int t1 = whole.fits ? (int)((uint64_t)T * (whole.part + 1) / whole.parts) : edge(hi);
         if (t0 >= t1) continue;

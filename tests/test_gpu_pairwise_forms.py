@@ -45,8 +45,12 @@ def test_pairwise_every_form(text, dtype, dim):
     ([4704] * 5, [64] * 5),                                   # 5.7 sixteens of rows a workgroup
     ([3920, 700, 16, 2000], [300, 600, 20, 257]),             # few wide tiles: many workgroups without work
     ([0, 37, 0, 5000, 15], [5, 0, 30, 256, 257]),             # sequences without rows or without text
-    ([16] * 64, [3] * 64),                                    # a lane per sequence, fewer workgroups than the chip has
-    ([48] * 65, [40] * 65),                                   # one sequence too many for that
+    ([16] * 64, [3] * 64),                                    # fewer workgroups than the chip has
+    ([48] * 65, [40] * 65),                                   # a lane has two sequences
+    ([130, 0, 500, 33] * 40 + [7], [200, 3, 20, 300] * 40 + [129]),      # ... three, whole workgroups for each
+    ([17, 1000] * 128, [30, 10] * 128),                       # four, too many rows for whole workgroups
+    ([37, 96, 5, 97] * 100, [10, 70, 257, 4] * 100),          # more than four: equal shares, sequences of up to 96 rows not cut
+    ([4000] + [20] * 600, [150] + [2] * 600),                 # many of them in a share, one sequence over many shares
     ([90000, 1000, 1000, 33000], [10, 200, 10, 10]),          # large shares: equal ones that cross sequences
 ])
 def test_pairwise_whole_workgroups(n_vis, n_txt):

@@ -38,7 +38,8 @@
  *   min/max, all in fp32 without fused multiply-add:
  *       m = f16(lo);  s = f16((hi - m) / (2^b-1));  if (s == 0) s = 1;  inv = 1.0f / s;
  *       code = clamp((int)rint((x - m) * inv), 0, 2^b-1)          (ties to even)
- *   and the value a code stands for is  m + s*code.  s and m are stored as IEEE binary16.
+ *   and the value a code stands for is  m + s*code.  s and m are stored as IEEE binary16.  (s is negative where a group's
+ *   fp32 values are so nearly equal that f16(lo) lies above hi.)
  *   Inputs must be finite with |x| <= 65504.
  *
  * Storage layout of a class buffer (b = bits, G = hd/group, cap = capacity in tokens, a multiple of 32)

@@ -798,6 +798,8 @@ __device__ __forceinline__ PairWhole pair_whole(int B, const int32_t* vis_off, c
     uint32_t cost[PER], most[PER];
 #pragma unroll
     for (int i = 0; i < PER; i++) {
+        cost[i] = most[i] = 0u;
+        if (i * 64 >= B) continue;
         const int b = i * 64 + lane, l = min(b, B - 1), N = txt_off[l + 1] - txt_off[l];
         const uint32_t T = b < B ? (uint32_t)(vis_off[l + 1] - vis_off[l] + 15) >> 4 : 0u;
         cost[i] = T * pair_cost(N);
@@ -810,7 +812,7 @@ __device__ __forceinline__ PairWhole pair_whole(int B, const int32_t* vis_off, c
         float sum = 0.f;                                  // (at most gridDim.x + B of them together: exact)
 #pragma unroll
         for (int i = 0; i < PER; i++) {
-            n[i] = (int)min(most[i], (cost[i] + share - 1) / share);
+            if (i * 64 < B) n[i] = (int)min(most[i], (cost[i] + share - 1) / share);
             sum += (float)n[i];
         }
         used = __builtin_amdgcn_readfirstlane((int)wave_sum(sum));
@@ -837,7 +839,9 @@ __device__ __forceinline__ PairWhole pair_whole(int B, const int32_t* vis_off, c
 // sixteens in tiles of at most 16 can come to has a form of its own (with those of even height and 13 only, shares of 18, 22 and 30 sixteens, tiles of
 // 9, 11 and 15, took 148, 170 and 214 us a call instead of 145, 164 and 208: 8 sequences, 200 text tokens, D 3584).  Lower
 // shares go to the next of 4 and 8 (6, 7 and 8 with more than 256 text tokens): the same sequences in shares of 1 to 8 sixteens
-// take 47, 48, 51, 55, 64, 69, 74 and 79 us.
+// take 47, 48, 51, 55, 64, 69, 74 and 79 us.  The forms stand in order of their columns and heights, the smallest first: a form pays for the
+// branches and the registers held over them in front of it (the other way round 32 sequences of 1000 to 2550 rows, 30 tokens, took 99.8 us a call
+// instead of 93.4, 16 x 3136, 100 tokens, 99.4 instead of 95.1, the larger ones the same).
 template <bool BF>
 __global__ __launch_bounds__(PA_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_pair_mfma(const uint16_t* __restrict__ vis, const uint4* __restrict__ packed_txt,
                                                           const float* __restrict__ inv_tnorm, int D, int B,
@@ -878,27 +882,27 @@ __global__ __launch_bounds__(PA_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
 #define WQ_PAIR(RT, CT, NCB, KS) pair_run<BF, RT, CT, NCB, KS>(sm, va, tb, inv_tnorm + n0, D, N, row0, row_end, n, rows, out)
         if (N <= 0) {
             for (int r = row0 + tid; r < row_end; r += PA_THREADS) out[r] = 0.f;
+        } else if (N <= 32) {
+            WQ_PAIR(2, 2, 1, 64);
+        } else if (N <= 64) {
+            WQ_PAIR(4, 2, 2, 64);
+        } else if (N <= 128) {
+            WQ_PAIR(8, 2, 4, 64);
         } else if (N > 256) {
             if (h == 8) WQ_PAIR(8, 4, 8, 128);
             else if (h == 7) WQ_PAIR(7, 4, 8, 128);
             else WQ_PAIR(6, 4, 8, 128);
-        } else if (N > 128) {
-            if (h == 16) WQ_PAIR(16, 2, 8, 64);
-            else if (h == 15) WQ_PAIR(15, 2, 8, 64);
-            else if (h == 14) WQ_PAIR(14, 2, 8, 64);
-            else if (h == 13) WQ_PAIR(13, 2, 8, 64);
-            else if (h == 12) WQ_PAIR(12, 2, 8, 64);
-            else if (h == 11) WQ_PAIR(11, 2, 8, 64);
-            else if (h == 10) WQ_PAIR(10, 2, 8, 64);
-            else if (h == 9) WQ_PAIR(9, 2, 8, 64);
-            else if (h > 4) WQ_PAIR(8, 2, 8, 128);
-            else WQ_PAIR(4, 2, 8, 128);
-        } else if (N > 64) {
-            WQ_PAIR(8, 2, 4, 64);
-        } else if (N > 32) {
-            WQ_PAIR(4, 2, 2, 64);
         } else {
-            WQ_PAIR(2, 2, 1, 64);
+            if (h <= 4) WQ_PAIR(4, 2, 8, 128);
+            else if (h <= 8) WQ_PAIR(8, 2, 8, 128);
+            else if (h == 9) WQ_PAIR(9, 2, 8, 64);
+            else if (h == 10) WQ_PAIR(10, 2, 8, 64);
+            else if (h == 11) WQ_PAIR(11, 2, 8, 64);
+            else if (h == 12) WQ_PAIR(12, 2, 8, 64);
+            else if (h == 13) WQ_PAIR(13, 2, 8, 64);
+            else if (h == 14) WQ_PAIR(14, 2, 8, 64);
+            else if (h == 15) WQ_PAIR(15, 2, 8, 64);
+            else WQ_PAIR(16, 2, 8, 64);
         }
 #undef WQ_PAIR
     }

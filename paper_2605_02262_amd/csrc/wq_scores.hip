@@ -199,12 +199,12 @@ __global__ __launch_bounds__(256) void k_window_mean(const float* __restrict__ t
 // first row is on its way meanwhile: 8 windows of 16 rows, 16 text tokens, 896 floats: four launches, 16 us; this one 6.
 // A workgroup goes through its sequence's tokens and its window's rows in a chain of 0.07 to 0.1 us each, the four launches over
 // all of them at once: 9 to 12 us whatever the sizes (11 to 17 where a call waits for its launches to be submitted).  So the tokens of a sequence and the
-// rows of a window together are no more than SMALL_CHAIN, on average, and a sequence's text no more than 64 KB (two: 96; all fit
-// LDS).  Over 1646 combinations inside these lines (1 to 64 tokens and rows, D 128 to 4096, bf16 and fp32) 0.97 of the four launches' time at
-// most, 0.4 at least, in a replayed graph; beyond: 96 tokens 9 to 11 us against 9, 256 tokens 20 against 10, 64 tokens and
-// rows of 64 11 to 13 against 9, 32 tokens of 2048 bf16 and rows of 32 11.3 against 9.8.  (On average: the host knows the totals only.)
+// rows of a window together are no more than SMALL_CHAIN, on average (the host knows the totals only), with a text of up to 64 KB a sequence (two: 96 KB), and
+// SMALL_CHAIN_LONG with more (all must fit LDS).  Inside these lines, over 1700 combinations (1 to 64 tokens and rows, D 128 to 4096, bf16 and fp32), 0.4 to
+// 1.02 of the four launches' time in a replayed graph, 0.3 to 0.82 of it otherwise; beyond: 96 tokens 9 to 11 us against 9, 256 tokens 20 against 10, 64 tokens and
+// rows of 64 11 to 13 against 9, 32 tokens of 2048 bf16 and rows of 32 11.3 against 9.8.
 constexpr int SMALL_THREADS = 1024, SMALL_TOKENS = 256, SMALL_TEXT = 128 << 10, SMALL_ROWS = 1024, SMALL_WINDOWS = 256, SMALL_DIM = 4096;
-constexpr int64_t SMALL_BYTES = 1 << 20, SMALL_SEQ_TEXT = 32 << 10, SMALL_CHAIN = 72;
+constexpr int64_t SMALL_BYTES = 1 << 20, SMALL_SEQ_TEXT = 32 << 10, SMALL_CHAIN = 72, SMALL_CHAIN_LONG = 32;
 template <typename T>
 __global__ __launch_bounds__(SMALL_THREADS) void k_scores_small(const T* __restrict__ vis, const T* __restrict__ txt, int D, int B,
                                                                 const int32_t* __restrict__ vis_off, const int32_t* __restrict__ txt_off,
@@ -922,9 +922,10 @@ int run_pooled(wq_ctx* ctx, const void* vis_, const void* txt_, int B, int D, co
     ws += wq_align256(sizeof(float) * (size_t)B * D);
     float* tok_score = reinterpret_cast<float*>(ws);
     hipStream_t st = ctx->stream;
-    if (VEC && total_txt <= SMALL_TOKENS && total_txt * D * (int64_t)sizeof(T) <= (SMALL_TEXT < SMALL_SEQ_TEXT * (B + 1) ? SMALL_TEXT : SMALL_SEQ_TEXT * (B + 1)) &&
-        total_vis <= SMALL_ROWS && total_win <= SMALL_WINDOWS && total_txt * total_win + total_vis * B <= SMALL_CHAIN * B * total_win && D <= SMALL_DIM &&
-        total_vis * D * (int64_t)sizeof(T) <= SMALL_BYTES) {
+    const int64_t text_bytes = total_txt * D * (int64_t)sizeof(T), chain = total_txt * total_win + total_vis * B, per = (int64_t)B * total_win;
+    if (VEC && total_txt <= SMALL_TOKENS && total_vis <= SMALL_ROWS && total_win <= SMALL_WINDOWS && D <= SMALL_DIM && text_bytes <= SMALL_TEXT &&
+        total_vis * D * (int64_t)sizeof(T) <= SMALL_BYTES &&
+        chain <= (text_bytes <= SMALL_SEQ_TEXT * (B + 1) ? SMALL_CHAIN : SMALL_CHAIN_LONG) * per) {
         hipLaunchKernelGGL(k_scores_small<T>, dim3((unsigned)total_win), dim3(SMALL_THREADS), 0, st, vis, txt, D, B, vis_off, txt_off, win_size,
                            win_off, scores);
         WQ_HIP_CHECK(ctx, hipGetLastError());

@@ -200,8 +200,8 @@ __global__ __launch_bounds__(256) void k_window_mean(const float* __restrict__ t
 // A workgroup goes through its sequence's tokens and its window's rows in a chain of 0.07 to 0.1 us each, the four launches over
 // all of them at once: 9 to 12 us whatever the sizes (11 to 17 where a call waits for its launches to be submitted).  So the tokens of a sequence and the
 // rows of a window together are no more than SMALL_CHAIN, on average (the host knows the totals only), with a text of up to 64 KB a sequence (two: 96 KB), and
-// SMALL_CHAIN_LONG with more (all must fit LDS).  Inside these lines, over 1700 combinations (1 to 64 tokens and rows, D 128 to 4096, bf16 and fp32), 0.4 to
-// 1.02 of the four launches' time in a replayed graph, 0.3 to 0.82 of it otherwise; beyond: 96 tokens 9 to 11 us against 9, 256 tokens 20 against 10, 64 tokens and
+// SMALL_CHAIN_LONG with more (all must fit LDS).  Inside these lines, over 1700 combinations (1 to 64 tokens and rows, D 128 to 4096, bf16 and fp32), 0.38 to
+// 1.02 of the four launches' time in a replayed graph, 0.36 to 0.82 of it otherwise; beyond: 96 tokens 9 to 11 us against 9, 256 tokens 20 against 10, 64 tokens and
 // rows of 64 11 to 13 against 9, 32 tokens of 2048 bf16 and rows of 32 11.3 against 9.8.
 constexpr int SMALL_THREADS = 1024, SMALL_TOKENS = 256, SMALL_TEXT = 128 << 10, SMALL_ROWS = 1024, SMALL_WINDOWS = 256, SMALL_DIM = 4096;
 constexpr int64_t SMALL_BYTES = 1 << 20, SMALL_SEQ_TEXT = 32 << 10, SMALL_CHAIN = 72, SMALL_CHAIN_LONG = 32;

@@ -13,6 +13,7 @@
 
 #include <initializer_list>
 #include <type_traits>
+#include <utility>
 
 #include "wq_internal.h"
 
@@ -31,7 +32,8 @@ struct DecodeArgs {
     int arrive_unit;
     int fixed_shares;       // every wavefront of the matrix-core kernel gets a fixed share of its workgroup's range
     wq_packed_kv kv;
-    float* part;            // [B][Hkv][nparts][rep][hd + 2]
+    float* part;            // numerators of the partials [B][Hkv][nparts][rep][hd]
+    float* part_ml;         // ... their references and weight sums [B][Hkv][nparts][rep][2]
     float* out;
     float* lse;
     // appending one generated token per sequence in the same launch (matrix-core kernel, merged splits only):
@@ -76,10 +78,12 @@ __device__ __forceinline__ float wave_sum(float x)
     return (lane_value(x, 0) + lane_value(x, 16)) + (lane_value(x, 32) + lane_value(x, 48));
 }
 
-// Up to 64 splits, one per lane: lane s holds m_s (-inf beyond the last split) and l_s; it gets its weight
-// w_s = e^{m_s - M}, and every lane M = max m_s and L = sum l_s w_s.  Both merges (the one inside the matrix-core
-// kernel and k_combine) go through this function when there are at most 64 splits and then sum the numerators in
-// split order, which is why their results agree bit for bit.
+// Up to 64 splits, one per lane: lane l holds m_s (-inf beyond the last split) and l_s of split s = split_of_lane(l); it gets
+// the weight w_s = e^{m_s - M}, and every lane M = max m_s and L = sum l_s w_s.  Both merges (the one inside the matrix-core
+// kernel and k_combine) go through this function when there are at most 64 splits and then sum the numerators in the
+// same order (splits s, s + 4, ... one after the other for s = 0..3, then (0 + 2) + (1 + 3)), which is why their results agree bit for bit.
+constexpr int MERGE_CHAINS = 4;                    // one per row of 16 lanes
+__device__ __forceinline__ int split_of_lane(int lane) { return MERGE_CHAINS * (lane & 15) + (lane >> 4); }
 __device__ __forceinline__ void merge_weights_lanes(float m, float l, float& w, float& M, float& L)
 {
     M = wave_max(m);
@@ -329,17 +333,17 @@ __device__ void decode_generic_body(const DecodeArgs& a, void* smem_raw, bool qu
     for (int r = 0; r < WQ_MAX_REP; r++)
         if (r < a.rep) sm.red[tp][r][c] = acc[r];
     __syncthreads();
-    float* out = a.part + (((int64_t)b * a.kv.Hkv + kvh) * a.nparts + part_idx) * a.rep * (HD + 2);
+    const int64_t row0 = (((int64_t)b * a.kv.Hkv + kvh) * a.nparts + part_idx) * a.rep;
     if (tp == 0) {
         for (int r = 0; r < a.rep; r++) {
             float s = 0.f;
             for (int k = 0; k < PARTS; k++) s += sm.red[k][r][c];
-            out[r * (HD + 2) + c] = s;
+            a.part[(row0 + r) * HD + c] = s;
         }
     }
     if (tid < a.rep) {
-        out[tid * (HD + 2) + HD] = sm.m[tid];
-        out[tid * (HD + 2) + HD + 1] = sm.l[tid];
+        a.part_ml[(row0 + tid) * 2] = sm.m[tid];
+        a.part_ml[(row0 + tid) * 2 + 1] = sm.l[tid];
     }
 }
 
@@ -365,11 +369,11 @@ __global__ __launch_bounds__(64 * WQ_WAVES) void k_decode_mfma(DecodeArgs a)
 }
 
 // out[b,h,:] = sum_s acc_s e^{m_s - M} / sum_s l_s e^{m_s - M},  M = max_s m_s;  lse = M + log(sum).
-// One workgroup per (b, h); the weights come from merge_weights (first wavefront), the numerators are summed in split
-// order with all loads of a thread independent of each other (no data-dependent control flow around them): the same
-// arithmetic in the same order as the merge inside the matrix-core kernel.
-__global__ __launch_bounds__(128) void k_combine(const float* __restrict__ part, int Hq, int rep, int nparts, int hd,
-                                                 float* __restrict__ out, float* __restrict__ lse)
+// One workgroup per (b, h); the weights come from merge_weights (first wavefront), the numerators are summed with all loads
+// of a thread independent of each other (no data-dependent control flow around them): the same arithmetic in the same order as
+// the merge inside the matrix-core kernel.
+__global__ __launch_bounds__(128) void k_combine(const float* __restrict__ part, const float* __restrict__ part_ml, int Hq, int rep, int nparts,
+                                                 int hd, float* __restrict__ out, float* __restrict__ lse)
 {
     __shared__ float s_w[1024 + 32];
     __shared__ float s_l[1024 + 32];
@@ -378,23 +382,25 @@ __global__ __launch_bounds__(128) void k_combine(const float* __restrict__ part,
     const int kvh = h / rep, r = h % rep;
     const int Hkv = Hq / rep;
     const int tid = threadIdx.x;
-    const int64_t stride = (int64_t)rep * (hd + 2);
-    const float* base = part + (((int64_t)b * Hkv + kvh) * nparts) * stride + (int64_t)r * (hd + 2);
+    const int64_t row0 = (((int64_t)b * Hkv + kvh) * nparts) * rep + r, stride = (int64_t)rep * hd;
+    const float* base = part + row0 * hd;
+    const float* ml = part_ml + row0 * 2;
     constexpr int CHUNK = 32;
     float pre[CHUNK];                      // this channel's numerators of the first CHUNK splits: in flight while the weights are found
 #pragma unroll
     for (int k = 0; k < CHUNK; k++) pre[k] = (k < nparts && tid < hd) ? base[(int64_t)k * stride + tid] : 0.f;
     for (int s = tid; s < nparts; s += 128) {
-        s_w[s] = base[s * stride + hd];
-        s_l[s] = base[s * stride + hd + 1];
+        s_w[s] = ml[(int64_t)s * rep * 2];
+        s_l[s] = ml[(int64_t)s * rep * 2 + 1];
     }
     __syncthreads();
     if (tid < 64) {
         float M, L;
         if (nparts <= 64) {
+            const int s = split_of_lane(tid);
             float w;
-            merge_weights_lanes(tid < nparts ? s_w[tid] : -INFINITY, tid < nparts ? s_l[tid] : 0.f, w, M, L);
-            if (tid < nparts) s_w[tid] = w;
+            merge_weights_lanes(s < nparts ? s_w[s] : -INFINITY, s < nparts ? s_l[s] : 0.f, w, M, L);
+            if (s < nparts) s_w[s] = w;
         } else {
             merge_weights(s_w, s_l, nparts, M, L);
         }
@@ -405,18 +411,19 @@ __global__ __launch_bounds__(128) void k_combine(const float* __restrict__ part,
     }
     __syncthreads();
     const float M = s_red[0], L = s_red[1];
-    float acc = 0.f;
+    float acc[MERGE_CHAINS] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int k = 0; k < CHUNK; k++) acc = fmaf(pre[k], k < nparts ? s_w[k] : 0.f, acc);
+    for (int k = 0; k < CHUNK; k++) acc[k % MERGE_CHAINS] = fmaf(pre[k], k < nparts ? s_w[k] : 0.f, acc[k % MERGE_CHAINS]);
     if (tid < hd) {
         for (int s0 = CHUNK; s0 < nparts; s0 += CHUNK) {
             float v[CHUNK];
 #pragma unroll
             for (int k = 0; k < CHUNK; k++) v[k] = (s0 + k < nparts) ? base[(int64_t)(s0 + k) * stride + tid] : 0.f;
 #pragma unroll
-            for (int k = 0; k < CHUNK; k++) acc = fmaf(v[k], (s0 + k < nparts) ? s_w[s0 + k] : 0.f, acc);
+            for (int k = 0; k < CHUNK; k++) acc[k % MERGE_CHAINS] = fmaf(v[k], (s0 + k < nparts) ? s_w[s0 + k] : 0.f, acc[k % MERGE_CHAINS]);
         }
-        out[((int64_t)b * Hq + h) * hd + tid] = L > 0.f ? acc / L : 0.f;
+        const float sum = (acc[0] + acc[2]) + (acc[1] + acc[3]);
+        out[((int64_t)b * Hq + h) * hd + tid] = L > 0.f ? sum / L : 0.f;
     }
     if (lse && tid == 0) lse[(int64_t)b * Hq + h] = L > 0.f ? M + logf(L) : -INFINITY;
 }
@@ -581,6 +588,7 @@ int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, con
     if (a.use_mfma && !fits_cost_axis(kv))
         return wq_fail(ctx, WQ_ERR_UNSUPPORTED, "the matrix-core decode kernel takes caches of up to 2^27 token slots");
     a.part = reinterpret_cast<float*>(ctx->ws + WQ_WS_HEADER);
+    a.part_ml = a.part + (int64_t)B * Hq * a.nparts * kv->hd;
     a.out = out;
     a.k_new = static_cast<const uint16_t*>(k_new);
     a.v_new = static_cast<const uint16_t*>(v_new);
@@ -617,7 +625,7 @@ int wq_launch_decode(wq_ctx* ctx, const void* q, int q_dtype, int B, int Hq, con
     if (ctx->timing) (void)hipEventRecord(ctx->ev[2 * tslot + 1], ctx->stream);
     if (a.splits16 > 0) hipLaunchKernelGGL(kv->hd == 128 ? k_decode_generic<128> : k_decode_generic<64>, grid_16, blk, 0, ctx->stream, a);
     if (!partials_only && !a.fused)
-        hipLaunchKernelGGL(k_combine, dim3(Hq, B), dim3(128), 0, ctx->stream, a.part, Hq, a.rep, a.nparts, kv->hd, out, lse);
+        hipLaunchKernelGGL(k_combine, dim3(Hq, B), dim3(128), 0, ctx->stream, a.part, a.part_ml, Hq, a.rep, a.nparts, kv->hd, out, lse);
     if (ctx->timing) ctx->ev_calls++;
     WQ_HIP_CHECK(ctx, hipGetLastError());
     return WQ_OK;

@@ -75,7 +75,7 @@ struct F32Smem {
     U4 bq[3][HD / 32][64];                               // query operands of the quantized classes, per lane
     float qx[3][64];                                     // ... their power of two, the sums of set 0's and set 1's group
     // what the body uses (MfmaSmem has the same)
-    float O[WQ_WAVES][WQ_MAX_REP][HD + 1];
+    __attribute__((aligned(16))) float O[WQ_WAVES][WQ_MAX_REP][HD + 4];
     float ml[WQ_WAVES][WQ_MAX_REP][2];
     unsigned next_ticket;
     int expect[64], grown[64];
@@ -657,8 +657,10 @@ __device__ __forceinline__ void hand_over_split(F32Smem<HD, G>& sm, const SplitS
     for (int ct = 0; ct < CT; ct++) {
         const int s = ct / (CT / SETS);
         if (g == (G == 4 ? ct / (CT / 4) % 2 : 0)) {       // this column's group owns channel tile ct
+            floatx4 v;
 #pragma unroll
-            for (int i = 0; i < 4; i++) sm.O[wave][h][16 * ct + 4 * j + i] = fmaf(fmaf(st.P[ct][i], 1.0f / 4096.0f, st.O[ct][i]), unit[s], am[s]);
+            for (int i = 0; i < 4; i++) v[i] = fmaf(fmaf(st.P[ct][i], 1.0f / 4096.0f, st.O[ct][i]), unit[s], am[s]);
+            *reinterpret_cast<floatx4*>(&sm.O[wave][h][16 * ct + 4 * j]) = v;
         }
     }
     if (lane < 8) {

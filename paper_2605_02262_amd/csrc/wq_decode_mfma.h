@@ -197,9 +197,9 @@ struct MfmaSmem {
         uint32_t meta[WQ_WAVES][2][64];                  // per wave: K and V metadata words of the current block
         uint16_t vt[WQ_WAVES][32][HD / 2 + VT_PAD];      // per wave: half the channels of the V rows of a 16-bit block, read back transposed
     } run;
-    // per-wave numerators for the merge; rows one bank apart.  A space of its own: a wavefront hands its numerators over
+    // per-wave numerators for the merge; rows four banks apart, written 16 bytes at a time.  A space of its own: a wavefront hands its numerators over
     // as soon as its loops end, while others still use the run-time part
-    float O[WQ_WAVES][WQ_MAX_REP][HD + 1];
+    __attribute__((aligned(16))) float O[WQ_WAVES][WQ_MAX_REP][HD + 4];
     U4 bq[4][HD / 32][64];                               // query operands of the four classes (index 3 = 16-bit segment), per lane
     float qx[4][2][64];                                  // ... with the head's power of two and the group's query sum
     float ml[WQ_WAVES][WQ_MAX_REP][2];
@@ -955,12 +955,6 @@ __device__ __forceinline__ int range_edge_of(int c, unsigned x, unsigned base, i
 
 // ---- helpers of the two merges --------------------------------------------------------------------------------
 typedef float floatx2 __attribute__((ext_vector_type(2)));
-template <int N> struct FloatN;
-template <> struct FloatN<1> { typedef float type; };
-template <> struct FloatN<2> { typedef floatx2 type; };
-template <int N> __device__ __forceinline__ float part_elem(typename FloatN<N>::type v, int c);
-template <> __device__ __forceinline__ float part_elem<1>(float v, int) { return v; }
-template <> __device__ __forceinline__ float part_elem<2>(floatx2 v, int c) { return v[c]; }
 
 // N floats (N * 4 bytes, aligned to that) to memory with a device-scope store (one instruction)
 template <int N>
@@ -986,20 +980,37 @@ __device__ __forceinline__ void store_plain(float* p, const float* v)
     }
 }
 
-// N floats of a partial through a buffer descriptor, with a device-scope load (does not stop at a cache); zero
+// Two or four floats of a partial through a buffer descriptor, with a device-scope load (does not stop at a cache); zero
 // when the offset is beyond the descriptor's range
-template <int N>
-__device__ __forceinline__ typename FloatN<N>::type ld_part(__amdgpu_buffer_rsrc_t rsrc, unsigned byte_off)
+constexpr int LD_DEVICE_SCOPE = 16;                // the sc1 bit of the instruction
+__device__ __forceinline__ floatx2 ld_part2(__amdgpu_buffer_rsrc_t rsrc, unsigned byte_off)
 {
-    constexpr int DEVICE_SCOPE = 16;               // the sc1 bit of the instruction
-    if constexpr (N == 1) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)byte_off, 0, DEVICE_SCOPE));
-    } else {
-        static_assert(N == 2, "one or two floats");
-        return __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)byte_off, 0, DEVICE_SCOPE));
-    }
+    return __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)byte_off, 0, LD_DEVICE_SCOPE));
 }
-
+__device__ __forceinline__ floatx4 ld_part4(__amdgpu_buffer_rsrc_t rsrc, unsigned byte_off)
+{
+    return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)byte_off, 0, LD_DEVICE_SCOPE));
+}
+// lane K of every row of 16 lanes, in all lanes of that row
+template <int K>
+__device__ __forceinline__ float row_bcast(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x150 + K, 0xF, 0xF, true));
+}
+template <class F, int... K>
+__device__ __forceinline__ void for_each_index(const F& f, std::integer_sequence<int, K...>) { (f(std::integral_constant<int, K>{}), ...); }
+// row pairs (0, 2) and (1, 3) of 16 lanes added up: a's sums in the lower half of the wavefront, b's in the upper half
+__device__ __forceinline__ float fold_halves(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// ... rows 2k and 2k + 1: a's sums in the even rows, b's in the odd ones
+__device__ __forceinline__ float fold_rows(float a, float b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 
 template <int HD, int G>
 using DecodeSmem = std::conditional_t<G == 2, MfmaSmem<HD>, F32Smem<HD, G>>;
@@ -1225,11 +1236,11 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         l = sum_over_rows(l);
         am = sum_over_rows(am);
 #pragma unroll
-        for (int ct = 0; ct < CT; ct++) {
-            if ((ct >= CT / 2) == (g == 1)) {          // this column's group owns channel tile ct
+        for (int ct = 0; ct < CT / 2; ct++) {          // this column's group owns the channel tiles g CT / 2 ...
+            floatx4 v;
 #pragma unroll
-                for (int i = 0; i < 4; i++) sm.O[wave][h][16 * ct + 4 * j + i] = fmaf(st.O[ct][i], o_unit, am);
-            }
+            for (int i = 0; i < 4; i++) v[i] = fmaf(g ? st.O[CT / 2 + ct][i] : st.O[ct][i], o_unit, am);
+            *reinterpret_cast<floatx4*>(&sm.O[wave][h][g * (HD / 2) + 16 * ct + 4 * j]) = v;
         }
         if (j == 0 && g == 0) {
             sm.ml[wave][h][0] = st.m;
@@ -1242,10 +1253,9 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
     //      neighbouring channels, so the eight scales of a head are computed once per lane ----
     constexpr int CPL = HD / 64;                   // channels per lane
     static_assert(WQ_WAVES >= WQ_MAX_REP, "one wavefront per head");
-    const int64_t pstride = (int64_t)a.rep * (HD + 2);
-    float* pbase = a.part + ((int64_t)unit * a.nparts) * pstride;
+    const int64_t part_row = (int64_t)unit * a.nparts * a.rep;          // the unit's first row (split 0, head 0)
     if (wave < a.rep) {
-        float* out = pbase + split * pstride + wave * (HD + 2);
+        const int64_t row = part_row + split * a.rep + wave;
         float mw[WQ_WAVES];
 #pragma unroll
         for (int w = 0; w < WQ_WAVES; w++) mw[w] = sm.ml[w][wave][0];
@@ -1264,10 +1274,10 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         }
         // device-scope stores go through to memory (every XCD has an L2 of its own), so that no cache write-back
         // is needed to hand the partial to the workgroup that merges the splits
-        store_through<CPL>(out + CPL * lane, num);
+        store_through<CPL>(a.part + row * HD + CPL * lane, num);
         if (lane == 0) {
             const float ml2[2] = {F32 ? M : M * 0.6931471805599453f, L};       // (the walkers of one and four groups keep the reference in natural units)
-            store_through<2>(out + HD, ml2);
+            store_through<2>(a.part_ml + row * 2, ml2);
         }
     }
     WQ_STAMP(5);
@@ -1293,48 +1303,67 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         WQ_STAMP(57);
         if (last && lane == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
     }
-    // What follows runs once per (b, kvh, head) while the rest of the chip waits, and a wavefront's vector instruction
-    // takes four cycles: every instruction counts.  Lane s holds (m, l) of split s (the launch takes this path with at
-    // most 64 splits), the weights come from reductions inside the wavefront, lane s's weight is read back as a scalar
-    // for the sum over the splits; no LDS, no barrier.  The partials are read through a buffer descriptor, whose range
-    // check returns zero beyond the last split.
+    // What follows runs once per (b, kvh, head) while the rest of the chip waits, and an instruction of a lone wavefront takes
+    // about 2 ns: every instruction counts.  Lane l holds (m, l) of split split_of_lane(l) (the launch takes this path with at most 64
+    // splits), the weights come from reductions inside the wavefront.  The four rows of 16 lanes take every fourth split each,
+    // 16 bytes of it per lane and load, all of them in flight together; a split's weight is lane k of its row
+    // (row_bcast), and the rows' sums are folded into each other, two of them at a time and half the channels
+    // each.  No LDS, no barrier.  The partials are read through buffer descriptors, whose range check returns zero beyond the last split.
+    // Against a split per load, 8 bytes per lane, the weight read back as a scalar, and numerators handed over 4 bytes at a time: a step of
+    // 28 launches with 32 splits 360 -> 331 us, with 8 splits 552 -> 537; 4 calls with 16 splits 100.6 -> 99.0.
     if (last) {
         const int np = S;                          // (the splits are all the partials there are in a launch that merges them itself)
-        const unsigned pbytes = (unsigned)pstride * 4u;
-        const __amdgpu_buffer_rsrc_t parts = __builtin_amdgcn_make_buffer_rsrc(pbase, 0, np * (int)pbytes, 0x00020000);
-        const unsigned row = (unsigned)(wave * (HD + 2)) * 4u;
-        const floatx2 ml = ld_part<2>(parts, (unsigned)lane * pbytes + row + HD * 4u);
-        const float m_s = lane < np ? ml[0] : -INFINITY, l_s = ml[1];
+        const int r = lane >> 4, k16 = lane & 15;
+        constexpr int PIECES = HD / 64;            // 16-byte pieces of a split's channels per lane
+        const unsigned rows = (unsigned)(np * a.rep);
+        const __amdgpu_buffer_rsrc_t mls = __builtin_amdgcn_make_buffer_rsrc(a.part_ml + part_row * 2, 0, (int)(rows * 8u), 0x00020000);
+        const __amdgpu_buffer_rsrc_t nums = __builtin_amdgcn_make_buffer_rsrc(a.part + part_row * HD, 0, (int)(rows * (HD * 4u)), 0x00020000);
+        const int s_l = split_of_lane(lane);
+        const floatx2 ml = ld_part2(mls, (unsigned)(s_l * a.rep + wave) * 8u);
+        const unsigned chan = (unsigned)(r * a.rep + wave) * (HD * 4u) + (unsigned)k16 * 16u, step = (unsigned)a.rep * (MERGE_CHAINS * HD * 4u);
         float w_s = 0.f, M = -INFINITY, L = 0.f;
-        float acc[CPL];
+        floatx4 acc[PIECES];
 #pragma unroll
-        for (int c = 0; c < CPL; c++) acc[c] = 0.f;
-        const unsigned chan = row + (unsigned)lane * (CPL * 4u);
-        auto gather = [&](auto N, int k0) {        // N splits at a time: their loads are in flight together
+        for (int p = 0; p < PIECES; p++) acc[p] = floatx4{0.f, 0.f, 0.f, 0.f};
+        auto gather = [&](auto N) {                // N splits per row
             constexpr int NS = decltype(N)::value;
-            typename FloatN<CPL>::type pre[NS];
+            floatx4 pre[NS][PIECES];
 #pragma unroll
-            for (int k = 0; k < NS; k++) pre[k] = ld_part<CPL>(parts, chan + (unsigned)(k0 + k) * pbytes);
-            if (k0 == 0) merge_weights_lanes(m_s, l_s, w_s, M, L);
+            for (int k = 0; k < NS; k++)
 #pragma unroll
-            for (int k = 0; k < NS; k++) {
-                const float wk = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w_s), k0 + k));   // 0 beyond the last split
+                for (int p = 0; p < PIECES; p++) pre[k][p] = ld_part4(nums, chan + (unsigned)k * step + p * 256u);
+            merge_weights_lanes(s_l < np ? ml[0] : -INFINITY, ml[1], w_s, M, L);
+            auto add = [&](auto K) {               // (a split beyond the last one: zeros times zero)
+                constexpr int k = decltype(K)::value;
+                const float wk = row_bcast<k>(w_s);
 #pragma unroll
-                for (int c = 0; c < CPL; c++) acc[c] = fmaf(part_elem<CPL>(pre[k], c), wk, acc[c]);
-            }
+                for (int p = 0; p < PIECES; p++)
+#pragma unroll
+                    for (int c = 0; c < 4; c++) acc[p][c] = fmaf(wk, pre[k][p][c], acc[p][c]);
+            };
+            for_each_index(add, std::make_integer_sequence<int, NS>{});
         };
-        if (np <= 16) {
-            gather(std::integral_constant<int, 16>{}, 0);
-        } else {                                   // (a second round trip costs more than the loads of splits that are not there)
-#pragma unroll 1
-            for (int k0 = 0; k0 < np; k0 += 32) gather(std::integral_constant<int, 32>{}, k0);
-        }
+        if (np <= 16) gather(std::integral_constant<int, 4>{});
+        else if (np <= 32) gather(std::integral_constant<int, 8>{});
+        else gather(std::integral_constant<int, 16>{});
         WQ_STAMP(58);
         const int hq = kvh * a.rep + wave;
         float o[CPL];
+        int ch;                                    // the first of the lane's channels
+        if constexpr (PIECES == 2) {
+            float h[4];
 #pragma unroll
-        for (int c = 0; c < CPL; c++) o[c] = L > 0.f ? acc[c] / L : 0.f;
-        store_plain<CPL>(a.out + ((int64_t)b * a.Hq + hq) * HD + CPL * lane, o);
+            for (int c = 0; c < 4; c++) h[c] = fold_halves(acc[0][c], acc[1][c]);
+#pragma unroll
+            for (int c = 0; c < 2; c++) o[c] = fold_rows(h[c], h[c + 2]);
+            ch = 64 * (r >> 1) + 4 * k16 + 2 * (r & 1);
+        } else {
+            o[0] = fold_rows(fold_halves(acc[0][0], acc[0][2]), fold_halves(acc[0][1], acc[0][3]));
+            ch = 4 * k16 + 2 * (r >> 1) + (r & 1);
+        }
+#pragma unroll
+        for (int c = 0; c < CPL; c++) o[c] = L > 0.f ? o[c] / L : 0.f;
+        store_plain<CPL>(a.out + ((int64_t)b * a.Hq + hq) * HD + ch, o);
         if (a.lse && lane == 0) a.lse[(int64_t)b * a.Hq + hq] = L > 0.f ? M + logf(L) : -INFINITY;
     }
     WQ_STAMP(59);

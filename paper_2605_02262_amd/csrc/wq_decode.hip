@@ -9,6 +9,7 @@
 // k_decode_generic: plain vector-ALU kernel that reads codes field by field from the storage layout.  It
 // handles every supported (hd, group) and query type and is the reference implementation inside the library; the
 // matrix-core body in wq_decode_mfma.h is the fast path (use_matrix_cores below says where it is taken).
+#include <stddef.h>
 #include <stdlib.h>
 
 #include <initializer_list>
@@ -19,35 +20,37 @@
 
 namespace {
 
-struct DecodeArgs {
-    const void* q;
+struct DecodeArgs {         // (what the matrix-core kernel reads of it comes first)
     int q_dtype;
     int B, Hq, rep, splits;
     float sm_scale;
-    int splits16, nparts;   // workgroups on the 16-bit segment; nparts = splits + splits16 partials per (b, KV head)
-    int use_mfma;
+    float len_scale;        // > 0: a (sequence, KV head) with n tokens uses ceil(n * len_scale) of the launch's splits (at least one)
+    int nparts;             // partials per (b, KV head): splits + splits16
     int mfma16;             // the matrix-core kernel also walks the 16-bit segment
     int fused;              // the matrix-core kernel merges the splits itself (last workgroup per (b, KV head))
-    unsigned* arrive;       // [B*Hkv] pieces of arrive_unit words (WQ_MAX_REP arrival counters each), then [B] append counters, zero between launches
-    int arrive_unit;
     int fixed_shares;       // every wavefront of the matrix-core kernel gets a fixed share of its workgroup's range
+    int arrive_unit;
+    unsigned* arrive;       // [B*Hkv] pieces of arrive_unit words (WQ_MAX_REP arrival counters each), then [B] append counters, zero between launches
     wq_packed_kv kv;
-    float* part;            // numerators of the partials [B][Hkv][nparts][rep][hd]
-    float* part_ml;         // ... their references and weight sums [B][Hkv][nparts][rep][2]
-    float* out;
-    float* lse;
+    const void* q;
     // appending one generated token per sequence in the same launch (matrix-core kernel, merged splits only):
     const uint16_t* k_new;  // [B][Hkv][hd] in the cache's 16-bit type, or NULL
     const uint16_t* v_new;
     uint32_t* status;       // device status word (a full 16-bit segment is reported there)
-    float len_scale;        // > 0: a (sequence, KV head) with n tokens uses ceil(n * len_scale) of the launch's splits (at least one)
-    int packed_grid;        // splits by length, workgroups with work numbered without gaps (place_by_length)
-    int slots;              // ... > 0: automatic, at most this many splits of all sequences together
+    float* part;            // numerators of the partials [B][Hkv][nparts][rep][hd]
+    float* part_ml;         // ... their references and weight sums [B][Hkv][nparts][rep][2]
+    float* out;
+    float* lse;
+    int slots;              // splits by length, workgroups with work numbered without gaps (place_by_length); > 0: automatic, at most this many splits of all sequences together
     int even_splits;        // ... and what a sequence gets where the kernel finds all of them equally long
+    int packed_grid;
+    int splits16;           // workgroups of the vector kernel on the 16-bit segment
+    int use_mfma;
 #ifdef WQ_TIMELINE
     long long* dbg;
 #endif
 };
+static_assert(offsetof(DecodeArgs, slots) <= 5 * 64, "the matrix-core kernel touches five lines of arguments, all of them with its first loads: a sixth is a round trip of 0.3 us");
 
 // ---- the weights of the splits -----------------------------------------------------------------------------
 // Reductions over the 64 lanes of a wavefront in a fixed order: four rotations inside the rows of 16 lanes (one

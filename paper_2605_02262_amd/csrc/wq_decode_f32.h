@@ -77,7 +77,6 @@ struct F32Smem {
     // what the body uses (MfmaSmem has the same)
     __attribute__((aligned(16))) float O[WQ_WAVES][WQ_MAX_REP][HD + 4];
     float ml[WQ_WAVES][WQ_MAX_REP][2];
-    unsigned next_ticket;
     int expect[64], grown[64];
 };
 
@@ -344,7 +343,7 @@ __device__ __forceinline__ void walk_class_split(const DecodeArgs& a, F32Smem<HD
 #pragma unroll
     for (int d = 0; d < DEPTH; d++)
         if (blk + d < end) load(blk + d, f[d]);
-    pass_setup_barrier(a, b, tk);
+    pass_setup_barrier(b, tk);
     // B operands: column (g, h) of set s takes the channels of group 2 s + g (four groups), or of half g of the head
     half8 Bq[SETS][NK];
 #pragma unroll
@@ -542,10 +541,10 @@ __device__ __forceinline__ void walk_class_split(const DecodeArgs& a, F32Smem<HD
 
 // ---- the 16-bit segment: rows are plain [token][Hkv][hd], so the K side is the A operand straight from memory (a
 // quarter of a token's row per lane); V rows go through LDS and are read back one channel per lane.  Rows past the end stand
-// in as zeros.  new_row >= 0: row new_row (= len - 1) is not in the cache yet, it is read from knew / vnew.
+// in as zeros.  new_row >= 0: row new_row (= len - 1) is not in the cache yet, it is read from k_new / v_new.
 template <int HD, bool BF, int G>
 __device__ __forceinline__ void walk_seg16_f32(const DecodeArgs& a, F32Smem<HD, G>& sm, int b, int kvh, int len, int first_row, int blk, int end,
-                                               Tickets& tk, F32State<HD>& st, int new_row, const uint16_t* knew, const uint16_t* vnew)
+                                               Tickets& tk, F32State<HD>& st, int new_row)
 {
     constexpr int CT = HD / 16, KDW = HD / 8, VIT = 32 * HD * 2 / (16 * 64);       // VIT: 16-byte pieces of V per lane
     constexpr int PITCH = F32Smem<HD, G>::PITCH;
@@ -554,9 +553,10 @@ __device__ __forceinline__ void walk_seg16_f32(const DecodeArgs& a, F32Smem<HD, 
     const int64_t rstride = (int64_t)kv.Hkv * HD;
     const uint16_t* k16 = static_cast<const uint16_t*>(kv.k16) + first_row * rstride + (int64_t)kvh * HD;
     const uint16_t* v16 = static_cast<const uint16_t*>(kv.v16) + first_row * rstride + (int64_t)kvh * HD;
+    const uint16_t *const knew = a.k_new + ((int64_t)b * kv.Hkv + kvh) * HD, *const vnew = a.v_new + ((int64_t)b * kv.Hkv + kvh) * HD;     // (read where there is a new row)
     uint16_t* const vt = &sm.vt[wave][0][0];
     auto number = [](uint32_t u) { return BF ? wq_bf16_bits_to_float(u) : wq_f16_bits_to_float(u); };
-    pass_setup_barrier(a, b, tk);
+    pass_setup_barrier(b, tk);
     for (; blk < end; blk++) {
         const int nv = len - blk * 32;
         uint32_t kd[2][KDW];

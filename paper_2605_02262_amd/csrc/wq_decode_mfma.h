@@ -157,6 +157,23 @@ __device__ __forceinline__ half8 v_operand(const uint32_t* x, int ct)
     }
 }
 
+// The launch's arguments, read from memory once more: for what is needed late or by few.  What the whole body keeps in scalar
+// registers has to fit them: one table too many, and the compiler waits for a part of the tables to set it aside before it
+// sends for the next part (three round trips in front of the first block instead of one, 0.9 us a launch).
+__device__ __forceinline__ const DecodeArgs& args_again()
+{
+    const __attribute__((address_space(4))) void* p = (const __attribute__((address_space(4))) void*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const DecodeArgs*)p;
+}
+
+// ... and a pointer among them, as what it is (arguments that the compiler did not see arrive could point anywhere)
+template <class T>
+__device__ __forceinline__ T* in_memory(T* p)
+{
+    return (T*)(__attribute__((address_space(1))) T*)p;
+}
+
 template <int HD>
 struct WaveState {
     floatx4 O[HD / 16];   // O^T tiles: row = channel 16ct + 4j + i, column = (g,h)
@@ -345,13 +362,13 @@ __device__ __forceinline__ void fetch_q_operands(const MfmaSmem<HD>& sm, int c, 
 // range of tickets (normally one) and keeps tickets that stand for blocks of a later class until it gets there.
 // The ticket that replaces a spent one is drawn at the start of a block's arithmetic and read at its end; LDS
 // operations have a counter of their own, so the draw never waits for the block loads that are in flight.
-// With WQ_DECODE_FIXED_SHARES the range is divided among the wavefronts by cost instead and no tickets are drawn.
+// With WQ_DECODE_FIXED_SHARES the range is divided among the wavefronts by cost instead: each holds its tickets from the start.
 struct Tickets {
     unsigned* ctr;      // the workgroup's counter (LDS)
-    unsigned held, end; // tickets held: [held, end)
-    bool spent;         // none left: another one is due
-    bool dealt;         // the fixed first tickets are the whole range: there is nothing to draw
+    unsigned held, end; // tickets held: [held, end); none left: another one is due
+    bool dealt;         // the tickets held are all that this wavefront gets: there is nothing to draw
     bool synced;        // this wavefront has passed the workgroup's set-up barrier
+    bool appends;       // the launch appends a token
     unsigned taper;     // from this ticket on (the workgroup's last WQ_TAPER_TICKETS) a wavefront refills only every other pipeline slot
 };
 
@@ -364,21 +381,23 @@ struct Tickets {
 // The sequence's last workgroup in dispatch order (highest KV head, highest split; every other one of the sequence was
 // dispatched before it and waits for nobody before it counts itself) waits at its very end until the count is complete,
 // clears the counter for the next launch and writes the new length.
-__device__ __forceinline__ void count_tables_read(const DecodeArgs& a, int b)
+__device__ __forceinline__ void count_tables_read(bool appends, int b)
 {
-    if (a.k_new && threadIdx.x == 0)
-        __hip_atomic_fetch_add(a.arrive + a.B * a.kv.Hkv * a.arrive_unit + b * WQ_ARRIVE_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!appends) return;
+    const DecodeArgs& a = args_again();
+    if (threadIdx.x == 0)
+        __hip_atomic_fetch_add(in_memory(a.arrive) + a.B * a.kv.Hkv * a.arrive_unit + b * WQ_ARRIVE_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The set-up barrier (staged query operands, initial value of the block counter) is taken by every wavefront
 // exactly once: after the first loads of the first class it walks have been issued, or, by a wavefront that has
 // no blocks at all, before the final merge.
-__device__ __forceinline__ void pass_setup_barrier(const DecodeArgs& a, int b, Tickets& t)
+__device__ __forceinline__ void pass_setup_barrier(int b, Tickets& t)
 {
     if (!t.synced) {
         __syncthreads();
         t.synced = true;
-        count_tables_read(a, b);
+        count_tables_read(t.appends, b);
     }
 }
 
@@ -393,39 +412,46 @@ __device__ __forceinline__ unsigned draw_tickets(unsigned* ctr, unsigned n)
 __device__ __forceinline__ unsigned ticket_value(unsigned v) { return (unsigned)__builtin_amdgcn_readfirstlane((int)v); }
 
 struct BlockSrc {
-    int cur, end;            // this wavefront's own blocks of the class
-    int pool_first;          // first block of the class's part of the workgroup's pool
-    unsigned tk_lo, tk_hi;   // tickets that stand for those pool blocks
+    int pool_first;          // first block of the class's part of the workgroup's range
+    unsigned tk_lo, tk_hi;   // tickets that stand for those blocks (tk_hi = 0: there are none)
 };
 
-// draws n tickets and waits for them (filling the pipeline at the start of a class)
-__device__ __forceinline__ void settle_tickets(Tickets& t, unsigned n)
-{
-    if (t.spent) {
-        t.held = t.dealt ? 0xFFFFFFFEu : ticket_value(draw_tickets(t.ctr, n));
-        t.end = t.dealt ? 0xFFFFFFFFu : t.held + n;
-        t.spent = false;
-    }
-}
-
+// Are there blocks of the class for this wavefront?  With no ticket left it draws `fill` of them and waits (at the start of a class).
 __device__ __forceinline__ bool has_blocks(const BlockSrc& s, Tickets& t, unsigned fill)
 {
-    if (s.cur < s.end) return true;
-    if (s.tk_lo >= s.tk_hi) return false;
-    settle_tickets(t, fill);
+    if (t.held == t.end) {
+        t.held = t.dealt ? 0xFFFFFFFEu : ticket_value(draw_tickets(t.ctr, fill));
+        t.end = t.dealt ? 0xFFFFFFFFu : t.held + fill;
+    }
     return t.held < s.tk_hi;
 }
 
-// next block of the class for this wavefront, or -1 (and then -1 on every later call for the class)
-__device__ __forceinline__ int next_block(BlockSrc& s, Tickets& t, unsigned fill)
+// next block of the class for this wavefront, or -1 (and then -1 on every later call for the class): a ticket for a block of a
+// later class is kept.  (A ticket is drawn beside the arithmetic of a block that has left none, so only a wavefront that gets no more has none here.)
+__device__ __forceinline__ int next_block(const BlockSrc& s, Tickets& t)
 {
-    if (s.cur < s.end) return s.cur++;
-    if (s.tk_lo >= s.tk_hi) return -1;
-    settle_tickets(t, fill);
-    if (t.held >= s.tk_hi) return -1;        // a block of a later class, or none: keep the tickets
-    const unsigned v = t.held++;
-    t.spent = t.held == t.end;
-    return s.pool_first + (int)(v - s.tk_lo);
+    if (t.held >= min(t.end, s.tk_hi)) return -1;
+    return s.pool_first + (int)(t.held++ - s.tk_lo);
+}
+
+// The first DEPTH blocks of the class (there is at least one): of the tickets held, and of those drawn where they don't reach
+template <int DEPTH>
+__device__ __forceinline__ void first_blocks(const BlockSrc& s, Tickets& t, int (&bi)[DEPTH])
+{
+    int n = (int)min(min(t.end, s.tk_hi) - t.held, (unsigned)DEPTH), at = s.pool_first + (int)(t.held - s.tk_lo);
+#pragma unroll
+    for (int d = 0; d < DEPTH; d++) bi[d] = d < n ? at + d : -1;
+    t.held += (unsigned)n;
+    if (n < DEPTH && t.held == t.end && !t.dealt) {
+        const unsigned more = (unsigned)(DEPTH - n);
+        t.held = ticket_value(draw_tickets(t.ctr, more));
+        t.end = t.held + more;
+        const unsigned in = min(max(s.tk_hi, t.held), t.end) - t.held;
+        at = s.pool_first + (int)(t.held - s.tk_lo) - n;
+#pragma unroll
+        for (int d = 0; d < DEPTH; d++) bi[d] = d >= n && d < n + (int)in ? at + d : bi[d];
+        t.held += in;
+    }
 }
 
 template <int HD, int BITS>
@@ -461,7 +487,7 @@ __device__ __forceinline__ void load_dwords(const uint32_t* __restrict__ p, uint
 // One class of one (sequence, KV head): this wavefront's share of its 32-token blocks (len tokens from token slot
 // tok_base of the class buffers).
 template <int HD, int BITS, int DEPTH>
-__device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD>& sm, int b, int kvh, int len, int tok_base, BlockSrc& src,
+__device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD>& sm, int b, int kvh, int len, int tok_base, const BlockSrc& src,
                                                 Tickets& tk, float c_log2, WaveState<HD>& st)
 {
     constexpr int C = BITS == 2 ? 0 : (BITS == 4 ? 1 : 2);
@@ -493,12 +519,11 @@ __device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD
     // software pipeline: DEPTH blocks in flight per wavefront; the first loads go out before anything else
     F f[DEPTH];
     int bi[DEPTH];
+    first_blocks<DEPTH>(src, tk, bi);
 #pragma unroll
-    for (int d = 0; d < DEPTH; d++) {
-        bi[d] = next_block(src, tk, DEPTH - d);
+    for (int d = 0; d < DEPTH; d++)
         if (bi[d] >= 0) load(bi[d], f[d]);
-    }
-    pass_setup_barrier(a, b, tk);
+    pass_setup_barrier(b, tk);
     U4 Bqw[NK];
     float qexp, qsum;
     fetch_q_operands<HD>(sm, C, Bqw, qexp, qsum);
@@ -519,7 +544,7 @@ __device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD
     for (int v = 0; v < 4; v++) ms[v] = st.m + v_slot_shift<BITS>(v) - st.up;
 
     auto compute = [&](int blk, const F& f) {
-        const bool redraw = tk.spent;
+        const bool redraw = tk.held == tk.end && !tk.dealt;
         unsigned drawn = 0;
         if (redraw) drawn = draw_tickets(tk.ctr, 1u);
         if (blk * 32 + 32 > len) {
@@ -598,7 +623,6 @@ __device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD
         if (redraw) {
             tk.held = got;
             tk.end = got + 1u;
-            tk.spent = false;
         }
     };
 
@@ -613,7 +637,7 @@ __device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD
                     bi[d] = -1;
                     continue;
                 }
-                bi[d] = next_block(src, tk, 1u);
+                bi[d] = next_block(src, tk);
                 if (bi[d] >= 0) load(bi[d], f[d]);
             }
         }
@@ -644,11 +668,9 @@ __device__ __forceinline__ floatx4 mfma16(uint32_t a0, uint32_t a1, uint32_t a2,
 // the bf16 instruction with the exact bf16 query and the weights split into two bf16 terms (p = hi + lo);
 // fp16 caches use the f16 instruction.  Accumulators are in true units here (no 2^-24).
 template <int HD, bool BF>
-// new_row >= 0: row new_row (= len - 1) is not in the cache yet: it is read from knew / vnew, this (sequence, KV head)'s
-// [hd] slices of the token that the launch appends.
-__device__ __forceinline__ void walk_seg16_mfma(const DecodeArgs& a, MfmaSmem<HD>& sm, int b, int kvh, int len, int first_row, BlockSrc& src,
-                                                Tickets& tk, float c_log2, WaveState<HD>& st, int new_row, const uint16_t* knew,
-                                                const uint16_t* vnew)
+// new_row >= 0: row new_row (= len - 1) is not in the cache yet: it is read from k_new / v_new, the token that the launch appends.
+__device__ __forceinline__ void walk_seg16_mfma(const DecodeArgs& a, MfmaSmem<HD>& sm, int b, int kvh, int len, int first_row, const BlockSrc& src,
+                                                Tickets& tk, float c_log2, WaveState<HD>& st, int new_row)
 {
     constexpr int NK = HD / 32, CT = HD / 16, PITCH = HD / 2 + VT_PAD, KDW = HD / 8;
     if (!has_blocks(src, tk, 1u)) return;
@@ -659,16 +681,17 @@ __device__ __forceinline__ void walk_seg16_mfma(const DecodeArgs& a, MfmaSmem<HD
     const int64_t rstride = (int64_t)kv.Hkv * HD;
     const uint16_t* k16 = static_cast<const uint16_t*>(kv.k16) + (int64_t)kvh * HD;
     const uint16_t* v16 = static_cast<const uint16_t*>(kv.v16) + (int64_t)kvh * HD;
-    pass_setup_barrier(a, b, tk);
+    const uint16_t *const knew = a.k_new + ((int64_t)b * kv.Hkv + kvh) * HD, *const vnew = a.v_new + ((int64_t)b * kv.Hkv + kvh) * HD;     // (read where there is a new row)
+    pass_setup_barrier(b, tk);
     U4 Bq[NK];
     float qexp, qsum;
     fetch_q_operands<HD>(sm, 3, Bq, qexp, qsum);
     const float cexp = c_log2 * qexp;
     uint16_t* vt = &sm.run.vt[wave][0][0];
 
-    for (int blk = next_block(src, tk, 1u); blk >= 0; blk = next_block(src, tk, 1u)) {
+    for (int blk = next_block(src, tk); blk >= 0; blk = next_block(src, tk)) {
         const int nv = len - blk * 32;
-        const bool redraw = tk.spent;
+        const bool redraw = tk.held == tk.end && !tk.dealt;
         unsigned drawn = 0;
         if (redraw) drawn = draw_tickets(tk.ctr, 1u);
         // ---- all loads of the block up front: one memory round trip per block ----
@@ -781,7 +804,6 @@ __device__ __forceinline__ void walk_seg16_mfma(const DecodeArgs& a, MfmaSmem<HD
         if (redraw) {
             tk.held = got;
             tk.end = got + 1u;
-            tk.spent = false;
         }
     }
 }
@@ -798,18 +820,18 @@ constexpr long long WQ_APPEND_WAIT_TICKS = 400000000ll;   // 4 s of the 100 MHz 
 __device__ __forceinline__ void finish_append(const DecodeArgs& a, int b, int kvh, int split, int new_row)
 {
     if (!a.k_new || threadIdx.x != 0 || kvh != a.kv.Hkv - 1 || split != a.splits - 1) return;
-    unsigned* ctr = a.arrive + a.B * a.kv.Hkv * a.arrive_unit + b * WQ_ARRIVE_STRIDE;
+    unsigned* ctr = in_memory(a.arrive) + a.B * a.kv.Hkv * a.arrive_unit + b * WQ_ARRIVE_STRIDE;
     const unsigned all = (unsigned)a.kv.Hkv * (unsigned)a.splits;
     const long long t_start = wall_clock64();
     while (__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != all) {
         if (wall_clock64() - t_start > WQ_APPEND_WAIT_TICKS) {
-            atomicOr(a.status, WQ_DEV_APPEND_TIMEOUT);
+            atomicOr(in_memory(a.status), WQ_DEV_APPEND_TIMEOUT);
             break;
         }
         __builtin_amdgcn_s_sleep(8);
     }
     __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (new_row >= 0) a.kv.len16[b] = new_row + 1;
+    if (new_row >= 0) in_memory(a.kv.len16)[b] = new_row + 1;
 }
 
 // ---- which part of which sequence a workgroup of a launch by length gets (at most 64 sequences: one per lane) ----
@@ -913,20 +935,20 @@ __device__ __forceinline__ void finish_append_by_length(const DecodeArgs& a, Sme
     const int lane = threadIdx.x;
     const bool mine = lane < a.B;
     const unsigned expect = (unsigned)sm.expect[lane];
-    unsigned* const ctr = a.arrive + a.B * a.kv.Hkv * a.arrive_unit + (mine ? lane : 0) * WQ_ARRIVE_STRIDE;
+    unsigned* const ctr = in_memory(a.arrive) + a.B * a.kv.Hkv * a.arrive_unit + (mine ? lane : 0) * WQ_ARRIVE_STRIDE;
     const long long t_start = wall_clock64();
     while (true) {
         const bool there = !mine || __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == expect;
         if (__builtin_amdgcn_ballot_w64(!there) == 0) break;
         if (wall_clock64() - t_start > WQ_APPEND_WAIT_TICKS) {
-            if (lane == 0) atomicOr(a.status, WQ_DEV_APPEND_TIMEOUT);
+            if (lane == 0) atomicOr(in_memory(a.status), WQ_DEV_APPEND_TIMEOUT);
             break;
         }
         __builtin_amdgcn_s_sleep(8);
     }
     if (mine) {
         __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (sm.grown[lane] >= 0) a.kv.len16[lane] = sm.grown[lane];
+        if (sm.grown[lane] >= 0) in_memory(a.kv.len16)[lane] = sm.grown[lane];
     }
 }
 
@@ -1032,14 +1054,14 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
     const bool bf16seg = a.kv.dtype16 == WQ_BF16;
     WQ_STAMP(0);
 
-    // ---- the sequence's tables first (their loads are in flight while the query operands are built) ----
+    // ---- the sequence's tables first ----
     int cls_len[4], cls_off[4], end16;
     float v_scale_max;
     if constexpr (PACKED) {
         const Place p = place_by_length<HD, G>(a, sm, (int)blockIdx.x);
         if (p.b < 0) {
             if (a.k_new) __syncthreads();
-            count_tables_read(a, 0);
+            count_tables_read(a.k_new != nullptr, 0);
             finish_append_by_length(a, sm, (int)blockIdx.x);
             return;
         }
@@ -1064,25 +1086,15 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
     }
     const int unit = b * a.kv.Hkv + kvh;
     // a token appended by this launch becomes the last row of the 16-bit segment: read from k_new / v_new by whoever
-    // walks its block, copied into the cache by the first split's workgroup, counted in len16 once every workgroup of
-    // the sequence has read len16 (finish_append)
+    // walks its block, copied into the cache by the first split's workgroup (at its end: the copy is a round trip to memory that
+    // stood in front of that workgroup's first loads), counted in len16 once every workgroup of the sequence has read len16 (finish_append)
     int new_row = -1;
-    const uint16_t *knew = nullptr, *vnew = nullptr;
     if (a.k_new) {
-        const int64_t row = (int64_t)cls_off[3] + cls_len[3];
-        if (row < end16 && row < a.kv.cap16) {
-            new_row = cls_len[3];
-            cls_len[3] += 1;
-            knew = a.k_new + ((int64_t)b * a.kv.Hkv + kvh) * HD;
-            vnew = a.v_new + ((int64_t)b * a.kv.Hkv + kvh) * HD;
-            if (split == 0 && tid < 2 * (HD / 8)) {
-                const int plane = tid / (HD / 8), piece = tid % (HD / 8);
-                uint16_t* dst = static_cast<uint16_t*>(plane ? a.kv.v16 : a.kv.k16) + (row * a.kv.Hkv + kvh) * HD + piece * 8;
-                *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>((plane ? vnew : knew) + piece * 8);
-            }
-        } else if (split == 0 && kvh == 0 && tid == 0) {
-            atomicOr(a.status, WQ_DEV_SEG16_OVERFLOW);      // the segment is full: nothing is appended
-        }
+        const uint32_t row = (uint32_t)cls_off[3] + (uint32_t)cls_len[3];
+        const bool room = row < (uint32_t)end16 && ((uint64_t)a.kv.cap16 >> 32 != 0 || row < (uint32_t)a.kv.cap16);
+        new_row = room ? cls_len[3] : -1;
+        cls_len[3] += room ? 1 : 0;
+        if (!room && split == 0 && kvh == 0 && tid == 0) atomicOr(in_memory(args_again().status), WQ_DEV_SEG16_OVERFLOW);      // the segment is full: nothing is appended
     }
     WQ_WSTAMP(5, wall_clock64() + (long long)((cls_len[0] + cls_len[1] + cls_len[2] + cls_len[3] + cls_off[0] + cls_off[1] + cls_off[2] + cls_off[3]) & 0));   // the tables have arrived
     if (!PACKED && a.len_scale > 0.f) {     // (more than 64 sequences: the sequence's share of the launch's splits, the other workgroups have nothing to do)
@@ -1090,7 +1102,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         S = max(1, min(a.splits, (int)ceilf((float)tokens * a.len_scale)));
         if (split >= S) {
             if (a.k_new) __syncthreads();
-            count_tables_read(a, b);
+            count_tables_read(a.k_new != nullptr, b);
             finish_append(a, b, kvh, split, new_row);
             return;
         }
@@ -1099,14 +1111,13 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
     if constexpr (F32) stage_q_split<HD, G>(a, sm, b, kvh, wave);
     else stage_q_operands<HD>(a, sm, b, kvh, wave, bf16seg);
 
-    // ---- the workgroup's range of the stream [16-bit | 8-bit | 4-bit | 2-bit] of (b, kvh), and this wavefront's
-    //      fixed share of it (none unless the launch asks for fixed shares or the walkers are those of one and four groups: then there is no pool) ----
-    const bool fixed_shares = F32 || a.fixed_shares;
+    // ---- the workgroup's range of the stream [16-bit | 8-bit | 4-bit | 2-bit] of (b, kvh), and what of it this wavefront has from the
+    //      start: a few tickets, all of them where the launch asks for fixed shares, or (one and four groups) blocks own[c] up to own_end[c] ----
     Tickets tk;
-    tk.ctr = &sm.next_ticket;
     tk.synced = false;
-    tk.taper = 0xFFFFFFFFu;
+    tk.appends = a.k_new != nullptr;
     BlockSrc src[4];
+    int own[4], own_end[4];
     {
         int nb[4];
 #pragma unroll
@@ -1115,49 +1126,59 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         unsigned total = 0u;
 #pragma unroll
         for (int c = 0; c < 4; c++) total += (unsigned)nb[c] * (unsigned)block_cost<HD, G>(c);
-        // cost at which split x starts: floor(total * x / S) up to rounding (one reciprocal, the same bits in every
-        // wavefront of the launch); split 0 starts at cost 0, the last one ends behind everything
-        const float rS = __builtin_amdgcn_rcpf((float)S);
-        auto start_of = [&](int x) {
-            return min(total, (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)((float)total * ((float)x * rS))));
-        };
-        const unsigned G0 = split == 0 ? 0u : start_of(split);
-        const unsigned G1 = split == S - 1 ? total : start_of(split + 1);
-        unsigned base = 0u;
-        unsigned t = 0;
+        // cost at which split x starts: floor(total * x / S) up to rounding (one reciprocal, the same bits in every wavefront of
+        // the launch; even lanes find this split's, odd ones the next one's); split 0 starts at cost 0, the last one ends behind everything
+        const unsigned start = min(total, (unsigned)((float)total * ((float)(split + (lane & 1)) * __builtin_amdgcn_rcpf((float)S))));
+        const unsigned G0 = (unsigned)__builtin_amdgcn_readlane((int)start, 0), next = (unsigned)__builtin_amdgcn_readlane((int)start, 1);
+        const unsigned G1 = split == S - 1 ? total : next;
+        // ... and the wavefront's share of the cost, where it has one
+        static_assert(WQ_WAVES == 8, "the shifts");
+        const unsigned long long span = G1 - G0;
+        const unsigned x0 = G0 + (unsigned)((span * (unsigned)wave) >> 3), x1 = G0 + (unsigned)((span * (unsigned)(wave + 1)) >> 3);
+        unsigned base = 0u, t = 0u;
+        if constexpr (F32) {
 #pragma unroll
-        for (int c = 3; c >= 0; c--) {
-            const int e0 = range_edge_of<HD, G>(c, G0, base, nb[c]);
-            const int e1 = range_edge_of<HD, G>(c, G1, base, nb[c]);
-            if (fixed_shares) {                    // the range is divided among the wavefronts by cost; no pool
-                const unsigned long long span = G1 - G0;
-                const unsigned x0 = G0 + (unsigned)((span * (unsigned)wave) >> 3), x1 = G0 + (unsigned)((span * (unsigned)(wave + 1)) >> 3);
-                static_assert(WQ_WAVES == 8, "the shift above");
-                src[c].cur = wave == 0 ? e0 : range_edge_of<HD, G>(c, x0, base, nb[c]);
-                src[c].end = wave == WQ_WAVES - 1 ? e1 : range_edge_of<HD, G>(c, x1, base, nb[c]);
-                src[c].pool_first = e1;
-                src[c].tk_lo = src[c].tk_hi = t;
-            } else {                               // the whole range is the pool
-                src[c].cur = src[c].end = 0;
+            for (int c = 3; c >= 0; c--) {
+                own[c] = range_edge_of<HD, G>(c, x0, base, nb[c]);
+                own_end[c] = range_edge_of<HD, G>(c, x1, base, nb[c]);
+                base += (unsigned)nb[c] * (unsigned)block_cost<HD, G>(c);
+            }
+        } else {
+            unsigned bases[4];
+#pragma unroll
+            for (int c = 3; c >= 0; c--) {
+                bases[c] = base;
+                const int e0 = range_edge_of<HD, G>(c, G0, base, nb[c]);
+                const int e1 = range_edge_of<HD, G>(c, G1, base, nb[c]);
                 src[c].pool_first = e0;
                 src[c].tk_lo = t;
                 t += (unsigned)(e1 - e0);
-                src[c].tk_hi = t;
+                src[c].tk_hi = e1 > e0 ? t : 0u;
+                base += (unsigned)nb[c] * (unsigned)block_cost<HD, G>(c);
             }
-            base += (unsigned)nb[c] * (unsigned)block_cost<HD, G>(c);
+            // The first tickets are fixed, so that the first loads can go out before the workgroup's set-up barrier; the counter
+            // starts behind them.  WQ_FIRST_TICKETS consecutive blocks per wavefront, or, in a range of fewer blocks, what
+            // spreads them over all eight: a block's arithmetic is half a microsecond, and with four blocks each the first
+            // wavefronts of a short range walked it one block after the other beside idle ones (5 blocks, heads of 64: 9.0 -> 6.6 us
+            // a call; 13 blocks, heads of 128: 15.8 -> 13.3)
+            const unsigned first = min((unsigned)WQ_FIRST_TICKETS, (t + (unsigned)WQ_WAVES - 1u) / (unsigned)WQ_WAVES);
+            tk.held = (unsigned)wave * first;
+            tk.end = tk.held + first;
+            tk.dealt = first * (unsigned)WQ_WAVES >= t;
+            tk.taper = t > (unsigned)WQ_TAPER_TICKETS ? t - (unsigned)WQ_TAPER_TICKETS : 0xFFFFFFFFu;
+            tk.ctr = &sm.next_ticket;
+            if (tid == 0) sm.next_ticket = first * (unsigned)WQ_WAVES;
+            if (a.fixed_shares) {
+                tk.held = tk.end = 0u;
+#pragma unroll
+                for (int c = 3; c >= 0; c--) {
+                    tk.held += (unsigned)(range_edge_of<HD, G>(c, x0, bases[c], nb[c]) - src[c].pool_first);
+                    tk.end += (unsigned)(range_edge_of<HD, G>(c, x1, bases[c], nb[c]) - src[c].pool_first);
+                }
+                tk.dealt = true;
+                tk.taper = 0xFFFFFFFFu;
+            }
         }
-        if (!fixed_shares && t > (unsigned)WQ_TAPER_TICKETS) tk.taper = t - (unsigned)WQ_TAPER_TICKETS;
-        // The first tickets are fixed, so that the first loads can go out before the workgroup's set-up barrier; the counter
-        // starts behind them.  WQ_FIRST_TICKETS consecutive blocks per wavefront, or, in a range of fewer blocks, what
-        // spreads them over all eight: a block's arithmetic is half a microsecond, and with four blocks each the first
-        // wavefronts of a short range walked it one block after the other beside idle ones (5 blocks, heads of 64: 9.0 -> 6.6 us
-        // a call; 13 blocks, heads of 128: 15.8 -> 13.3)
-        const unsigned first = min((unsigned)WQ_FIRST_TICKETS, (t + (unsigned)WQ_WAVES - 1u) / (unsigned)WQ_WAVES);
-        tk.held = (unsigned)wave * first;
-        tk.end = tk.held + first;
-        tk.spent = first == 0u;
-        tk.dealt = !fixed_shares && first * (unsigned)WQ_WAVES >= t;
-        if (tid == 0) sm.next_ticket = first * (unsigned)WQ_WAVES;
     }
 
     WQ_STAMP(1);
@@ -1181,7 +1202,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
             st.accM[s] = 0.f;
             st.place[s] = 1.0f;
         }
-        if (src[3].cur < src[3].end) {
+        if (own[3] < own_end[3]) {
             F32State<HD> st16;
 #pragma unroll
             for (int ct = 0; ct < CT; ct++) st16.O[ct][0] = st16.O[ct][1] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -1189,14 +1210,14 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
             st16.l = 0.f;
             load_q_quarter<HD>(a, b, kvh, st16.q);
             if (bf16seg)
-                walk_seg16_f32<HD, true, G>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3].cur, src[3].end, tk, st16, new_row, knew, vnew);
+                walk_seg16_f32<HD, true, G>(a, sm, b, kvh, cls_len[3], cls_off[3], own[3], own_end[3], tk, st16, new_row);
             else
-                walk_seg16_f32<HD, false, G>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3].cur, src[3].end, tk, st16, new_row, knew, vnew);
+                walk_seg16_f32<HD, false, G>(a, sm, b, kvh, cls_len[3], cls_off[3], own[3], own_end[3], tk, st16, new_row);
             carry_on<HD, G>(st16, st);
         }
-        walk_class_split<HD, 8, G, G == 4 ? 1 : 2>(a, sm, b, kvh, cls_len[2], cls_off[2], src[2].cur, src[2].end, tk, st);
-        walk_class_split<HD, 4, G, 2>(a, sm, b, kvh, cls_len[1], cls_off[1], src[1].cur, src[1].end, tk, st);
-        walk_class_split<HD, 2, G, 2>(a, sm, b, kvh, cls_len[0], cls_off[0], src[0].cur, src[0].end, tk, st);
+        walk_class_split<HD, 8, G, G == 4 ? 1 : 2>(a, sm, b, kvh, cls_len[2], cls_off[2], own[2], own_end[2], tk, st);
+        walk_class_split<HD, 4, G, 2>(a, sm, b, kvh, cls_len[1], cls_off[1], own[1], own_end[1], tk, st);
+        walk_class_split<HD, 2, G, 2>(a, sm, b, kvh, cls_len[0], cls_off[0], own[0], own_end[0], tk, st);
         hand_over_split<HD, G>(sm, st);
     } else {
         const float c_log2 = a.sm_scale * 1.4426950408889634f;
@@ -1211,9 +1232,9 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         WQ_WSTAMP(0, wall_clock64());
         if (has_blocks(src[3], tk, 1u)) {              // (most wavefronts have no block of the 16-bit segment and go straight on)
             if (bf16seg)
-                walk_seg16_mfma<HD, true>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3], tk, c_log2, st, new_row, knew, vnew);
+                walk_seg16_mfma<HD, true>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3], tk, c_log2, st, new_row);
             else
-                walk_seg16_mfma<HD, false>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3], tk, c_log2, st, new_row, knew, vnew);
+                walk_seg16_mfma<HD, false>(a, sm, b, kvh, cls_len[3], cls_off[3], src[3], tk, c_log2, st, new_row);
             // the quantized classes accumulate 2^(up-24) * (p s_v code); bring the 16-bit part to the same unit (exact)
             const float to_unit = pow2_of(st.up - 24.0f);
 #pragma unroll
@@ -1247,15 +1268,27 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
             sm.ml[wave][h][1] = l;
         }
     }
-    pass_setup_barrier(a, b, tk);
+    pass_setup_barrier(b, tk);
+    // what the end needs of the arguments: there when the other wavefronts are
+    const DecodeArgs& e = F32 ? a : args_again();         // (with the walkers of one and four groups they fit the scalar registers)
+    int rep = e.rep, nparts = e.nparts, Hq = e.Hq, fused = e.fused, arrive_unit = e.arrive_unit;
+    unsigned* arrive = e.arrive;
+    float *part = e.part, *part_ml = e.part_ml, *out = e.out, *lse = e.lse;
+    if constexpr (!F32)
+        asm volatile("" : "+s"(rep), "+s"(nparts), "+s"(Hq), "+s"(fused), "+s"(arrive_unit), "+s"(arrive), "+s"(part), "+s"(part_ml), "+s"(out), "+s"(lse));
+    if (new_row >= 0 && split == 0 && wave == WQ_WAVES - 1 && lane < 2 * (HD / 8)) {
+        const int plane = lane / (HD / 8), piece = lane % (HD / 8);
+        uint16_t* const dst = in_memory(static_cast<uint16_t*>(plane ? e.kv.v16 : e.kv.k16)) + (((int64_t)cls_off[3] + new_row) * e.kv.Hkv + kvh) * HD + piece * 8;
+        *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(in_memory(plane ? e.v_new : e.k_new) + (int64_t)unit * HD + piece * 8);
+    }
     __syncthreads();
     // ---- merge the wavefronts, write the partial (m in natural-log units): wavefront r takes head r, a lane CPL
     //      neighbouring channels, so the eight scales of a head are computed once per lane ----
     constexpr int CPL = HD / 64;                   // channels per lane
     static_assert(WQ_WAVES >= WQ_MAX_REP, "one wavefront per head");
-    const int64_t part_row = (int64_t)unit * a.nparts * a.rep;          // the unit's first row (split 0, head 0)
-    if (wave < a.rep) {
-        const int64_t row = part_row + split * a.rep + wave;
+    const int64_t part_row = (int64_t)unit * nparts * rep;          // the unit's first row (split 0, head 0)
+    if (wave < rep) {
+        const int64_t row = part_row + split * rep + wave;
         float mw[WQ_WAVES];
 #pragma unroll
         for (int w = 0; w < WQ_WAVES; w++) mw[w] = sm.ml[w][wave][0];
@@ -1274,14 +1307,14 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         }
         // device-scope stores go through to memory (every XCD has an L2 of its own), so that no cache write-back
         // is needed to hand the partial to the workgroup that merges the splits
-        store_through<CPL>(a.part + row * HD + CPL * lane, num);
+        store_through<CPL>(in_memory(part) + row * HD + CPL * lane, num);
         if (lane == 0) {
             const float ml2[2] = {F32 ? M : M * 0.6931471805599453f, L};       // (the walkers of one and four groups keep the reference in natural units)
-            store_through<2>(a.part_ml + row * 2, ml2);
+            store_through<2>(in_memory(part_ml) + row * 2, ml2);
         }
     }
     WQ_STAMP(5);
-    if (!a.fused) return;
+    if (!fused) return;
 
     // ---- the last workgroup of (b, kvh) to get here merges the partials of all splits, in split order; head by head:
     //      head r's partial was written by wavefront r alone, so wavefront r reports in for it on a counter of its own
@@ -1292,10 +1325,10 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
     // device-scope loads that do not stop at a cache.  This costs one memory round trip; a device-scope release fence
     // would add a write-back of the whole L2 (measured: 19 us per call).
     bool last = false;
-    if (wave < a.rep) {
+    if (wave < rep) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         WQ_STAMP(56);
-        unsigned* const counter = a.arrive + unit * a.arrive_unit + wave * (a.arrive_unit / WQ_MAX_REP);
+        unsigned* const counter = in_memory(arrive) + unit * arrive_unit + wave * (arrive_unit / WQ_MAX_REP);
         static_assert(WQ_ARRIVE_STRIDE >= WQ_MAX_REP, "one counter per head inside a unit's piece");
         unsigned old = 0u;
         if (lane == 0) old = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1315,12 +1348,13 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         const int np = S;                          // (the splits are all the partials there are in a launch that merges them itself)
         const int r = lane >> 4, k16 = lane & 15;
         constexpr int PIECES = HD / 64;            // 16-byte pieces of a split's channels per lane
-        const unsigned rows = (unsigned)(np * a.rep);
-        const __amdgpu_buffer_rsrc_t mls = __builtin_amdgcn_make_buffer_rsrc(a.part_ml + part_row * 2, 0, (int)(rows * 8u), 0x00020000);
-        const __amdgpu_buffer_rsrc_t nums = __builtin_amdgcn_make_buffer_rsrc(a.part + part_row * HD, 0, (int)(rows * (HD * 4u)), 0x00020000);
+        const unsigned rows = (unsigned)(np * rep);
+        const int first_row = __builtin_amdgcn_readfirstlane((int)part_row);         // (few units, few splits: merges_itself)
+        const __amdgpu_buffer_rsrc_t mls = __builtin_amdgcn_make_buffer_rsrc(part_ml + (int64_t)first_row * 2, 0, (int)(rows * 8u), 0x00020000);
+        const __amdgpu_buffer_rsrc_t nums = __builtin_amdgcn_make_buffer_rsrc(part + (int64_t)first_row * HD, 0, (int)(rows * (HD * 4u)), 0x00020000);
         const int s_l = split_of_lane(lane);
-        const floatx2 ml = ld_part2(mls, (unsigned)(s_l * a.rep + wave) * 8u);
-        const unsigned chan = (unsigned)(r * a.rep + wave) * (HD * 4u) + (unsigned)k16 * 16u, step = (unsigned)a.rep * (MERGE_CHAINS * HD * 4u);
+        const floatx2 ml = ld_part2(mls, (unsigned)(s_l * rep + wave) * 8u);
+        const unsigned chan = (unsigned)(r * rep + wave) * (HD * 4u) + (unsigned)k16 * 16u, step = (unsigned)rep * (MERGE_CHAINS * HD * 4u);
         float w_s = 0.f, M = -INFINITY, L = 0.f;
         floatx4 acc[PIECES];
 #pragma unroll
@@ -1347,7 +1381,7 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         else if (np <= 32) gather(std::integral_constant<int, 8>{});
         else gather(std::integral_constant<int, 16>{});
         WQ_STAMP(58);
-        const int hq = kvh * a.rep + wave;
+        const int hq = kvh * rep + wave;
         float o[CPL];
         int ch;                                    // the first of the lane's channels
         if constexpr (PIECES == 2) {
@@ -1363,14 +1397,14 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         }
 #pragma unroll
         for (int c = 0; c < CPL; c++) o[c] = L > 0.f ? o[c] / L : 0.f;
-        store_plain<CPL>(a.out + ((int64_t)b * a.Hq + hq) * HD + ch, o);
-        if (a.lse && lane == 0) a.lse[(int64_t)b * a.Hq + hq] = L > 0.f ? M + logf(L) : -INFINITY;
+        store_plain<CPL>(in_memory(out) + ((int64_t)b * Hq + hq) * HD + ch, o);
+        if (lse && lane == 0) in_memory(lse)[(int64_t)b * Hq + hq] = L > 0.f ? M + logf(L) : -INFINITY;
     }
     WQ_STAMP(59);
     if constexpr (PACKED)
-        finish_append_by_length(a, sm, (int)blockIdx.x);
+        finish_append_by_length(e, sm, (int)blockIdx.x);
     else
-        finish_append(a, b, kvh, split, new_row);
+        finish_append(e, b, kvh, split, new_row);
 }
 
 }  // namespace

@@ -485,22 +485,25 @@ static bool merges_itself(const void* q, int q_dtype, int B, const wq_packed_kv*
 // counts is (rounds) x (fixed cost of a workgroup + its blocks).  A round begun for a few workgroups costs as much as a full
 // one (9 sequences x 4 KV heads of 12800 tokens: 7 splits 20.8 us, 8 splits 30.4 us; 5 sequences: 12 splits 15.3, 13 splits
 // 22.9), and several full rounds can beat one with idle compute units (20 x 8 of 12800: 1 split 68.8, 3 splits 63.3).  Up
-// to 16 splits are merged in one round trip, up to 32 in one twice as large, more in two: 1.2 and 3.5 us in the sum.
-// Within that, the finer the better down to a few blocks per workgroup (28/4 heads of 128, 12800 tokens, batch 1: 13
-// splits 13.2 us, 32 splits 11.9; 1600 tokens: 2 splits 11.1, 12 splits 8.3).
+// to 16 splits are merged with 4 loads in flight per row of lanes, up to 32 with 8, up to 64 with 16: 0.3 and 1.4 us in the sum (28/4 heads of
+// 128, 1600 tokens, batch 1: 16 splits 7.5 us, 20 splits 7.9, 40 splits 8.9, 64 splits 9.7).
+// Within that, the finer the better down to a few blocks per workgroup (28/4 heads of 128, 12800 tokens, batch 1: 16
+// splits 10.5 us, 32 splits 9.7, 64 splits 9.9; 39200 tokens: 17.8, 13.3, 12.8; 14/2 heads of 64, 12800 tokens: 16 splits 8.1, 32 splits 7.4; group 64, 39200 tokens: 32 splits 12.3, 64 splits 9.7).
 static int splits_for_rounds(int B, const wq_packed_kv* kv, int64_t max_seq_tokens, int most)
 {
     const int64_t units = (int64_t)B * kv->Hkv, blocks = (max_seq_tokens + 31) / 32;
-    // a block's cost, averaged over the cache's slots; a block of cost 100 takes 0.12 us of a compute unit (0.08 with heads of 64)
+    const bool two = kv->hd / kv->group == 2, large = kv->hd == 128;
+    // a block's cost, averaged over the cache's slots
     const double slots = (double)kv->cap[0] + (double)kv->cap[1] + (double)kv->cap[2] + (double)kv->cap16;
-    const int* const unit = kv->hd / kv->group != 2 ? WQ_BLOCK_COST_F32 : kv->hd == 64 ? WQ_BLOCK_COST_64 : WQ_BLOCK_COST;
+    const int* const unit = !two ? WQ_BLOCK_COST_F32 : large ? WQ_BLOCK_COST : WQ_BLOCK_COST_64;
     const double cost = slots > 0 ? ((double)kv->cap[0] * unit[0] + (double)kv->cap[1] * unit[1] +
                                      (double)kv->cap[2] * unit[2] + (double)kv->cap16 * unit[3]) / slots : unit[0];
-    const double block_us = cost * (kv->hd == 128 ? 1.2e-3 : 0.8e-3), fixed_us = kv->hd == 128 ? 8.0 : 6.5;
+    // a compute unit's time for it, with little traffic besides (what memory takes when the whole chip is at it depends little on the splits)
+    const double block_us = cost * (two ? (large ? 0.85e-3 : 0.55e-3) : (large ? 1.45e-3 : 0.95e-3)), fixed_us = large ? 8.0 : 6.5;
     int best = 1;
     double best_us = 0;
     for (int s = 1; s <= most && s <= (blocks > 1 ? blocks : 1); s++) {
-        const double us = (double)((units * s + 255) / 256) * (fixed_us + block_us * (double)blocks / s) + (s > 32 ? 3.5 : s > 16 ? 1.2 : 0.0);
+        const double us = (double)((units * s + 255) / 256) * (fixed_us + block_us * (double)blocks / s) + (s > 32 ? 1.4 : s > 16 ? 0.3 : 0.0);
         if (s == 1 || us < best_us) { best_us = us; best = s; }
     }
     return best;

@@ -99,6 +99,21 @@ __device__ __forceinline__ void wq_ld8(const __half* p, float* x)
     }
 }
 
+// 8 consecutive elements of a row that is read once, past the caches' replacement order.  For the 16-bit types, where a
+// wavefront's load takes whole lines: an fp32 row's pieces of 32 bytes per lane come in two loads that share every line, and
+// the second one would fetch it again.
+template <typename T>
+__device__ __forceinline__ void wq_ld8_once(const T* p, float* x)
+{
+    if constexpr (sizeof(T) == 2) {
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        const u4 u = __builtin_nontemporal_load(reinterpret_cast<const u4*>(p));
+        wq_ld8(reinterpret_cast<const T*>(&u), x);
+    } else {
+        wq_ld8(p, x);
+    }
+}
+
 // first b in [0,B) with off[b+1] > x  (off ascending, off[0] <= x < off[B] assumed)
 __device__ __forceinline__ int wq_find_seq(const int32_t* off, int B, int64_t x)
 {

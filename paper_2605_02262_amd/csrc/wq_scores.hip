@@ -113,7 +113,10 @@ __global__ __launch_bounds__(256) void k_text_mean(const T* __restrict__ txt, co
 }
 
 // c_k = (w_k . tbar) / |w_k|.  VEC: one wavefront takes WQ_TS_ROWS consecutive rows so that each 32-byte piece of the pooled
-// text vector is loaded once per WQ_TS_ROWS rows; 16 bytes of every row per lane and iteration.
+// text vector is loaded once per WQ_TS_ROWS rows; 16 bytes of every row per lane and iteration.  Bound by HBM.  The rows are read
+// once and their loads say so (non-temporal): 4 x 50176 rows of 3584 bf16 246 -> 229 us a call (6.0 -> 6.5 TB/s in this kernel), 50176 of 896 35.8 ->
+// 31.6, rows that have just been written included (64.3 -> 61.4 with the copy that writes 12544 of 3584); 5 % slower only where the same 25 to 110 MB are
+// scored again and again and nothing else is read (50176 of 896: 29.6 -> 31.5).  fp32 rows keep plain loads (10 % faster: wq_ld8_once).
 template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void k_token_score(const T* __restrict__ vis, const float* __restrict__ tbar, int D, int B,
                                                      const int32_t* __restrict__ vis_off, int64_t total_vis,
@@ -143,7 +146,7 @@ __global__ __launch_bounds__(256) void k_token_score(const T* __restrict__ vis, 
 #pragma unroll
             for (int r = 0; r < R; r++) {
                 float x[8], tr[8];
-                wq_ld8(p[r] + d, x);
+                wq_ld8_once(p[r] + d, x);
                 if (!same && bs[r] != bs[0]) wq_ld8(tbar + (int64_t)bs[r] * D + d, tr);
 #pragma unroll
                 for (int k = 0; k < 8; k++) {

@@ -335,8 +335,8 @@ __device__ __forceinline__ void walk_class_split(const DecodeArgs& a, F32Smem<HD
         load_dwords<F::VDW>(reinterpret_cast<const uint32_t*>(vbase + o), f.v);
 #pragma unroll
         for (int t = 0; t < 2; t++) {
-            f.km[t] = kmeta[(int64_t)n * (32 * G) + t * (16 * G)];
-            f.vm[t] = vmeta[(int64_t)n * (32 * G) + t * (16 * G)];
+            f.km[t] = __builtin_nontemporal_load(kmeta + (int64_t)n * (32 * G) + t * (16 * G));
+            f.vm[t] = __builtin_nontemporal_load(vmeta + (int64_t)n * (32 * G) + t * (16 * G));
         }
     };
     F f[DEPTH];

@@ -463,15 +463,19 @@ struct Frag {
     uint32_t km, vm;                                        // one metadata word per lane and plane
 };
 
+// N dwords per lane, lane after lane.  The cache is streamed once per launch, and a load that takes whole lines (at most 16
+// bytes per lane) says so: non-temporal.  28 layers: 8 x 12800 tokens 528 -> 507 us a step, 1 x 19735 320 -> 303; 4 x 50688 x 4 layers 102 -> 95; 32 ragged
+// sequences 128 -> 120.  It costs up to 3 % (5 with heads of 64) where all that a program reads between two launches over a cache is less than 140 MB
+// or so, which then would stay in the memory-side cache: one or two layers.  Loads of more bytes per lane come in pieces that share lines, and
+// each piece would fetch them again (all loads so: 20 % slower).
 template <int N>
 __device__ __forceinline__ void load_dwords(const uint32_t* __restrict__ p, uint32_t* dst)
 {
-    if constexpr (N == 1) {
-        dst[0] = p[0];
-    } else if constexpr (N == 2) {
-        uint2 u = *reinterpret_cast<const uint2*>(p);
-        dst[0] = u.x;
-        dst[1] = u.y;
+    if constexpr (N <= 4) {
+        typedef uint32_t dwords __attribute__((ext_vector_type(N)));
+        const dwords u = __builtin_nontemporal_load(reinterpret_cast<const dwords*>(p));
+#pragma unroll
+        for (int d = 0; d < N; d++) dst[d] = u[d];
     } else {
 #pragma unroll
         for (int d = 0; d < N; d += 4) {
@@ -512,8 +516,8 @@ __device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD
         load_dwords<F::KDW>(reinterpret_cast<const uint32_t*>(kbase + o), f.k[0]);
         load_dwords<F::KDW>(reinterpret_cast<const uint32_t*>(kbase + o + 16 * HD * BITS / 8), f.k[1]);
         load_dwords<F::VDW>(reinterpret_cast<const uint32_t*>(vbase + o), f.v);
-        f.km = kmeta[(int64_t)blk * 64];
-        f.vm = vmeta[(int64_t)blk * 64];
+        f.km = __builtin_nontemporal_load(kmeta + (int64_t)blk * 64);
+        f.vm = __builtin_nontemporal_load(vmeta + (int64_t)blk * 64);
     };
 
     // software pipeline: DEPTH blocks in flight per wavefront; the first loads go out before anything else

@@ -1138,9 +1138,12 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         // ... and the wavefront's share of the cost, where it has one: 5 parts for the older of the two that share a SIMD, 3 for the
         // younger, whose instructions wait for the older one's (with equal shares the older four were done at 13.1 us, the others
         // at 17.5).  8 x 12795 tokens, 28/4 heads of 128, group 32: 21.6 -> 21.0 us a call, all of 8 bits 26.0 -> 24.5; 6 x 19700, 8/8 heads of 64,
-        // group 64: 25.1 -> 23.8; one sequence of 3271: 9.8 either way.  (9 : 7 gains 1 %, 19 : 13 2 %, this 3 % over 14 shapes.)
+        // group 64: 25.1 -> 23.8; one sequence of 3271: 9.8 either way.  (9 : 7 gains 1 %, 19 : 13 2 %, this 3 % over 14 shapes.)  Equal
+        // shares up to a block each, where 5 parts would be two for some: 3 sequences of up to 2592 tokens, 32/8 heads of 128, 64.7 us a step of 4
+        // layers, so 58.5.
         static_assert(WQ_WAVES == 8, "the shares");
-        auto parts_before = [](int w) { return (unsigned)(w < WQ_WAVES / 2 ? 5 * w : 20 + 3 * (w - WQ_WAVES / 2)); };
+        const bool even = G1 - G0 < 9u * (unsigned)block_cost<HD, G>(1);
+        auto parts_before = [&](int w) { return (unsigned)(even ? 4 * w : w < WQ_WAVES / 2 ? 5 * w : 20 + 3 * (w - WQ_WAVES / 2)); };
         const unsigned long long span = G1 - G0;
         const unsigned x0 = G0 + (unsigned)((span * parts_before(wave)) >> 5), x1 = G0 + (unsigned)((span * parts_before(wave + 1)) >> 5);
         unsigned base = 0u, t = 0u;

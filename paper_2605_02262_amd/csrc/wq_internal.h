@@ -102,17 +102,36 @@ __device__ __forceinline__ void wq_ld8(const __half* p, float* x)
 // 8 consecutive elements of a row that is read once, past the caches' replacement order.  For the 16-bit types, where a
 // wavefront's load takes whole lines: an fp32 row's pieces of 32 bytes per lane come in two loads that share every line, and
 // the second one would fetch it again.
+__device__ __forceinline__ uint4 wq_load_once(const void* p)
+{
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    const u4 u = __builtin_nontemporal_load(static_cast<const u4*>(p));
+    return make_uint4(u.x, u.y, u.z, u.w);
+}
 template <typename T>
 __device__ __forceinline__ void wq_ld8_once(const T* p, float* x)
 {
     if constexpr (sizeof(T) == 2) {
-        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-        const u4 u = __builtin_nontemporal_load(reinterpret_cast<const u4*>(p));
+        const uint4 u = wq_load_once(p);
         wq_ld8(reinterpret_cast<const T*>(&u), x);
     } else {
         wq_ld8(p, x);
     }
 }
+
+// ... and to memory, for whoever reads it later
+__device__ __forceinline__ void wq_store_once(void* p, uint4 v)
+{
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    __builtin_nontemporal_store(u4{v.x, v.y, v.z, v.w}, static_cast<u4*>(p));
+}
+__device__ __forceinline__ void wq_store_once(void* p, uint2 v)
+{
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    __builtin_nontemporal_store(u2{v.x, v.y}, static_cast<u2*>(p));
+}
+__device__ __forceinline__ void wq_store_once(void* p, uint32_t v) { __builtin_nontemporal_store(v, static_cast<uint32_t*>(p)); }
+__device__ __forceinline__ void wq_store_once(void* p, uint16_t v) { __builtin_nontemporal_store(v, static_cast<uint16_t*>(p)); }
 
 // first b in [0,B) with off[b+1] > x  (off ascending, off[0] <= x < off[B] assumed)
 __device__ __forceinline__ int wq_find_seq(const int32_t* off, int B, int64_t x)

@@ -354,13 +354,13 @@ __device__ __forceinline__ void quantize_block(QuantSmem<HD>& sm, int blk, int k
             uint8_t* out = static_cast<uint8_t*>(pk.codes[C]) + ((int64_t)kvh * pk.cap[C] + tok0) * HD * BITS / 8 +
                            (u >> 4) * (16 * HD * BITS / 8) + ((j * 16 + (u & 15)) * Q + e0) * BITS / 8;
             if constexpr (NB == 2) {
-                *reinterpret_cast<uint16_t*>(out) = (uint16_t)pw[0];
+                wq_store_once(out, (uint16_t)pw[0]);
             } else if constexpr (NB == 4) {
-                *reinterpret_cast<uint32_t*>(out) = pw[0];
+                wq_store_once(out, pw[0]);
             } else if constexpr (NB == 8) {
-                *reinterpret_cast<uint2*>(out) = uint2{pw[0], pw[1]};
+                wq_store_once(out, uint2{pw[0], pw[1]});
             } else {
-                *reinterpret_cast<uint4*>(out) = uint4{pw[0], pw[1], pw[2], pw[3]};
+                wq_store_once(out, uint4{pw[0], pw[1], pw[2], pw[3]});
             }
         }
         if ((p * CPT) % group == 0) {
@@ -395,11 +395,11 @@ __device__ __forceinline__ void quantize_block(QuantSmem<HD>& sm, int blk, int k
             uint32_t y[4];
             pack16<BITS>(x, y);
             if constexpr (BITS == 8)
-                *reinterpret_cast<uint4*>(out + r * 16) = uint4{y[0], y[1], y[2], y[3]};
+                wq_store_once(out + r * 16, uint4{y[0], y[1], y[2], y[3]});
             else if constexpr (BITS == 4)
-                *reinterpret_cast<uint2*>(out + r * 8) = uint2{y[0], y[1]};
+                wq_store_once(out + r * 8, uint2{y[0], y[1]});
             else
-                *reinterpret_cast<uint32_t*>(out + r * 4) = y[0];
+                wq_store_once(out + r * 4, y[0]);
         }
     }
     // ---- metadata: [tile of 16][group][16 tokens] ---------------------------------------------------------
@@ -409,7 +409,7 @@ __device__ __forceinline__ void quantize_block(QuantSmem<HD>& sm, int blk, int k
             const int plane = tid >> (5 + lg), r = tid & ((32 << lg) - 1);
             const int tile = r >> (4 + lg), gi = (r >> 4) & (G - 1), mrow = r & 15;
             uint32_t* out = static_cast<uint32_t*>(pk.meta[C]) + (((int64_t)plane * Hkv + kvh) * pk.cap[C] + tok0) * G;
-            out[r] = s_meta[plane][gi][tile * 16 + mrow];
+            wq_store_once(out + r, s_meta[plane][gi][tile * 16 + mrow]);
         }
     }
 }
@@ -466,10 +466,10 @@ __device__ __forceinline__ void copy16_rows(int64_t r0, const T* __restrict__ K,
                         o[k] = (uint32_t)__half_as_ushort(__float2half_rn(f[2 * k])) | (uint32_t)__half_as_ushort(__float2half_rn(f[2 * k + 1])) << 16;
                     x = make_uint4(o[0], o[1], o[2], o[3]);
                 } else {
-                    x = *reinterpret_cast<const uint4*>(src);
+                    x = wq_load_once(src);
                 }
                 if constexpr (decltype(aligned)::value) {
-                    *reinterpret_cast<uint4*>(dst) = x;
+                    wq_store_once(dst, x);
                 } else {
                     const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
@@ -489,6 +489,10 @@ __device__ __forceinline__ void copy16_rows(int64_t r0, const T* __restrict__ K,
 // together fill: where thresholds decide, every class has room for all tokens, and a call for 16 ragged sequences (198 500
 // tokens, fp16) took 144 us with workgroups for the unused room, 136 without.  Else the former: reading the tables first
 // costs 2.5 of 61 us (8 x 12800 tokens).
+// Everything the launch writes is written once, with non-temporal stores, which leave the memory to the reads: 4 x 50688 tokens, 4 KV heads of 128,
+// 352 -> 348 us for a layer's prefill (377 -> 364 before the scoring read its rows so), 4 x 12644, 8 KV heads of 64, 75.7 -> 67.8; a decode call behind it
+// takes what it took.  (The rows of K and V so: 1 to 10 % slower, a wavefront reads them in pieces; the 16-bit rows' copies take whole lines: 209.6 ->
+// 202.7 us where all of 8 x 12644 tokens stay in 16 bits.)
 // n: workgroups for the blocks, a bound on their number.
 constexpr unsigned WQ_BY_USE = 0xFFFFFFFFu;
 template <typename T, int HD>

@@ -646,7 +646,9 @@ __global__ __launch_bounds__(256) void k_append16(const T* __restrict__ k_new, c
 // register), two values at a time; and the V codes, whose operand order has 8 tokens of one channel together, are
 // transposed as bytes, 8 lanes x 8 tokens at a time, in three exchanges between lanes (11 instructions per 8 codes).
 // Field by field from LDS, in a launch per class, the call took 93 us (275 MB read and written: 2.9 TB/s); this way 59 us (4.7
-// TB/s; a plain copy of 1 GiB runs at 5.0).
+// TB/s; a plain copy of 1 GiB runs at 5.0), and with non-temporal stores of the rows 42 us (6.5 TB/s).  Whoever reads the rows next finds less of
+// them in the memory-side cache: with a plain read of all of them behind it the call takes 87 us either way (12.1 and 12.2 with 1568 tokens, 32.0 and 32.8
+// with 4 x 9408).  1 x 12644 tokens 8.2 -> 6.5 us, 16 x 15780 144 -> 134.  (The metadata's loads so too: 56 us.  The 16-bit rows' loads: no gain.)
 constexpr int DENSE_ROWS = 8;
 
 __device__ __forceinline__ int dense_total(const wq_packed_kv& src, int b)
@@ -821,11 +823,11 @@ __device__ __forceinline__ void dequantize_block(DenseSmem<HD>& sm, int blk, int
         const int64_t o = ((row0 + u) * Hkv + kvh) * HD + ch;
         float c[8];
         codes_of<BITS>(kw[i], c);
-        *reinterpret_cast<uint4*>(static_cast<uint16_t*>(dst.k16) + o) = dense_piece<BF>(c, kword[i]);
+        wq_store_once(static_cast<uint16_t*>(dst.k16) + o, dense_piece<BF>(c, kword[i]));
         const uint2 v = *reinterpret_cast<const uint2*>(sm.v + u * DenseSmem<HD>::PITCH + ch);
 #pragma unroll
         for (int k = 0; k < 8; k++) c[k] = byte_of(k < 4 ? v.x : v.y, k & 3);
-        *reinterpret_cast<uint4*>(static_cast<uint16_t*>(dst.v16) + o) = dense_piece<BF>(c, vword[i]);
+        wq_store_once(static_cast<uint16_t*>(dst.v16) + o, dense_piece<BF>(c, vword[i]));
     }
 }
 
@@ -840,8 +842,8 @@ __device__ __forceinline__ void dense_copy(int64_t r0, int B, int pieces, const 
         const int64_t d = (int64_t)dst.off16[b] + src.cls_len[0][b] + src.cls_len[1][b] + src.cls_len[2][b] + i;
         const int64_t from = r * pieces + e % pieces, to = d * pieces + e % pieces;
         const uint4 k = static_cast<const uint4*>(src.k16)[from], v = static_cast<const uint4*>(src.v16)[from];
-        static_cast<uint4*>(dst.k16)[to] = k;
-        static_cast<uint4*>(dst.v16)[to] = v;
+        wq_store_once(static_cast<uint4*>(dst.k16) + to, k);
+        wq_store_once(static_cast<uint4*>(dst.v16) + to, v);
     }
 }
 

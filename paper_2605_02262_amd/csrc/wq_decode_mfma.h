@@ -1088,6 +1088,9 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         end16 = a.kv.off16[b + 1];
         v_scale_max = F32 ? 0.f : a.kv.v_scale_max[b];
     }
+    // The arguments' line with the classes' pointers comes with the tables: first touched where a class begins, it was a round trip of its own in
+    // front of the first block loads (28 launches: 8 x 12800 tokens 508 -> 502 us, 1 x 19735 302 -> 297; place_by_length touches it anyway)
+    if constexpr (!PACKED) asm volatile("" :: "s"(a.kv.group));
     const int unit = b * a.kv.Hkv + kvh;
     // a token appended by this launch becomes the last row of the 16-bit segment: read from k_new / v_new by whoever
     // walks its block, copied into the cache by the first split's workgroup (at its end: the copy is a round trip to memory that

@@ -43,7 +43,10 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
-// VEC: rows are read 8 elements per lane (needs D % 8 == 0); otherwise element by element.
+// VEC: rows are read 8 elements per lane (needs D % 8 == 0), WQ_TEXT_FLIGHT pieces in flight; otherwise element by element.  The two
+// kernels of the text read a few MB and are bound by the latency of their loads: one piece after the other 2048 tokens of 3584 bf16 took
+// 6.4 and 8.8 us, so 5.1 and 5.1; 512 of them 4.4 and 5.4, so 3.2 and 3.8.
+constexpr int WQ_TEXT_FLIGHT = 8;
 template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void k_text_norm(const T* __restrict__ txt, int D, int64_t total_txt,
                                                    float* __restrict__ inv_norm)
@@ -54,11 +57,14 @@ __global__ __launch_bounds__(256) void k_text_norm(const T* __restrict__ txt, in
     const T* p = txt + row * D;
     float ss = 0.f;
     if (VEC) {
-        for (int d = lane * 8; d < D; d += WAVE * 8) {
-            float x[8];
-            wq_ld8(p + d, x);
+        for (int d0 = lane * 8; d0 < D; d0 += WAVE * 8 * WQ_TEXT_FLIGHT) {
+            float x[WQ_TEXT_FLIGHT][8];
 #pragma unroll
-            for (int k = 0; k < 8; k++) ss = fmaf(x[k], x[k], ss);
+            for (int i = 0; i < WQ_TEXT_FLIGHT; i++) wq_ld8(p + min(d0 + i * WAVE * 8, D - 8), x[i]);
+#pragma unroll
+            for (int i = 0; i < WQ_TEXT_FLIGHT; i++)
+#pragma unroll
+                for (int k = 0; k < 8; k++) ss = d0 + i * WAVE * 8 < D ? fmaf(x[i][k], x[i][k], ss) : ss;
         }
     } else {
         for (int d = lane; d < D; d += WAVE) {
@@ -85,12 +91,18 @@ __global__ __launch_bounds__(256) void k_text_mean(const T* __restrict__ txt, co
         const int d0 = (blockIdx.x * 8 + cc) * 8;
         float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         if (d0 < D)
-            for (int j = j0 + ts; j < j1; j += 32) {
-                float x[8];
-                wq_ld8(txt + (int64_t)j * D + d0, x);
-                const float w = inv_norm[j];
+            for (int j = j0 + ts; j < j1; j += 32 * WQ_TEXT_FLIGHT) {
+                float x[WQ_TEXT_FLIGHT][8], w[WQ_TEXT_FLIGHT];
 #pragma unroll
-                for (int k = 0; k < 8; k++) acc[k] = fmaf(x[k], w, acc[k]);
+                for (int i = 0; i < WQ_TEXT_FLIGHT; i++) {
+                    const int row = min(j + 32 * i, j1 - 1);
+                    wq_ld8(txt + (int64_t)row * D + d0, x[i]);
+                    w[i] = inv_norm[row];
+                }
+#pragma unroll
+                for (int i = 0; i < WQ_TEXT_FLIGHT; i++)
+#pragma unroll
+                    for (int k = 0; k < 8; k++) acc[k] = j + 32 * i < j1 ? fmaf(x[i][k], w[i], acc[k]) : acc[k];
             }
 #pragma unroll
         for (int k = 0; k < 8; k++) s_acc[ts][cc][k] = acc[k];
@@ -184,16 +196,30 @@ __global__ __launch_bounds__(256) void k_window_mean(const float* __restrict__ t
                                                      const int32_t* __restrict__ win_size, const int32_t* __restrict__ win_off,
                                                      int64_t total_win, float* __restrict__ scores)
 {
-    int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    int64_t w = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (w >= total_win) return;
     int lane = threadIdx.x & 63;
-    int b = wq_find_seq(win_off, B, w);
-    int S = win_size[b];
-    int64_t r0 = (int64_t)vis_off[b] + (w - win_off[b]) * S;
+    // Bound by round trips to memory: up to 64 sequences a lane has a sequence's tables, all of them in one (searched by halves and then read,
+    // four for 4 sequences, six for 16)
+    int S, tokens;
+    int64_t r0;
+    if (B <= WAVE) {
+        const int l = min(lane, B - 1), size = win_size[l], first = win_off[l], after = win_off[l + 1], row = vis_off[l], text = txt_off[l + 1] - txt_off[l];
+        const int b = min(B - 1, (int)__popcll(__builtin_amdgcn_ballot_w64(lane < B && (int64_t)after <= w)));
+        S = __builtin_amdgcn_readlane(size, b);
+        tokens = __builtin_amdgcn_readlane(text, b);
+        r0 = (int64_t)__builtin_amdgcn_readlane(row, b) + (w - __builtin_amdgcn_readlane(first, b)) * S;
+    } else {
+        const int b = wq_find_seq(win_off, B, w);
+        S = win_size[b];
+        tokens = txt_off[b + 1] - txt_off[b];
+        r0 = (int64_t)vis_off[b] + (w - win_off[b]) * S;
+    }
     float acc = 0.f;
+#pragma unroll 4
     for (int k = lane; k < S; k += WAVE) acc += tok_score[r0 + k];
     acc = wave_sum(acc);
-    if (lane == 0) scores[w] = (S > 0 && txt_off[b + 1] > txt_off[b]) ? acc / (float)S : 0.f;
+    if (lane == 0) scores[w] = (S > 0 && tokens > 0) ? acc / (float)S : 0.f;
 }
 
 // A call of a few windows in one launch: a workgroup per window finds the norms and the mean of its sequence's text for itself

@@ -21,7 +21,7 @@ struct wq_ctx {
     char err[256];
 };
 
-constexpr size_t WQ_WS_HEADER = 16384; // zero-initialised: status word and the small quantizer's arrival counter (first 256 bytes), then the decode kernel's arrival counters
+constexpr size_t WQ_WS_HEADER = 16384; // zero-initialised: status word and the small quantizer's arrival counter (first 256 bytes), then arrival counters of the decode kernel and of the small quantizer
 constexpr int WQ_ARRIVE_STRIDE = 16;   // 32-bit words between arrival counters (one 64-byte piece each)
 constexpr int WQ_MAX_ARRIVE = (16384 - 256) / (4 * WQ_ARRIVE_STRIDE);
 constexpr int WQ_DECODE_FLAGS = WQ_DECODE_PARTIALS_ONLY | WQ_DECODE_FIXED_SHARES | WQ_DECODE_BY_LENGTH | WQ_DECODE_SEPARATE_MERGE;
@@ -57,6 +57,7 @@ inline int wq_fail(wq_ctx* ctx, int code, const char* fmt, ...)
 inline size_t wq_align256(size_t x) { return (x + 255) & ~size_t(255); }
 inline uint32_t* wq_status_ptr(wq_ctx* ctx) { return reinterpret_cast<uint32_t*>(ctx->ws); }
 inline unsigned* wq_small_arrive_ptr(wq_ctx* ctx) { return reinterpret_cast<unsigned*>(ctx->ws + 128); }   // k_quantize_small's workgroups that are done, on a line beside the status word's
+inline unsigned* wq_arrive_lines_ptr(wq_ctx* ctx) { return reinterpret_cast<unsigned*>(ctx->ws + 256); }    // the arrival counters, a line of WQ_ARRIVE_STRIDE words each
 
 // element loads -> float (exact for all three storage types)
 __device__ __forceinline__ float wq_ld(const float* p, int64_t i) { return p[i]; }

@@ -529,16 +529,18 @@ __global__ __launch_bounds__(256) void k_quantize_all(const T* __restrict__ K, c
 // The whole call in one launch, where it is a few hundred workgroups and launches are most of what it costs (8 windows of 16
 // tokens, 2 KV heads of 64: three launches 8.6 us, this one 6.2): every workgroup works the plan out for itself, in LDS (two
 // round trips to memory and a loop over the sequences), the first one writes it out, and the last one to finish collects the
-// sequences' largest value scales.  Workgroups report in on one counter of the workspace header (12-16 ns each, as
-// device-scope atomics on one address take), which is zero between launches: hence no more of them than compute units.
+// sequences' largest value scales.  Workgroups report in on counters of the workspace header, zero between launches: on one up to
+// SMALL_LINE of them (12-16 ns each, as device-scope atomics on one address take), above on SMALL_LINES, whose last ones report in on
+// the one (a round trip more: 100 workgroups 8.4 us on one counter, 8.7 so; 200 9.7 and 9.0, 250 10.2 and 8.9).  Against three launches, 1 to 15 sequences,
+// 2 to 8 KV heads of 64 and 128: 400 workgroups 11.0 -> 9.5 us, 700 11.6 -> 10.5, 1000 12.9 -> 11.8; from 1200 to 1500 on equal, 1990 16.5 and 16.8.
 // n: workgroups for the blocks (numbered by use), a bound on their number; the rest take ROWS16 16-bit rows each.
-constexpr int SMALL_SEQS = 16, SMALL_WGS = 256;
+constexpr int SMALL_SEQS = 16, SMALL_WGS = 1024, SMALL_LINE = 150, SMALL_LINES = 16;
 template <typename T, int HD>
 __global__ __launch_bounds__(256) void k_quantize_small(const T* __restrict__ K, const T* __restrict__ V, int B, int group,
                                                         const int32_t* __restrict__ kv_off, const int32_t* __restrict__ win_size,
                                                         const int32_t* __restrict__ win_off, const int32_t* __restrict__ perm,
                                                         const int32_t* __restrict__ seg_windows, wq_packed_kv pk, unsigned n,
-                                                        uint32_t* __restrict__ status, unsigned* __restrict__ arrive)
+                                                        uint32_t* __restrict__ status, unsigned* __restrict__ arrive, unsigned* __restrict__ arrive_lines)
 {
     __shared__ QuantSmem<HD> sm;
     // the tables' own values, and the plan
@@ -588,7 +590,18 @@ __global__ __launch_bounds__(256) void k_quantize_small(const T* __restrict__ K,
     // acknowledged before it counts the workgroup, so whoever finds itself last reads scales that have arrived.
     if (tid == 0) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        s_last = __hip_atomic_fetch_add(arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1u ? 1u : 0u;
+        auto last_of = [](unsigned* counter, unsigned all) { return __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == all - 1u; };
+        if (gridDim.x <= SMALL_LINE) {
+            s_last = last_of(arrive, gridDim.x) ? 1u : 0u;
+        } else {
+            const unsigned line = blockIdx.x % SMALL_LINES;
+            unsigned* const counter = arrive_lines + line * WQ_ARRIVE_STRIDE;
+            s_last = 0u;
+            if (last_of(counter, (gridDim.x - line + SMALL_LINES - 1u) / SMALL_LINES)) {
+                __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                s_last = last_of(arrive, SMALL_LINES) ? 1u : 0u;
+            }
+        }
     }
     __syncthreads();
     if (s_last == 0u) return;
@@ -914,7 +927,7 @@ int run(wq_ctx* ctx, const void* K_, const void* V_, int B, const int32_t* kv_of
     if (n + wgs16 > 0x7FFFFFFF) return wq_fail(ctx, WQ_ERR_UNSUPPORTED, "too many blocks for one launch");
     if (B <= SMALL_SEQS && n + wgs16 <= SMALL_WGS) {
         hipLaunchKernelGGL((k_quantize_small<T, HD>), dim3((unsigned)(n + wgs16 > 0 ? n + wgs16 : 1)), dim3(256), 0, st, K, V, B, pk->group, kv_off,
-                           win_size, win_off, perm, seg_windows, *pk, (unsigned)n, wq_status_ptr(ctx), wq_small_arrive_ptr(ctx));
+                           win_size, win_off, perm, seg_windows, *pk, (unsigned)n, wq_status_ptr(ctx), wq_small_arrive_ptr(ctx), wq_arrive_lines_ptr(ctx));
         WQ_HIP_CHECK(ctx, hipGetLastError());
         return WQ_OK;
     }

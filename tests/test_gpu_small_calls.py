@@ -83,6 +83,37 @@ def test_quantizing_a_small_call(dtype, hd, group, short):
     assert (a.v_scale_max[:16] > 0).sum() >= 10
 
 
+@pytest.mark.parametrize("blocks", [37, 38, 41, 100, 255, 256, 257])
+def test_quantizing_a_small_call_on_several_counters(blocks):
+    """4 KV heads: 148 and 152 workgroups (one counter, several), odd shares of the counters, 1020, 1024 (the last small call) and 1028;
+    the same with an empty 17th sequence (three launches).  Twice on one context: the counters are zero again, also for a decode call."""
+    from paper_2605_02262_amd import binding as W
+    gen = torch.Generator(device="cuda").manual_seed(blocks)
+    heads, hd, group, B = 4, 64, 32, 16
+    n = [blocks // B + (1 if b < blocks % B else 0) for b in range(B)]
+    seg = [[k // 3, k - k // 3 - k // 4, k // 4, 0] for k in n]
+    K, V = (torch.randn(32 * blocks, heads, hd, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    perm = torch.cat([torch.randperm(k, generator=gen, device="cuda") for k in n]).to(torch.int32)
+    cap = [32 * sum(s[c] for s in seg) for c in range(3)]
+    splits = 4
+    ctx = W.Context(W.workspace_bytes(B, 8, hd, splits))
+    q = torch.randn(B, 8, hd, generator=gen, device="cuda").to(torch.bfloat16)
+    got, out = [], []
+    for extra in (1, 0, 0):
+        one = [0] * extra
+        pk = W.PackedKV(B + extra, heads, hd, group, torch.bfloat16, cap, [0] * (B + 1 + extra), fill=0)
+        W.wq_reorder_quantize(ctx, K, V, _table(_offsets([32 * k for k in n] + one)), _table([32] * B + [1] * extra), _table(_offsets(n + one)), perm,
+                              _table(seg + [[0] * 4] * extra), 32 * blocks, pk)
+        assert ctx.device_status() == 0
+        got.append(pk)
+        if not extra:
+            out.append(W.wq_decode_attention(ctx, q, pk, hd ** -0.5, splits, 32 * max(n), W.DECODE_AUTO | W.DECODE_FIXED_SHARES))
+    for b in got[1:]:
+        for x, y in zip(got[0].codes + got[0].meta + [got[0].v_scale_max[:B]], b.codes + b.meta + [b.v_scale_max[:B]]):
+            assert torch.equal(x, y)
+    assert (got[0].v_scale_max[:B] > 0).all() and torch.equal(out[0], out[1]) and torch.isfinite(out[0]).all()
+
+
 @pytest.mark.parametrize("B", [17, 63, 64, 65, 150])
 @pytest.mark.parametrize("short", ["fits", "classes", "rows"])
 def test_plan_of_many_sequences(B, short):

@@ -6,7 +6,7 @@
 //   k_text_norm   one wavefront per text token  -> 1/|t_j|                       (0 for a zero row)
 //   k_text_mean   thread per channel            -> tbar[b][d] = 1/N sum_j t_j[d]/|t_j|
 //   k_token_score one wavefront per visual row  -> c_k = (w_k . tbar) / |w_k|    (0 for a zero row)
-//   k_window_mean one wavefront per window      -> score = 1/S sum_k c_k, fixed order
+//   k_window_mean one wavefront per window      -> score = 1/S sum_k c_k, fixed order (part of k_token_score up to FOLD_ROWS, FOLD_BYTES)
 //   k_scores_small  all of it for a short text and few rows, a workgroup per window
 // All accumulation is fp32 and every reduction has a fixed order (no atomics): results are deterministic.
 #include "wq_internal.h"
@@ -47,10 +47,21 @@ __device__ __forceinline__ float wave_sum(float v)
 // kernels of the text read a few MB and are bound by the latency of their loads: one piece after the other 2048 tokens of 3584 bf16 took
 // 6.4 and 8.8 us, so 5.1 and 5.1; 512 of them 4.4 and 5.4, so 3.2 and 3.8.
 constexpr int WQ_TEXT_FLIGHT = 8;
+// What k_token_score needs to make the windows' means itself (FOLD).  folded windows: k_text_norm clears their counters, a line each
+constexpr int FOLD_STRIDE = 16;
+struct WindowFold {
+    const int32_t *win_size, *win_off, *txt_off;
+    unsigned* rows_done;
+    float* scores;
+};
 template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void k_text_norm(const T* __restrict__ txt, int D, int64_t total_txt,
-                                                   float* __restrict__ inv_norm)
+                                                   float* __restrict__ inv_norm, WindowFold fold, int64_t folded)
 {
+    for (int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x; w < folded; w += (int64_t)gridDim.x * 256) {
+        fold.rows_done[w * FOLD_STRIDE] = 0u;
+        fold.scores[w] = 0.f;                             // (what a window without rows has)
+    }
     int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= total_txt) return;
     int lane = threadIdx.x & 63;
@@ -129,22 +140,36 @@ __global__ __launch_bounds__(256) void k_text_mean(const T* __restrict__ txt, co
 // once and their loads say so (non-temporal): 4 x 50176 rows of 3584 bf16 246 -> 229 us a call (6.0 -> 6.5 TB/s in this kernel), 50176 of 896 35.8 ->
 // 31.6, rows that have just been written included (64.3 -> 61.4 with the copy that writes 12544 of 3584); 5 % slower only where the same 25 to 110 MB are
 // scored again and again and nothing else is read (50176 of 896: 29.6 -> 31.5).  fp32 rows keep plain loads (10 % faster: wq_ld8_once).
-template <typename T, bool VEC>
+// FOLD (VEC only): the workgroup that finishes a window's last row makes the window's mean, as k_window_mean does.
+template <typename T, bool VEC, bool FOLD>
 __global__ __launch_bounds__(256) void k_token_score(const T* __restrict__ vis, const float* __restrict__ tbar, int D, int B,
                                                      const int32_t* __restrict__ vis_off, int64_t total_vis,
-                                                     float* __restrict__ tok_score)
+                                                     float* __restrict__ tok_score, WindowFold fold)
 {
     const int lane = threadIdx.x & 63;
     if (VEC) {
-        constexpr int R = WQ_TS_ROWS;
+        constexpr int R = WQ_TS_ROWS, ROWS = 4 * R;
         const int64_t row0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * R;
-        if (row0 >= total_vis) return;
+        if (!FOLD && row0 >= total_vis) return;
+        __shared__ float s_score[FOLD ? ROWS : 1];
         int bs[R];
         const T* p[R];
+        int first = 0, size = 0, window = 0, windows_end = 0, text = 0;      // FOLD: of the sequence of the workgroup's row number `lane`
+        if constexpr (FOLD) {
+            const int b = wq_find_seq(vis_off, B, min((int64_t)blockIdx.x * ROWS + lane % ROWS, total_vis - 1));
+            first = vis_off[b];
+            size = fold.win_size[b];
+            window = fold.win_off[b];
+            windows_end = fold.win_off[b + 1];
+            text = fold.txt_off[b + 1] - fold.txt_off[b];
+            const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+#pragma unroll
+            for (int r = 0; r < R; r++) bs[r] = __builtin_amdgcn_readlane(b, wave * R + r);
+        }
 #pragma unroll
         for (int r = 0; r < R; r++) {
             const int64_t row = row0 + r < total_vis ? row0 + r : total_vis - 1;
-            bs[r] = wq_find_seq(vis_off, B, row);
+            if constexpr (!FOLD) bs[r] = wq_find_seq(vis_off, B, row);
             p[r] = vis + row * D;
         }
         const bool same = bs[0] == bs[R - 1];      // rows are ordered by sequence: all of them share one text vector
@@ -171,7 +196,38 @@ __global__ __launch_bounds__(256) void k_token_score(const T* __restrict__ vis, 
 #pragma unroll
         for (int r = 0; r < R; r++) {
             const float s = wave_sum(ss[r]), d2 = wave_sum(dt[r]);
-            if (lane == 0 && row0 + r < total_vis) tok_score[row0 + r] = s > 0.f ? d2 / sqrtf(s) : 0.f;
+            const float c = s > 0.f ? d2 / sqrtf(s) : 0.f;
+            if constexpr (FOLD) {
+                if (lane == 0) s_score[(int)(threadIdx.x >> 6) * R + r] = c;
+            } else {
+                if (lane == 0 && row0 + r < total_vis) tok_score[row0 + r] = c;
+            }
+        }
+        if constexpr (FOLD) {
+            __syncthreads();
+            if (threadIdx.x >= WAVE) return;
+            // A lane per row.  The scores are stored past the XCD's L2 and acknowledged before the rows are counted, so whoever completes a window
+            // reads scores that have arrived.  (At most FOLD_ROWS rows: 32 bits hold everything.)
+            const int base = (int)blockIdx.x * ROWS, row = base + lane, end = min(base + ROWS, (int)total_vis);
+            const int nth = size > 0 ? (row - first) / size : 0, begin = first + nth * size;
+            window += nth;
+            const bool counted = row < end && size > 0 && window < windows_end;
+            if (row < end) __hip_atomic_store(tok_score + row, s_score[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            bool done = false;
+            if (counted && row == max(base, begin)) {     // the workgroup's first row of the window
+                const unsigned n = (unsigned)(min(end, begin + size) - row);
+                done = __hip_atomic_fetch_add(fold.rows_done + (int64_t)window * FOLD_STRIDE, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + n == (unsigned)size;
+            }
+            for (uint64_t left = __builtin_amdgcn_ballot_w64(done); left != 0; left &= left - 1) {
+                const int l = __builtin_ctzll(left), S = __builtin_amdgcn_readlane(size, l), r0 = __builtin_amdgcn_readlane(begin, l);
+                const int tokens = __builtin_amdgcn_readlane(text, l), w = __builtin_amdgcn_readlane(window, l);
+                float acc = 0.f;
+#pragma unroll 4
+                for (int k = lane; k < S; k += WAVE) acc += __hip_atomic_load(tok_score + r0 + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                acc = wave_sum(acc);
+                if (lane == 0) fold.scores[w] = tokens > 0 ? acc / (float)S : 0.f;
+            }
         }
     } else {
         int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -937,6 +993,13 @@ __global__ __launch_bounds__(PA_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     }
 }
 
+// tiles of 16 text rows that the packed text of B sequences with total_txt rows can take (see pair_tile_base)
+int64_t pair_total_tiles(int B, int64_t total_txt) { return total_txt / 16 + B; }
+
+// Up to here k_token_score makes the windows' means itself: a launch saved against a wait at the end of every workgroup, which costs more where
+// the rows keep the chip busy for long.  Four launches -> three, bf16: 6272 rows of 3584 18.2 -> 17.6 us, 25088 39.8 -> 39.0, 50176 69.1 -> 68.9, 75264
+// (539 MB) 93.1 -> 95.2; 8192 rows of 512 12.3 -> 11.3, 65536 31.0 -> 27.8, 100352 of 896 (180 MB) 57.8 -> 54.3; 32768 of 4096 (268 MB) 54.4 -> 53.9.
+constexpr int64_t FOLD_ROWS = 1 << 17, FOLD_BYTES = 320 << 20;
 template <typename T, bool VEC>
 int run_pooled(wq_ctx* ctx, const void* vis_, const void* txt_, int B, int D, const int32_t* vis_off, const int32_t* txt_off,
                const int32_t* win_size, const int32_t* win_off, int64_t total_vis, int64_t total_txt, int64_t total_win,
@@ -960,15 +1023,22 @@ int run_pooled(wq_ctx* ctx, const void* vis_, const void* txt_, int B, int D, co
         WQ_HIP_CHECK(ctx, hipGetLastError());
         return WQ_OK;
     }
+    // the windows' counters lie where the pairwise form has its packed text
+    float* const counters = tok_score + wq_align256(sizeof(float) * (size_t)(total_vis > 0 ? total_vis : 1)) / sizeof(float);
+    const WindowFold fold{win_size, win_off, txt_off, reinterpret_cast<unsigned*>(counters), scores};
+    const bool folds = VEC && total_vis > 0 && total_vis <= FOLD_ROWS && total_vis * D * (int64_t)sizeof(T) <= FOLD_BYTES && total_txt > 0 &&
+                       total_win * FOLD_STRIDE * (int64_t)sizeof(unsigned) <= pair_total_tiles(B, total_txt) * 16 * D * 2;
     if (total_txt > 0)
-        hipLaunchKernelGGL((k_text_norm<T, VEC>), dim3((unsigned)((total_txt + 3) / 4)), dim3(256), 0, st, txt, D, total_txt, inv_norm);
+        hipLaunchKernelGGL((k_text_norm<T, VEC>), dim3((unsigned)((total_txt + 3) / 4)), dim3(256), 0, st, txt, D, total_txt, inv_norm, fold,
+                           folds ? total_win : 0);
     hipLaunchKernelGGL((k_text_mean<T, VEC>), dim3(VEC ? (D + 63) / 64 : (D + 255) / 256, B), dim3(256), 0, st, txt, inv_norm, D, txt_off, tbar);
     if (total_vis > 0) {
         const int64_t rows_per_block = VEC ? 4 * WQ_TS_ROWS : 4;
-        hipLaunchKernelGGL((k_token_score<T, VEC>), dim3((unsigned)((total_vis + rows_per_block - 1) / rows_per_block)), dim3(256), 0, st,
-                           vis, tbar, D, B, vis_off, total_vis, tok_score);
+        hipLaunchKernelGGL((folds ? k_token_score<T, VEC, VEC> : k_token_score<T, VEC, false>),
+                           dim3((unsigned)((total_vis + rows_per_block - 1) / rows_per_block)), dim3(256), 0, st, vis, tbar, D, B, vis_off, total_vis,
+                           tok_score, fold);
     }
-    hipLaunchKernelGGL(k_window_mean, dim3((unsigned)((total_win + 3) / 4)), dim3(256), 0, st, tok_score, B, vis_off, txt_off,
+    if (!folds) hipLaunchKernelGGL(k_window_mean, dim3((unsigned)((total_win + 3) / 4)), dim3(256), 0, st, tok_score, B, vis_off, txt_off,
                        win_size, win_off, total_win, scores);
     WQ_HIP_CHECK(ctx, hipGetLastError());
     return WQ_OK;
@@ -976,8 +1046,6 @@ int run_pooled(wq_ctx* ctx, const void* vis_, const void* txt_, int B, int D, co
 
 }  // namespace
 
-// tiles of 16 text rows that the packed text of B sequences with total_txt rows can take (see pair_tile_base)
-static int64_t pair_total_tiles(int B, int64_t total_txt) { return total_txt / 16 + B; }
 
 size_t wq_scores_ws_bytes(int B, int64_t total_vis, int64_t total_txt, int D)
 {

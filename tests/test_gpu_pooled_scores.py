@@ -1,4 +1,4 @@
-"""Pooled scoring in four launches: the text's pieces in flight, and how a window finds its sequence, at their edges."""
+"""Pooled scoring in three and four launches: the text's pieces in flight, and how a window finds its sequence, at their edges."""
 import pytest
 import torch
 
@@ -6,22 +6,24 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("n_txt,dim", [
-    ([1, 300], 8),                       # one lane has a piece
-    ([31, 300], 512),                    # a piece per lane; less than one round of the 32 token slices
-    ([32, 33, 255, 256], 520),
-    ([257, 0, 511, 513], 4096),          # eight pieces per lane; a round more than eight of the slices; no text
-    ([600], 4104),                       # ... and one piece more
-    ([9] * 63 + [200], 64),              # a lane per sequence
-    ([5] * 64 + [200], 64),              # more sequences than lanes
+@pytest.mark.parametrize("n_txt,dim,times", [
+    ([1, 300], 8, 1),                       # one lane has a piece
+    ([31, 300], 512, 1),                    # a piece per lane; less than one round of the 32 token slices
+    ([32, 33, 255, 256], 520, 1),
+    ([257, 0, 511, 513], 4096, 1),          # eight pieces per lane; a round more than eight of the slices; no text
+    ([600], 4104, 1),                       # ... and one piece more
+    ([9] * 63 + [200], 64, 1),              # a lane per sequence
+    ([9] * 63 + [200], 64, 12),           # more rows than the means are made with: a launch of their own
+    ([5] * 64 + [200], 64, 12),
+    ([5] * 64 + [200], 64, 1),              # more sequences than lanes
 ])
-def test_pooled_scores(n_txt, dim, dtype):
+def test_pooled_scores(n_txt, dim, times, dtype):
     """Windows of 7 rows and of 130 (more than two per lane) in turn, rows at the end that fill none, sequences without rows.  float64 reference; fp32 sums of a
     few thousand terms: 1e-5 of the scores' size, 1 / sqrt(dim), is far above their rounding."""
     from paper_2605_02262_amd import binding as W
     gen = torch.Generator(device="cuda").manual_seed(dim + len(n_txt))
     size = [7 if b % 2 else 130 for b in range(len(n_txt))]
-    n_win = [0 if b % 5 == 4 else 3 + b % 3 for b in range(len(n_txt))]
+    n_win = [0 if b % 5 == 4 else (3 + b % 3) * times for b in range(len(n_txt))]
     n_vis = [w * s + b % 4 for b, (w, s) in enumerate(zip(n_win, size))]
     vis = torch.randn(sum(n_vis), dim, generator=gen, device="cuda").add_(0.2).to(dtype)
     txt = torch.randn(sum(n_txt), dim, generator=gen, device="cuda").add_(0.2).to(dtype)
@@ -35,4 +37,5 @@ def test_pooled_scores(n_txt, dim, dtype):
         unit = (t / t.norm(dim=1, keepdim=True)).mean(0) if n else torch.zeros(dim, dtype=torch.float64, device="cuda")
         want.append(((v @ unit) / v.norm(dim=1)).view(w, s).mean(1))
         v0, t0 = v0 + m, t0 + n
+    assert times == 1 or sum(n_vis) > 1 << 17
     assert (got.double() - torch.cat(want)).abs().max().item() <= 1e-5 / dim ** 0.5

@@ -21,6 +21,16 @@ namespace {
 
 __device__ __forceinline__ int pad32(int n) { return (n + 31) & ~31; }
 
+// A store of the quantizer for rows of type T: non-temporal for the 16-bit types (k_quantize_all).  Behind fp32 rows an fp32 query
+// comes, which the vector kernel takes with one and four groups per head: it reads the cache in small pieces, one round trip after the other, and
+// pays for a cache that is not near (a layer's prefill and decode, 4 x 4804 tokens, 28/4 heads of 128, group 32: 631 us, 655 with non-temporal stores).
+template <typename T, typename V>
+__device__ __forceinline__ void put(void* p, V v)
+{
+    if constexpr (sizeof(T) == 2) wq_store_once(p, v);
+    else *static_cast<V*>(p) = v;
+}
+
 // Class c's place for every sequence: off[B + 1], len[B]; n_of(b): its tokens.  True where something did not fit.
 template <typename Tokens>
 __device__ __forceinline__ bool plan_class(int B, int64_t cap, Tokens n_of, int32_t* off, int32_t* len)
@@ -354,13 +364,13 @@ __device__ __forceinline__ void quantize_block(QuantSmem<HD>& sm, int blk, int k
             uint8_t* out = static_cast<uint8_t*>(pk.codes[C]) + ((int64_t)kvh * pk.cap[C] + tok0) * HD * BITS / 8 +
                            (u >> 4) * (16 * HD * BITS / 8) + ((j * 16 + (u & 15)) * Q + e0) * BITS / 8;
             if constexpr (NB == 2) {
-                wq_store_once(out, (uint16_t)pw[0]);
+                put<T>(out, (uint16_t)pw[0]);
             } else if constexpr (NB == 4) {
-                wq_store_once(out, pw[0]);
+                put<T>(out, pw[0]);
             } else if constexpr (NB == 8) {
-                wq_store_once(out, uint2{pw[0], pw[1]});
+                put<T>(out, uint2{pw[0], pw[1]});
             } else {
-                wq_store_once(out, uint4{pw[0], pw[1], pw[2], pw[3]});
+                put<T>(out, uint4{pw[0], pw[1], pw[2], pw[3]});
             }
         }
         if ((p * CPT) % group == 0) {
@@ -395,11 +405,11 @@ __device__ __forceinline__ void quantize_block(QuantSmem<HD>& sm, int blk, int k
             uint32_t y[4];
             pack16<BITS>(x, y);
             if constexpr (BITS == 8)
-                wq_store_once(out + r * 16, uint4{y[0], y[1], y[2], y[3]});
+                put<T>(out + r * 16, uint4{y[0], y[1], y[2], y[3]});
             else if constexpr (BITS == 4)
-                wq_store_once(out + r * 8, uint2{y[0], y[1]});
+                put<T>(out + r * 8, uint2{y[0], y[1]});
             else
-                wq_store_once(out + r * 4, y[0]);
+                put<T>(out + r * 4, y[0]);
         }
     }
     // ---- metadata: [tile of 16][group][16 tokens] ---------------------------------------------------------
@@ -409,7 +419,7 @@ __device__ __forceinline__ void quantize_block(QuantSmem<HD>& sm, int blk, int k
             const int plane = tid >> (5 + lg), r = tid & ((32 << lg) - 1);
             const int tile = r >> (4 + lg), gi = (r >> 4) & (G - 1), mrow = r & 15;
             uint32_t* out = static_cast<uint32_t*>(pk.meta[C]) + (((int64_t)plane * Hkv + kvh) * pk.cap[C] + tok0) * G;
-            wq_store_once(out + r, s_meta[plane][gi][tile * 16 + mrow]);
+            put<T>(out + r, s_meta[plane][gi][tile * 16 + mrow]);
         }
     }
 }
@@ -469,7 +479,7 @@ __device__ __forceinline__ void copy16_rows(int64_t r0, const T* __restrict__ K,
                     x = wq_load_once(src);
                 }
                 if constexpr (decltype(aligned)::value) {
-                    wq_store_once(dst, x);
+                    put<T>(dst, x);
                 } else {
                     const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
@@ -489,7 +499,7 @@ __device__ __forceinline__ void copy16_rows(int64_t r0, const T* __restrict__ K,
 // together fill: where thresholds decide, every class has room for all tokens, and a call for 16 ragged sequences (198 500
 // tokens, fp16) took 144 us with workgroups for the unused room, 136 without.  Else the former: reading the tables first
 // costs 2.5 of 61 us (8 x 12800 tokens).
-// Everything the launch writes is written once, with non-temporal stores, which leave the memory to the reads: 4 x 50688 tokens, 4 KV heads of 128,
+// Everything the launch writes is written once, for 16-bit rows with non-temporal stores, which leave the memory to the reads: 4 x 50688 tokens, 4 KV heads of 128,
 // 352 -> 348 us for a layer's prefill (377 -> 364 before the scoring read its rows so), 4 x 12644, 8 KV heads of 64, 75.7 -> 67.8; a decode call behind it
 // takes what it took.  (The rows of K and V so: 1 to 10 % slower, a wavefront reads them in pieces; the 16-bit rows' copies take whole lines: 209.6 ->
 // 202.7 us where all of 8 x 12644 tokens stay in 16 bits.)

@@ -330,13 +330,13 @@ __device__ __forceinline__ void walk_class_split(const DecodeArgs& a, F32Smem<HD
 
     auto load = [&](int n, F& f) {
         const int64_t o = (int64_t)n * (32 * HD * BITS / 8);
-        load_dwords<F::KDW>(reinterpret_cast<const uint32_t*>(kbase + o), f.k[0]);
-        load_dwords<F::KDW>(reinterpret_cast<const uint32_t*>(kbase + o + 16 * HD * BITS / 8), f.k[1]);
-        load_dwords<F::VDW>(reinterpret_cast<const uint32_t*>(vbase + o), f.v);
+        load_dwords<HD, F::KDW>(reinterpret_cast<const uint32_t*>(kbase + o), f.k[0]);
+        load_dwords<HD, F::KDW>(reinterpret_cast<const uint32_t*>(kbase + o + 16 * HD * BITS / 8), f.k[1]);
+        load_dwords<HD, F::VDW>(reinterpret_cast<const uint32_t*>(vbase + o), f.v);
 #pragma unroll
         for (int t = 0; t < 2; t++) {
-            f.km[t] = __builtin_nontemporal_load(kmeta + (int64_t)n * (32 * G) + t * (16 * G));
-            f.vm[t] = __builtin_nontemporal_load(vmeta + (int64_t)n * (32 * G) + t * (16 * G));
+            f.km[t] = load_word<HD>(kmeta + (int64_t)n * (32 * G) + t * (16 * G));
+            f.vm[t] = load_word<HD>(vmeta + (int64_t)n * (32 * G) + t * (16 * G));
         }
     };
     F f[DEPTH];
@@ -564,7 +564,7 @@ __device__ __forceinline__ void walk_seg16_f32(const DecodeArgs& a, F32Smem<HD, 
         for (int t = 0; t < 2; t++) {
             const int tok = min(blk * 32 + 16 * t + m, len - 1);
             const uint16_t* src_k = tok == new_row ? knew : k16 + tok * rstride;
-            load_dwords<KDW>(reinterpret_cast<const uint32_t*>(src_k + j * (HD / 4)), kd[t]);
+            load_dwords<HD, KDW>(reinterpret_cast<const uint32_t*>(src_k + j * (HD / 4)), kd[t]);
         }
         uint4 vd[VIT];
 #pragma unroll

@@ -463,17 +463,19 @@ struct Frag {
     uint32_t km, vm;                                        // one metadata word per lane and plane
 };
 
-// N dwords per lane, lane after lane.  The cache is streamed once per launch, and a load that takes whole lines (at most 16
+// N dwords per lane, lane after lane.  The cache is streamed once per launch, and with heads of 128 a load that takes whole lines (at most 16
 // bytes per lane) says so: non-temporal.  28 layers: 8 x 12800 tokens 528 -> 507 us a step, 1 x 19735 320 -> 303; 4 x 50688 x 4 layers 102 -> 95; 32 ragged
-// sequences 128 -> 120.  It costs up to 3 % (5 with heads of 64) where all that a program reads between two launches over a cache is less than 140 MB
-// or so, which then would stay in the memory-side cache: one or two layers.  Loads of more bytes per lane come in pieces that share lines, and
-// each piece would fetch them again (all loads so: 20 % slower).
-template <int N>
+// sequences 128 -> 120.  It costs up to 3 % where all that a program reads between two launches over a cache is less than 140 MB
+// or so, which then would stay in the memory-side cache: one or two layers.  With heads of 64 that costs more (8 x 12744 tokens, 8/8 heads, three
+// caches in turn: 17.4 us a call, 19.5 with non-temporal loads; 12 layers of 3336 tokens 125.5 and 118.5): plain loads.  Loads of more bytes per lane come
+// in pieces that share lines, and each piece would fetch them again (all loads so: 20 % slower).
+template <int HD, int N>
 __device__ __forceinline__ void load_dwords(const uint32_t* __restrict__ p, uint32_t* dst)
 {
     if constexpr (N <= 4) {
         typedef uint32_t dwords __attribute__((ext_vector_type(N)));
-        const dwords u = __builtin_nontemporal_load(reinterpret_cast<const dwords*>(p));
+        const dwords* const from = reinterpret_cast<const dwords*>(p);
+        const dwords u = HD == 128 ? __builtin_nontemporal_load(from) : *from;
 #pragma unroll
         for (int d = 0; d < N; d++) dst[d] = u[d];
     } else {
@@ -487,6 +489,8 @@ __device__ __forceinline__ void load_dwords(const uint32_t* __restrict__ p, uint
         }
     }
 }
+template <int HD>
+__device__ __forceinline__ uint32_t load_word(const uint32_t* p) { return HD == 128 ? __builtin_nontemporal_load(p) : *p; }
 
 // One class of one (sequence, KV head): this wavefront's share of its 32-token blocks (len tokens from token slot
 // tok_base of the class buffers).
@@ -513,11 +517,11 @@ __device__ __forceinline__ void walk_class_mfma(const DecodeArgs& a, MfmaSmem<HD
 
     auto load = [&](int blk, F& f) {
         const int64_t o = (int64_t)blk * (32 * HD * BITS / 8);
-        load_dwords<F::KDW>(reinterpret_cast<const uint32_t*>(kbase + o), f.k[0]);
-        load_dwords<F::KDW>(reinterpret_cast<const uint32_t*>(kbase + o + 16 * HD * BITS / 8), f.k[1]);
-        load_dwords<F::VDW>(reinterpret_cast<const uint32_t*>(vbase + o), f.v);
-        f.km = __builtin_nontemporal_load(kmeta + (int64_t)blk * 64);
-        f.vm = __builtin_nontemporal_load(vmeta + (int64_t)blk * 64);
+        load_dwords<HD, F::KDW>(reinterpret_cast<const uint32_t*>(kbase + o), f.k[0]);
+        load_dwords<HD, F::KDW>(reinterpret_cast<const uint32_t*>(kbase + o + 16 * HD * BITS / 8), f.k[1]);
+        load_dwords<HD, F::VDW>(reinterpret_cast<const uint32_t*>(vbase + o), f.v);
+        f.km = load_word<HD>(kmeta + (int64_t)blk * 64);
+        f.vm = load_word<HD>(vmeta + (int64_t)blk * 64);
     };
 
     // software pipeline: DEPTH blocks in flight per wavefront; the first loads go out before anything else
@@ -704,7 +708,7 @@ __device__ __forceinline__ void walk_seg16_mfma(const DecodeArgs& a, MfmaSmem<HD
         for (int t = 0; t < 2; t++) {
             const int tok = min(blk * 32 + 16 * t + col, len - 1);      // rows past the end re-read the last row, masked below
             const uint16_t* src_k = tok == new_row ? knew : k16 + (row0 + tok) * rstride;
-            load_dwords<KDW>(reinterpret_cast<const uint32_t*>(src_k + j * (HD / 4)), kd[t]);
+            load_dwords<HD, KDW>(reinterpret_cast<const uint32_t*>(src_k + j * (HD / 4)), kd[t]);
         }
         constexpr int VIT = (32 * (HD / 2) * 2) / (16 * 64);          // 16-byte pieces per lane and channel half
         uint4 vd[2][VIT];

@@ -136,12 +136,13 @@ __global__ __launch_bounds__(256) void k_text_mean(const T* __restrict__ txt, co
 }
 
 // c_k = (w_k . tbar) / |w_k|.  VEC: one wavefront takes WQ_TS_ROWS consecutive rows so that each 32-byte piece of the pooled
-// text vector is loaded once per WQ_TS_ROWS rows; 16 bytes of every row per lane and iteration.  Bound by HBM.  The rows are read
-// once and their loads say so (non-temporal): 4 x 50176 rows of 3584 bf16 246 -> 229 us a call (6.0 -> 6.5 TB/s in this kernel), 50176 of 896 35.8 ->
-// 31.6, rows that have just been written included (64.3 -> 61.4 with the copy that writes 12544 of 3584); 5 % slower only where the same 25 to 110 MB are
-// scored again and again and nothing else is read (50176 of 896: 29.6 -> 31.5).  fp32 rows keep plain loads (10 % faster: wq_ld8_once).
+// text vector is loaded once per WQ_TS_ROWS rows; 16 bytes of every row per lane and iteration.  Bound by HBM.  With ONCE the
+// rows' loads say that they are read once (non-temporal): 4 x 50176 rows of 3584 bf16 246 -> 229 us a call (6.0 -> 6.5 TB/s in this kernel), 50176 of 896
+// 35.8 -> 31.6, 64.3 -> 61.4 with a copy that has just written the 12544 of 3584 in front of it.  Up to ONCE_FROM bytes plain loads, which the memory-side
+// cache serves where a few such inputs are scored in turn (three of 30000 rows of 896: 22.7 us with non-temporal loads, 21.0 so; three of 10000 of 3584: 21.8 and 20.8; behind a
+// matrix product that writes them the two are the same to 1 %).  fp32 rows keep plain loads (10 % faster: wq_ld8_once).
 // FOLD (VEC only): the workgroup that finishes a window's last row makes the window's mean, as k_window_mean does.
-template <typename T, bool VEC, bool FOLD>
+template <typename T, bool VEC, bool FOLD, bool ONCE>
 __global__ __launch_bounds__(256) void k_token_score(const T* __restrict__ vis, const float* __restrict__ tbar, int D, int B,
                                                      const int32_t* __restrict__ vis_off, int64_t total_vis,
                                                      float* __restrict__ tok_score, WindowFold fold)
@@ -183,7 +184,8 @@ __global__ __launch_bounds__(256) void k_token_score(const T* __restrict__ vis, 
 #pragma unroll
             for (int r = 0; r < R; r++) {
                 float x[8], tr[8];
-                wq_ld8_once(p[r] + d, x);
+                if constexpr (ONCE) wq_ld8_once(p[r] + d, x);
+                else wq_ld8(p[r] + d, x);
                 if (!same && bs[r] != bs[0]) wq_ld8(tbar + (int64_t)bs[r] * D + d, tr);
 #pragma unroll
                 for (int k = 0; k < 8; k++) {
@@ -999,7 +1001,7 @@ int64_t pair_total_tiles(int B, int64_t total_txt) { return total_txt / 16 + B; 
 // Up to here k_token_score makes the windows' means itself: a launch saved against a wait at the end of every workgroup, which costs more where
 // the rows keep the chip busy for long.  Four launches -> three, bf16: 6272 rows of 3584 18.2 -> 17.6 us, 25088 39.8 -> 39.0, 50176 69.1 -> 68.9, 75264
 // (539 MB) 93.1 -> 95.2; 8192 rows of 512 12.3 -> 11.3, 65536 31.0 -> 27.8, 100352 of 896 (180 MB) 57.8 -> 54.3; 32768 of 4096 (268 MB) 54.4 -> 53.9.
-constexpr int64_t FOLD_ROWS = 1 << 17, FOLD_BYTES = 320 << 20;
+constexpr int64_t FOLD_ROWS = 1 << 17, FOLD_BYTES = 320 << 20, ONCE_FROM = 80 << 20;
 template <typename T, bool VEC>
 int run_pooled(wq_ctx* ctx, const void* vis_, const void* txt_, int B, int D, const int32_t* vis_off, const int32_t* txt_off,
                const int32_t* win_size, const int32_t* win_off, int64_t total_vis, int64_t total_txt, int64_t total_win,
@@ -1026,7 +1028,8 @@ int run_pooled(wq_ctx* ctx, const void* vis_, const void* txt_, int B, int D, co
     // the windows' counters lie where the pairwise form has its packed text
     float* const counters = tok_score + wq_align256(sizeof(float) * (size_t)(total_vis > 0 ? total_vis : 1)) / sizeof(float);
     const WindowFold fold{win_size, win_off, txt_off, reinterpret_cast<unsigned*>(counters), scores};
-    const bool folds = VEC && total_vis > 0 && total_vis <= FOLD_ROWS && total_vis * D * (int64_t)sizeof(T) <= FOLD_BYTES && total_txt > 0 &&
+    const int64_t row_bytes = total_vis * D * (int64_t)sizeof(T);
+    const bool folds = VEC && total_vis > 0 && total_vis <= FOLD_ROWS && row_bytes <= FOLD_BYTES && total_txt > 0 &&
                        total_win * FOLD_STRIDE * (int64_t)sizeof(unsigned) <= pair_total_tiles(B, total_txt) * 16 * D * 2;
     if (total_txt > 0)
         hipLaunchKernelGGL((k_text_norm<T, VEC>), dim3((unsigned)((total_txt + 3) / 4)), dim3(256), 0, st, txt, D, total_txt, inv_norm, fold,
@@ -1034,7 +1037,7 @@ int run_pooled(wq_ctx* ctx, const void* vis_, const void* txt_, int B, int D, co
     hipLaunchKernelGGL((k_text_mean<T, VEC>), dim3(VEC ? (D + 63) / 64 : (D + 255) / 256, B), dim3(256), 0, st, txt, inv_norm, D, txt_off, tbar);
     if (total_vis > 0) {
         const int64_t rows_per_block = VEC ? 4 * WQ_TS_ROWS : 4;
-        hipLaunchKernelGGL((folds ? k_token_score<T, VEC, VEC> : k_token_score<T, VEC, false>),
+        hipLaunchKernelGGL((!folds ? k_token_score<T, VEC, false, true> : row_bytes < ONCE_FROM ? k_token_score<T, VEC, VEC, false> : k_token_score<T, VEC, VEC, true>),
                            dim3((unsigned)((total_vis + rows_per_block - 1) / rows_per_block)), dim3(256), 0, st, vis, tbar, D, B, vis_off, total_vis,
                            tok_score, fold);
     }

@@ -211,9 +211,11 @@ __global__ __launch_bounds__(256) void k_token_score(const T* __restrict__ vis, 
             // A lane per row.  The scores are stored past the XCD's L2 and acknowledged before the rows are counted, so whoever completes a window
             // reads scores that have arrived.  (At most FOLD_ROWS rows: 32 bits hold everything.)
             const int base = (int)blockIdx.x * ROWS, row = base + lane, end = min(base + ROWS, (int)total_vis);
-            const int nth = size > 0 ? (row - first) / size : 0, begin = first + nth * size;
+            // (rows may lie in front of the first sequence's, whose windows are counted back from it as k_window_mean does; the ones that
+            // would come before the first window or begin before the first row are none)
+            const int ahead = row - first, nth = size <= 0 ? 0 : ahead >= 0 ? ahead / size : ~(~ahead / size), begin = first + nth * size;
             window += nth;
-            const bool counted = row < end && size > 0 && window < windows_end;
+            const bool counted = row < end && size > 0 && window >= 0 && window < windows_end && begin >= 0;
             if (row < end) __hip_atomic_store(tok_score + row, s_score[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             bool done = false;

@@ -39,3 +39,37 @@ def test_pooled_scores(n_txt, dim, times, dtype):
         v0, t0 = v0 + m, t0 + n
     assert times == 1 or sum(n_vis) > 1 << 17
     assert (got.double() - torch.cat(want)).abs().max().item() <= 1e-5 / dim ** 0.5
+
+
+@pytest.mark.parametrize("front,size,first", [(64, 16, 0), (63, 7, 0), (21, 7, 0), (5, 7, 0), (390, 130, 0), (64, 16, 4), (40, 7, 5)])
+def test_rows_in_front_of_the_first_sequence(front, size, first):
+    """vis_off[0] = front, whole numbers of windows and not; windows counted from 0 or from `first` (then the rows in front hold the ones before it).
+    Twice on one context, whose workspace the first call leaves as it is, and with more rows than the means are made with: the same bits, nothing
+    written in front of the scores or behind them; float64 reference, bound as above."""
+    from paper_2605_02262_amd import binding as W
+    gen = torch.Generator(device="cuda").manual_seed(front + size)
+    dim, n_txt, sizes, n_win, guard = 64, [300, 20], [size, 11], [10, 6], 128
+    rows = [10 * size + 3, 6 * 11 + 1]
+    vis = torch.randn(front + sum(rows) + (1 << 17), dim, generator=gen, device="cuda").add_(0.2).to(torch.bfloat16)
+    txt = torch.randn(sum(n_txt), dim, generator=gen, device="cuda").add_(0.2).to(torch.bfloat16)
+    table = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")  # noqa: E731
+    win_off, total_win = [first, first + 10, first + 16], first + 16
+    got, ctx = [], None
+    for more in (0, 0, 1 << 17):
+        vis_off = [front, front + rows[0], front + sum(rows) + more]
+        if more or ctx is None:
+            ctx = W.Context(W.workspace_bytes(2, 0, 0, 0, vis_off[-1], sum(n_txt), dim))
+        out = torch.full((guard + total_win + guard,), 7.0, device="cuda")
+        W.wq_window_scores(ctx, vis[:vis_off[-1]], txt, table(vis_off), table([0, 300, 320]), table(sizes), table(win_off), vis_off[-1], sum(n_txt), total_win,
+                           scores=out[guard:guard + total_win])
+        assert (out[:guard] == 7.0).all() and (out[guard + total_win:] == 7.0).all()
+        got.append(out[guard:guard + total_win])
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+    want, n0 = [], 0
+    for b, t in enumerate(n_txt):
+        unit = torch.nn.functional.normalize(txt[n0:n0 + t].double(), dim=1).mean(0)
+        lo, n = (front - first * size, first + 10) if b == 0 else (front + rows[0], 6)
+        v = vis[lo:lo + n * sizes[b]].double()
+        want.append(((v @ unit) / v.norm(dim=1)).view(n, sizes[b]).mean(1))
+        n0 += t
+    assert (got[0].double() - torch.cat(want)).abs().max().item() <= 1e-5 / dim ** 0.5

@@ -138,9 +138,9 @@ __global__ __launch_bounds__(256) void k_text_mean(const T* __restrict__ txt, co
 // c_k = (w_k . tbar) / |w_k|.  VEC: one wavefront takes WQ_TS_ROWS consecutive rows so that each 32-byte piece of the pooled
 // text vector is loaded once per WQ_TS_ROWS rows; 16 bytes of every row per lane and iteration.  Bound by HBM.  With ONCE the
 // rows' loads say that they are read once (non-temporal): 4 x 50176 rows of 3584 bf16 246 -> 229 us a call (6.0 -> 6.5 TB/s in this kernel), 50176 of 896
-// 35.8 -> 31.6, 64.3 -> 61.4 with a copy that has just written the 12544 of 3584 in front of it.  Up to ONCE_FROM bytes plain loads, which the memory-side
-// cache serves where a few such inputs are scored in turn (three of 30000 rows of 896: 22.7 us with non-temporal loads, 21.0 so; three of 10000 of 3584: 21.8 and 20.8; behind a
-// matrix product that writes them the two are the same to 1 %).  fp32 rows keep plain loads (10 % faster: wq_ld8_once).
+// 35.8 -> 31.6, 64.3 -> 61.4 with a copy that has just written the 12544 of 3584 in front of it.  Below ONCE_FROM bytes plain loads, which the memory-side
+// cache serves where a few such inputs are scored in turn (three of 30000 rows of 896: 22.7 us with non-temporal loads, 21.0 so; three of 10000 of 3584: 21.8 and 20.8; four
+// launches, 8624 rows of 896 and a text of 14 tokens: 12.1 and 11.6; behind a matrix product that writes them the two are the same to 1 %).  fp32 rows keep plain loads (10 % faster: wq_ld8_once).
 // FOLD (VEC only): the workgroup that finishes a window's last row makes the window's mean, as k_window_mean does.
 template <typename T, bool VEC, bool FOLD, bool ONCE>
 __global__ __launch_bounds__(256) void k_token_score(const T* __restrict__ vis, const float* __restrict__ tbar, int D, int B,
@@ -1003,7 +1003,11 @@ int64_t pair_total_tiles(int B, int64_t total_txt) { return total_txt / 16 + B; 
 // Up to here k_token_score makes the windows' means itself: a launch saved against a wait at the end of every workgroup, which costs more where
 // the rows keep the chip busy for long.  Four launches -> three, bf16: 6272 rows of 3584 18.2 -> 17.6 us, 25088 39.8 -> 39.0, 50176 69.1 -> 68.9, 75264
 // (539 MB) 93.1 -> 95.2; 8192 rows of 512 12.3 -> 11.3, 65536 31.0 -> 27.8, 100352 of 896 (180 MB) 57.8 -> 54.3; 32768 of 4096 (268 MB) 54.4 -> 53.9.
-constexpr int64_t FOLD_ROWS = 1 << 17, FOLD_BYTES = 320 << 20, ONCE_FROM = 80 << 20;
+// The counters must fit where the pairwise form has its packed text, D / 2 windows per 16 text tokens and per sequence: more windows over a short text, or no text at
+// all, keep the fourth launch.
+constexpr int64_t FOLD_ROWS = 1 << 17, FOLD_BYTES = 320 << 20;
+// 16-bit rows from here on have non-temporal loads, whoever makes the means (k_token_score)
+constexpr int64_t ONCE_FROM = 80 << 20;
 template <typename T, bool VEC>
 int run_pooled(wq_ctx* ctx, const void* vis_, const void* txt_, int B, int D, const int32_t* vis_off, const int32_t* txt_off,
                const int32_t* win_size, const int32_t* win_off, int64_t total_vis, int64_t total_txt, int64_t total_win,
@@ -1039,7 +1043,10 @@ int run_pooled(wq_ctx* ctx, const void* vis_, const void* txt_, int B, int D, co
     hipLaunchKernelGGL((k_text_mean<T, VEC>), dim3(VEC ? (D + 63) / 64 : (D + 255) / 256, B), dim3(256), 0, st, txt, inv_norm, D, txt_off, tbar);
     if (total_vis > 0) {
         const int64_t rows_per_block = VEC ? 4 * WQ_TS_ROWS : 4;
-        hipLaunchKernelGGL((!folds ? k_token_score<T, VEC, false, true> : row_bytes < ONCE_FROM ? k_token_score<T, VEC, VEC, false> : k_token_score<T, VEC, VEC, true>),
+        constexpr bool CAN = VEC && sizeof(T) == 2;       // (other rows have one kind of loads)
+        const bool once = CAN && row_bytes >= ONCE_FROM;
+        hipLaunchKernelGGL((folds ? once ? k_token_score<T, VEC, VEC, CAN> : k_token_score<T, VEC, VEC, false>
+                                  : once ? k_token_score<T, VEC, false, CAN> : k_token_score<T, VEC, false, false>),
                            dim3((unsigned)((total_vis + rows_per_block - 1) / rows_per_block)), dim3(256), 0, st, vis, tbar, D, B, vis_off, total_vis,
                            tok_score, fold);
     }

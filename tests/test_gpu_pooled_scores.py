@@ -73,3 +73,25 @@ def test_rows_in_front_of_the_first_sequence(front, size, first):
         want.append(((v @ unit) / v.norm(dim=1)).view(n, sizes[b]).mean(1))
         n0 += t
     assert (got[0].double() - torch.cat(want)).abs().max().item() <= 1e-5 / dim ** 0.5
+
+
+@pytest.mark.parametrize("dim,size", [(1024, 3), (4096, 1)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_as_many_windows_as_there_is_room_to_count(dim, size, dtype):
+    """A text of 4 tokens leaves room for the counters of dim / 2 windows (cleared 256 at a time): that many, one more (four launches) and fewer, on one
+    context whose workspace holds other bytes: the same bits.  float64 reference, bound as above."""
+    from paper_2605_02262_amd import binding as W
+    gen = torch.Generator(device="cuda").manual_seed(dim)
+    most = dim // 2
+    vis = torch.randn((most + 1) * size, dim, generator=gen, device="cuda").add_(0.2).to(dtype)
+    txt = torch.randn(4, dim, generator=gen, device="cuda").add_(0.2).to(dtype)
+    table = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")  # noqa: E731
+    ctx = W.Context(W.workspace_bytes(1, 0, 0, 0, (most + 1) * size, 4, dim))
+    got = []
+    for n in (most, most + 1, 300):
+        ctx.ws[16384:] = 0x5A
+        got.append(W.wq_window_scores(ctx, vis[:n * size], txt, table([0, n * size]), table([0, 4]), table([size]), table([0, n]), n * size, 4, n))
+    assert torch.equal(got[0], got[1][:most]) and torch.equal(got[2], got[1][:300])
+    unit, v = torch.nn.functional.normalize(txt.double(), dim=1).mean(0), vis.double()
+    want = ((v @ unit) / v.norm(dim=1)).view(-1, size).mean(1)
+    assert (got[1].double() - want).abs().max().item() <= 1e-5 / dim ** 0.5

@@ -44,9 +44,11 @@ __device__ __forceinline__ float wave_sum(float v)
 }
 
 // VEC: rows are read 8 elements per lane (needs D % 8 == 0), WQ_TEXT_FLIGHT pieces in flight; otherwise element by element.  The two
-// kernels of the text read a few MB and are bound by the latency of their loads: one piece after the other 2048 tokens of 3584 bf16 took
-// 6.4 and 8.8 us, so 5.1 and 5.1; 512 of them 4.4 and 5.4, so 3.2 and 3.8.
-constexpr int WQ_TEXT_FLIGHT = 8;
+// kernels of the text read a few MB and are bound by the latency of their loads: one piece after the other 4 x 512 tokens of 3584 bf16 take
+// 5.9 and 8.0 us, so 4.7 and 4.8; 512 of them 4.5 and 8.2, so 4.0 and 4.5.  Pieces past the row's or the text's end are loaded all the same: with eight in
+// flight short texts lose by it (a call for 2000 rows of 512: 14 tokens 9.1 us with one, 8.6 with four, 9.1 with eight; 600 tokens 14.6, 10.7, 11.2;
+// 100 sizes, 5 to 600 tokens of 512 to 4096: four 1.146 times as fast as one on average, 0.991 at least; eight 1.111 and 0.982, two 1.119 and 0.996).
+constexpr int WQ_TEXT_FLIGHT = 4;
 // What k_token_score needs to make the windows' means itself (FOLD).  folded windows: k_text_norm clears their counters, a line each
 constexpr int FOLD_STRIDE = 16;
 struct WindowFold {

@@ -95,3 +95,9 @@ def test_as_many_windows_as_there_is_room_to_count(dim, size, dtype):
     unit, v = torch.nn.functional.normalize(txt.double(), dim=1).mean(0), vis.double()
     want = ((v @ unit) / v.norm(dim=1)).view(-1, size).mean(1)
     assert (got[1].double() - want).abs().max().item() <= 1e-5 / dim ** 0.5
+
+
+@pytest.mark.parametrize("n_txt,dim", [([1, 300], 2040), ([127, 128, 129], 2048), ([300], 2056), ([97, 160, 161, 31], 1536)])
+def test_pieces_in_flight(n_txt, dim):
+    """Four pieces of a row per lane, one more and one less than they hold; four rounds of the 32 token slices and beside it."""
+    test_pooled_scores(n_txt, dim, 1, torch.bfloat16)

@@ -1149,19 +1149,45 @@ __device__ void wq_decode_mfma_body(const DecodeArgs& a, void* smem_raw)
         // shares up to a block each, where 5 parts would be two for some: 3 sequences of up to 2592 tokens, 32/8 heads of 128, 64.7 us a step of 4
         // layers, so 58.5.
         static_assert(WQ_WAVES == 8, "the shares");
-        const bool even = G1 - G0 < 9u * (unsigned)block_cost<HD, G>(1);
-        auto parts_before = [&](int w) { return (unsigned)(even ? 4 * w : w < WQ_WAVES / 2 ? 5 * w : 20 + 3 * (w - WQ_WAVES / 2)); };
-        const unsigned long long span = G1 - G0;
-        const unsigned x0 = G0 + (unsigned)((span * parts_before(wave)) >> 5), x1 = G0 + (unsigned)((span * parts_before(wave + 1)) >> 5);
-        unsigned base = 0u, t = 0u;
+        const unsigned cost = G1 - G0;
+        const bool few = cost < 9u * (unsigned)block_cost<HD, G>(1);
+        unsigned t = 0u;
         if constexpr (F32) {
+            // A share is whole blocks, and those of the 16-bit class cost as much as three others: which wavefronts get one more, and
+            // which SIMD two wavefronts with some, decides a short range.  So both ways of sharing are laid out, 5 : 3 in lanes 0 to 8 and equal ones in
+            // lanes 16 to 24 (lane w: where wavefront w begins), and the one whose slowest SIMD is done first is taken: after the older
+            // one's cost, or the younger one's and two fifths of the older one's (it gets 3 instructions in while the older one issues 5).  Ranges of up to 16
+            // 16-bit blocks; above, rounding to blocks matters less than the 5 : 3.  8 x 4000 tokens, 500 of them in 16 bits, 28/4 heads of 128, group
+            // 128: equal shares 12.6 us a call, 5 : 3 13.8, so 12.7; 13 x 2600, 100 in 16 bits, 14/2 heads of 64: 8.3, 7.5 and 7.6; 16 x 1040, 60 in 16 bits, 32/8
+            // heads of 128: 11.7, 12.7 and 11.6; over 300 shapes 1.012 times as fast as by the count of blocks alone (all edges by lanes, instead of two per
+            // class one after the other on the scalar unit, is 0.1 us of it), 0.93 at least.
+            const unsigned w = min((unsigned)lane & 15u, (unsigned)WQ_WAVES), parts = (lane & 16) ? 4u * w : min(5u * w, 3u * w + 8u);
+            const unsigned x = G0 + (cost >> 5) * parts + (((cost & 31u) * parts) >> 5);
+            int at[4], mine = 0;
+            unsigned base = 0u;
 #pragma unroll
             for (int c = 3; c >= 0; c--) {
-                own[c] = range_edge_of<HD, G>(c, x0, base, nb[c]);
-                own_end[c] = range_edge_of<HD, G>(c, x1, base, nb[c]);
+                at[c] = range_edge_of<HD, G>(c, x, base, nb[c]);
+                const int n = __builtin_amdgcn_update_dpp(0, at[c], 0x101, 0xF, 0xF, true) - at[c];         // (row_shl:1: the next lane's)
+                mine += __mul24(n, block_cost<HD, G>(c));
                 base += (unsigned)nb[c] * (unsigned)block_cost<HD, G>(c);
             }
+            const int younger = __builtin_amdgcn_update_dpp(0, mine, 0x104, 0xF, 0xF, true);                // (row_shl:4)
+            int done = 2 * mine + max(3 * mine, 5 * younger);                                               // (fifths)
+            done = max(done, __builtin_amdgcn_update_dpp(0, done, 0xB1, 0xF, 0xF, true));                   // (quad_perm: of the four SIMDs, lanes 0 to 3 of a row)
+            done = max(done, __builtin_amdgcn_update_dpp(0, done, 0x4E, 0xF, 0xF, true));
+            const int uneven = __builtin_amdgcn_readlane(done, 0), equal = __builtin_amdgcn_readlane(done, 16);
+            const int l = wave + (cost <= 16u * (unsigned)block_cost<HD, G>(3) && (equal < uneven || (equal == uneven && few)) ? 16 : 0);
+#pragma unroll
+            for (int c = 3; c >= 0; c--) {
+                own[c] = __builtin_amdgcn_readlane(at[c], l);
+                own_end[c] = __builtin_amdgcn_readlane(at[c], l + 1);
+            }
         } else {
+            auto parts_before = [&](int w) { return (unsigned)(few ? 4 * w : min(5 * w, 3 * w + 8)); };
+            const unsigned long long span = cost;
+            const unsigned x0 = G0 + (unsigned)((span * parts_before(wave)) >> 5), x1 = G0 + (unsigned)((span * parts_before(wave + 1)) >> 5);
+            unsigned base = 0u;
             unsigned bases[4];
 #pragma unroll
             for (int c = 3; c >= 0; c--) {

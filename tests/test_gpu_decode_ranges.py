@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import wq_oracle as O
 from paper_2605_02262_amd import synth
 from tests.test_gpu_decode_groups import TIGHT
 
@@ -34,6 +35,31 @@ def test_ranges_of_few_blocks(first_class):
         for flags in (0, W.DECODE_FIXED_SHARES):
             out = W.wq_decode_attention(ctx, q, run.pk, sm, splits, 1400, flags)
             assert H.attention_error(out.cpu().numpy(), o.out) <= TIGHT, (splits, flags)
+    assert ctx.device_status() == 0
+
+
+@pytest.mark.parametrize("hd,g", [(64, 64), (128, 32), (128, 128)])
+@pytest.mark.parametrize("rows16", [0, 1, 2, 3, 7, 17, 40])
+def test_shares_of_ranges_with_blocks_in_16_bits(hd, g, rows16):
+    """One and four groups per head: 1 to 65 quantized blocks beside `rows16` blocks of 16-bit rows, cut into 1 to 9 ranges whose wavefronts get
+    equal shares or 5 : 3 by what their blocks cost; a larger batch whose ranges are all 5 : 3."""
+    from paper_2605_02262_amd import binding as W
+    from tests import wq_harness as H
+    specs = []
+    for n in (1, 4, 9, 16, 24, 37, 65) if rows16 < 40 else (70, 200):
+        top = n // 3
+        specs.append(synth.SeqSpec(n, 32, 32, max(1, 32 * rows16 - 3), (top, (n - top) // 2, n - top - (n - top) // 2)))
+    w = synth.Workload("shares", synth.BF16, synth.BF16, 6, 2, hd, g, 64, 1.0, specs, 800 + rows16 + g, pin_first=0)
+    bt = synth.batch(w, with_embeddings=False)
+    sc = np.random.default_rng(4).standard_normal(int(bt.t.win_off[-1])).astype(np.float32)
+    run = H.run_gpu(bt, splits=1, with_scores=False, scores_override=sc)
+    o = H.run_oracle(bt, scores_override=sc, with_scores=False)
+    ctx = W.Context(W.workspace_bytes(w.B, w.Hq, w.hd, 9))
+    q, sm = H.to_dev(bt.q, w.dtype), w.hd ** -0.5
+    o.out = O.decode_attention(bt.q, o.pk, sm)
+    for splits in range(1, 10):
+        out = W.wq_decode_attention(ctx, q, run.pk, sm, splits, 8000)
+        assert H.attention_error(out.cpu().numpy(), o.out) <= TIGHT, splits
     assert ctx.device_status() == 0
 
 

@@ -3,8 +3,9 @@
 //
 // One workgroup per (split, KV head, sequence) walks its share of the 2-, 4-, 8- and 16-bit segments with an
 // online softmax (running max m, running sum l, unnormalised accumulator), writes one partial (m, l, acc) per
-// query head; k_combine merges the partials of all splits by log-sum-exp in split order.  No float atomics:
-// the result is deterministic for a given split count.
+// query head; k_combine, or the matrix-core kernel itself, merges the partials of all splits by log-sum-exp: splits s, s + 4, ... one after the
+// other for s = 0..3, then (0 + 2) + (1 + 3).  No float atomics: with fixed shares, which one and four groups per head always have, and in the
+// vector kernel a split count fixes every bit.
 //
 // k_decode_generic: plain vector-ALU kernel that reads codes field by field from the storage layout.  It
 // handles every supported (hd, group) and query type and is the reference implementation inside the library; the
@@ -50,7 +51,7 @@ struct DecodeArgs {         // (what the matrix-core kernel reads of it comes fi
     long long* dbg;
 #endif
 };
-static_assert(offsetof(DecodeArgs, slots) <= 5 * 64, "the matrix-core kernel touches five lines of arguments, all of them with its first loads: a sixth is a round trip of 0.3 us");
+static_assert(offsetof(DecodeArgs, slots) <= 5 * 64, "the matrix-core kernel touches five lines of arguments, all of them with its first loads (by length one more, behind its tables): a sixth is a round trip of 0.3 us");
 
 // ---- the weights of the splits -----------------------------------------------------------------------------
 // Reductions over the 64 lanes of a wavefront in a fixed order: four rotations inside the rows of 16 lanes (one
@@ -524,8 +525,11 @@ static bool packs_by_length(int B, const wq_packed_kv* kv, int64_t max_seq_token
 // decides that: the capacities say what the classes have room for, not what they hold (where thresholds decide, every class
 // has room for all tokens; a cache in use has room to grow).  Even sequences lose 1 to 2 us by it (8 x 12800: 17.0 us, 18.7
 // with the flag), uneven ones gain far more (20 that fill 0.49 of the longest one's length: 40.2 us with even counts, 29.5 so;
-// 32 that fill 0.52: 78.6 and 57.4); one sequence has nothing to differ from.  A second round trip of the merge pays from
-// about 900 blocks in the longest sequence.
+// 32 that fill 0.52: 78.6 and 57.4); one sequence has nothing to differ from.  Up to 900 blocks in the longest sequence 32 splits at
+// most: beyond, the merge has 16 loads in flight per row of lanes instead of 8, and short sequences are cut into more workgroups than they have work for
+// (2 sequences of up to 3300 tokens, 28/4 heads of 128, group 64: 8.9 us a call, 9.9 with up to 48 or 64; up to 12900: 9.3 and 10.3).  Over 300 batches of 2 to 8
+// sequences of up to 100 to 1100 blocks 48 and 64 are 0.995 times as fast: 0.98 with two groups per head, 1.00 with four, 1.02 with one and heads of 64
+// (2 of up to 12900 tokens, 14/2 heads: 9.3 us, with 48 8.6), 1.005 above 1000 blocks.
 int wq_decode_pick_splits(const void* q, int q_dtype, int B, const wq_packed_kv* kv, int64_t max_seq_tokens, int plain_splits, int algo)
 {
     // the same count where the caller has the merge done by a second kernel or left out (there are no counts by length then):

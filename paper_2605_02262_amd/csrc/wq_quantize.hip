@@ -501,7 +501,9 @@ __device__ __forceinline__ void copy16_rows(int64_t r0, const T* __restrict__ K,
 // costs 2.5 of 61 us (8 x 12800 tokens).
 // Everything the launch writes is written once, for 16-bit rows with non-temporal stores, which leave the memory to the reads: 4 x 50688 tokens, 4 KV heads of 128,
 // 352 -> 348 us for a layer's prefill (377 -> 364 before the scoring read its rows so), 4 x 12644, 8 KV heads of 64, 75.7 -> 67.8; a decode call behind it
-// takes what it took.  (The rows of K and V so: 1 to 10 % slower, a wavefront reads them in pieces; the 16-bit rows' copies take whole lines: 209.6 ->
+// takes what it took.  Small calls pay where what they write would have stayed near: the same caches written again and again, 8 x 2369 tokens, 4 KV heads of 128,
+// 18.1 -> 19.3 us (17 x 1148: 20.9 -> 22.7), and 17 x 1148 into one of 33 caches with a decode call behind it 35.0 -> 37.0; they gain where K and V have just been written and the
+// cache has not, as in a model's prefill (two copies and the call: 32.5 -> 30.5, 35.9 -> 34.4; 12 shapes of up to 70 MB 0.99 to 1.09).  (The rows of K and V so: 1 to 10 % slower, a wavefront reads them in pieces; the 16-bit rows' copies take whole lines: 209.6 ->
 // 202.7 us where all of 8 x 12644 tokens stay in 16 bits.)
 // n: workgroups for the blocks, a bound on their number.
 constexpr unsigned WQ_BY_USE = 0xFFFFFFFFu;

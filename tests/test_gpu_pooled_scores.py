@@ -101,3 +101,24 @@ def test_as_many_windows_as_there_is_room_to_count(dim, size, dtype):
 def test_pieces_in_flight(n_txt, dim):
     """Four pieces of a row per lane, one more and one less than they hold; four rounds of the 32 token slices and beside it."""
     test_pooled_scores(n_txt, dim, 1, torch.bfloat16)
+
+
+def test_one_context_for_calls_of_other_shapes():
+    """Windows' counters lie behind what depends on a call's sizes: calls of several shapes in turn on one context, twice, have the bits that each has on
+    one of its own."""
+    from paper_2605_02262_amd import binding as W
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    table = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")  # noqa: E731
+    starts = lambda v: table([sum(v[:i]) for i in range(len(v) + 1)])  # noqa: E731
+    calls = []
+    for n_txt, n_win, size, dim in (([300], [40], 33, 512), ([20, 400], [3, 500], 7, 256), ([260], [1], 1500, 128), ([5] * 70, [9] * 70, 5, 1024), ([299], [41], 33, 512)):
+        rows = [n * size + b % 3 for b, n in enumerate(n_win)]
+        vis = torch.randn(sum(rows), dim, generator=gen, device="cuda").to(torch.bfloat16)
+        txt = torch.randn(sum(n_txt), dim, generator=gen, device="cuda").to(torch.bfloat16)
+        calls.append((vis, txt, starts(rows), starts(n_txt), table([size] * len(rows)), starts(n_win), sum(rows), sum(n_txt), sum(n_win)))
+    need = [W.workspace_bytes(c[4].numel(), 0, 0, 0, c[6], c[7], c[0].shape[1]) for c in calls]
+    own = [W.wq_window_scores(W.Context(n), *c) for n, c in zip(need, calls)]
+    ctx = W.Context(max(need))
+    for _ in range(2):
+        for c, want in zip(calls, own):
+            assert torch.equal(W.wq_window_scores(ctx, *c), want) and torch.isfinite(want).all()

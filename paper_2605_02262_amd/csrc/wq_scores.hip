@@ -6,7 +6,7 @@
 //   k_text_norm   one wavefront per text token  -> 1/|t_j|                       (0 for a zero row)
 //   k_text_mean   thread per channel            -> tbar[b][d] = 1/N sum_j t_j[d]/|t_j|
 //   k_token_score one wavefront per visual row  -> c_k = (w_k . tbar) / |w_k|    (0 for a zero row)
-//   k_window_mean one wavefront per window      -> score = 1/S sum_k c_k, fixed order (part of k_token_score up to FOLD_ROWS, FOLD_BYTES)
+//   k_window_mean one wavefront per window      -> score = 1/S sum_k c_k, fixed order (part of k_token_score up to FOLD_ROWS, FOLD_BYTES where the counters fit)
 //   k_scores_small  all of it for a short text and few rows, a workgroup per window
 // All accumulation is fp32 and every reduction has a fixed order (no atomics): results are deterministic.
 #include "wq_internal.h"
